@@ -44,3 +44,33 @@ def test_softmax_attention_with_large_scores_stays_finite():
     got = msla.msla_softmax_attention(torch.from_numpy(qkv).half().cuda(), heads, d).double().cpu().numpy()
     ref = sm.softmax_attention(qkv, heads, d)
     assert np.isfinite(got).all() and np.abs(got - ref).max() <= 5e-3 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# one image and few heads: the keys split over a workgroup's waves; 64 heads: 128 queries a workgroup.  Tile edges
+# of 32 and 128 on both sides, fewer keys than one wave's share, waves whose keys are all past the end.
+@pytest.mark.parametrize("B,N,heads", [(1, 31, 2), (1, 33, 2), (1, 127, 1), (1, 129, 3), (1, 300, 2),
+                                       (4, 127, 64), (4, 128, 64), (4, 129, 64), (4, 161, 64)])
+def test_softmax_attention_tiles_and_growing_scores(dtype, B, N, heads):
+    # the keys grow along the sequence, so the running maximum keeps rising and every rescale path is taken; the
+    # first query of each image is zero (equal weights)
+    d = 16
+    print(f"softmax tiles {dtype} B={B} N={N} heads={heads}", flush=True)
+    rng = np.random.default_rng(7 * N + heads)
+    qkv = rng.standard_normal((B, N, heads, 3, d))
+    qkv[:, :, :, 1] *= np.linspace(0.1, 6.0, N)[None, :, None, None]
+    qkv[:, 0, :, 0] = 0.0
+    qkv = wk.round_to_dtype(qkv.reshape(B, N, 3 * heads * d), dtype)
+    dev = torch.from_numpy(qkv).to(TDT[dtype]).cuda()
+    # (rows behind the last token must stay as they are)
+    att = torch.full((B * N + 1, heads * d), 7.0, dtype=TDT[dtype], device="cuda")
+    msla.msla_softmax_attention(dev, heads, d, att=att[:B * N].view(B, N, heads * d))
+    torch.cuda.synchronize()
+    got = att[:B * N].view(B, N, heads * d).double().cpu().numpy()
+    ref = sm.softmax_attention(qkv, heads, d)
+    assert np.isfinite(got).all() and bool((att[B * N] == 7.0).all())
+    # one rounding of the weights and one of the result: a weighted mean of V moves by at most 2 u max|V| with the
+    # type's unit roundoff u; the 32-bit sums stay far below the rest of the bar
+    u = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]
+    vmax = np.abs(qkv.reshape(B, N, heads, 3, d)[:, :, :, 2]).max()
+    assert np.abs(got - ref).max() <= 2.5 * u * vmax
