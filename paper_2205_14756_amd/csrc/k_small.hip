@@ -88,11 +88,65 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
     const int cb = blockIdx.x % n_cb;
     const long first_tile = blockIdx.x / n_cb;
     const long tile_step = gridDim.x / n_cb;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
     const int g16 = (x16 >> 1) & 7;
     const int ch0 = cb * kSmallChanBlock + wave * 16;       // this wave's 16 output channels
     const unsigned row_bytes = (unsigned)K * 2u;
+
+    // tile -> first token (in the whole map) and number of live rows
+    struct Origin {
+        long tok0;
+        int rows;
+    };
+    auto origin = [&](long tile) {
+        if constexpr (kAtt) {
+            const long b = tile / tiles_per_image;
+            const int n0 = (int)(tile - b * tiles_per_image) * kSmallTB;
+            return Origin{b * aa.N + n0, aa.N - n0 < kSmallTB ? aa.N - n0 : kSmallTB};
+        } else {
+            const long tok0 = tile * kSmallTB;
+            return Origin{tok0, n_tokens - tok0 < kSmallTB ? (int)(n_tokens - tok0) : kSmallTB};
+        }
+    };
+    // ---- a tile's rows (tokens, or Q tokens of every head-branch) in row order; rows past the last
+    // token and slots past K read zero
+    constexpr int kVecs = KC * 4 * kSmallTB / kSmallThreads;      // 16-byte vectors per thread
+    static_assert(kVecs * kSmallThreads == KC * 4 * kSmallTB, "tile copy");
+    u32x4 v[kVecs];
+    auto fetch_tile = [&](Origin o) {
+        const BufRsrc sres = make_rsrc(src + o.tok0 * K, (long)o.rows * row_bytes);
+#pragma unroll
+        for (int i = 0; i < kVecs; ++i) {
+            const int id = i * kSmallThreads + threadIdx.x;
+            const int row = id / (KC * 4), c = id - row * (KC * 4);
+            v[i] = buf_load16(sres, c * 16u < row_bytes ? row * row_bytes + c * 16u : kOobOffset, 0);
+        }
+    };
+    // ---- state operands of the wave's head-branches m = wave, wave + 8, ...: a ring of kRing, so that an
+    // attention unit does not wait for memory
+    constexpr int kUnitsM = KC / 4, kRing = 4;
+    static_assert(kUnitsM >= kRing, "ring");
+    Vec a_kv[kRing], a_ks[kRing];
+    float eps_s[kRing];
+    auto fetch_state_of = [&](long img, int i, int m) {
+        const long sid = img * aa.n_hb + (m < aa.n_hb ? m : 0);
+        a_kv[i % kRing] = __builtin_bit_cast(Vec, *(const u32x4*)(aa.kvfrag + sid * 2048 + lane * 16));
+        a_ks[i % kRing] = __builtin_bit_cast(Vec, *(const u32x4*)(aa.kvfrag + sid * 2048 + 1024 + lane * 16));
+        eps_s[i % kRing] = aa.eps * aa.kvscale[sid];
+    };
+    auto fetch_state = [&](long img, int i) { fetch_state_of(img, i, wave + 8 * i); };
+    // requested ahead of the weights: everything a workgroup's first tile waits for is in flight at once
+    // (bf16 with 32 chunks has no registers for that beside its weights: with it, 46 registers spilled and a module of
+    // 2 x 4096 tokens, 512 channels went from 88 to 126 us.  It asks for each thing where it uses it.)
+    constexpr bool kEarly = !(kHiLo && KC == 32);
+    Origin org = origin(first_tile);
+    auto fetch_first = [&]() {
+        fetch_tile(org);
+        if constexpr (kAtt && kEarly)
+            static_for<0, kRing>([&](auto i_c) { fetch_state(org.tok0 / aa.N, decltype(i_c)::value); });
+    };
+    if constexpr (kEarly) fetch_first();
 
     // ---- weights: lane (channel x16, q) ends up with w[ch0 + x16][32 kk + 8 q .. + 8] for every chunk
     // kk.  They are fetched in row order -- a wave-level load covers two rows' 512 contiguous bytes;
@@ -136,52 +190,29 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
     }
 
     for (long tile = first_tile; tile < n_tiles; tile += tile_step) {
-        // tile -> first token (in the whole map) and number of live rows
-        long tok0;
-        int rows;
-        if constexpr (kAtt) {
-            const long b = tile / tiles_per_image;
-            const int n0 = (int)(tile - b * tiles_per_image) * kSmallTB;
-            tok0 = b * aa.N + n0;
-            rows = aa.N - n0 < kSmallTB ? aa.N - n0 : kSmallTB;
-        } else {
-            tok0 = tile * kSmallTB;
-            rows = n_tokens - tok0 < kSmallTB ? (int)(n_tokens - tok0) : kSmallTB;
+        if constexpr (!kEarly) fetch_first();
+        const long tok0 = org.tok0;
+        const int rows = org.rows;
+#pragma unroll
+        for (int i = 0; i < kVecs; ++i) {
+            const int id = i * kSmallThreads + threadIdx.x;
+            const int row = id / (KC * 4), c = id - row * (KC * 4);
+            *(u32x4*)(tile_hi + (c >> 3) * kSlabBytes + row * 128 + swz(row, c & 7) * 16) = v[i];
         }
-        const BufRsrc sres = make_rsrc(src + tok0 * K, (long)rows * row_bytes);
-
-        {
-            // ---- copy the tile's rows (tokens, or Q tokens of every head-branch) in row order; rows
-            // past the last token and slots past K read zero
-            constexpr int kVecs = KC * 4 * kSmallTB / kSmallThreads;      // 16-byte vectors per thread
-            static_assert(kVecs * kSmallThreads == KC * 4 * kSmallTB, "tile copy");
-            u32x4 v[kVecs];
-#pragma unroll
-            for (int i = 0; i < kVecs; ++i) {
-                const int id = i * kSmallThreads + threadIdx.x;
-                const int row = id / (KC * 4), c = id - row * (KC * 4);
-                v[i] = buf_load16(sres, c * 16u < row_bytes ? row * row_bytes + c * 16u : kOobOffset, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < kVecs; ++i) {
-                const int id = i * kSmallThreads + threadIdx.x;
-                const int row = id / (KC * 4), c = id - row * (KC * 4);
-                *(u32x4*)(tile_hi + (c >> 3) * kSlabBytes + row * 128 + swz(row, c & 7) * 16) = v[i];
-            }
+        const bool more = tile + tile_step < n_tiles;
+        if (more) {
+            org = origin(tile + tile_step);
+            if constexpr (kEarly) fetch_tile(org);
         }
         if constexpr (kAtt) {
             // ---- attention rows (Eq. (3)), made in place: unit = (16 tokens jt, head-branch m); the
             // wave takes m = wave, wave + 8, ...  Lane (token x16, q) reads channels 4q..4q+3 of its
             // token's Q from the tile and writes the attention row's same channels where they were.
             __syncthreads();
-            const long img = tok0 / aa.N;
+            const long img = tok0 / aa.N, img_next = org.tok0 / aa.N;
             const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-            for (int m = wave; m < KC * 2; m += 8) {
+            auto unit = [&](int m, Vec s_kv, Vec s_ks, float s_eps) {
                 const bool live = m < aa.n_hb;
-                const long sid = img * aa.n_hb + (live ? m : 0);
-                const Vec a_kv = __builtin_bit_cast(Vec, *(const u32x4*)(aa.kvfrag + sid * 2048 + lane * 16));
-                const Vec a_ks = __builtin_bit_cast(Vec, *(const u32x4*)(aa.kvfrag + sid * 2048 + 1024 + lane * 16));
-                const float eps_s = aa.eps * aa.kvscale[sid];
 #pragma unroll
                 for (int jt = 0; jt < 2; ++jt) {
                     const int row = jt * 16 + x16;
@@ -190,9 +221,9 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
                     Vec b;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) { b[r] = qf[r]; b[4 + r] = qf[r]; }     // pairs with {hi, lo} of the state
-                    const f32x4 num = Tr::mma_vec(z, a_kv, b);
-                    const f32x4 den = Tr::mma_vec(z, a_ks, b);
-                    const float inv = live ? __builtin_amdgcn_rcpf(den[0] + eps_s) : 0.f;
+                    const f32x4 num = Tr::mma_vec(z, s_kv, b);
+                    const f32x4 den = Tr::mma_vec(z, s_ks, b);
+                    const float inv = live ? __builtin_amdgcn_rcpf(den[0] + s_eps) : 0.f;
                     const f32x4 o = {num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv};
                     if constexpr (kHiLo) {
                         Frag hi, lo;
@@ -202,6 +233,21 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
                     } else {
                         store_frag<T>(tile_hi + off, frag_from_f32<T>(o));
                     }
+                }
+            };
+            if constexpr (kEarly) {
+                static_for<0, kUnitsM>([&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    unit(wave + 8 * i, a_kv[i % kRing], a_ks[i % kRing], eps_s[i % kRing]);
+                    // this slot's next occupant: unit i + kRing of this tile, or of the next tile
+                    if constexpr (i + kRing < kUnitsM) fetch_state(img, i + kRing);
+                    else if (more) fetch_state(img_next, i % kRing);
+                });
+            } else {
+#pragma unroll 1
+                for (int i = 0; i < kUnitsM; ++i) {
+                    fetch_state_of(img, 0, wave + 8 * i);
+                    unit(wave + 8 * i, a_kv[0], a_ks[0], eps_s[0]);
                 }
             }
         }
@@ -239,12 +285,16 @@ hipError_t run_small(const void* src, const void* w, Dest dest, SmallAttArgs aa,
                      long n_tiles, int tiles_per_image, hipStream_t stream) {
     const int n_cb = (c_out + kSmallChanBlock - 1) / kSmallChanBlock;
     if (n_tiles <= 0 || (long)c_out * K * 2 >= 0x7fffffffL) return hipErrorInvalidValue;
-    // up to two workgroups' worth of tiles per CU at once; beyond that a workgroup walks several tiles
-    long groups = (2L * compute_units() + n_cb - 1) / n_cb;
-    if (groups > n_tiles) groups = n_tiles;
-    if (groups < 1) groups = 1;
     constexpr int kTileBytes = (KC / 2) * kSlabBytes * ((kAtt && Traits<T>::kHiLo) ? 2 : 1);
     constexpr int kLds = kTileBytes > 4 * kSmallChanBlock * 128 ? kTileBytes : 4 * kSmallChanBlock * 128;   // tile(s), or a round of weights
+    // One workgroup a CU, each walking ceil(n_tiles / groups) tiles: the weights are half of a workgroup's first tile's
+    // time, and a second round of workgroups fetches them again (2048 tokens, 512 channels, 32 + 32 heads, fp16: 34.8 us
+    // a module with one a CU, 35.6 with two where they fit, 37.1 with a grid for two and a remainder;
+    // 3 x 1961 tokens, 192 channels, 36 head-branches, bf16: 70.1 against 74.2).
+    long groups = compute_units() / n_cb;
+    if (groups < 1) groups = 1;
+    const long per = (n_tiles + groups - 1) / groups;
+    groups = (n_tiles + per - 1) / per;
     const hipError_t e = allow_dynamic_lds<small_project_kernel<T, KC, kAtt, Dest>>(kLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((small_project_kernel<T, KC, kAtt, Dest>), dim3((unsigned)(groups * n_cb)),
