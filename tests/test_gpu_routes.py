@@ -1,8 +1,11 @@
 """GPU parity at the edges of the dispatch rules: the smallest and largest shapes of each kernel variant, ragged tiles,
 workgroups that walk over several tiles and images.  Oracle, bar and protocol are those of test_gpu_parity.py."""
+import numpy as np
 import pytest
+import torch
 
 import test_gpu_parity as base
+from paper_2205_14756_amd import msla
 from paper_2205_14756_amd import workloads as wk
 
 pytestmark = pytest.mark.gpu
@@ -16,3 +19,59 @@ pytestmark = pytest.mark.gpu
 def test_long_contraction_walks_tiles_of_several_images(dtype, B, C, H, W, heads, scales):
     print(f"routes: long contraction {dtype} {B}x{C}x{H}x{W} heads={heads}", flush=True)
     base.check_module(wk.random_module(41 + heads, dtype, B, C, H, W, heads, 16, scales), dtype, heads, 16, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+# H*W a multiple of 16 bytes' elements on no, on one and on every storage type; one partial tile, several tiles
+@pytest.mark.parametrize("B,C,H,W", [(2, 32, 3, 5), (1, 48, 10, 10), (2, 80, 16, 9), (1, 64, 33, 67)])
+def test_channel_planar_layout_equals_token_major_bit_for_bit(dtype, B, C, H, W):
+    print(f"routes: planar {dtype} {B}x{C}x{H}x{W}", flush=True)
+    t = wk.random_module(5 + H, dtype, B, C, H, W, C // 16, 16, (5,))
+    x = base.dev(t["x"], dtype)
+    wdw, wg = base.weights(t, dtype, (5,))
+    w = (base.dev(t["w_qkv"], dtype), wdw, wg, base.dev(t["w_proj"], dtype))
+    want = msla.msla_forward(x, *w, C // 16, 16, (5,))
+    # (bytes around the planar result must stay as they are)
+    room = torch.full((x.numel() + 64,), 7.0, dtype=x.dtype, device="cuda")
+    out = room[32:32 + x.numel()].view(B, C, H, W)
+    msla.msla_forward(x.permute(0, 3, 1, 2).contiguous(), *w, C // 16, 16, (5,), out=out, layout=msla.MSLA_NCHW)
+    torch.cuda.synchronize()
+    assert torch.equal(out.permute(0, 2, 3, 1), want)
+    assert bool((room[:32] == 7.0).all()) and bool((room[32 + x.numel():] == 7.0).all())
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# heads of 32: few heads with many partial states each (their sum is split over waves), and one chunk only
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 96, 45, 70, 3, (3, 5)), (1, 32, 4, 9, 1, (3,))])
+def test_head_size_32_partial_state_sums(dtype, B, C, H, W, heads, scales):
+    print(f"routes: head size 32 {dtype} {B}x{C}x{H}x{W}", flush=True)
+    base.check_module(wk.random_module(61 + heads, dtype, B, C, H, W, heads, 32, scales), dtype, heads, 32, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+# 14 head-branches (the last quad half empty); one token; waves of several token groups, the last run shorter
+@pytest.mark.parametrize("B,H,W,heads", [(1, 1, 1, 7), (3, 5, 7, 7), (2, 128, 129, 7)])
+def test_core_writes_attention_rows(dtype, B, H, W, heads):
+    print(f"routes: core {dtype} {B}x{H}x{W} heads={heads}", flush=True)
+    t = wk.random_module(71 + H, dtype, B, 16 * heads, H, W, heads, 16, (3,))
+    rng = np.random.default_rng(H)
+    qkv = wk.round_to_dtype(rng.standard_normal((B, H, W, 48 * heads)), dtype)
+    wdw, wg = base.weights(t, dtype, (3,))
+    rows = B * H * W
+    room = torch.full((rows + 1, 32 * heads), 7.0, dtype=base.TDT[dtype], device="cuda")
+    msla.msla_core_forward(base.dev(qkv, dtype), wdw, wg, heads, 16, (3,), att=room[:rows].view(B, H, W, 32 * heads))
+    torch.cuda.synchronize()
+    assert bool((room[rows] == 7.0).all())
+    # the states and the stored Q tokens the same call chain leaves, applied row by row in fp64 on the CPU: one rounding of
+    # the result (unit roundoff u) on top of the 32-bit arithmetic of Eq. (3) and the state operands' 2^-16 (bf16 pairs)
+    q_ms, kv = msla.msla_multiscale_state(base.dev(qkv, dtype), wdw, wg, heads, 16, (3,))
+    q = np.maximum(base.host(q_ms).reshape(B, H * W, 2, heads, 16), 0.0)
+    kv = base.host(kv)
+    num = np.einsum("bnshe,bshef->bnshf", q, kv[..., :16])
+    den = np.einsum("bnshe,bshe->bnsh", q, kv[..., 16])[..., None] + 1e-15
+    ref = (num / den).reshape(rows, 32 * heads)
+    u = {"f32": 2.0 ** -20, "f16": 2.0 ** -10.5, "bf16": 2.0 ** -7.9}[dtype]
+    # Eq. (3) is a weighted mean of KV[e, :] / Ksum[e]: its rounding errors are relative to the largest of those
+    hull = np.abs(kv[..., :16] / np.maximum(kv[..., 16:], 1e-30)).max(axis=(3, 4))
+    bar = (u * np.broadcast_to(hull[:, None, :, :, None], num.shape)).reshape(rows, 32 * heads)
+    assert (np.abs(base.host(room[:rows]) - ref) <= bar + 1e-12).all()
