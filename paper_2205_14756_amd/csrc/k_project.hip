@@ -1,8 +1,8 @@
 // 1x1 projections  y[n, o] = sum_c x[n, c] * w[o, c]  (Section 3.1: Q = x W_Q,
 // K = x W_K, V = x W_V; also the stand-alone form of the final projection).
 // Two forms: a tiled one (256 output channels x 128 tokens per workgroup, any contraction length,
-// every storage type) and, for 16-bit types with at most 256 contraction slots, a weight-stationary
-// one that keeps the weights in registers and streams the tokens.
+// every storage type) and, for at most 256 contraction slots, a weight-stationary one that keeps the
+// weights in registers and streams the tokens.
 #include "gemm_tile.h"
 #include "msla_kernels.h"
 
@@ -375,8 +375,8 @@ __global__ __launch_bounds__(ProjTile<T>::kThreads) void project_kernel(const T*
 }
 
 // ---------------------------------------------------------------- weight-stationary form
-// When a weight row is at most 512 bytes (the contraction is short, as in this module's 1x1
-// projections), a wave keeps its 48 output channels' weights in registers for the whole kernel --
+// When the contraction is at most 256 slots (as in this module's 1x1 projections), a wave keeps its
+// output channels' weights (48 of them for the 16-bit types) in registers for the whole kernel --
 // KCH operand fragments per 16 channels -- and only the tokens stream: a workgroup of 4 waves owns
 // 192 channels and walks over token tiles of 32.  A tile is copied HBM -> registers -> LDS once
 // (double-buffered, one barrier per tile) and every wave reads all of it as MFMA operands.
@@ -386,8 +386,8 @@ __global__ __launch_bounds__(ProjTile<T>::kThreads) void project_kernel(const T*
 // by the other's matrix instructions.
 template <class T, int KCH, int IO_ = MSLA_WS_IO>
 struct WsShape {
-    static_assert(sizeof(T) == 2 && KCH % 2 == 0, "16-bit elements, whole 128-byte slabs");
-    static constexpr int kWaves = 4, kThreads = 256, kResident = MSLA_WS_RESIDENT;
+    static_assert(KCH % 2 == 0, "whole 128-byte slabs");
+    static constexpr int kWaves = 4, kThreads = 256;
     static constexpr int IO = IO_;                       // 16-channel groups per wave
     static constexpr int JT = 2;                         // 16-token groups per tile
     static constexpr int kChanWave = IO * 16, kChanBlock = kWaves * kChanWave;
@@ -399,6 +399,8 @@ struct WsShape {
     static constexpr int kWeightStage = kChanBlock * kRow;        // one slab of the workgroup's weight rows
     static constexpr int kLds = 2 * kBuf > kWeightStage ? 2 * kBuf : kWeightStage;
     static_assert(TB * 8 == kThreads, "one 16-byte vector per thread and slab");
+    // workgroups per CU that the grid is made for (fp32 with 16 channels a wave: a third where the LDS has room)
+    static constexpr int kResident = sizeof(T) == 4 && 3 * kLds <= 160 * 1024 ? 3 : MSLA_WS_RESIDENT;
 };
 
 template <class T, int KCH, int IO, class Epilogue>
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
     if (t_begin >= t_end) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
-    const unsigned row_bytes = (unsigned)c_in * 2u;
+    const unsigned row_bytes = (unsigned)c_in * (unsigned)sizeof(T);
     const int ch0 = cg * S::kChanBlock + wave * S::kChanWave;     // this wave's first channel
 
     // token tile copy: thread = (row tid/8, 16-byte chunk tid%8) of each of the NS slabs
@@ -494,22 +496,33 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
 #pragma unroll
         for (int jt = 0; jt < S::JT; ++jt) pend[io][jt] = frag_zero<T>();
     auto dest = ep.none();
-    // A fragment is 8 bytes a lane: channels 4q..4q+3 of one 16-channel block for token x16.  Two of
+    // A fragment of a 16-bit type is 8 bytes a lane: channels 4q..4q+3 of one 16-channel block for token x16.  Two of
     // them leave in one 16-byte store: the odd 16-lane groups of one are swapped with the even
     // groups of the other, after which a lane holds 8 consecutive channels.  Blocks 2m and 2m+1 of
     // the same 16 tokens pair up (the lane then has channels 32m + 16*(q%2) + 8*(q/2) .. +7 of token
     // x16); an odd block count leaves the last block, which pairs its two token groups instead
     // (channels 8*(q/2) .. +7 of token 16*(q%2) + x16).  The lane's store offsets are fixed for the
-    // kernel.
+    // kernel.  An fp32 fragment is such a 16-byte word already: one job a fragment, nothing paired.
+    constexpr bool kPaired = sizeof(T) == 2;
     constexpr int kPairs = S::IO / 2;                         // channel-block pairs per token group
-    constexpr int kJobs = S::JT * kPairs + (S::IO % 2) * (S::JT / 2);
-    static_assert(S::JT % 2 == 0 && kJobs <= KCH, "one flush job per contraction chunk at most");
-    typename Epilogue::Lane where_pair[kPairs > 0 ? kPairs : 1], where_last;
+    constexpr int kJobs = kPaired ? S::JT * kPairs + (S::IO % 2) * (S::JT / 2) : S::IO * S::JT;
+    static_assert(S::JT % 2 == 0 && (!kPaired || kJobs <= KCH), "one flush job per contraction chunk at most");
+    typename Epilogue::Lane where_pair[kPaired ? (kPairs > 0 ? kPairs : 1) : S::IO], where_last;
+    if constexpr (kPaired) {
 #pragma unroll
-    for (int m = 0; m < kPairs; ++m)
-        where_pair[m] = ep.lane(x16, ch0 + 32 * m + (q & 1) * 16 + (q >> 1) * 8, true);
-    where_last = ep.lane((q & 1) * 16 + x16, ch0 + (S::IO - 1) * 16 + (q >> 1) * 8, true);
+        for (int m = 0; m < kPairs; ++m)
+            where_pair[m] = ep.lane(x16, ch0 + 32 * m + (q & 1) * 16 + (q >> 1) * 8, true);
+        where_last = ep.lane((q & 1) * 16 + x16, ch0 + (S::IO - 1) * 16 + (q >> 1) * 8, true);
+    } else {
+#pragma unroll
+        for (int io = 0; io < S::IO; ++io) where_pair[io] = ep.lane(x16, ch0 + io * 16 + q * 4, true);
+    }
     auto flush_job = [&](int job) {
+        if constexpr (!kPaired) {
+            const int io = job / S::JT, jt = job % S::JT;
+            Epilogue::store(dest, where_pair[io], ch0 + io * 16, ch0 + io * 16 + 16, io * 16, jt * 16,
+                            __builtin_bit_cast(u32x4, pend[io][jt]));
+        } else {
         u32x2 even, odd;
         const bool last = job >= S::JT * kPairs;              // the unpaired block, two token groups
         const int jt = last ? 2 * (job - S::JT * kPairs) : job / (kPairs > 0 ? kPairs : 1);
@@ -526,6 +539,7 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
         const u32x4 v = {s0[0], s1[0], s0[1], s1[1]};
         if (last) Epilogue::store(dest, where_last, ch0 + (S::IO - 1) * 16, ch0 + S::IO * 16, (S::IO - 1) * 16, jt * 16, v);
         else Epilogue::store(dest, where_pair[m], ch0 + 32 * m, ch0 + 32 * m + 32, 32 * m, jt * 16, v);
+        }
     };
 
     park(lds);
@@ -548,9 +562,11 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
         };
         read_b(0);
         read_b(1);
+        const bool live = ch0 < c_out;         // (fp32: a wave past the last channel leaves the matrix cores to the others)
         static_for<0, KCH>([&](auto kk_c) {
             constexpr int kk = decltype(kk_c)::value;
             if constexpr (kk + 2 < KCH) read_b(kk + 2);
+            if (sizeof(T) == 2 || live)
 #pragma unroll
             for (int io = 0; io < S::IO; ++io)
 #pragma unroll
@@ -583,7 +599,7 @@ hipError_t run_project_ws(const void* x, const void* w, long n_tokens, int c_in,
     const int n_cg = (c_out + S::kChanBlock - 1) / S::kChanBlock;
     const long n_tt = (n_tokens + S::TB - 1) / S::TB;
     if (n_tt <= 0 || n_tt * n_cg > 0x7fffffffL) return hipErrorInvalidValue;
-    if ((long)c_out * c_in * 2 >= 0x7fffffffL) return hipErrorInvalidValue;
+    if ((long)c_out * c_in * (long)sizeof(T) >= 0x7fffffffL) return hipErrorInvalidValue;
     // kResident workgroups per CU; the channel groups of one token range sit next to each other
     const long slots = (long)compute_units() * S::kResident;
     const long groups = slots / n_cg > 0 ? slots / n_cg : 1;
@@ -600,25 +616,26 @@ hipError_t run_project_ws(const void* x, const void* w, long n_tokens, int c_in,
 #define MSLA_PROJ_RESIDENT 1
 #endif
 
+// fp32, weight-stationary: rows of at most 1024 bytes, 16 output channels a wave.  The fp32 matrix instructions (32 cycles
+// for 16x16x4) bound it and their operands cost the LDS little, so small pieces win: no channels of padding, and every
+// SIMD gets its share (48 channels a wave: 130 against 126 us for the module of 4 x 8192 tokens, 128 channels; two
+// resident workgroups instead of three 129).  Against the tiled form, whose 256-channel x 128-token pieces leave most of
+// the chip idle on small maps and compute padding on narrow ones: that module 140 -> 126 us (this kernel 46 -> 33),
+// 1024 tokens of 64 channels 47 -> 38, 2 x 11550 of 176 189 -> 156, 576 of 256 106 -> 77.
 template <class T, class Epilogue>
-hipError_t run_project(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
-                       hipStream_t stream) {
-    if constexpr (sizeof(T) == 2) {
-        // short contraction: weights stay in registers
-#ifndef MSLA_PROJ_NO_WS
-        if (!ep.has_residual()) {      // (the weight-stationary form has no residual path)
-            // 64 channels a wave where that divides the output and 48 does not (the FFN's expand projection:
-            // 1024 channels are four such workgroups instead of five and a third of the 48-channel kind;
-            // 42 against 57 us there, 24 against 31 at 512 channels, but 39.5 against 37 at 768), else 48
-            if (c_out % 256 == 0 && c_out % 192 != 0) {
-                if (c_in <= 128) return run_project_ws<T, 4, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-                if (c_in <= 256) return run_project_ws<T, 8, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-            }
-            if (c_in <= 128) return run_project_ws<T, 4, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-            if (c_in <= 256) return run_project_ws<T, 8, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-        }
-#endif
-    }
+hipError_t run_project_ws32(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
+                            hipStream_t stream) {
+    if (c_in <= 32) return run_project_ws<T, 2, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    if (c_in <= 64) return run_project_ws<T, 4, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    if (c_in <= 96) return run_project_ws<T, 6, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    if (c_in <= 128) return run_project_ws<T, 8, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    if (c_in <= 192) return run_project_ws<T, 12, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    return run_project_ws<T, 16, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+}
+
+template <class T, class Epilogue>
+hipError_t run_project_tiled(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
+                             hipStream_t stream) {
     typedef ProjTile<T> G;
     const int n_rb = (c_out + G::BR - 1) / G::BR;
     const long n_cb = (n_tokens + G::BC - 1) / G::BC;
@@ -637,6 +654,33 @@ hipError_t run_project(const void* x, const void* w, long n_tokens, int c_in, in
     hipLaunchKernelGGL((project_kernel<T, Epilogue>), dim3((unsigned)nblocks), dim3(G::kThreads), kLds, stream,
                        (const T*)x, (const T*)w, n_tokens, c_in, c_out, n_rb, n_tiles, per, ep);
     return hipGetLastError();
+}
+
+template <class T, class Epilogue>
+hipError_t run_project(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
+                       hipStream_t stream) {
+    if constexpr (sizeof(T) == 4) {
+        if (!ep.has_residual()) {
+            if (c_in <= 256) return run_project_ws32<T>(x, w, n_tokens, c_in, c_out, ep, stream);
+        }
+    }
+    if constexpr (sizeof(T) == 2) {
+        // short contraction: weights stay in registers
+#ifndef MSLA_PROJ_NO_WS
+        if (!ep.has_residual()) {      // (the weight-stationary form has no residual path)
+            // 64 channels a wave where that divides the output and 48 does not (the FFN's expand projection:
+            // 1024 channels are four such workgroups instead of five and a third of the 48-channel kind;
+            // 42 against 57 us there, 24 against 31 at 512 channels, but 39.5 against 37 at 768), else 48
+            if (c_out % 256 == 0 && c_out % 192 != 0) {
+                if (c_in <= 128) return run_project_ws<T, 4, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+                if (c_in <= 256) return run_project_ws<T, 8, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+            }
+            if (c_in <= 128) return run_project_ws<T, 4, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+            if (c_in <= 256) return run_project_ws<T, 8, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+        }
+#endif
+    }
+    return run_project_tiled<T>(x, w, n_tokens, c_in, c_out, ep, stream);
 }
 
 }  // namespace
@@ -687,9 +731,13 @@ hipError_t run_qkv_project(const void* x, const void* w_qkv, void* q_ms, long q_
         if (c_in <= 256) return run_project_ws<T, 8, 3, QkvHeadDest<T>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
     }
 #endif
-    return run_project<T>(x, w_qkv, n_tokens, c_in, c_out,
-                          QkvSplitDest<T>{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span,
-                                          n_tokens, heads * 16}, stream);
+    if constexpr (sizeof(T) == 4) {
+        const QkvSplitDest<T> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
+        if (c_in <= 256) return run_project_ws32<T>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
+    }
+    return run_project_tiled<T>(x, w_qkv, n_tokens, c_in, c_out,
+                                QkvSplitDest<T>{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span,
+                                                n_tokens, heads * 16}, stream);
 }
 
 hipError_t launch_qkv_project(int dt, const void* x, const void* w_qkv, void* q_ms, long q_ms_stride,
