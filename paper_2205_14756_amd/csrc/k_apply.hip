@@ -711,6 +711,206 @@ hipError_t run_apply_project_ws(const void* q_ms, const void* kvfrag, const floa
     return hipGetLastError();
 }
 
+// ------------------------------------------- att fused into projection, fp32, weight-stationary
+// fp32 storage, contractions of at most 512 slots (n_hb <= 32).  The fp32 matrix instructions bound it (32 cycles for
+// 16x16x4), as in the fp32 projection: small pieces, so that every SIMD has its share and nothing is padded.  A workgroup
+// of W waves owns W*16 output channels -- a wave keeps its 16 channels' weights in registers, KCH fragments of 16 slots --
+// and walks over tiles of JT*16 tokens of one image.  Per tile every wave makes attention rows: unit (16 tokens, head-branch
+// m) is four matrix instructions with the state from LDS; the denominator is a dot product on the vector ALU, whose
+// partial sums cross the lane groups in two register swaps (with the Ksum rows of channel 0 and of channel 8: they differ
+// where a state is two heads of 8 side by side).  Rows go to one of two LDS tiles, so there is one barrier a
+// tile; Q is requested a tile ahead.  (The tiled kernel's 256-channel x 64- or 128-token pieces leave most of the chip idle
+// on small maps and compute channels that are not there; its denominators are matrix instructions as well.)
+// Whole modules, this kernel against the tiled one: 1024 tokens, 64 channels, 8 head-branches 37.7 -> 27.7 us; 576, 256, 32
+// 77 -> 39; 4 x 8192, 128, 16 126 -> 114; 2 x 4096, 256, 32 113 -> 99; 2 x 11550, 176, 22 156 -> 158.  Tiles of 32 tokens:
+// 0.5-3 us more on the small ones, 1 us less on the largest.
+// LDS tile: [token][KCH*16 slots], rows unpadded, the 16-byte chunk index XOR-ed with token % 8: an operand read (16 tokens,
+// one chunk each) and an attention row's store (the same) touch every bank once per eight lanes.
+template <int KCH, int W, int JT>
+struct Ws32Apply {
+    static constexpr int kThreads = W * 64, TB = JT * 16, kHb = KCH;
+    static constexpr int kRow = KCH * 64;
+    static constexpr int kTile = TB * kRow;
+    static constexpr int kState = 1024 + 128;             // KV operand (64 lanes x 16 bytes), then two rows of 16 Ksum
+    static constexpr int kStates = kHb * kState;
+    static constexpr int kLds = 2 * kTile + kStates;
+    static constexpr int kUnits = (JT * kHb + W - 1) / W; // attention units a wave, at most
+    // resident waves a SIMD: what the registers (4 KCH of weights) and the LDS allow, in whole workgroups
+    static constexpr int kByRegs = KCH <= 8 ? 4 : KCH <= 16 ? 3 : 2;
+    static constexpr int kResident = 160 * 1024 / kLds < kByRegs * 4 / W ? 160 * 1024 / kLds : kByRegs * 4 / W;
+    static_assert(kResident >= 1, "one workgroup fits a CU");
+};
+
+template <int KCH, int W, int JT>
+__global__ __launch_bounds__(W * 64, (Ws32Apply<KCH, W, JT>::kResident * W / 4)) void apply_project_ws32_kernel(const float* __restrict__ q_ms,
+                                                                    const char* __restrict__ kvfrag,
+                                                                    const float* __restrict__ w_proj, float* __restrict__ out,
+                                                                    int N, int n_hb, int c_out, int n_cg, int tiles_per_image,
+                                                                    long n_tt, long tiles_per_block, float eps,
+                                                                    const float* __restrict__ res) {
+    typedef Ws32Apply<KCH, W, JT> S;
+    typedef Traits<float> Tr;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    char* const states = lds + 2 * S::kTile;
+
+    const unsigned L = xcd_remap(blockIdx.x, gridDim.x);
+    const int cg = (int)(L % (unsigned)n_cg);
+    const long t_begin = (long)(L / (unsigned)n_cg) * tiles_per_block;
+    const long t_end = t_begin + tiles_per_block < n_tt ? t_begin + tiles_per_block : n_tt;
+    if (t_begin >= t_end) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
+    const int K = n_hb * 16;
+    const int ch0 = cg * W * 16 + wave * 16;
+    const bool live = ch0 < c_out;
+    const int units = JT * n_hb;
+
+    // this wave's Q fragments of a tile: units wave, wave + W, ... (unit = m * JT + jt).  A token past the image's end reads
+    // the last one; it is never stored.
+    f32x4 qv[S::kUnits];
+    auto fetch_q = [&](long t) {
+        const int b = (int)(t / tiles_per_image), n0 = (int)(t % tiles_per_image) * S::TB;
+#pragma unroll
+        for (int i = 0; i < S::kUnits; ++i) {
+            const int u = wave + i * W;
+            if (u < units) {
+                const int n = n0 + (u % JT) * 16 + x16;
+                qv[i] = *(const f32x4*)(q_ms + ((long)b * N + (n < N ? n : N - 1)) * K + (u / JT) * 16 + q * 4);
+            }
+        }
+    };
+    fetch_q(t_begin);
+
+    // weights: lane (channel x16, q) holds slots 16 kk + 4q .. + 3 of its channel; slots past K are zero
+    f32x4 wf[KCH];
+    {
+        const float* row = w_proj + (long)(ch0 + x16 < c_out ? ch0 + x16 : c_out - 1) * K + q * 4;
+#pragma unroll
+        for (int kk = 0; kk < KCH; ++kk) wf[kk] = kk < n_hb ? *(const f32x4*)(row + kk * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    int img = -1;
+    auto load_states = [&](int b) {
+        img = b;
+        for (int i = threadIdx.x; i < n_hb * 72; i += S::kThreads) {
+            const int m = i / 72, c = i % 72;
+            const long sid = (long)b * n_hb + m;
+            // (row f of the Ksum operand: quarter q sits in lane 16q + f)
+            *(u32x4*)(states + m * S::kState + c * 16) =
+                *(const u32x4*)(kvfrag + sid * 2048 + (c < 64 ? c * 16 : 1024 + (c & 3) * 256 + (c < 68 ? 0 : 128)));
+        }
+    };
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    const int sw = x16 & 7;
+    // attention rows of the tile whose Q is in qv -> LDS tile at byte offset `to`
+    auto make_rows = [&](int b, int to) {
+#pragma unroll
+        for (int i = 0; i < S::kUnits; ++i) {
+            const int u = wave + i * W;
+            if (u < units) {
+                const int m = u / JT, jt = u % JT;
+                const char* st = states + m * S::kState;
+                const f32x4 kv = *(const f32x4*)(st + lane * 16);
+                const f32x4 ka = *(const f32x4*)(st + 1024 + q * 16), kb = *(const f32x4*)(st + 1024 + 64 + q * 16);
+                const f32x4 qf = frag_relu<float>(qv[i]);
+                const f32x4 num = Tr::mma16(z, kv, qf);
+                // this lane's quarter of the dot products, then lanes 0..31 add up the first over the lane groups, lanes
+                // 32..63 (channels 8..15) the second
+                const float da = (qf[0] * ka[0] + qf[1] * ka[1]) + (qf[2] * ka[2] + qf[3] * ka[3]);
+                const float db = (qf[0] * kb[0] + qf[1] * kb[1]) + (qf[2] * kb[2] + qf[3] * kb[3]);
+                const u32x2 s32 = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, da),
+                                                                   __builtin_bit_cast(unsigned, db), false, false);
+                const unsigned a0 = s32[0], a1 = s32[1];
+                const unsigned half = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1));
+                const u32x2 s16 = __builtin_amdgcn_permlane16_swap(half, half, false, false);
+                const unsigned b0 = s16[0], b1 = s16[1];
+                const float den = __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+                const float inv = 1.0f / (den + eps);       // (fp32 states are not rescaled)
+                *(f32x4*)(lds + to + (jt * 16 + x16) * S::kRow + ((m * 4 + q) ^ sw) * 16) =
+                    f32x4{num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv};
+            }
+        }
+    };
+
+    // slots past K are read with zero weights: they must hold numbers
+    for (int i = threadIdx.x; i < 2 * S::TB * (KCH - n_hb) * 4; i += S::kThreads) {
+        const int row = i / ((KCH - n_hb) * 4), c = n_hb * 4 + i % ((KCH - n_hb) * 4);
+        *(u32x4*)(lds + row * S::kRow + (c ^ (row & 7)) * 16) = u32x4{0u, 0u, 0u, 0u};
+    }
+    load_states((int)(t_begin / tiles_per_image));
+    __syncthreads();
+    make_rows(img, 0);
+    for (long t = t_begin; t < t_end; ++t) {
+        const int here = (int)((t - t_begin) & 1) * S::kTile, next = S::kTile - here;
+        const bool more = t + 1 < t_end;
+        if (more) fetch_q(t + 1);
+        __syncthreads();                    // rows of tile t complete; nobody reads the other tile any more
+        const int b = (int)(t / tiles_per_image), n0 = (int)(t % tiles_per_image) * S::TB;
+        f32x4 acc[JT];
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) acc[jt] = z;
+        if (live) {
+#pragma unroll
+            for (int kk = 0; kk < KCH; ++kk)
+#pragma unroll
+                for (int jt = 0; jt < JT; ++jt)
+                    acc[jt] = Tr::mma16(acc[jt], wf[kk], *(const f32x4*)(lds + here + (jt * 16 + x16) * S::kRow + ((kk * 4 + q) ^ sw) * 16));
+        }
+        if (more) {
+            const int b_next = (int)((t + 1) / tiles_per_image);
+            if (b_next != img) {            // (the same for every wave; the old states were last read before the barrier above)
+                load_states(b_next);
+                __syncthreads();
+            }
+            make_rows(b_next, next);
+        }
+        if (live) {
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) {
+                const int n = n0 + jt * 16 + x16, oc = ch0 + q * 4;
+                if (n < N) {
+                    const long at = ((long)b * N + n) * c_out + oc;
+                    f32x4 v = acc[jt];
+                    if (res != nullptr) v += *(const f32x4*)(res + at);
+                    *(f32x4*)(out + at) = v;
+                }
+            }
+        }
+    }
+}
+
+template <int KCH, int W, int JT>
+hipError_t run_apply_project_ws32(const void* q_ms, const void* kvfrag, const void* w_proj, void* out,
+                                  const void* res, long n_tokens, int N, int n_hb, int c_out, float eps, hipStream_t stream) {
+    typedef Ws32Apply<KCH, W, JT> S;
+    const int n_cg = (c_out + W * 16 - 1) / (W * 16);
+    const int tiles_per_image = (N + S::TB - 1) / S::TB;
+    const long n_tt = (n_tokens / N) * tiles_per_image;
+    if (n_tt <= 0 || n_tt * n_cg > 0x7fffffffL) return hipErrorInvalidValue;
+    const long slots = (long)compute_units() * S::kResident;
+    const long groups = slots / n_cg > 0 ? slots / n_cg : 1;
+    const long tiles_per_block = (n_tt + groups - 1) / groups;
+    const long nblocks = (n_tt + tiles_per_block - 1) / tiles_per_block * n_cg;
+    const hipError_t e = allow_dynamic_lds<apply_project_ws32_kernel<KCH, W, JT>>(S::kLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((apply_project_ws32_kernel<KCH, W, JT>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds, stream,
+                       (const float*)q_ms, (const char*)kvfrag, (const float*)w_proj, (float*)out, N, n_hb, c_out, n_cg,
+                       tiles_per_image, n_tt, tiles_per_block, eps, (const float*)res);
+    return hipGetLastError();
+}
+
+template <int KCH>
+hipError_t run_apply_project_f32(const void* q_ms, const void* kvfrag, const void* w_proj, void* out, const void* res,
+                                 long n_tokens, int N, int n_hb, int c_out, float eps, hipStream_t stream) {
+    // 128 channels a workgroup (the attention rows are made once per channel group: 64 takes 122.8 instead of 114.0 us for
+    // the module of 4 x 8192 tokens, 128 channels), except where that leaves half of the compute units without one and
+    // there are channels to spread (576 tokens, 256 channels: 42.1 us with 128, 39.0 with 64)
+    const long tiles = (n_tokens / N) * ((N + 15) / 16);
+    if (c_out > 64 && 2 * tiles * ((c_out + 127) / 128) < compute_units())
+        return run_apply_project_ws32<KCH, 4, 1>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+    return run_apply_project_ws32<KCH, 8, 1>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+}
+
 template <class T>
 hipError_t run_apply(const void* q_ms, const void* kvfrag, const float* kvscale, void* att, long n_tokens,
                      int N, int n_hb, float eps, hipStream_t stream) {
@@ -769,6 +969,12 @@ hipError_t run_apply_project(const void* q_ms, const void* kvfrag, const float* 
         }
     }
 #endif
+    if constexpr (sizeof(T) == 4) {
+        if (n_hb <= 8) return run_apply_project_f32<8>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+        if (n_hb <= 16) return run_apply_project_f32<16>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+        if (n_hb <= 24) return run_apply_project_f32<24>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+        if (n_hb <= 32) return run_apply_project_f32<32>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+    }
     // Tiled form: 64 x 64 per wave, 256 channels x 128 tokens per workgroup; a map too small to give
     // every CU such a tile takes 64-token tiles (measured on the 2048- and 1024-token workloads: 33
     // against 45 us and 17 against 25 us; still smaller workgroups were slower again)
