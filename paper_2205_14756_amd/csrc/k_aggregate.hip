@@ -38,10 +38,17 @@ struct AggLds {
     static constexpr int P = (KS - 1) / 2;
     static constexpr int LH = TH + 2 * P, LW = TW + 2 * P;
     // One map (Q, K or V: 16 channels) of the halo tile at a time, two buffers: the next map is fetched while
-    // the current one is swept.  16 channels + 8 bytes a pixel: the strip stride (4 pixels) is then 8 banks
-    // mod 32, which spreads the 64 lanes' 8-byte reads over the banks.
-    static constexpr int kPixBytes = 16 * (int)sizeof(T) + 8;
-    static constexpr int kMapBytes = LH * LW * kPixBytes;
+    // the current one is swept.  A map is four planes, one per channel quad, of one slot (4 elements) a pixel, so a
+    // fragment is one 16-byte (8-byte) read.  The sixteen lanes that a read serves together are eight strips (4 slots
+    // apart) of two tile rows: a slot is skipped every 16 columns and a tile row is 2 slots mod 4, which gives them
+    // sixteen different slots mod 16.  (With the quads of a pixel side by side, at 72 bytes a pixel, 62 % of the LDS'
+    // active cycles were bank conflicts in fp32.)  Planes are 4 slots mod 16 apart, for the staging stores.
+    static constexpr int kSlot = 4 * (int)sizeof(T);
+    static constexpr int kRowSlots = (LW + (LW - 1) / 16 + 1) / 4 * 4 + 2;
+    static constexpr int kPlane = ((LH * kRowSlots + 11) / 16 * 16 + 4) * kSlot;
+    static constexpr int kMapBytes = 4 * kPlane;
+    static __device__ __forceinline__ int at(int row, int col) { return (row * kRowSlots + col + (col >> 4)) * kSlot; }
+    static_assert(kRowSlots >= LW + (LW - 1) / 16 && kPlane >= LH * kRowSlots * kSlot, "pixels fit");
     static constexpr int kTileBytes = 2 * kMapBytes;
     static constexpr int kWtsBytes = 3 * KS * KS * 16 * 4;     // fp32 [t][tap][16 ch]
     static constexpr int kRedBytes = 4 * (2 * 256 + 2 * 16) * 4;   // per wave: 2 x 64 lanes x 4 + 2 x 16 Ksum
@@ -118,33 +125,52 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
     constexpr int kItems = L::LH * L::LW * VPT;
     constexpr int kPer = (kItems + kAggThreads - 1) / kAggThreads;
     u32x4 pre[kPer];
+    // this thread's pixels of a halo tile: row and column in it (a row no image has for those past the last)
+    int item_y[kPer], item_x[kPer];
+    const int item_v = threadIdx.x % VPT;
+    static_assert(kAggThreads % VPT == 0, "a thread keeps its channels");
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int it = threadIdx.x + j * kAggThreads, pix = it / VPT;
+        item_y[j] = it < kItems ? pix / L::LW : 1 << 30;
+        item_x[j] = pix % L::LW;
+    }
     auto fetch = [&](int tile_id, int pass) {
         const int ty0 = (tile_id / tiles_x) * TH, tx0 = (tile_id % tiles_x) * TW;
         const T* base = pass == 0 ? maps.k : pass == 1 ? maps.v : maps.q;
         const long ts = pass == 0 ? maps.k_ts : pass == 1 ? maps.v_ts : maps.q_ts;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const int it = threadIdx.x + j * kAggThreads;
-            const int vi = it % VPT, pix = it / VPT;
-            const int ly = pix / L::LW, lx = pix - ly * L::LW;
-            const int gy = ty0 - P + ly, gx = tx0 - P + lx;
+            const int gy = ty0 - P + item_y[j], gx = tx0 - P + item_x[j];
             u32x4 val = {0u, 0u, 0u, 0u};
-            if (it < kItems && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W)
-                val = *(const u32x4*)(base + (img_tok0 + (long)gy * a.W + gx) * ts + vi * Tr::kVec);
+            if ((unsigned)gy < (unsigned)a.H && (unsigned)gx < (unsigned)a.W)
+                val = *(const u32x4*)(base + (img_tok0 + (long)gy * a.W + gx) * ts + item_v * Tr::kVec);
             pre[j] = val;
         }
     };
     auto stash = [&](char* buf) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const int it = threadIdx.x + j * kAggThreads;
-            if (it < kItems) {
-                const int vi = it % VPT, pix = it / VPT;
-                char* dst = buf + pix * L::kPixBytes + vi * 16;
-                ((u32x2*)dst)[0] = u32x2{pre[j][0], pre[j][1]};
-                ((u32x2*)dst)[1] = u32x2{pre[j][2], pre[j][3]};
+            if (item_y[j] < L::LH) {
+                char* dst = buf + item_v * (4 / VPT) * L::kPlane + L::at(item_y[j], item_x[j]);
+                if constexpr (SZ == 4) {
+                    *(u32x4*)dst = pre[j];
+                } else {
+                    *(u32x2*)dst = u32x2{pre[j][0], pre[j][1]};
+                    *(u32x2*)(dst + L::kPlane) = u32x2{pre[j][2], pre[j][3]};
+                }
             }
         }
+    };
+    // this lane's strip: byte offset of its pixels 4j .. 4j+3 (columns scol + 4j ..) in a tile row of its plane
+    constexpr int kQuads = (4 + KS - 1 + 3) / 4;
+    int lane_at[kQuads];
+#pragma unroll
+    for (int j = 0; j < kQuads; ++j) lane_at[j] = q * L::kPlane + L::at(srow, scol + 4 * j);
+    auto pixel = [&](const char* src, int u, int c) {       // row srow + u, column scol + c
+        const char* p = src + lane_at[c >> 2] + (u * L::kRowSlots + (c & 3)) * L::kSlot;
+        if constexpr (SZ == 4) return __builtin_bit_cast(Frag, *(const u32x4*)p);
+        else return __builtin_bit_cast(Frag, *(const u32x2*)p);
     };
     int cur = 0;
     if (tile_begin < tile_end) {
@@ -173,20 +199,20 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
                 for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
             const bool more = pass < 2 || tile_id + 1 < tile_end;
             if (more) fetch(pass < 2 ? tile_id : tile_id + 1, pass < 2 ? pass + 1 : 0);
-            const char* src = tile + cur * L::kMapBytes + q * 4 * SZ;
+            const char* src = tile + cur * L::kMapBytes;
             const float* wt = wts + t * KS * KS * 16 + q * 4;
             // raw tokens of the strip (the centre tap), for the raw branch / the raw-Q copy
             Frag center[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                center[r] = load_frag<T>(src + ((srow + P) * L::LW + scol + r + P) * L::kPixBytes);
+                center[r] = pixel(src, P, r + P);
             // one filter row per iteration: 4+KS-1 pixels feed 4 tokens x KS taps x 4 channels
 #pragma unroll 1
             for (int u = 0; u < KS; ++u) {
                 Frag rowv[4 + KS - 1];
 #pragma unroll
                 for (int c = 0; c < 4 + KS - 1; ++c)
-                    rowv[c] = load_frag<T>(src + ((srow + u) * L::LW + scol + c) * L::kPixBytes);
+                    rowv[c] = pixel(src, u, c);
 #pragma unroll
                 for (int v = 0; v < KS; ++v) {
                     const f32x4 w4 = *(const f32x4*)(wt + (u * KS + v) * 16);
