@@ -60,6 +60,7 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     long target_blocks = 1024;
     if (n_scales > 0 && dt == MSLA_F32) {
         tiles = (long)((H + msla::kAggTileH - 1) / msla::kAggTileH) * ((W + msla::kAggTileW - 1) / msla::kAggTileW);
+        target_blocks = 512;   // two resident workgroups a CU (4 x 8192 tokens, 8 heads: 1024 104.5 us a module, 512 99.9, 256 108)
     } else if (n_scales > 0) {
         tiles = (long)((H + msla::kAggMfmaTileH - 1) / msla::kAggMfmaTileH) *
                 ((W + msla::kAggMfmaTileW - 1) / msla::kAggMfmaTileW);
