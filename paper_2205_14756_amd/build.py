@@ -21,7 +21,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
 # kernels whose MFMA results are consumed by vector instructions right away: let the matrix
 # instructions write VGPRs instead of AGPRs (saves one copy per result register)
 PER_SOURCE = {"k_aggregate_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-              "k_aggregate.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+              "k_aggregate.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "k_aggregate32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

@@ -38,17 +38,10 @@ struct AggLds {
     static constexpr int P = (KS - 1) / 2;
     static constexpr int LH = TH + 2 * P, LW = TW + 2 * P;
     // One map (Q, K or V: 16 channels) of the halo tile at a time, two buffers: the next map is fetched while
-    // the current one is swept.  A map is four planes, one per channel quad, of one slot (4 elements) a pixel, so a
-    // fragment is one 16-byte (8-byte) read.  The sixteen lanes that a read serves together are eight strips (4 slots
-    // apart) of two tile rows: a slot is skipped every 16 columns and a tile row is 2 slots mod 4, which gives them
-    // sixteen different slots mod 16.  (With the quads of a pixel side by side, at 72 bytes a pixel, 62 % of the LDS'
-    // active cycles were bank conflicts in fp32.)  Planes are 4 slots mod 16 apart, for the staging stores.
-    static constexpr int kSlot = 4 * (int)sizeof(T);
-    static constexpr int kRowSlots = (LW + (LW - 1) / 16 + 1) / 4 * 4 + 2;
-    static constexpr int kPlane = ((LH * kRowSlots + 11) / 16 * 16 + 4) * kSlot;
-    static constexpr int kMapBytes = 4 * kPlane;
-    static __device__ __forceinline__ int at(int row, int col) { return (row * kRowSlots + col + (col >> 4)) * kSlot; }
-    static_assert(kRowSlots >= LW + (LW - 1) / 16 && kPlane >= LH * kRowSlots * kSlot, "pixels fit");
+    // the current one is swept (HaloPlanes; with the quads of a pixel side by side, at 72 bytes a pixel, 62 % of the LDS'
+    // active cycles were bank conflicts in fp32).
+    typedef HaloPlanes<LH, LW, (int)sizeof(T), 4> Planes;
+    static constexpr int kMapBytes = 4 * Planes::kPlane;
     static constexpr int kTileBytes = 2 * kMapBytes;
     static constexpr int kWtsBytes = 3 * KS * KS * 16 * 4;     // fp32 [t][tap][16 ch]
     static constexpr int kRedBytes = 4 * (2 * 256 + 2 * 16) * 4;   // per wave: 2 x 64 lanes x 4 + 2 x 16 Ksum
@@ -152,12 +145,12 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             if (item_y[j] < L::LH) {
-                char* dst = buf + item_v * (4 / VPT) * L::kPlane + L::at(item_y[j], item_x[j]);
+                char* dst = buf + item_v * (4 / VPT) * L::Planes::kPlane + L::Planes::at(item_y[j], item_x[j]);
                 if constexpr (SZ == 4) {
                     *(u32x4*)dst = pre[j];
                 } else {
                     *(u32x2*)dst = u32x2{pre[j][0], pre[j][1]};
-                    *(u32x2*)(dst + L::kPlane) = u32x2{pre[j][2], pre[j][3]};
+                    *(u32x2*)(dst + L::Planes::kPlane) = u32x2{pre[j][2], pre[j][3]};
                 }
             }
         }
@@ -166,9 +159,9 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
     constexpr int kQuads = (4 + KS - 1 + 3) / 4;
     int lane_at[kQuads];
 #pragma unroll
-    for (int j = 0; j < kQuads; ++j) lane_at[j] = q * L::kPlane + L::at(srow, scol + 4 * j);
+    for (int j = 0; j < kQuads; ++j) lane_at[j] = q * L::Planes::kPlane + L::Planes::at(srow, scol + 4 * j);
     auto pixel = [&](const char* src, int u, int c) {       // row srow + u, column scol + c
-        const char* p = src + lane_at[c >> 2] + (u * L::kRowSlots + (c & 3)) * L::kSlot;
+        const char* p = src + lane_at[c >> 2] + (u * L::Planes::kRowSlots + (c & 3)) * L::Planes::kSlot;
         if constexpr (SZ == 4) return __builtin_bit_cast(Frag, *(const u32x4*)p);
         else return __builtin_bit_cast(Frag, *(const u32x2*)p);
     };

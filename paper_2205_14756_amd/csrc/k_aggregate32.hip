@@ -13,6 +13,11 @@
 // channels of its own token, and the raw branch rides along through an identity matrix, which is exact.
 // Operand precision as in the head-size-16 kernel: depthwise sums and aggregated K/V as hi + lo pairs for
 // bf16; for fp16 the Q sums as hi + lo, the K and V operands rounded once.
+// What bounds it is the vector ALU (two thirds of a SIMD's cycles with two waves on it).  Two waves a SIMD is what the
+// register plan is for: the grouped 1x1 operands and the raw tokens are read from LDS where they are used, a filter row's
+// pixels and taps are not read ahead, matrix results go to ordinary registers (compiler flag).  8 x 8 heads, 64 x 128
+// tokens, fp16: this kernel 136 -> 85 us, the module 239 -> 193; with one wave a SIMD and 388 registers, half of them on
+// their way between register files, the reads ahead did not hide what a second wave does.
 // Per-workgroup partial states [32][33] go to the buffer that the plain finalize kernel sums in a fixed order.
 #include "msla_device.h"
 #include "msla_kernels.h"
@@ -29,26 +34,28 @@ template <class T, int KS>
 struct Agg32Lds {
     static constexpr int P = (KS - 1) / 2;
     static constexpr int LH = TH + 2 * P, LW = TW + 2 * P;
-    // One map (Q, K or V: 32 channels) of the halo tile at a time, two buffers: the next map is fetched while
-    // the current one is swept, and two workgroups fit a CU.  32 channels + 8 bytes a pixel: a strip (4
-    // pixels) is then 72 words on, 8 banks mod 32 (see lane_at in the kernel for the banks' low bits).
-    static constexpr int kPixBytes = D32 * (int)sizeof(T) + 8;
-    static constexpr int kMapBytes = LH * LW * kPixBytes;
+    // One map (Q, K or V: 32 channels = eight quads) of the halo tile at a time, two buffers: the next map is fetched while
+    // the current one is swept.
+    typedef HaloPlanes<LH, LW, (int)sizeof(T), 2> Planes;
+    static constexpr int kMapBytes = 2 * 4 * Planes::kPlane;
     static constexpr int kTileBytes = 2 * kMapBytes;
-    static constexpr int kWtsBytes = 3 * KS * KS * D32 * 4;          // fp32 [t][tap][32 ch]
+    // filter taps [t][tap][32 ch]: fp16 as they are (the multiply-add takes them), bf16 widened
+    typedef typename std::conditional<std::is_same<T, _Float16>::value, _Float16, float>::type Tap;
+    static constexpr int kWtsBytes = 3 * KS * KS * D32 * (int)sizeof(Tap);
+    static constexpr int kGpwBytes = 3 * NB * NB * 64 * 8;           // grouped 1x1 operands [t][out block][in block][lane]
     // per wave: [branch][K block][V block][lane] accumulator quads, then [branch][32] Ksum
     static constexpr int kWaveFloats = 2 * NB * NB * 256 + 2 * D32;
     static constexpr int kRedBytes = 4 * kWaveFloats * 4;
-    static constexpr int kBytes = (kTileBytes > kRedBytes ? kTileBytes : kRedBytes) + kWtsBytes;
+    static constexpr int kBytes = (kTileBytes > kRedBytes ? kTileBytes : kRedBytes) + kWtsBytes + kGpwBytes;
+    // waves a SIMD: two workgroups a CU where the LDS allows it
+    static constexpr int kWaves = 2 * kBytes <= 160 * 1024 ? 2 : 1;
 };
 
-// (build knob, for experiments: waves a SIMD the register allocation is held to; 1 = no cap)
-#ifndef MSLA_AGG32_WAVES
-#define MSLA_AGG32_WAVES 1
-#endif
-
-template <class T, int KS>
-__global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kernel(AggregateArgs a) {
+// kRaw: the raw branch rides along (its state and the copy of its Q).  A template argument and not a run-time branch: with
+// the branch, the compiler (ROCm 7.2) left out the wait states between a matrix instruction before it and the conversion of
+// its result behind it, on the path that skips the raw branch, and the second V block of the state came out wrong.
+template <class T, int KS, bool kRaw>
+__global__ __launch_bounds__(kThreads32, (Agg32Lds<T, KS>::kWaves)) void aggregate32_kernel(AggregateArgs a) {
     static_assert(sizeof(T) == 2, "16-bit storage types");
     typedef Traits<T> Tr;
     typedef typename Tr::Frag Frag;
@@ -57,7 +64,9 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
     constexpr int SZ = (int)sizeof(T);
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* tile = lds;
-    float* wts = (float*)(lds + (L::kBytes - L::kWtsBytes));
+    typedef typename L::Tap Tap;
+    Tap* wts = (Tap*)(lds + (L::kBytes - L::kWtsBytes - L::kGpwBytes));
+    char* gpw_lds = lds + (L::kBytes - L::kGpwBytes);
     float* red = (float*)lds;   // reused after the last tile
 
     const unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
@@ -71,24 +80,22 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
     const int x16 = lane & 15, q = lane >> 4;
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 
-    // depthwise filters of this head -> LDS as fp32 [t][tap][32]
+    // depthwise filters of this head -> LDS as [t][tap][32]
     {
         const T* wdw = (const T*)a.w_dw + (long)h * 3 * D32 * KS * KS;
         for (int it = threadIdx.x; it < 3 * D32 * KS * KS; it += kThreads32) {
             const int ch = it / (KS * KS), tap = it - ch * (KS * KS);
-            wts[((ch / D32) * KS * KS + tap) * D32 + (ch % D32)] = Tr::to_f32(wdw[it]);
+            wts[((ch / D32) * KS * KS + tap) * D32 + (ch % D32)] = (Tap)wdw[it];
         }
     }
     // grouped 1x1 weights of (h, t), block (out ob, in ib), as an MFMA operand: lane (o, q) holds
-    // w[ob*16 + o][ib*16 + 4q .. 4q+3]
-    Frag gpw[3][NB][NB];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-            for (int ib = 0; ib < NB; ++ib)
-                gpw[t][ob][ib] = load_frag<T>((const T*)a.w_gpw + ((long)(h * 3 + t) * D32 + ob * 16 + x16) * D32 + ib * 16 + q * 4);
+    // w[ob*16 + o][ib*16 + 4q .. 4q+3].  They wait in LDS: in registers they would cost the second wave of the SIMD.
+    for (int it = wave; it < 3 * NB * NB; it += 4) {
+        const int t = it / (NB * NB), ob = (it / NB) % NB, ib = it % NB;
+        store_frag<T>(gpw_lds + (it * 64 + lane) * 8,
+                      load_frag<T>((const T*)a.w_gpw + ((long)(h * 3 + t) * D32 + ob * 16 + x16) * D32 + ib * 16 + q * 4));
+    }
+    auto gpw = [&](int t, int ob, int ib) { return load_frag<T>(gpw_lds + (((t * NB + ob) * NB + ib) * 64 + lane) * 8); };
     Frag ident;
 #pragma unroll
     for (int r = 0; r < 4; ++r) ident[r] = Tr::from_f32(x16 == q * 4 + r ? 1.0f : 0.0f);
@@ -114,16 +121,14 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
     // this lane's strip inside the tile
     const int srow = wave * 2 + (x16 >> 3);
     const int scol = (x16 & 7) * 4;
-    // Byte offset of pixel scol + c inside a tile row, this lane's channel quad included.  The two 16-byte
-    // halves of every 32 bytes of a pixel are swapped in pixels whose column has bit 4 set: the 32 lanes
-    // that an 8-byte read serves together (q = 0, 1) would otherwise use half of the banks twice (a
-    // strip's 800 bytes and a tile row are both 8 banks on, which leaves the banks' low bits to q).
-    // (scol is a multiple of 4, so the bit is the same for the four pixels scol + 4j .. scol + 4j + 3: one
-    // base per j, the pixels of a block at constant distances from it)
-    int lane_at[(4 + KS - 1 + 3) / 4];
+    // byte offset of its pixels 4j .. 4j+3 (columns scol + 4j ..) in a tile row of its quad's plane
+    constexpr int kQuads = (4 + KS - 1 + 3) / 4;
+    int lane_at[kQuads];
 #pragma unroll
-    for (int j = 0; j < (4 + KS - 1 + 3) / 4; ++j)
-        lane_at[j] = scol * L::kPixBytes + ((q * 4 * SZ) ^ ((((scol + 4 * j) >> 4) & 1) * 16));
+    for (int j = 0; j < kQuads; ++j) lane_at[j] = q * L::Planes::kPlane + L::Planes::at(srow, scol + 4 * j);
+    auto pixel = [&](const char* map, int ib, int u, int c) {       // block ib of row srow + u, column scol + c
+        return load_frag<T>(map + ib * 4 * L::Planes::kPlane + lane_at[c >> 2] + (u * L::Planes::kRowSlots + (c & 3)) * L::Planes::kSlot);
+    };
 
     // Stages: (tile, pass) with the passes in the order K, V, Q.  A stage's map goes global -> registers while
     // the stage before it is swept, registers -> LDS after that sweep, one barrier a stage.
@@ -132,31 +137,35 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
     constexpr int kPer = (kItems + kThreads32 - 1) / kThreads32;
     u32x4 pre[kPer];
     auto map_of = [](int pass) { return pass == 0 ? 1 : pass == 1 ? 2 : 0; };
+    // this thread's pixels of a halo tile: row and column in it (a row no image has for those past the last)
+    int item_yx[kPer];
+    const int item_v = threadIdx.x % VPT;
+    static_assert(kThreads32 % VPT == 0, "a thread keeps its channels");
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int it = threadIdx.x + j * kThreads32, pix = it / VPT;
+        item_yx[j] = it < kItems ? (pix / L::LW) << 8 | (pix % L::LW) : 0x7f << 8;
+    }
+    static_assert(L::LW < 256 && L::LH < 0x7f, "a pixel's place is packed");
     auto fetch = [&](int tile_id, int pass) {
         const int ty0 = (tile_id / tiles_x) * TH, tx0 = (tile_id % tiles_x) * TW;
         const int t = map_of(pass);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const int it = threadIdx.x + j * kThreads32;
-            const int vi = it % VPT, pix = it / VPT;
-            const int ly = pix / L::LW, lx = pix - ly * L::LW;
-            const int gy = ty0 - P + ly, gx = tx0 - P + lx;
+            const int gy = ty0 - P + (item_yx[j] >> 8), gx = tx0 - P + (item_yx[j] & 255);
             u32x4 val = {0u, 0u, 0u, 0u};
-            if (it < kItems && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W)
-                val = *(const u32x4*)(maps[t] + (img_tok0 + (long)gy * a.W + gx) * map_ts[t] + vi * Tr::kVec);
+            if (item_yx[j] < (L::LH << 8) && (unsigned)gy < (unsigned)a.H && (unsigned)gx < (unsigned)a.W)
+                val = *(const u32x4*)(maps[t] + (img_tok0 + (long)gy * a.W + gx) * map_ts[t] + item_v * Tr::kVec);
             pre[j] = val;
         }
     };
     auto stash = [&](char* buf) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const int it = threadIdx.x + j * kThreads32;
-            if (it < kItems) {
-                const int vi = it % VPT, pix = it / VPT;
-                const int lx = pix % L::LW;
-                char* dst = buf + pix * L::kPixBytes + ((vi * 16) ^ (((lx >> 4) & 1) * 16));
-                ((u32x2*)dst)[0] = u32x2{pre[j][0], pre[j][1]};
-                ((u32x2*)dst)[1] = u32x2{pre[j][2], pre[j][3]};
+            if (item_yx[j] < (L::LH << 8)) {
+                char* dst = buf + item_v * 2 * L::Planes::kPlane + L::Planes::at(item_yx[j] >> 8, item_yx[j] & 255);
+                *(u32x2*)dst = u32x2{pre[j][0], pre[j][1]};
+                *(u32x2*)(dst + L::Planes::kPlane) = u32x2{pre[j][2], pre[j][3]};
             }
         }
     };
@@ -186,7 +195,12 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
             const bool more = pass < 2 || tile_id + 1 < tile_end;
             if (more) fetch(pass < 2 ? tile_id : tile_id + 1, pass < 2 ? pass + 1 : 0);
             const char* map = tile + cur * L::kMapBytes;
-            Frag dwf[NB][4], dwl[NB][4], center[NB][4];
+            Frag dwf[NB][4], dwl[NB][4];
+            // the strip's raw tokens (the centre tap), for the raw branch and the raw-Q copy
+            auto center = [&](int ib, int r) {
+                const Frag f = pixel(map, ib, P, r + P);
+                return valid[r] ? f : frag_zero<T>();
+            };
 #pragma unroll
             for (int ib = 0; ib < NB; ++ib) {
                 float acc[4][4];
@@ -194,52 +208,33 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
-                const char* src = map + ib * 16 * SZ;
-                const float* wt = wts + t * KS * KS * D32 + ib * 16 + q * 4;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    center[ib][r] = load_frag<T>(src + (srow + P) * L::LW * L::kPixBytes + lane_at[(r + P) >> 2] + (r + P) * L::kPixBytes);
-                // one filter row at a time: 4+KS-1 pixels feed 4 tokens x KS taps x 4 channels.  A row's pixels
-                // and taps are read from LDS while the row before it is worked on (two register sets in turn:
-                // with one wave a SIMD nothing else hides those reads)
-                struct Row {
+                const Tap* wt = wts + t * KS * KS * D32 + ib * 16 + q * 4;
+                // one filter row at a time: 4+KS-1 pixels feed 4 tokens x KS taps x 4 channels
+#pragma unroll 1
+                for (int u = 0; u < KS; ++u) {
                     Frag px[4 + KS - 1];
-                    f32x4 w[KS];
-                };
-                auto read_row = [&](int u, Row& row) {
 #pragma unroll
-                    for (int c = 0; c < 4 + KS - 1; ++c)
-                        row.px[c] = load_frag<T>(src + (srow + u) * L::LW * L::kPixBytes + lane_at[c >> 2] + c * L::kPixBytes);
+                    for (int c = 0; c < 4 + KS - 1; ++c) px[c] = pixel(map, ib, u, c);
 #pragma unroll
-                    for (int v = 0; v < KS; ++v) row.w[v] = *(const f32x4*)(wt + (u * KS + v) * D32);
-                };
-                auto sweep_row = [&](const Row& row) {
-#pragma unroll
-                    for (int v = 0; v < KS; ++v)
+                    for (int v = 0; v < KS; ++v) {
+                        const Tap* w = wt + (u * KS + v) * D32;
+                        f32x4 w4;
+                        if constexpr (sizeof(Tap) == 2) w4 = frag_to_f32<T>(load_frag<T>(w));
+                        else w4 = *(const f32x4*)w;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            const f32x4 d4 = frag_to_f32<T>(row.px[r + v]);
+                            const f32x4 d4 = frag_to_f32<T>(px[r + v]);
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(row.w[v][c], d4[c], acc[r][c]);
+                            for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(w4[c], d4[c], acc[r][c]);
                         }
-                };
-                Row even, odd;
-                read_row(0, even);
-#pragma unroll 1
-                for (int u = 0; u + 1 < KS; u += 2) {      // KS is odd: u + 2 <= KS - 1 here
-                    read_row(u + 1, odd);
-                    sweep_row(even);
-                    read_row(u + 2, even);
-                    sweep_row(odd);
+                    }
                 }
-                sweep_row(even);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     f32x4 a4 = {acc[r][0], acc[r][1], acc[r][2], acc[r][3]};
                     if (!valid[r]) a4 = z;       // tokens outside the image contribute nothing
                     if (wide) frag_split<T>(a4, dwf[ib][r], dwl[ib][r]);
                     else dwf[ib][r] = frag_from_f32<T>(a4);
-                    if (!valid[r]) center[ib][r] = frag_zero<T>();
                 }
             }
 #pragma unroll
@@ -251,16 +246,16 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
                         f32x4 kf = z;
 #pragma unroll
                         for (int ib = 0; ib < NB; ++ib) {
-                            kf = Tr::mma16(kf, dwf[ib][r], gpw[1][ob][ib]);
-                            if constexpr (Tr::kHiLo) kf = Tr::mma16(kf, dwl[ib][r], gpw[1][ob][ib]);
+                            kf = Tr::mma16(kf, dwf[ib][r], gpw(1, ob, ib));
+                            if constexpr (Tr::kHiLo) kf = Tr::mma16(kf, dwl[ib][r], gpw(1, ob, ib));
                         }
 #pragma unroll
                         for (int c = 0; c < 4; ++c) kf[c] = fmaxf(kf[c], 0.f);      // Eq. (2): relu(K)
                         ks_agg[ob] += (kf[0] + kf[1]) + (kf[2] + kf[3]);
                         if constexpr (Tr::kHiLo) frag_split<T>(kf, aggK[ob][r], aggK_lo[ob][r]);
                         else aggK[ob][r] = frag_from_f32<T>(kf);
-                        if (a.do_raw) {
-                            const Frag rk = frag_relu<T>(frag_from_f32<T>(Tr::mma16(z, center[ob][r], ident)));
+                        if constexpr (kRaw) {
+                            const Frag rk = frag_relu<T>(frag_from_f32<T>(Tr::mma16(z, center(ob, r), ident)));
                             rawK[ob][r] = rk;
                             const f32x4 rf = frag_to_f32<T>(rk);
                             ks_raw[ob] += (rf[0] + rf[1]) + (rf[2] + rf[3]);
@@ -272,15 +267,15 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
                         f32x4 vf = z;
 #pragma unroll
                         for (int ib = 0; ib < NB; ++ib) {
-                            vf = Tr::mma16(vf, dwf[ib][r], gpw[2][ov][ib]);
-                            if constexpr (Tr::kHiLo) vf = Tr::mma16(vf, dwl[ib][r], gpw[2][ov][ib]);
+                            vf = Tr::mma16(vf, dwf[ib][r], gpw(2, ov, ib));
+                            if constexpr (Tr::kHiLo) vf = Tr::mma16(vf, dwl[ib][r], gpw(2, ov, ib));
                         }
                         // KV[e][f] += sum_n relu(K_n[e]) V_n[f], block (K block ok, V block ov)
                         Frag vh, vl;
                         if constexpr (Tr::kHiLo) frag_split<T>(vf, vh, vl);
                         else vh = frag_from_f32<T>(vf);
                         Frag rv;
-                        if (a.do_raw) rv = frag_from_f32<T>(Tr::mma16(z, center[ov][r], ident));
+                        if constexpr (kRaw) rv = frag_from_f32<T>(Tr::mma16(z, center(ov, r), ident));
 #pragma unroll
                         for (int ok = 0; ok < NB; ++ok) {
                             kv_agg[ok][ov] = Tr::mma16(kv_agg[ok][ov], aggK[ok][r], vh);
@@ -288,7 +283,7 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
                                 kv_agg[ok][ov] = Tr::mma16(kv_agg[ok][ov], aggK[ok][r], vl);
                                 kv_agg[ok][ov] = Tr::mma16(kv_agg[ok][ov], aggK_lo[ok][r], vh);
                             }
-                            if (a.do_raw) kv_raw[ok][ov] = Tr::mma16(kv_raw[ok][ov], rawK[ok][r], rv);
+                            if constexpr (kRaw) kv_raw[ok][ov] = Tr::mma16(kv_raw[ok][ov], rawK[ok][r], rv);
                         }
                     }
                 } else {
@@ -298,13 +293,13 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
                         f32x4 qq = z;
 #pragma unroll
                         for (int ib = 0; ib < NB; ++ib) {
-                            qq = Tr::mma16(qq, gpw[0][ob][ib], dwf[ib][r]);
-                            qq = Tr::mma16(qq, gpw[0][ob][ib], dwl[ib][r]);
+                            qq = Tr::mma16(qq, gpw(0, ob, ib), dwf[ib][r]);
+                            qq = Tr::mma16(qq, gpw(0, ob, ib), dwl[ib][r]);
                         }
                         if (valid[r]) {
                             T* dst = q_ms + (tok0 + r) * q_ms_ts + h * D32 + ob * 16 + q * 4;
                             store_frag<T>(dst + (long)a.branch * Ct, frag_from_f32<T>(qq));
-                            if (a.copy_raw_q) store_frag<T>(dst, center[ob][r]);
+                            if constexpr (kRaw) store_frag<T>(dst, center(ob, r));
                         }
                     }
                 }
@@ -345,7 +340,7 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
     __syncthreads();
     for (int j = threadIdx.x; j < 2 * kState32; j += kThreads32) {
         const int which = j / kState32, idx = j - which * kState32;   // 0: aggregated, 1: raw
-        if (which == 1 && !a.do_raw) continue;
+        if (which == 1 && !kRaw) continue;
         const int e = idx / (D32 + 1), f = idx - e * (D32 + 1);
         // KV[e][f] sits in block (e / 16, f / 16), lane (f % 16, (e % 16) / 4), element e % 4
         const int src = f < D32 ? ((which * NB + (e >> 4)) * NB + (f >> 4)) * 256 + ((((e & 15) >> 2) * 16) + (f & 15)) * 4 + (e & 3)
@@ -356,14 +351,19 @@ __global__ __launch_bounds__(kThreads32, MSLA_AGG32_WAVES) void aggregate32_kern
     }
 }
 
-template <class T, int KS>
-hipError_t run_ks32(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
+template <class T, int KS, bool kRaw>
+hipError_t run_ks32_raw(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
     constexpr int kLds = Agg32Lds<T, KS>::kBytes;
     static_assert(kLds <= 160 * 1024, "the halo tile of a head of 32 channels fits the LDS");
-    const hipError_t e = allow_dynamic_lds<aggregate32_kernel<T, KS>>(kLds);
+    const hipError_t e = allow_dynamic_lds<aggregate32_kernel<T, KS, kRaw>>(kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((aggregate32_kernel<T, KS>), dim3(nblocks), dim3(kThreads32), kLds, stream, a);
+    hipLaunchKernelGGL((aggregate32_kernel<T, KS, kRaw>), dim3(nblocks), dim3(kThreads32), kLds, stream, a);
     return hipGetLastError();
+}
+template <class T, int KS>
+hipError_t run_ks32(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
+    if ((a.do_raw != 0) != (a.copy_raw_q != 0)) return hipErrorInvalidValue;
+    return a.do_raw ? run_ks32_raw<T, KS, true>(a, nblocks, stream) : run_ks32_raw<T, KS, false>(a, nblocks, stream);
 }
 
 template <class T>

@@ -247,6 +247,20 @@ __device__ __forceinline__ void buf_store8(BufRsrc r, unsigned voffset, u32x2 v)
 }
 
 
+// LDS layout of one map (Q, K or V of one head) of a halo tile of LH x LW pixels, for the kernels whose lanes walk strips of
+// four pixels: planes, one per channel quad, of one slot (4 elements of SZ bytes) a pixel, so a fragment is one 16-byte
+// (8-byte) read.  The sixteen lanes that a read serves together are eight strips (4 slots apart) of two tile rows: a slot
+// is skipped every 16 columns and a tile row is 2 slots mod 4, which gives them sixteen different slots mod 16.  Planes are
+// kPlaneMod slots mod 16 apart, so that the staging stores (a pixel's quads from neighbouring lanes) spread as well.
+template <int LH, int LW, int SZ, int kPlaneMod>
+struct HaloPlanes {
+    static constexpr int kSlot = 4 * SZ;
+    static constexpr int kRowSlots = (LW + (LW - 1) / 16 + 1) / 4 * 4 + 2;
+    static constexpr int kPlane = ((LH * kRowSlots + 15 - kPlaneMod) / 16 * 16 + kPlaneMod) * kSlot;
+    static __device__ __forceinline__ int at(int row, int col) { return (row * kRowSlots + col + (col >> 4)) * kSlot; }
+    static_assert(kRowSlots >= LW + (LW - 1) / 16 && kPlane >= LH * kRowSlots * kSlot, "pixels fit");
+};
+
 // Workgroup id -> logical id so that consecutive logical ids run on the same
 // XCD.  The hardware deals workgroups round-robin over the 8 XCDs (each with
 // its own L2); neighbours in the logical order share cache lines, so they
