@@ -421,6 +421,9 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
         auto stage1 = [&](int it, f32x4 o) {
             const int t = pass_t(it / NR), y = it % NR - (KS - 1);
             const int gy = gy0 + y;
+            // the wait states between a 4x4x4 matrix instruction and a reader of its result, written out: the compiler (ROCm
+            // 7.2) leaves them out on the path that jumps over the masking below (bf16, paired launch)
+            if (t == 1) asm volatile("s_nop 4" : "+v"(o));
             if (t == 1 && ragged) {
                 // tokens outside the image contribute nothing: their aggregated K is made 0, which
                 // also removes their V from the state; Q rows of such tokens are simply not stored.
