@@ -204,18 +204,31 @@ __global__ __launch_bounds__(512) void ffn_dw_project_kernel(const T* __restrict
 // so every buffer written in a step was last read in the step before.  Rows are 128 bytes, unpadded, with
 // the 16-byte chunk index XOR-ed with (row / 2) % 8 (full rate for operand reads and row-order writes).
 // Requires one image's expanded map to stay below 2^31 bytes (32-bit offsets in a buffer resource).
-template <class T, int ACT>
+//
+// RPL: output rows a producer lane makes; a block is 4*RPL rows of 16 tokens.  BR: output channels (256 or 128); eight
+// consumer waves are BR/64 channel groups of 64 times the token groups that are left.
+template <class T, int RPL, int BR>
+struct FfnSplit {
+    static constexpr int TR = 4 * RPL, TC = 16, TB = TR * TC;
+    static constexpr int kHaloW = TC + 2, kHaloH = TR + 2, kHaloTok = kHaloW * kHaloH;
+    static constexpr int kWt = BR * 128, kTok = TB * 128, kPlane = kHaloTok * 16 + 16, kHalo = 8 * kPlane;
+    static constexpr int WRC = BR / 64, WCC = 8 / WRC;         // consumer waves: channel groups x token groups
+    static constexpr int JT = TB / WCC / 16;                   // 16-token groups per consumer wave
+    static constexpr int kStageRow = 64 * 4 + 16, kStageWave = 16 * kStageRow;      // epilogue: 16 tokens x 64 channels, fp32
+    static constexpr int kLds = 2 * (kWt + kTok + kHalo);
+    static_assert(JT >= 1 && 8 * kStageWave <= kLds && kLds <= 160 * 1024, "the blocks fit");
+};
+template <class T, int ACT, int RPL, int BR>
 __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __restrict__ h, const T* __restrict__ w_dw,
                                                                    const T* __restrict__ w2, const T* __restrict__ res,
                                                                    T* __restrict__ out, int H, int W, int E, int c_out,
                                                                    int tiles_x, int tiles_y, int n_rb) {
     static_assert(sizeof(T) == 2, "16-bit storage types");
-    typedef GemmTile<T, 4, 2> G;
+    typedef FfnSplit<T, RPL, BR> S;
     typedef Traits<T> Tr;
     typedef typename Tr::Vec Vec;
     constexpr int BK = 64;                           // hidden channels per slab (128 bytes)
-    constexpr int kHaloW = 34, kHaloH = 6, kHaloTok = kHaloW * kHaloH;
-    constexpr int kWt = 256 * 128, kTok = 128 * 128, kHalo = kHaloTok * 128 + 128;
+    constexpr int kHaloW = S::kHaloW, kHaloTok = S::kHaloTok, kWt = S::kWt, kTok = S::kTok, JT = S::JT;
     constexpr int kHaloVec = (kHaloTok * 8 + 511) / 512;      // 16-byte vectors per producer thread and slab
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* const ldsW = lds;                          // 2 weight tiles
@@ -229,96 +242,113 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
     rest /= tiles_x;
     const int ty = rest % tiles_y;
     const int b = rest / tiles_y;
-    const int y0 = ty * 4, x0 = tx * 32, oc0 = rb * G::BR;
+    const int y0 = ty * S::TR, x0 = tx * S::TC, oc0 = rb * BR;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_slab = (E + BK - 1) / BK;
     const unsigned e_bytes = (unsigned)E * 2u;
 
     if (wave < 8) {
         // ------------------------------------------------------------ consumers
-        const int wr = wave % 4, wc = wave / 4;
+        const int wr = wave % S::WRC, wc = wave / S::WRC;
         const int lane = lane_id(), x16 = lane & 15, q = lane >> 4, g16 = (x16 >> 1) & 7;
-        f32x4 acc[4][4];
-        G::zero(acc);
+        f32x4 acc[4][JT];
+#pragma unroll
+        for (int io = 0; io < 4; ++io)
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) acc[io][jt] = f32x4{0.f, 0.f, 0.f, 0.f};
         // weight slab: thread = (row v / 8, chunk v % 8) of vectors v = tid + i * 512
         const BufRsrc wres = make_rsrc(w2, (long)c_out * e_bytes);
-        unsigned w_glb[4], w_lds[4];
+        const bool live = oc0 + wr * 64 < c_out;
+        constexpr int kWVec = BR * 8 / 512;
+        unsigned w_glb[kWVec], w_lds[kWVec];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kWVec; ++i) {
             const int v = threadIdx.x + i * 512;
             const int row = v >> 3, chunk = v & 7;
             w_glb[i] = oc0 + row < c_out ? (unsigned)(oc0 + row) * e_bytes + chunk * 16 : kOobOffset;
             w_lds[i] = row * 128 + ((chunk ^ ((row >> 1) & 7)) * 16);
         }
         const int w_chunk = threadIdx.x & 7;
-        u32x4 rw[4];
+        u32x4 rw[kWVec];
         // operand offsets of this lane for the two 32-slot halves of a slab
-        const int a_off = (wr * 64 + x16) * 128, b_off = (wc * 64 + x16) * 128;
+        const int a_off = (wr * 64 + x16) * 128, b_off = (wc * JT * 16 + x16) * 128;
         const int c_lo = ((0 * 4 + q) ^ g16) * 16, c_hi = ((1 * 4 + q) ^ g16) * 16;
         for (int i = -3; i < n_slab; ++i) {
             if (i + 1 >= 0 && i + 1 < n_slab) {
                 char* dst = ldsW + ((i + 1) & 1) * kWt;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) *(u32x4*)(dst + w_lds[j]) = rw[j];
+                for (int j = 0; j < kWVec; ++j) *(u32x4*)(dst + w_lds[j]) = rw[j];
             }
             if (i + 2 >= 0 && i + 2 < n_slab) {
                 const unsigned k_bytes = (unsigned)(i + 2) * 128u;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < kWVec; ++j)
                     rw[j] = buf_load16(wres, (w_glb[j] != kOobOffset && k_bytes + w_chunk * 16 < e_bytes) ? w_glb[j] + k_bytes
                                                                                                      : kOobOffset, 0);
             }
-            if (i >= 0) {
+            if (i >= 0 && live) {
                 const char* wt = ldsW + (i & 1) * kWt + a_off;
                 const char* ct = ldsC + (i & 1) * kTok + b_off;
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
                     const int co = kk ? c_hi : c_lo;
-                    Vec fa[4], fb[4];
+                    Vec fa[4], fb[JT];
 #pragma unroll
                     for (int io = 0; io < 4; ++io) fa[io] = __builtin_bit_cast(Vec, *(const u32x4*)(wt + io * 16 * 128 + co));
 #pragma unroll
-                    for (int jt = 0; jt < 4; ++jt) fb[jt] = __builtin_bit_cast(Vec, *(const u32x4*)(ct + jt * 16 * 128 + co));
+                    for (int jt = 0; jt < JT; ++jt) fb[jt] = __builtin_bit_cast(Vec, *(const u32x4*)(ct + jt * 16 * 128 + co));
 #pragma unroll
                     for (int io = 0; io < 4; ++io)
 #pragma unroll
-                        for (int jt = 0; jt < 4; ++jt) acc[io][jt] = Tr::mma_vec(acc[io][jt], fa[io], fb[jt]);
+                        for (int jt = 0; jt < JT; ++jt) acc[io][jt] = Tr::mma_vec(acc[io][jt], fa[io], fb[jt]);
                 }
             }
             __syncthreads();
         }
-        // ---- results: tile token t = (row t / 32, column t % 32) of the block; staged in the weight tiles
-        struct TileOut {
-            T* out;
-            long base;      // token index of (y0, x0)
-            int W, rows, cols, c_out;
-            __device__ __forceinline__ void store(int, int, int trow, int oc, u32x4 v) const {
-                const int r = trow >> 5, c = trow & 31;
-                if (r < rows && c < cols && oc < c_out) *(u32x4*)(out + (base + (long)r * W + c) * c_out + oc) = v;
-            }
-        };
+        // ---- results: block token t = (row t / 16, column t % 16).  The wave parks 16 tokens x 64 channels as fp32, each
+        // lane picks up the 8 channels it will write, adds the residual's same 16 bytes and rounds once.
         const long base = ((long)b * H + y0) * W + x0;
-        const int rows = H - y0 < 4 ? H - y0 : 4, cols = W - x0 < 32 ? W - x0 : 32;
-        const TileOut to{out, base, W, rows, cols, c_out};
-        static_assert(G::kStageResBytes <= 2 * kWt, "the epilogue stages in the weight tiles");
-        G::epilogue_lds_residual(acc, lds, oc0, wr, wc, to, [&](int trow, int oc) {
-            const int r = trow >> 5, c = trow & 31;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (r < rows && c < cols && oc < c_out) v = *(const u32x4*)(res + (base + (long)r * W + c) * c_out + oc);
-            return v;
-        });
+        const int rows = H - y0 < S::TR ? H - y0 : S::TR, cols = W - x0 < S::TC ? W - x0 : S::TC;
+        char* mine = lds + wave * S::kStageWave;
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int io = 0; io < 4; ++io) *(f32x4*)(mine + x16 * S::kStageRow + (io * 16 + q * 4) * 4) = acc[io][jt];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int v = lane + 64 * i, row = v >> 3, cv = v & 7;
+                const int t = (wc * JT + jt) * 16 + row, r = t >> 4, c = t & 15, oc = oc0 + wr * 64 + cv * 8;
+                if (r < rows && c < cols && oc < c_out) {
+                    const long at = (base + (long)r * W + c) * c_out + oc;
+                    const f32x4 a0 = *(const f32x4*)(mine + row * S::kStageRow + cv * 32);
+                    const f32x4 a1 = *(const f32x4*)(mine + row * S::kStageRow + cv * 32 + 16);
+                    const Vec add = __builtin_bit_cast(Vec, *(const u32x4*)(res + at));
+                    Vec o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        o[e] = Tr::from_f32(a0[e] + Tr::to_f32(add[e]));
+                        o[4 + e] = Tr::from_f32(a1[e] + Tr::to_f32(add[4 + e]));
+                    }
+                    *(u32x4*)(out + at) = __builtin_bit_cast(u32x4, o);
+                }
+            }
+        }
     } else {
         // ------------------------------------------------------------ producers
-        // A wave is one 16-byte channel vector of the slab (8 channels), its lanes the tile's columns and
-        // row pairs: the 72 filter taps a wave needs are then the same for all its lanes and live in scalar
+        // A wave is one 16-byte channel vector of the slab (8 channels), its lanes the block's 16 columns and
+        // four groups of RPL rows: the 72 filter taps a wave needs are then the same for all its lanes and live in scalar
         // registers, read straight from w_dw (8 channels x 9 taps are 144 consecutive bytes).  The halo is
         // kept as 8 planes [channel vector][halo token][16 bytes], so consecutive lanes read consecutive 16
         // bytes; a plane is padded by 16 bytes, which spreads the 8 planes a row-order copy writes to at once
         // over all banks.
         const int pt = threadIdx.x - 512;
-        const int dvec = wave - 8, lane = lane_id(), dcol = lane & 31, dhalf = lane >> 5;
-        constexpr int kPlane = kHaloTok * 16 + 16;
-        static_assert(8 * kPlane <= kHalo + 128, "planes fit the halo buffer");
+        const int dvec = wave - 8, lane = lane_id(), dcol = lane & 15, dgrp = lane >> 4;
+        constexpr int kPlane = S::kPlane;
         const BufRsrc hres = make_rsrc(h + (long)b * H * W * E, (long)H * W * e_bytes);
         // halo copy: vector id = j * 512 + pt -> halo token id / 8, chunk id % 8
         unsigned h_glb[kHaloVec];
@@ -333,9 +363,13 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
             h_glb[j] = ok ? (unsigned)(yy * W + xx) * e_bytes + v * 16 : kOobOffset;
             h_lds[j] = tok < kHaloTok ? v * kPlane + tok * 16 : -1;
         }
-        const int d_lds = dvec * kPlane + (2 * dhalf * kHaloW + dcol) * 16;
-        const int t0 = (2 * dhalf) * 32 + dcol, t1 = t0 + 32;
-        const int c_lds0 = t0 * 128 + ((dvec ^ ((t0 >> 1) & 7)) * 16), c_lds1 = t1 * 128 + ((dvec ^ ((t1 >> 1) & 7)) * 16);
+        const int d_lds = dvec * kPlane + (RPL * dgrp * kHaloW + dcol) * 16;
+        int c_lds[RPL];
+#pragma unroll
+        for (int y = 0; y < RPL; ++y) {
+            const int tok = (RPL * dgrp + y) * S::TC + dcol;
+            c_lds[y] = tok * 128 + ((dvec ^ ((tok >> 1) & 7)) * 16);
+        }
         u32x4 rh[kHaloVec];
         for (int i = -3; i < n_slab; ++i) {
             if (i + 2 >= 0 && i + 2 < n_slab) {           // park halo i+2
@@ -363,40 +397,70 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
                     if (ch < E) raw = *(const u32x4*)(w_dw + (long)ch * 9 + t * 8);
                     wt[t] = __builtin_bit_cast(Vec, raw);
                 }
-                float a0[8], a1[8];
+                float sum[RPL][8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) a0[j] = a1[j] = 0.f;
+                for (int y = 0; y < RPL; ++y)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {            // halo rows 2*dhalf + r
+                    for (int j = 0; j < 8; ++j) sum[y][j] = 0.f;
+#pragma unroll
+                for (int r = 0; r < RPL + 2; ++r) {      // halo rows RPL*dgrp + r
 #pragma unroll
                     for (int dx = 0; dx < 3; ++dx) {
                         const Vec f = __builtin_bit_cast(Vec, *(const u32x4*)(hs + (r * kHaloW + dx) * 16));
 #pragma unroll
                         for (int j = 0; j < 8; ++j) {
                             const float fj = Tr::to_f32(f[j]);
-                            if (r < 3) {            // output row 2*dhalf: tap row r
-                                const int e = j * 9 + r * 3 + dx;
-                                a0[j] = fmaf(Tr::to_f32(wt[e / 8][e % 8]), fj, a0[j]);
-                            }
-                            if (r > 0) {            // output row 2*dhalf + 1: tap row r - 1
-                                const int e = j * 9 + (r - 1) * 3 + dx;
-                                a1[j] = fmaf(Tr::to_f32(wt[e / 8][e % 8]), fj, a1[j]);
-                            }
+#pragma unroll
+                            for (int y = 0; y < RPL; ++y)
+                                if (r >= y && r < y + 3) {      // output row y: tap row r - y
+                                    const int e = j * 9 + (r - y) * 3 + dx;
+                                    sum[y][j] = fmaf(Tr::to_f32(wt[e / 8][e % 8]), fj, sum[y][j]);
+                                }
                         }
                     }
                 }
-                Vec o0, o1;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    o0[j] = Tr::from_f32(activate<ACT>(a0[j]));
-                    o1[j] = Tr::from_f32(activate<ACT>(a1[j]));
+                for (int y = 0; y < RPL; ++y) {
+                    Vec o;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) o[j] = Tr::from_f32(activate<ACT>(sum[y][j]));
+                    *(u32x4*)(cd + c_lds[y]) = __builtin_bit_cast(u32x4, o);
                 }
-                *(u32x4*)(cd + c_lds0) = __builtin_bit_cast(u32x4, o0);
-                *(u32x4*)(cd + c_lds1) = __builtin_bit_cast(u32x4, o1);
             }
             __syncthreads();
         }
     }
+}
+
+template <class T, int ACT, int RPL, int BR>
+hipError_t run_dw_project_split_as(const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B, int H,
+                                   int W, int E, int c_out, hipStream_t stream) {
+    typedef FfnSplit<T, RPL, BR> S;
+    const int tiles_x = (W + S::TC - 1) / S::TC, tiles_y = (H + S::TR - 1) / S::TR, n_rb = (c_out + BR - 1) / BR;
+    const long nblocks = (long)B * tiles_x * tiles_y * n_rb;
+    if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
+    const hipError_t e = allow_dynamic_lds<ffn_dw_project_split_kernel<T, ACT, RPL, BR>>(S::kLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((ffn_dw_project_split_kernel<T, ACT, RPL, BR>), dim3((unsigned)nblocks), dim3(1024), S::kLds, stream,
+                       (const T*)h, (const T*)w_dw, (const T*)w2, (const T*)res, (T*)out, H, W, E, c_out, tiles_x, tiles_y,
+                       n_rb);
+    return hipGetLastError();
+}
+template <class T, int ACT>
+hipError_t run_dw_project_split(const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B, int H,
+                                int W, int E, int c_out, hipStream_t stream) {
+    const long blocks = (long)B * ((W + 15) / 16) * ((H + 7) / 8) * ((c_out + 255) / 256);
+    // blocks of 128 tokens, or -- where those leave a quarter of the compute units or more without one -- of 64: half the time
+    // a slab and (at 128 channels) two resident workgroups a CU.  Modules of 16-bit maps, 128 / 64 tokens a block: 2 x 8192
+    // tokens, 128 -> 512 channels (128 blocks) 25.9 / 21.9 us, 2048, 256 -> 1024 (16) 41.0 / 28.5; 7 x 1928, 32 -> 128 (217)
+    // 13.4 / 15.4, 8 x 8192, 256 -> 1024 (512) 137.7 / 155.9.  (Blocks were 4 x 32 tokens by 256 channels throughout: 28.8,
+    // 39.0, 20.9, 138.5; a block of 8 x 16 has 180 halo tokens where 4 x 32 has 204.)
+    const bool small = 4 * blocks < 3L * compute_units();
+    if (c_out <= 128)
+        return small ? run_dw_project_split_as<T, ACT, 1, 128>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                     : run_dw_project_split_as<T, ACT, 2, 128>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+    return small ? run_dw_project_split_as<T, ACT, 1, 256>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                 : run_dw_project_split_as<T, ACT, 2, 256>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
 }
 
 template <class T>
@@ -410,23 +474,9 @@ hipError_t run_dw_project(const void* h, const void* w_dw, const void* w2, const
     hipError_t e;
     if constexpr (sizeof(T) == 2) {
         // waves specialised into depthwise producers and matrix-core consumers, where 32-bit offsets reach
-        if ((long)H * W * E * 2 < 0x7fffffffL && (long)c_out * E * 2 < 0x7fffffffL && (long)E * 18 < 0x7fffffffL) {
-            constexpr int kSplitLds = 2 * (256 * 128 + 128 * 128 + 204 * 128 + 128);
-            if (act == 0) {
-                e = allow_dynamic_lds<ffn_dw_project_split_kernel<T, 0>>(kSplitLds);
-                if (e != hipSuccess) return e;
-                hipLaunchKernelGGL((ffn_dw_project_split_kernel<T, 0>), dim3((unsigned)nblocks), dim3(1024), kSplitLds, stream,
-                                   (const T*)h, (const T*)w_dw, (const T*)w2, (const T*)res, (T*)out, H, W, E, c_out, tiles_x,
-                                   tiles_y, n_rb);
-            } else {
-                e = allow_dynamic_lds<ffn_dw_project_split_kernel<T, 1>>(kSplitLds);
-                if (e != hipSuccess) return e;
-                hipLaunchKernelGGL((ffn_dw_project_split_kernel<T, 1>), dim3((unsigned)nblocks), dim3(1024), kSplitLds, stream,
-                                   (const T*)h, (const T*)w_dw, (const T*)w2, (const T*)res, (T*)out, H, W, E, c_out, tiles_x,
-                                   tiles_y, n_rb);
-            }
-            return hipGetLastError();
-        }
+        if ((long)H * W * E * 2 < 0x7fffffffL && (long)c_out * E * 2 < 0x7fffffffL && (long)E * 18 < 0x7fffffffL)
+            return act == 0 ? run_dw_project_split<T, 0>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                            : run_dw_project_split<T, 1>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
     }
     constexpr int kLds = G::kLdsR + G::kLdsC + 204 * 160 + 9 * G::BK * 4;
     static_assert(G::kStageResBytes <= G::kLdsR + G::kLdsC, "the epilogue stages in the operand tiles");

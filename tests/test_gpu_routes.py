@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import test_gpu_block as block
 import test_gpu_parity as base
 from paper_2205_14756_amd import msla
 from paper_2205_14756_amd import workloads as wk
@@ -75,3 +76,40 @@ def test_core_writes_attention_rows(dtype, B, H, W, heads):
     hull = np.abs(kv[..., :16] / np.maximum(kv[..., 16:], 1e-30)).max(axis=(3, 4))
     bar = (u * np.broadcast_to(hull[:, None, :, :, None], num.shape)).reshape(rows, 32 * heads)
     assert (np.abs(base.host(room[:rows]) - ref) <= bar + 1e-12).all()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# blocks of 64 and of 128 tokens, up to 128 and up to 256 output channels a workgroup; ragged columns and rows, channel
+# groups past the output (48, 144), a hidden size that is no whole number of slabs, a narrow map, more than one group (272)
+@pytest.mark.parametrize("B,C,H,W,hidden", [(1, 48, 5, 17, 80), (3, 48, 61, 130, 80), (2, 144, 7, 33, 144),
+                                            (4, 144, 61, 113, 160), (2, 128, 50, 3, 128), (1, 272, 9, 18, 288)])
+def test_ffn_block_shapes(dtype, B, C, H, W, hidden):
+    block.test_ffn(dtype, 1, B, C, H, W, hidden)
+
+
+# fp32 projections and normalise-and-apply: 32, 64, 96, 128, 192 and 256 input channels (and the first beyond), 16 channels
+# short of each; few and many tiles a workgroup, several images, 8, 16, 24, 32 and more head-branches, channel groups past
+# the output
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 16, 3, 5, 1, (5,)), (2, 48, 9, 33, 4, (3,)), (5, 64, 40, 41, 4, (5,)),
+                                                  (2, 80, 7, 11, 8, (5,)), (3, 96, 30, 50, 6, (3, 5)), (1, 144, 6, 50, 9, (5,)),
+                                                  (2, 208, 33, 47, 13, (5,)), (3, 256, 5, 21, 16, (5,)), (2, 272, 6, 21, 17, (5,))])
+def test_fp32_weight_stationary_kernels(B, C, H, W, heads, scales):
+    print(f"routes: fp32 {B}x{C}x{H}x{W} heads={heads}", flush=True)
+    base.check_module(wk.random_module(91 + C, "f32", B, C, H, W, heads, 16, scales), "f32", heads, 16, scales)
+
+
+def test_fp32_paired_heads_of_eight_keep_their_own_denominators():
+    # two heads of 8 side by side in one state, keys of very different size: a denominator that mixed them would show
+    t = wk.random_module(97, "f32", 2, 64, 12, 23, 8, 8, (3, 5))
+    w = t["w_qkv"].reshape(8, 3, 8, 64).copy()
+    w[1::2, 1] *= 100.0
+    t["w_qkv"] = wk.round_to_dtype(w.reshape(192, 64), "f32")
+    base.check_module(t, "f32", 8, 8, (3, 5), stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# a 3x3 and a 5x5 scale in one launch, image-head-chunk counts that are no multiple of 8, either order; with the copy of the raw Q
+@pytest.mark.parametrize("B,H,W,heads,scales", [(1, 33, 40, 3, (3, 5)), (3, 20, 70, 5, (5, 3)), (1, 5, 4, 1, (3, 5))])
+def test_paired_scales(dtype, B, H, W, heads, scales):
+    base.test_multiscale_state_and_core(dtype, B, H, W, heads, scales)
+    base.check_module(wk.random_module(17 + W, dtype, B, 16 * heads, H, W, heads, 16, scales), dtype, heads, 16, scales, stages=False)
