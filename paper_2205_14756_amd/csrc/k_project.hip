@@ -27,10 +27,17 @@ namespace {
 template <class T>
 using ProjTile = GemmTile<T, MSLA_PROJ_WR, MSLA_PROJ_WC>;
 
+// kThrough in the destinations below: the weight-stationary kernel's stores go through to memory (the sc1 bit) instead of
+// staying dirty in L2.  What a kernel leaves dirty is written back before the next one starts, and on small maps nothing
+// else is left to cover that: 8192 tokens, 128 -> 384 channels (6 MB) a module of 23.9 us takes 23.4, an FFN of 2 x 8192,
+// 128 -> 512 (17 MB) 20.1 instead of 22.1.  A map of 25 MB: 42.7 and 43.0; 67 MB: 61.4 and 64.4; the next kernel then finds it
+// neither in L2 nor ahead of older lines in the memory-side cache.
+constexpr long kThroughBytes = 20L << 20;
+
 // Where the projection writes, and in which order it walks the weight rows.  tile(tok0) gives the
 // writer for the token tile starting at tok0: buffer resources based at that token, so offsets fit
 // 32 bits and rows past the last token are dropped by the range check.
-template <class T>
+template <class T, bool kThrough = false>
 struct PlainDest {
     T* y;
     long n_tokens;
@@ -84,7 +91,7 @@ struct PlainDest {
     // (piece0 .. piece_end: the channels the storing wave covers; local0: the stored piece's first
     // channel counted from the wave's first -- both unused here)
     static __device__ __forceinline__ void store(const Tile& t, const Lane& l, int, int, int, int row0, u32x4 v) {
-        buf_store16_at(t.y, l.off, (unsigned)row0 * t.row_bytes, v);
+        buf_store16_at_as<kThrough>(t.y, l.off, (unsigned)row0 * t.row_bytes, v);
     }
 };
 
@@ -98,7 +105,7 @@ struct PlainDest {
 // aggregation pass reads best (a head's tokens are contiguous); its token count is padded to whole
 // tiles, so the rows of a ragged last tile fall into the padding.  kv_span is the size of the map;
 // a head-major map must stay below 2^31 bytes (32-bit offsets inside a tile's resource).
-template <class T>
+template <class T, bool kThrough = false>
 struct QkvSplitDest {
     __host__ __device__ __forceinline__ bool has_residual() const { return false; }
     __device__ __forceinline__ u32x4 residual16(long, int) const { return u32x4{0u, 0u, 0u, 0u}; }
@@ -154,8 +161,8 @@ struct QkvSplitDest {
     }
     // piece0 .. piece_end: the wave's channel range, which tells (wave-uniformly) which maps it touches
     static __device__ __forceinline__ void store(const Tile& t, const Lane& l, int piece0, int piece_end, int, int row0, u32x4 v) {
-        if (piece0 < t.Ct) buf_store16_at(t.q, l.q, (unsigned)row0 * t.q_row_bytes, v);
-        if (piece_end > t.Ct) buf_store16_at(t.kv, l.kv, (unsigned)row0 * t.kv_row_bytes, v);
+        if (piece0 < t.Ct) buf_store16_at_as<kThrough>(t.q, l.q, (unsigned)row0 * t.q_row_bytes, v);
+        if (piece_end > t.Ct) buf_store16_at_as<kThrough>(t.kv, l.kv, (unsigned)row0 * t.kv_row_bytes, v);
     }
 };
 
@@ -164,7 +171,7 @@ struct QkvSplitDest {
 // pair up into one store of a token's 64-byte K|V run -- with a head-major map sixteen tokens' runs
 // are one contiguous kilobyte -- the Q block pairs its two token groups, and which map a store
 // goes to is known when the kernel is compiled: no branches, one offset a lane.
-template <class T>
+template <class T, bool kThrough = false>
 struct QkvHeadDest {
     __host__ __device__ __forceinline__ bool has_residual() const { return false; }
     __device__ __forceinline__ u32x4 residual16(long, int) const { return u32x4{0u, 0u, 0u, 0u}; }
@@ -204,8 +211,8 @@ struct QkvHeadDest {
         return Lane{(unsigned)row * (unsigned)(q_ms_stride * sizeof(T)) + (unsigned)(head * 16 + r - 32) * sz};
     }
     static __device__ __forceinline__ void store(const Tile& t, const Lane& l, int, int, int local0, int row0, u32x4 v) {
-        if (local0 < 32) buf_store16_at(t.kv, l.off, (unsigned)row0 * t.kv_row_bytes, v);
-        else buf_store16_at(t.q, l.off, (unsigned)row0 * t.q_row_bytes, v);
+        if (local0 < 32) buf_store16_at_as<kThrough>(t.kv, l.off, (unsigned)row0 * t.kv_row_bytes, v);
+        else buf_store16_at_as<kThrough>(t.q, l.off, (unsigned)row0 * t.q_row_bytes, v);
     }
 };
 
@@ -656,30 +663,31 @@ hipError_t run_project_tiled(const void* x, const void* w, long n_tokens, int c_
     return hipGetLastError();
 }
 
+// the weight-stationary form of a plain projection (at most 256 input channels, no residual)
+template <class T, class Epilogue>
+hipError_t run_project_ws_plain(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
+                                hipStream_t stream) {
+    if constexpr (sizeof(T) == 4) {
+        return run_project_ws32<T>(x, w, n_tokens, c_in, c_out, ep, stream);
+    } else {
+        // 64 channels a wave where that divides the output and 48 does not (the FFN's expand projection:
+        // 1024 channels are four such workgroups instead of five and a third of the 48-channel kind;
+        // 42 against 57 us there, 24 against 31 at 512 channels, but 39.5 against 37 at 768), else 48
+        if (c_out % 256 == 0 && c_out % 192 != 0)
+            return c_in <= 128 ? run_project_ws<T, 4, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream)
+                               : run_project_ws<T, 8, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+        return c_in <= 128 ? run_project_ws<T, 4, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream)
+                           : run_project_ws<T, 8, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    }
+}
+
 template <class T, class Epilogue>
 hipError_t run_project(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
                        hipStream_t stream) {
-    if constexpr (sizeof(T) == 4) {
-        if (!ep.has_residual()) {
-            if (c_in <= 256) return run_project_ws32<T>(x, w, n_tokens, c_in, c_out, ep, stream);
-        }
-    }
-    if constexpr (sizeof(T) == 2) {
-        // short contraction: weights stay in registers
-#ifndef MSLA_PROJ_NO_WS
-        if (!ep.has_residual()) {      // (the weight-stationary form has no residual path)
-            // 64 channels a wave where that divides the output and 48 does not (the FFN's expand projection:
-            // 1024 channels are four such workgroups instead of five and a third of the 48-channel kind;
-            // 42 against 57 us there, 24 against 31 at 512 channels, but 39.5 against 37 at 768), else 48
-            if (c_out % 256 == 0 && c_out % 192 != 0) {
-                if (c_in <= 128) return run_project_ws<T, 4, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-                if (c_in <= 256) return run_project_ws<T, 8, 4, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-            }
-            if (c_in <= 128) return run_project_ws<T, 4, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-            if (c_in <= 256) return run_project_ws<T, 8, MSLA_WS_IO, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-        }
-#endif
-    }
+    static_assert(std::is_same<Epilogue, PlainDest<T>>::value, "the Q/K/V projection chooses for itself");
+    if (n_tokens * c_out * (long)sizeof(T) <= kThroughBytes && !ep.has_residual() && c_in <= 256)
+        return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, PlainDest<T, true>{ep.y, n_tokens, c_out, nullptr, ep.act}, stream);
+    if (!ep.has_residual() && c_in <= 256) return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, ep, stream);
     return run_project_tiled<T>(x, w, n_tokens, c_in, c_out, ep, stream);
 }
 
@@ -718,22 +726,33 @@ hipError_t launch_linear_residual(int dt, const void* x, const void* w, const vo
     return hipErrorInvalidValue;
 }
 
+// the weight-stationary form of the Q/K/V projection (at most 256 input channels)
+template <class T, bool kThrough>
+hipError_t run_qkv_project_ws(const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw, long kv_tok_stride,
+                              long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads, hipStream_t stream) {
+    const int c_out = 3 * heads * 16;
+    if constexpr (sizeof(T) == 4) {
+        const QkvSplitDest<T, kThrough> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
+        return run_project_ws32<T>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
+    } else {
+        // one head (48 channels) a wave
+        const QkvHeadDest<T, kThrough> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
+        return c_in <= 128 ? run_project_ws<T, 4, 3, QkvHeadDest<T, kThrough>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream)
+                           : run_project_ws<T, 8, 3, QkvHeadDest<T, kThrough>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
+    }
+}
+
 template <class T>
 hipError_t run_qkv_project(const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw,
                            long kv_tok_stride, long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads,
                            hipStream_t stream) {
     const int c_out = 3 * heads * 16;
-#ifndef MSLA_PROJ_NO_WS
-    if constexpr (sizeof(T) == 2 && MSLA_WS_IO == 3) {
-        // weight-stationary with one head a wave
-        const QkvHeadDest<T> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
-        if (c_in <= 128) return run_project_ws<T, 4, 3, QkvHeadDest<T>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
-        if (c_in <= 256) return run_project_ws<T, 8, 3, QkvHeadDest<T>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
-    }
-#endif
-    if constexpr (sizeof(T) == 4) {
-        const QkvSplitDest<T> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
-        if (c_in <= 256) return run_project_ws32<T>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
+    if (c_in <= 256) {
+        const bool through = n_tokens * c_out * (long)sizeof(T) <= kThroughBytes;
+        return through ? run_qkv_project_ws<T, true>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span,
+                                                     n_tokens, c_in, heads, stream)
+                       : run_qkv_project_ws<T, false>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span,
+                                                      n_tokens, c_in, heads, stream);
     }
     return run_project_tiled<T>(x, w_qkv, n_tokens, c_in, c_out,
                                 QkvSplitDest<T>{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span,

@@ -239,6 +239,11 @@ __device__ __forceinline__ void buf_store16_at(BufRsrc r, unsigned voffset, unsi
 __device__ __forceinline__ void buf_store16_stream(BufRsrc r, unsigned voffset, u32x4 v) {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)voffset, 0, 16);
 }
+// ... with a wave-uniform byte offset (buf_store16_at), through or not
+template <bool kThrough>
+__device__ __forceinline__ void buf_store16_at_as(BufRsrc r, unsigned voffset, unsigned soffset, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(voffset + soffset), 0, kThrough ? 16 : 0);
+}
 __device__ __forceinline__ u32x2 buf_load8(BufRsrc r, unsigned voffset) {
     return __builtin_amdgcn_raw_buffer_load_b64(r, (int)voffset, 0, 0);
 }
