@@ -311,19 +311,25 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
 }
 
 // Branch-0 state when the module has no aggregated scale: the raw K, V tokens
-// of (image, head, chunk of 64-token groups), same operand path as above.
-template <class T>
-__global__ __launch_bounds__(kAggThreads) void raw_state_kernel(AggregateArgs a) {
+// of (image, head, chunk of 64-token groups), same operand path as above.  A workgroup is NH neighbouring heads, four waves
+// each: one, or -- where Q, K and V of all heads are interleaved in a token's row, so that four heads are three whole
+// cache lines -- four, and the lines come to a compute unit once (core of 65536 tokens, 16 heads, fp16: 69.9 -> 60.9 us; with
+// fewer heads than that half of the waves idle, 22.8 -> 23.7 us for the gradient of 1400 tokens, 2 heads; a map of K and V
+// only, whose heads are half lines, gains nothing).
+template <class T, int NH>
+__global__ __launch_bounds__(256 * NH) void raw_state_kernel(AggregateArgs a) {
     typedef Traits<T> Tr;
     typedef typename Tr::Frag Frag;
-    __shared__ float red[4 * kStateSize];
+    __shared__ float red[4 * NH * kStateSize];
     const unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
-    const int h = Lid % a.heads;
-    const int chunk = (Lid / a.heads) % a.nchunks;
-    const int b = Lid / (a.heads * a.nchunks);
+    const int hgroups = (a.heads + NH - 1) / NH;
+    const int h0 = (Lid % hgroups) * NH;
+    const int chunk = (Lid / hgroups) % a.nchunks;
+    const int b = Lid / (hgroups * a.nchunks);
     const int Ct = a.heads * 16;
     const long N = (long)a.H * a.W;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int h = h0 + wave % NH, part = wave / NH;        // the wave's head and its quarter of the token groups
     const int x16 = lane & 15, q = lane >> 4;
     Frag ident;
 #pragma unroll
@@ -341,7 +347,7 @@ __global__ __launch_bounds__(kAggThreads) void raw_state_kernel(AggregateArgs a)
     const long g_begin = (long)chunk * per_chunk;
     const long g_end = g_begin + per_chunk < n_groups ? g_begin + per_chunk : n_groups;
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-    for (long g = g_begin + wave; g < g_end; g += 4) {
+    for (long g = g_begin + part; g < g_end && h < a.heads; g += 4) {
         const long n = g * 16 + x16;
         const bool ok = n < N;
         const long tok = (long)b * N + n;
@@ -365,18 +371,16 @@ __global__ __launch_bounds__(kAggThreads) void raw_state_kernel(AggregateArgs a)
     for (int r = 0; r < 4; ++r) mine[(q * 4 + r) * 17 + x16] = kv[r];
     if (q == 0) mine[x16 * 17 + 16] = ks;
     __syncthreads();
-    for (int j = threadIdx.x; j < kStateSize; j += kAggThreads) {
-        const float s = (red[j] + red[kStateSize + j]) + (red[2 * kStateSize + j] + red[3 * kStateSize + j]);
-        a.partials[((((long)b * a.S + 0) * a.heads + h) * a.nchunks + chunk) * kStateSize + j] = s;
+    for (int i = threadIdx.x; i < NH * kStateSize; i += 256 * NH) {
+        const int w = i / kStateSize, j = i - w * kStateSize;
+        if (h0 + w >= a.heads) break;
+        const float* r = red + w * kStateSize + j;         // part p of head w is wave p * NH + w
+        constexpr int kPart = NH * kStateSize;
+        const float s = (r[0] + r[kPart]) + (r[2 * kPart] + r[3 * kPart]);
+        a.partials[((((long)b * a.S + 0) * a.heads + h0 + w) * a.nchunks + chunk) * kStateSize + j] = s;
     }
 }
 
-// The same state without the matrix cores: wavefront-level outer products on the vector ALUs and a
-// shuffle reduction.  Four lanes share a token: lane (token slot l / 4, part p = l % 4) holds the
-// token's 16 rectified K channels and its V channels 4p..4p+3, and accumulates KV[e][4p + j] for all
-// e (64 fp32 sums) plus, in part 0's lanes, Ksum[e]; a wave takes 16 tokens per step.  At the end the
-// 16 token slots are summed with xor-shuffles and the four waves through LDS.  It exists so that the
-// choice of MFMA for this contraction can be measured (msla_forward_opts, MSLA_OPT_STATE_VALU).
 template <class T>
 __global__ __launch_bounds__(kAggThreads) void raw_state_valu_kernel(AggregateArgs a) {
     typedef Traits<T> Tr;
@@ -568,8 +572,13 @@ hipError_t run_raw_state(const AggregateArgs& a, hipStream_t stream) {
     if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
     if (a.state_valu)
         hipLaunchKernelGGL((raw_state_valu_kernel<T>), dim3((unsigned)nblocks), dim3(kAggThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL((raw_state_kernel<T>), dim3((unsigned)nblocks), dim3(kAggThreads), 0, stream, a);
+    else {
+        if (a.heads >= 4 && a.k_ts == 48L * a.heads)
+            hipLaunchKernelGGL((raw_state_kernel<T, 4>), dim3((unsigned)((long)a.B * ((a.heads + 3) / 4) * a.nchunks)), dim3(1024),
+                               0, stream, a);
+        else
+            hipLaunchKernelGGL((raw_state_kernel<T, 1>), dim3((unsigned)nblocks), dim3(256), 0, stream, a);
+    }
     return hipGetLastError();
 }
 
