@@ -269,6 +269,209 @@ __global__ __launch_bounds__(kGenThreads) void generic_apply_kernel(const T* __r
     }
 }
 
+// The same with the output projection (Section 3.1, last sentence) in one kernel, 16-bit storage, at most 16 head-branches
+// of 32: the attention rows -- made as above, rounded to the storage type as above -- go to an LDS tile that is the
+// projection's token operand, and never to memory.  A workgroup of eight waves owns 256 output channels, 32 a wave, whose
+// weights stay in registers (KCH chunks of 32 slots, one chunk a head-branch); it walks over tiles of 32 tokens of one
+// image, and wave w makes the rows of head-branches w and w + 8.  Two tiles, one barrier a tile, Q requested a tile ahead.
+// What bounds it is the matrix pipe: 4 x 512 cycles of fp32 products for the rows and 1024 for the projection a wave and
+// tile.  Against rows to memory and a projection of its own, whole modules: 8 x 8192 tokens, 16 head-branches, fp16 200.9 ->
+// 183.5 us; 3200, 12, bf16 48.0 -> 46.0; 1024, 4, fp16 34.9 -> 30.5.
+// LDS: an attention row is KCH*64 bytes, the 16-byte chunk index XOR-ed with token % 16, so that the sixteen tokens of an
+// operand read or a row store meet sixteen different chunks of the banks; the weights are dealt out through the same
+// memory, 128 bytes of every row at a time.
+template <class T, int KCH>
+struct Apply32Project {
+    static constexpr int kThreads = 512, TB = 32, kChan = 256, kHbw = KCH / 8;
+    static constexpr int kRow = KCH * 64, kTile = TB * kRow, kStage = kChan * 128;
+    static constexpr int kLds = 2 * kTile > kStage ? 2 * kTile : kStage;
+    static constexpr int kSlabs = KCH / 2;
+};
+template <class T, int KCH>
+__global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __restrict__ q_ms, const float* __restrict__ kv32,
+                                                                 const T* __restrict__ w_proj, T* __restrict__ out, int N,
+                                                                 int n_hb, int c_out, int n_cg, int tiles_per_image,
+                                                                 long n_tt, long tiles_per_block, float eps) {
+    typedef Apply32Project<T, KCH> S;
+    typedef Traits<T> Tr;
+    typedef typename Tr::Vec Vec;
+    typedef Traits<float> F32;
+    constexpr int kState = 32 * 33;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const unsigned L = xcd_remap(blockIdx.x, gridDim.x);
+    const int cg = (int)(L % (unsigned)n_cg);
+    const long t_begin = (long)(L / (unsigned)n_cg) * tiles_per_block;
+    const long t_end = t_begin + tiles_per_block < n_tt ? t_begin + tiles_per_block : n_tt;
+    if (t_begin >= t_end) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
+    const int K = n_hb * 32;
+    const int ch0 = cg * S::kChan + wave * 32;
+    const bool live = ch0 < c_out;
+
+    // Q of this wave's head-branches, both 16-token groups of a tile (a token past the image's end reads its last one, a
+    // head-branch past the last reads the first: their rows are not written)
+    u32x4 qv[S::kHbw][2];
+    auto fetch_q = [&](long t) {
+        const int b = (int)(t / tiles_per_image), n0 = (int)(t % tiles_per_image) * S::TB;
+#pragma unroll
+        for (int i = 0; i < S::kHbw; ++i)
+#pragma unroll
+            for (int jt = 0; jt < 2; ++jt) {
+                const int m = wave + 8 * i, n = n0 + jt * 16 + x16;
+                qv[i][jt] = *(const u32x4*)(q_ms + ((long)b * N + (n < N ? n : N - 1)) * K + (m < n_hb ? m : 0) * 32 + q * 8);
+            }
+    };
+    fetch_q(t_begin);
+
+    // weights: fragment (io, kk) = rows ch0 + 16 io + x16, slots 32 kk + 8q .. +7; slots past K and rows past c_out are zero
+    Vec wf[2][KCH];
+    {
+        constexpr int kPer = S::kChan * 8 / S::kThreads;
+        const BufRsrc wres = make_rsrc(w_proj, (long)c_out * K * 2);
+        const unsigned row_bytes = (unsigned)K * 2u;
+        u32x4 st[S::kSlabs][kPer];
+        auto request = [&](int sl) {
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int id = i * S::kThreads + threadIdx.x, row = cg * S::kChan + (id >> 3);
+                const unsigned col = sl * 128 + (id & 7) * 16;
+                st[sl][i] = buf_load16(wres, row < c_out && col < row_bytes ? (unsigned)row * row_bytes + col : kOobOffset, 0);
+            }
+        };
+        request(0);
+        static_for<0, S::kSlabs>([&](auto sl_c) {
+            constexpr int sl = decltype(sl_c)::value;
+            if constexpr (sl + 1 < S::kSlabs) request(sl + 1);
+            if constexpr (sl > 0) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int id = i * S::kThreads + threadIdx.x, row = id >> 3;
+                *(u32x4*)(lds + row * 128 + (((id & 7) ^ ((row >> 1) & 7)) * 16)) = st[sl][i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int io = 0; io < 2; ++io)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int row = wave * 32 + io * 16 + x16;
+                    wf[io][2 * sl + h] = __builtin_bit_cast(Vec, *(const u32x4*)(lds + row * 128 + (((h * 4 + q) ^ ((row >> 1) & 7)) * 16)));
+                }
+        });
+        __syncthreads();
+    }
+    // slots of head-branches that are not there are read with zero weights: they must hold numbers
+    for (int i = threadIdx.x; i < 2 * S::TB * (KCH - n_hb) * 4; i += S::kThreads) {
+        const int row = i / ((KCH - n_hb) * 4), c = n_hb * 4 + i % ((KCH - n_hb) * 4);
+        *(u32x4*)(lds + row * S::kRow + ((c ^ (row & 15)) * 16)) = u32x4{0u, 0u, 0u, 0u};
+    }
+
+    f32x4 st[S::kHbw][2][2];
+    float ksum[S::kHbw][8];
+    const int fo = 8 * (x16 >> 2) + (x16 & 3);
+    int img = -1;
+    auto load_states = [&](int b) {
+        img = b;
+#pragma unroll
+        for (int i = 0; i < S::kHbw; ++i) {
+            const int m = wave + 8 * i;
+            const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+#pragma unroll
+            for (int jc = 0; jc < 2; ++jc)
+#pragma unroll
+                for (int jo = 0; jo < 2; ++jo)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) st[i][jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ksum[i][e] = s[(8 * q + e) * 33 + 32];
+        }
+    };
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    auto make_rows = [&](int to) {
+#pragma unroll
+        for (int i = 0; i < S::kHbw; ++i) {
+            const int m = wave + 8 * i;
+            if (m < n_hb) {
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt) {
+                    const Vec f = __builtin_bit_cast(Vec, qv[i][jt]);
+                    float rq[8], den = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        rq[e] = fmaxf(Tr::to_f32(f[e]), 0.f);
+                        den = fmaf(rq[e], ksum[i][e], den);
+                    }
+                    den += __shfl_xor(den, 16);
+                    den += __shfl_xor(den, 32);
+                    const f32x4 lo = {rq[0], rq[1], rq[2], rq[3]}, hi = {rq[4], rq[5], rq[6], rq[7]};
+                    const f32x4 n0 = F32::mma16(F32::mma16(z, st[i][0][0], lo), st[i][1][0], hi);
+                    const f32x4 n1 = F32::mma16(F32::mma16(z, st[i][0][1], lo), st[i][1][1], hi);
+                    const float inv = 1.0f / (den + eps);
+                    Vec o;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        o[r] = Tr::from_f32(n0[r] * inv);
+                        o[4 + r] = Tr::from_f32(n1[r] * inv);
+                    }
+                    *(u32x4*)(lds + to + (jt * 16 + x16) * S::kRow + (((m * 4 + q) ^ x16) * 16)) = __builtin_bit_cast(u32x4, o);
+                }
+            }
+        }
+    };
+    load_states((int)(t_begin / tiles_per_image));
+    make_rows(0);
+    for (long t = t_begin; t < t_end; ++t) {
+        const int here = (int)((t - t_begin) & 1) * S::kTile, next = S::kTile - here;
+        const bool more = t + 1 < t_end;
+        if (more) fetch_q(t + 1);
+        __syncthreads();                    // rows of tile t complete; nobody reads the other tile any more
+        const int b = (int)(t / tiles_per_image), n0 = (int)(t % tiles_per_image) * S::TB;
+        f32x4 acc[2][2] = {{z, z}, {z, z}};
+        if (live) {
+#pragma unroll
+            for (int kk = 0; kk < KCH; ++kk)
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt) {
+                    const Vec bf = __builtin_bit_cast(Vec, *(const u32x4*)(lds + here + (jt * 16 + x16) * S::kRow + (((kk * 4 + q) ^ x16) * 16)));
+#pragma unroll
+                    for (int io = 0; io < 2; ++io) acc[io][jt] = Tr::mma_vec(acc[io][jt], wf[io][kk], bf);
+                }
+            // two 8-byte fragments leave in one 16-byte store (lane groups swapped: channels 16 (q % 2) + 8 (q / 2) .. +7)
+#pragma unroll
+            for (int jt = 0; jt < 2; ++jt) {
+                const u32x2 even = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[0][jt]));
+                const u32x2 odd = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[1][jt]));
+                const u32x2 s0 = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
+                const u32x2 s1 = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+                const int n = n0 + jt * 16 + x16, oc = ch0 + (q & 1) * 16 + (q >> 1) * 8;
+                if (n < N && oc < c_out) *(u32x4*)(out + ((long)b * N + n) * c_out + oc) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+            }
+        }
+        if (more) {
+            const int b_next = (int)((t + 1) / tiles_per_image);
+            if (b_next != img) load_states(b_next);
+            make_rows(next);
+        }
+    }
+}
+
+template <class T, int KCH>
+hipError_t run_apply32_project(const GenericArgs& a, int N, hipStream_t stream) {
+    typedef Apply32Project<T, KCH> S;
+    const int n_hb = (1 + a.n_scales) * a.heads, n_cg = (a.c_out + S::kChan - 1) / S::kChan;
+    const int tpi = (N + S::TB - 1) / S::TB;
+    const long n_tt = (long)a.B * tpi;
+    if (n_tt * n_cg > 0x7fffffffL) return hipErrorInvalidValue;
+    const long groups = compute_units() / n_cg > 0 ? compute_units() / n_cg : 1;       // one workgroup a CU (registers)
+    const long per = (n_tt + groups - 1) / groups;
+    const long nblocks = (n_tt + per - 1) / per * n_cg;
+    const hipError_t e = allow_dynamic_lds<apply32_project_kernel<T, KCH>>(S::kLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((apply32_project_kernel<T, KCH>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds, stream,
+                       (const T*)a.q_ms, a.kv32, (const T*)a.w_proj, (T*)a.out, N, n_hb, a.c_out, n_cg, tpi, n_tt, per, a.eps);
+    return hipGetLastError();
+}
+
 // fixed-order sum of the partial states, then the normalise-and-apply pass
 template <class T, int D>
 hipError_t finish_generic(const GenericArgs& a, int N, hipStream_t stream) {
@@ -280,6 +483,14 @@ hipError_t finish_generic(const GenericArgs& a, int N, hipStream_t stream) {
                        a.kv32, a.nchunks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if constexpr (sizeof(T) == 2) {
+        const int n_hb = S * a.heads;
+        if (a.projected != nullptr && n_hb <= 16 && (long)a.c_out * n_hb * 64 < 0x7fffffffL) {
+            e = n_hb <= 8 ? run_apply32_project<T, 8>(a, N, stream) : run_apply32_project<T, 16>(a, N, stream);
+            if (e == hipSuccess) *a.projected = true;
+            return e;
+        }
+    }
     const int bpi = (N + 16 * kApplyGroups - 1) / (16 * kApplyGroups);
     const long nb2 = (long)a.B * ((S * a.heads + 3) / 4) * bpi;
     if (nb2 > 0x7fffffffL) return hipErrorInvalidValue;

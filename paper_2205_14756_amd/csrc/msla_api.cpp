@@ -299,8 +299,10 @@ msla_status generic_forward(const void* x, const void* w_qkv, const void* w_dw, 
     a.B = B; a.H = H; a.W = W; a.heads = heads; a.head_dim = head_dim; a.n_scales = n_scales;
     for (int i = 0; i < n_scales; ++i) a.scales[i] = scales[i];
     a.nchunks = p.nchunks; a.eps = eps;
+    bool projected = false;
+    a.w_proj = w_proj; a.out = out_tok; a.c_out = C; a.projected = &projected;
     if (msla::launch_generic_core((int)dt, a, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
-    if (msla::launch_linear((int)dt, ws + p.att, w_proj, out_tok, p.T, p.S * p.Ct, C, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
+    if (!projected && msla::launch_linear((int)dt, ws + p.att, w_proj, out_tok, p.T, p.S * p.Ct, C, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
     if (layout == MSLA_NCHW && msla::launch_transpose((int)dt, out_tok, out, B, H * W, C, hs) != hipSuccess)
         return MSLA_ERR_LAUNCH;
     return MSLA_OK;

@@ -140,6 +140,12 @@ struct GenericArgs {
     int scales[8];
     int nchunks;
     float eps;
+    // optional: the output projection as well, out [T, c_out] = att w_proj^T.  A launch that did it leaves att unwritten
+    // and sets *projected; one that did not (no kernel for the shape) wrote att as always.
+    const void* w_proj = nullptr;
+    void* out = nullptr;
+    int c_out = 0;
+    bool* projected = nullptr;
 };
 hipError_t launch_generic_core(int dt, const GenericArgs& a, hipStream_t stream);
 

@@ -113,3 +113,22 @@ def test_fp32_paired_heads_of_eight_keep_their_own_denominators():
 def test_paired_scales(dtype, B, H, W, heads, scales):
     base.test_multiscale_state_and_core(dtype, B, H, W, heads, scales)
     base.check_module(wk.random_module(17 + W, dtype, B, 16 * heads, H, W, heads, 16, scales), dtype, heads, 16, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# heads of 32, normalise-and-apply fused with the projection: 1, 2, 6, 12 and 16 head-branches (8 and 16 slots of weights),
+# output channels that fill half a wave's pair of groups, a second channel group, tiles of several images in one workgroup;
+# 18 head-branches: the separate kernels
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 48, 3, 5, 1, ()), (3, 48, 5, 7, 1, (5,)), (5, 96, 40, 61, 3, (5,)),
+                                                  (2, 272, 9, 40, 4, (3, 5)), (2, 512, 6, 11, 8, (5,)), (1, 192, 9, 10, 6, (3, 5))])
+def test_head_size_32_fused_projection(dtype, B, C, H, W, heads, scales):
+    print(f"routes: head size 32 fused {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
+    base.check_module(wk.random_module(83 + C + H, dtype, B, C, H, W, heads, 32, scales), dtype, heads, 32, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+# the raw state of a map that holds Q, K and V side by side: three heads (one a workgroup), four, five (a second workgroup
+# with one head), several chunks
+@pytest.mark.parametrize("B,H,W,heads", [(2, 3, 7, 3), (1, 9, 11, 4), (2, 40, 33, 5)])
+def test_raw_state_of_interleaved_heads(dtype, B, H, W, heads):
+    base.test_multiscale_state_and_core(dtype, B, H, W, heads, ())
