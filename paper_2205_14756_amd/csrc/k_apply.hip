@@ -1000,8 +1000,13 @@ hipError_t launch_apply(int dt, const void* q_ms, const void* kvfrag, const floa
 hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
                                 const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
                                 int n_hb, int c_out, float eps, hipStream_t stream) {
-    // more head-branches than the register-resident form holds: the long-contraction kernel
-    if (n_hb > 32 && small_product(dt, n_tokens, n_hb * 16, c_out))
+    // more head-branches than the register-resident form holds: the long-contraction kernel, which makes a token's attention
+    // rows once per 128 output channels and keeps the weights, where the tiled form makes them once per 256 and fetches the
+    // weights for every tile.  For few tokens, or up to three such channel groups (8 x 4096 tokens, 320 channels, 60
+    // head-branches, fp16: 190 us a module tiled, 172; 6 x 7055, 288, 54, bf16: 264, 246; with four, 8 x 4096, 512, 64: fp16 224,
+    // 229, bf16 239, 270)
+    const int K = n_hb * 16;
+    if (n_hb > 32 && (small_product(dt, n_tokens, K, c_out) || (dt != 0 && K <= 1024 && c_out <= 384)))
         return launch_small_apply_project(dt, q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out,
                                           eps, stream);
     switch (dt) {

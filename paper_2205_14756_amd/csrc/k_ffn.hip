@@ -205,11 +205,11 @@ __global__ __launch_bounds__(512) void ffn_dw_project_kernel(const T* __restrict
 // the 16-byte chunk index XOR-ed with (row / 2) % 8 (full rate for operand reads and row-order writes).
 // Requires one image's expanded map to stay below 2^31 bytes (32-bit offsets in a buffer resource).
 //
-// RPL: output rows a producer lane makes; a block is 4*RPL rows of 16 tokens.  BR: output channels (256 or 128); eight
+// RPL: output rows a producer lane makes, TC: columns of a block, which is then 64/TC*RPL rows of TC tokens.  BR: output channels (256 or 128); eight
 // consumer waves are BR/64 channel groups of 64 times the token groups that are left.
-template <class T, int RPL, int BR>
+template <class T, int RPL, int BR, int TC_>
 struct FfnSplit {
-    static constexpr int TR = 4 * RPL, TC = 16, TB = TR * TC;
+    static constexpr int TC = TC_, TR = 64 / TC * RPL, TB = TR * TC;
     static constexpr int kHaloW = TC + 2, kHaloH = TR + 2, kHaloTok = kHaloW * kHaloH;
     static constexpr int kWt = BR * 128, kTok = TB * 128, kPlane = kHaloTok * 16 + 16, kHalo = 8 * kPlane;
     static constexpr int WRC = BR / 64, WCC = 8 / WRC;         // consumer waves: channel groups x token groups
@@ -218,13 +218,13 @@ struct FfnSplit {
     static constexpr int kLds = 2 * (kWt + kTok + kHalo);
     static_assert(JT >= 1 && 8 * kStageWave <= kLds && kLds <= 160 * 1024, "the blocks fit");
 };
-template <class T, int ACT, int RPL, int BR>
+template <class T, int ACT, int RPL, int BR, int TC>
 __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __restrict__ h, const T* __restrict__ w_dw,
                                                                    const T* __restrict__ w2, const T* __restrict__ res,
                                                                    T* __restrict__ out, int H, int W, int E, int c_out,
                                                                    int tiles_x, int tiles_y, int n_rb) {
     static_assert(sizeof(T) == 2, "16-bit storage types");
-    typedef FfnSplit<T, RPL, BR> S;
+    typedef FfnSplit<T, RPL, BR, TC> S;
     typedef Traits<T> Tr;
     typedef typename Tr::Vec Vec;
     constexpr int BK = 64;                           // hidden channels per slab (128 bytes)
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
             }
             __syncthreads();
         }
-        // ---- results: block token t = (row t / 16, column t % 16).  The wave parks 16 tokens x 64 channels as fp32, each
+        // ---- results: block token t = (row t / TC, column t % TC).  The wave parks 16 tokens x 64 channels as fp32, each
         // lane picks up the 8 channels it will write, adds the residual's same 16 bytes and rounds once.
         const long base = ((long)b * H + y0) * W + x0;
         const int rows = H - y0 < S::TR ? H - y0 : S::TR, cols = W - x0 < S::TC ? W - x0 : S::TC;
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int v = lane + 64 * i, row = v >> 3, cv = v & 7;
-                const int t = (wc * JT + jt) * 16 + row, r = t >> 4, c = t & 15, oc = oc0 + wr * 64 + cv * 8;
+                const int t = (wc * JT + jt) * 16 + row, r = t / TC, c = t % TC, oc = oc0 + wr * 64 + cv * 8;
                 if (r < rows && c < cols && oc < c_out) {
                     const long at = (base + (long)r * W + c) * c_out + oc;
                     const f32x4 a0 = *(const f32x4*)(mine + row * S::kStageRow + cv * 32);
@@ -340,14 +340,14 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
         }
     } else {
         // ------------------------------------------------------------ producers
-        // A wave is one 16-byte channel vector of the slab (8 channels), its lanes the block's 16 columns and
-        // four groups of RPL rows: the 72 filter taps a wave needs are then the same for all its lanes and live in scalar
+        // A wave is one 16-byte channel vector of the slab (8 channels), its lanes the block's columns and
+        // groups of RPL rows: the 72 filter taps a wave needs are then the same for all its lanes and live in scalar
         // registers, read straight from w_dw (8 channels x 9 taps are 144 consecutive bytes).  The halo is
         // kept as 8 planes [channel vector][halo token][16 bytes], so consecutive lanes read consecutive 16
         // bytes; a plane is padded by 16 bytes, which spreads the 8 planes a row-order copy writes to at once
         // over all banks.
         const int pt = threadIdx.x - 512;
-        const int dvec = wave - 8, lane = lane_id(), dcol = lane & 15, dgrp = lane >> 4;
+        const int dvec = wave - 8, lane = lane_id(), dcol = lane % TC, dgrp = lane / TC;
         constexpr int kPlane = S::kPlane;
         const BufRsrc hres = make_rsrc(h + (long)b * H * W * E, (long)H * W * e_bytes);
         // halo copy: vector id = j * 512 + pt -> halo token id / 8, chunk id % 8
@@ -432,16 +432,16 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
     }
 }
 
-template <class T, int ACT, int RPL, int BR>
+template <class T, int ACT, int RPL, int BR, int TC>
 hipError_t run_dw_project_split_as(const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B, int H,
                                    int W, int E, int c_out, hipStream_t stream) {
-    typedef FfnSplit<T, RPL, BR> S;
+    typedef FfnSplit<T, RPL, BR, TC> S;
     const int tiles_x = (W + S::TC - 1) / S::TC, tiles_y = (H + S::TR - 1) / S::TR, n_rb = (c_out + BR - 1) / BR;
     const long nblocks = (long)B * tiles_x * tiles_y * n_rb;
     if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
-    const hipError_t e = allow_dynamic_lds<ffn_dw_project_split_kernel<T, ACT, RPL, BR>>(S::kLds);
+    const hipError_t e = allow_dynamic_lds<ffn_dw_project_split_kernel<T, ACT, RPL, BR, TC>>(S::kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((ffn_dw_project_split_kernel<T, ACT, RPL, BR>), dim3((unsigned)nblocks), dim3(1024), S::kLds, stream,
+    hipLaunchKernelGGL((ffn_dw_project_split_kernel<T, ACT, RPL, BR, TC>), dim3((unsigned)nblocks), dim3(1024), S::kLds, stream,
                        (const T*)h, (const T*)w_dw, (const T*)w2, (const T*)res, (T*)out, H, W, E, c_out, tiles_x, tiles_y,
                        n_rb);
     return hipGetLastError();
@@ -457,10 +457,16 @@ hipError_t run_dw_project_split(const void* h, const void* w_dw, const void* w2,
     // 39.0, 20.9, 138.5; a block of 8 x 16 has 180 halo tokens where 4 x 32 has 204.)
     const bool small = 4 * blocks < 3L * compute_units();
     if (c_out <= 128)
-        return small ? run_dw_project_split_as<T, ACT, 1, 128>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
-                     : run_dw_project_split_as<T, ACT, 2, 128>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
-    return small ? run_dw_project_split_as<T, ACT, 1, 256>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
-                 : run_dw_project_split_as<T, ACT, 2, 256>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+        return small ? run_dw_project_split_as<T, ACT, 1, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                     : run_dw_project_split_as<T, ACT, 2, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+    if (small) return run_dw_project_split_as<T, ACT, 1, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+    // 128 tokens as 4 x 32 or as 8 x 16: whichever takes fewer rounds of workgroups (one a CU) over the map's ragged edges --
+    // 6 x 61 x 70, 192 -> 768 channels, 288 blocks or 240: 66 us or 46 -- and 4 x 32 where they are equal (4 x 64 x 64, 384 ->
+    // 1536: 76.5 us or 79.1; 8 x 64 x 128, 256 -> 1024: 133.1 or 134.3)
+    const long n_rb = (c_out + 255) / 256, cus = compute_units();
+    const long rounds32 = ((long)B * ((W + 31) / 32) * ((H + 3) / 4) * n_rb + cus - 1) / cus, rounds16 = (blocks + cus - 1) / cus;
+    return rounds32 <= rounds16 ? run_dw_project_split_as<T, ACT, 2, 256, 32>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                                : run_dw_project_split_as<T, ACT, 2, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
 }
 
 template <class T>

@@ -79,10 +79,11 @@ def test_core_writes_attention_rows(dtype, B, H, W, heads):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-# blocks of 64 and of 128 tokens, up to 128 and up to 256 output channels a workgroup; ragged columns and rows, channel
+# blocks of 64 and of 128 tokens (as 4 x 32 and, the last, as 8 x 16), up to 128 and up to 256 output channels a workgroup; ragged columns and rows, channel
 # groups past the output (48, 144), a hidden size that is no whole number of slabs, a narrow map, more than one group (272)
 @pytest.mark.parametrize("B,C,H,W,hidden", [(1, 48, 5, 17, 80), (3, 48, 61, 130, 80), (2, 144, 7, 33, 144),
-                                            (4, 144, 61, 113, 160), (2, 128, 50, 3, 128), (1, 272, 9, 18, 288)])
+                                            (4, 144, 61, 113, 160), (2, 128, 50, 3, 128), (1, 272, 9, 18, 288),
+                                            (6, 144, 61, 70, 64)])
 def test_ffn_block_shapes(dtype, B, C, H, W, hidden):
     block.test_ffn(dtype, 1, B, C, H, W, hidden)
 
