@@ -149,13 +149,13 @@ __global__ __launch_bounds__(256) void softmax_attention_kernel(const T* __restr
 // kept off it.  The products are 32x32x16 matrix instructions (the contraction of K . Q^T is the head size, 16: the
 // 16x16 form spends the same cycles on a quarter of the scores).  A lane then holds 16 of the 32 keys of ONE query,
 // so a maximum needs one exchange between the wave's halves per 64 keys.  The sums of the weights are a row of ones
-// under V^T.  The accumulators are rescaled only when some query's maximum has grown by more than kSmSlack (the
-// weights are then at most 2^kSmSlack, far inside fp16's range; their relative rounding does not depend on the
-// scale), which after the first few blocks is hardly ever.  The key test exists in a ragged last tile only.
-// 8 x 16 heads, 2048 tokens, fp16 (537 M scores): 88 us; with 16x16 products and a rescaling in every block, 232 us.
-// Groups of 128 keys instead of 64 (three waves a SIMD): 87 us; of 32 keys: 91-94 us.
+// under V^T.  The accumulators are rescaled whenever one of the wave's queries finds a larger score, so that the weights
+// are at most 1 and the heaviest of a block lie just below it, where the 16-bit grid is relatively finest.  (Letting the
+// maximum lag behind by up to 2^8 saves most of the rescaling, 85 instead of 89 us, but spreads the weights over the whole
+// grid: relative error 2.92e-4 instead of 2.79e-4 in fp16, 2.33e-3 instead of 2.23e-3 in bf16.)  Weights below 2^-126
+// of the largest are flushed to zero by the exponential instruction.  The key test exists in a ragged last tile only.
+// 8 x 16 heads, 2048 tokens, fp16 (537 M scores): 89 us; with 16x16 products and a rescaling in every block, 232 us.
 constexpr int kSm2Keys = 128;           // keys per LDS tile
-constexpr float kSmSlack = 8.0f;        // (exponents of 2)
 constexpr int kSm2VRow = kSm2Keys * 2 + 16;                 // V^T row in LDS, padded by one 16-byte slot
 constexpr int kSm2KBytes = kSm2Keys * 32;                   // K tile: two planes [half of d][key][16 bytes]
 constexpr int kSm2VBytes = 18 * kSm2VRow;                   // 16 channels, a row of ones, a row of zeros
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256, 4) void softmax_attention32_kernel(const T* __
         const auto both = __builtin_amdgcn_permlane32_swap(mx_bits, mx_bits, false, false);
         const unsigned mx_lo = both[0], mx_hi = both[1];           // the lower and the upper half's maximum
         mx = fmaxf(__builtin_bit_cast(float, mx_lo), __builtin_bit_cast(float, mx_hi)) * kScale;
-        if (__any(mx > m_run + kSmSlack)) {
+        if (__any(mx > m_run)) {
             const float m_new = fmaxf(m_run, mx);
             // (nothing seen yet, or nothing but masked keys: no weight is in o)
             const float keep = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
