@@ -280,17 +280,24 @@ __global__ __launch_bounds__(256, 4) void softmax_attention32_kernel(const T* __
     __syncthreads();
     const int n_full = N / kSm2Keys, n_tiles = (N + kSm2Keys - 1) / kSm2Keys;
     const int first = kSplit ? wave : 0, last = kSplit ? wave + 1 : 4;
+    // a wave whose queries are all past the end has nothing to do, nor has anyone with the last tile's groups that are
+    // (2048 sequences of 64 tokens 12.1 -> 7.8 us, 4096 of 16 20.5 -> 8.6; with 64 queries a workgroup and 16x16 products 9.5
+    // and 11.8)
+    const bool live = kSplit || qb * 128 + wave * 32 < N;
     for (int tile = 0; tile < n_full; ++tile) {
         const int buf = tile & 1, k0 = tile * kSm2Keys;
         if (tile + 1 < n_tiles) fetch(k0 + kSm2Keys);
+        if (live) {
 #pragma unroll 2
-        for (int g = first; g < last; g += nsub) sweep(nsub, std::false_type{}, buf, g, k0);
+            for (int g = first; g < last; g += nsub) sweep(nsub, std::false_type{}, buf, g, k0);
+        }
         if (tile + 1 < n_tiles) park(buf ^ 1);
         __syncthreads();
     }
     if (n_full < n_tiles) {             // the ragged last tile
 #pragma unroll 1
-        for (int g = first; g < last; g += nsub) sweep(nsub, std::true_type{}, n_full & 1, g, n_full * kSm2Keys);
+        for (int g = first; g < last && live && n_full * kSm2Keys + g * 32 < N; g += nsub)
+            sweep(nsub, std::true_type{}, n_full & 1, g, n_full * kSm2Keys);
         __syncthreads();
     }
 

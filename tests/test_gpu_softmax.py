@@ -114,3 +114,10 @@ def test_softmax_weights_lose_no_precision_to_the_running_maximum(dtype, B, N, h
     # over these 2.6e5 to 1.0e6 roundings the two norms agree to about 0.3 %; blocks of 32 or 128 keys move the model's by up to
     # 0.8 %.  Weights of any size up to 2^8 (a maximum that may lag behind) lie on all parts of the grid: 3 to 5 % more.
     assert err <= 1.015 * want
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# 128 queries a workgroup, some or most of whose waves have none; the last tile's groups of keys partly past the end
+@pytest.mark.parametrize("N", [1, 16, 32, 33, 64, 65, 97, 160])
+def test_softmax_short_sequences_of_many_heads(dtype, N):
+    test_softmax_attention_tiles_and_growing_scores(dtype, 8, N, 64)
