@@ -446,27 +446,32 @@ hipError_t run_dw_project_split_as(const void* h, const void* w_dw, const void* 
                        n_rb);
     return hipGetLastError();
 }
+// Rounds of workgroups, one a compute unit, over the map's ragged edges decide the block.  Blocks of 64 tokens take two
+// thirds of the time of blocks of 128 (and two of 128 channels fit a unit together): they are taken where they need no more rounds.
+// 16-bit FFNs, us with 64 / 128 tokens a block (rounds): 8192 tokens, 256 -> 1024 channels 32.4 / 42.0 (1 / 1), 16384 39.6 / 48.5
+// (1 / 1), 20480 of 192 49.0 / 41.4 (2 / 1), 24576 62.7 / 52.7 (2 / 1), 32768 79.1 / 68.0 (2 / 1), 40960, 256 -> 512 56.8 / 56.8 (3 / 2);
+// 16384, 128 -> 512 20.0 / 24.1 (1 / 1), 20480 30.6 / 26.3 (2 / 1), 32768 34.6 / 31.2 (2 / 1).
+// 128 tokens are 8 x 16 or 4 x 32, whichever takes fewer rounds (6 x 61 x 70, 192 -> 768 channels, 288 blocks of 4 x 32 or 240 of
+// 8 x 16: 66 or 46 us; 16 x 4 x 512, 128 -> 512, 256 or 512: 31.4 or 44.1).  Where they are equal, 4 x 32 for 256 channels a
+// workgroup (4 x 64 x 64, 384 -> 1536: 76.5 us or 79.1) and 8 x 16 for 128 (20480, 128 -> 512: 26.7 or 26.3).
 template <class T, int ACT>
 hipError_t run_dw_project_split(const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B, int H,
                                 int W, int E, int c_out, hipStream_t stream) {
-    const long blocks = (long)B * ((W + 15) / 16) * ((H + 7) / 8) * ((c_out + 255) / 256);
-    // blocks of 128 tokens, or -- where those leave a quarter of the compute units or more without one -- of 64: half the time
-    // a slab and (at 128 channels) two resident workgroups a CU.  Modules of 16-bit maps, 128 / 64 tokens a block: 2 x 8192
-    // tokens, 128 -> 512 channels (128 blocks) 25.9 / 21.9 us, 2048, 256 -> 1024 (16) 41.0 / 28.5; 7 x 1928, 32 -> 128 (217)
-    // 13.4 / 15.4, 8 x 8192, 256 -> 1024 (512) 137.7 / 155.9.  (Blocks were 4 x 32 tokens by 256 channels throughout: 28.8,
-    // 39.0, 20.9, 138.5; a block of 8 x 16 has 180 halo tokens where 4 x 32 has 204.)
-    const bool small = 4 * blocks < 3L * compute_units();
-    if (c_out <= 128)
-        return small ? run_dw_project_split_as<T, ACT, 1, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
-                     : run_dw_project_split_as<T, ACT, 2, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
-    if (small) return run_dw_project_split_as<T, ACT, 1, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
-    // 128 tokens as 4 x 32 or as 8 x 16: whichever takes fewer rounds of workgroups (one a CU) over the map's ragged edges --
-    // 6 x 61 x 70, 192 -> 768 channels, 288 blocks or 240: 66 us or 46 -- and 4 x 32 where they are equal (4 x 64 x 64, 384 ->
-    // 1536: 76.5 us or 79.1; 8 x 64 x 128, 256 -> 1024: 133.1 or 134.3)
-    const long n_rb = (c_out + 255) / 256, cus = compute_units();
-    const long rounds32 = ((long)B * ((W + 31) / 32) * ((H + 3) / 4) * n_rb + cus - 1) / cus, rounds16 = (blocks + cus - 1) / cus;
-    return rounds32 <= rounds16 ? run_dw_project_split_as<T, ACT, 2, 256, 32>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
-                                : run_dw_project_split_as<T, ACT, 2, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+    const long cus = compute_units(), n_rb = c_out <= 128 ? 1 : (c_out + 255) / 256;
+    auto rounds = [&](int rows, int cols) {
+        return ((long)B * ((H + rows - 1) / rows) * ((W + cols - 1) / cols) * n_rb + cus - 1) / cus;
+    };
+    const long r64 = rounds(4, 16), r8x16 = rounds(8, 16), r4x32 = rounds(4, 32);
+    if (c_out <= 128) {
+        if (r64 <= r8x16 && r64 <= r4x32)
+            return run_dw_project_split_as<T, ACT, 1, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+        return r8x16 <= r4x32 ? run_dw_project_split_as<T, ACT, 2, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                              : run_dw_project_split_as<T, ACT, 2, 128, 32>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+    }
+    if (r64 <= r8x16 && r64 <= r4x32)
+        return run_dw_project_split_as<T, ACT, 1, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
+    return r4x32 <= r8x16 ? run_dw_project_split_as<T, ACT, 2, 256, 32>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
+                          : run_dw_project_split_as<T, ACT, 2, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
 }
 
 template <class T>

@@ -133,3 +133,10 @@ def test_head_size_32_fused_projection(dtype, B, C, H, W, heads, scales):
 @pytest.mark.parametrize("B,H,W,heads", [(2, 3, 7, 3), (1, 9, 11, 4), (2, 40, 33, 5)])
 def test_raw_state_of_interleaved_heads(dtype, B, H, W, heads):
     base.test_multiscale_state_and_core(dtype, B, H, W, heads, ())
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# maps of few rows, many workgroups: blocks of 4 x 32 tokens by up to 128 output channels; and by 256, one row short of a block
+@pytest.mark.parametrize("B,C,H,W,hidden", [(40, 48, 3, 200, 80), (40, 144, 3, 200, 80)])
+def test_ffn_blocks_of_flat_maps(dtype, B, C, H, W, hidden):
+    block.test_ffn(dtype, 1, B, C, H, W, hidden)
