@@ -140,3 +140,24 @@ def test_raw_state_of_interleaved_heads(dtype, B, H, W, heads):
 @pytest.mark.parametrize("B,C,H,W,hidden", [(40, 48, 3, 200, 80), (40, 144, 3, 200, 80)])
 def test_ffn_blocks_of_flat_maps(dtype, B, C, H, W, hidden):
     block.test_ffn(dtype, 1, B, C, H, W, hidden)
+
+
+# fp32 states: workgroups that walk 16 tiles of 8 x 32 tokens, and fewer, over a ragged map
+@pytest.mark.parametrize("B,H,W,heads,scales", [(4, 64, 128, 64, (5,)), (6, 81, 100, 11, (3, 7))])
+def test_fp32_states_take_one_rounding_a_tile(B, H, W, heads, scales):
+    print(f"routes: fp32 states {B}x{H}x{W} heads={heads}", flush=True)
+    t = wk.random_module(29 + H, "f32", 1, 16 * heads, 1, 1, heads, 16, scales)
+    g = torch.Generator(device="cuda").manual_seed(H)
+    qkv = torch.randn(B, H, W, 48 * heads, generator=g, device="cuda")
+    wdw, wg = base.weights(t, "f32", scales)
+    _, kv = msla.msla_multiscale_state(qkv, wdw, wg, heads, 16, scales)
+    k, v = (qkv.view(B, H * W, heads, 3, 16)[:, :, :, i].double().permute(0, 2, 1, 3) for i in (1, 2))
+    k = k.clamp(min=0)
+    want = torch.cat([k.transpose(2, 3) @ v, k.sum(2).unsqueeze(3)], 3)
+    d = kv[:, 0].double() - want
+    err = float(d[..., :16].norm() / want[..., :16].norm())
+    print(f"  relative error of the raw branch's KV {err:.2e}", flush=True)
+    # Sums of n terms of either sign carry a relative error of about 0.6 u sqrt(n / 2), u = 2^-24: 16 matrix instructions a
+    # tile and wave and up to 16 tiles, added separately, 0.6 u sqrt(8 + 8) = 1.4e-7; in one chain of 256, 4.0e-7 (of 176, 3.4e-7)
+    assert err <= 2.0e-7
+    assert float(d[..., 16].norm() / want[..., 16].norm()) <= 1.0e-7
