@@ -35,6 +35,33 @@ struct Shape {
     int nchunks, tiles_per_chunk;
 };
 
+// How many workgroups share a state's tiles in the fp32 aggregation kernels, at most `most`.  Two of them are resident on a
+// compute unit (one with a 7x7 filter, by its LDS), so what a grid costs is its rounds over those places, each the
+// workgroup's tiles and 1.4 more for its start and end, 0.2 with the long tiles of a 7x7 filter (4 x 8192 tokens, 8 heads,
+// 5x5: one round of 8 tiles 99.9 us a module, two rounds of 4 104.5).  The numbers that fill 1 .. 4 times 256 places are
+// tried, and `most`; of equals the smallest is taken.  6 x 50 x 144 tokens, 14 heads, the core, 504 workgroups with 6 tiles each
+// against 588 with 5, which are two rounds: 5x5 125 and 149 us, 7x7 196 and 282.
+long fp32_chunks(const Shape* s, long tiles, long most) {
+    const long states = (long)s->B * s->heads;
+    long best = most, best_cost = 0;
+    for (int r = 0; r <= 4; ++r) {
+        const long want = r < 4 ? 256L * (r + 1) / states : most;
+        if (want < 1 || want > most) continue;
+        const long tpc = (tiles + want - 1) / want, blocks = states * ((tiles + tpc - 1) / tpc);
+        long cost = 0;
+        for (int i = 0; i < s->n_scales; ++i) {
+            const bool wide = s->scales[i] == 7;
+            const long places = wide ? 256 : 512;
+            cost += (blocks + places - 1) / places * (5 * tpc + (wide ? 1 : 7));
+        }
+        if (best_cost == 0 || cost < best_cost) {
+            best = want;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 // Checks everything about the shape that does not involve pointers.
 msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int* scales, int n_scales,
                         int dt, Shape* s) {
@@ -60,7 +87,6 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     long target_blocks = 1024;
     if (n_scales > 0 && dt == MSLA_F32) {
         tiles = (long)((H + msla::kAggTileH - 1) / msla::kAggTileH) * ((W + msla::kAggTileW - 1) / msla::kAggTileW);
-        target_blocks = 512;   // two resident workgroups a CU (4 x 8192 tokens, 8 heads: 1024 104.5 us a module, 512 99.9, 256 108)
     } else if (n_scales > 0) {
         tiles = (long)((H + msla::kAggMfmaTileH - 1) / msla::kAggMfmaTileH) *
                 ((W + msla::kAggMfmaTileW - 1) / msla::kAggMfmaTileW);
@@ -74,6 +100,7 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     long want = (target_blocks + (long)B * heads - 1) / ((long)B * heads);
     if (want < 1) want = 1;
     if (want > tiles) want = tiles;
+    if (n_scales > 0 && dt == MSLA_F32) want = fp32_chunks(s, tiles, want);
     const long tpc = (tiles + want - 1) / want;
     s->tiles_per_chunk = (int)tpc;
     s->nchunks = (int)((tiles + tpc - 1) / tpc);

@@ -169,3 +169,26 @@ def test_forward_opts_rejects_unknown_bits_and_stage_bits_with_nchw(lib):
                                                       layout, None, opts)
     assert call(0, 64) == INVALID and call(0, 0x80000000) == INVALID
     assert call(1, 2) == UNSUPPORTED and call(1, 16 | 1) == UNSUPPORTED
+
+
+def _fp32_chunks(lib, B, H, W, heads, scales):
+    """Workgroups a state in the fp32 aggregation, from the size of the workspace that holds their partial states."""
+    up = lambda v: (v + 255) // 256 * 256
+    T, Ct, states = B * H * W, 16 * heads, B * heads * (1 + len(scales))
+    fixed = up(T * (1 + len(scales)) * Ct * 4) + up((T + 31) // 32 * 32 * 2 * Ct * 4) + up(states * 1088) + up(states * 2048) + up(states * 4)
+    st, n = _ws(lib, B, Ct, H, W, heads, 16, scales, F32)
+    assert st == OK
+    return [c for c in range(1, 1025) if fixed + up(states * c * 1088) == n]
+
+
+@pytest.mark.parametrize("B,H,W,heads,scales,chunks", [
+    (1, 32, 32, 4, (5,), 4),                # four tiles: one each
+    (4, 64, 128, 8, (5,), 16),              # 512 workgroups are one round of two a compute unit
+    (6, 50, 144, 14, (5,), 6),              # 504 in one round, not 588 in two
+    (20, 40, 40, 15, (3, 5), 3),            # 900 in two rounds with 4 tiles, not 600 in two with 5
+    (6, 50, 144, 14, (7,), 3),              # 7x7, one workgroup a compute unit: 252
+    (32, 16, 16, 12, (7,), 2),              # 768 in three rounds of one tile, not 384 in two of two
+    (2, 64, 128, 400, (5,), 1),             # more states than places
+])
+def test_fp32_workgroups_fill_whole_rounds(lib, B, H, W, heads, scales, chunks):
+    assert chunks in _fp32_chunks(lib, B, H, W, heads, scales)
