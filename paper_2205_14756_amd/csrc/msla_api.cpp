@@ -40,7 +40,7 @@ struct Shape {
 // workgroup's tiles and 1.4 more for its start and end, 0.2 with the long tiles of a 7x7 filter (4 x 8192 tokens, 8 heads,
 // 5x5: one round of 8 tiles 99.9 us a module, two rounds of 4 104.5).  The numbers that fill 1 .. 4 times 256 places are
 // tried, and `most`; of equals the smallest is taken.  6 x 50 x 144 tokens, 14 heads, the core, 504 workgroups with 6 tiles each
-// against 588 with 5, which are two rounds: 5x5 125 and 149 us, 7x7 196 and 282.
+// against 588 with 5, which are two rounds: 5x5 125 and 152 us; 7x7, 252 with 12 against those 588, three rounds: 197 and 242.
 long fp32_chunks(const Shape* s, long tiles, long most) {
     const long states = (long)s->B * s->heads;
     long best = most, best_cost = 0;
