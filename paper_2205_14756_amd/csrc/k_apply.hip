@@ -949,6 +949,21 @@ hipError_t run_apply_project_tiled(const void* q_ms, const void* kvfrag, const f
     return hipGetLastError();
 }
 
+// Whether an fp32 map of up to 32 head-branches is the tiled form's.  Its pieces are 256 channels x 64 tokens (128 where those
+// give every compute unit one), all or nothing: what it computes is its rounds over the compute units.  The weight-stationary
+// form computes no more than the map, but makes a token's attention rows once for every 128 channels, and is a quarter slower
+// for each.  So the tiled form pays where its pieces are at least three quarters as full as the other's.  Whole modules, us tiled /
+// weight-stationary: 16384 tokens of 256 channels (full pieces, both) 104 / 109, 2 x 16384 182 / 195, 8 x 16384 681 / 756; 12288
+// (three quarters of the first round) 89.5 / 87.7, 4096 59 / 44; 16384 of 128 (half of each piece) 47.8 / 43.7; 8192 of 320 93.4 / 98.1,
+// 20480 263 / 223.
+bool tiled_fp32_pays(long images, int N, int c_out) {
+    const long cus = compute_units(), rb = (c_out + 255) / 256;
+    const long b64 = images * ((N + 63) / 64) * rb, b128 = images * ((N + 127) / 128) * rb;
+    const long rounds = b128 < cus ? (b64 + cus - 1) / cus : (b128 + cus - 1) / cus * 2;        // of 64 tokens x 256 channels
+    const long other = images * ((N + 15) / 16) * 16 * ((c_out + 127) / 128) * 128;             // tokens x channels
+    return 4 * other >= 3 * rounds * cus * (64 * 256);
+}
+
 template <class T>
 hipError_t run_apply_project(const void* q_ms, const void* kvfrag, const float* kvscale, const void* w_proj,
                              void* out, const void* res, long n_tokens, int N, int n_hb, int c_out, float eps,
@@ -970,10 +985,12 @@ hipError_t run_apply_project(const void* q_ms, const void* kvfrag, const float* 
     }
 #endif
     if constexpr (sizeof(T) == 4) {
-        if (n_hb <= 8) return run_apply_project_f32<8>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-        if (n_hb <= 16) return run_apply_project_f32<16>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-        if (n_hb <= 24) return run_apply_project_f32<24>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-        if (n_hb <= 32) return run_apply_project_f32<32>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+        if (n_hb <= 32 && !tiled_fp32_pays(n_tokens / N, N, c_out)) {
+            if (n_hb <= 8) return run_apply_project_f32<8>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+            if (n_hb <= 16) return run_apply_project_f32<16>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+            if (n_hb <= 24) return run_apply_project_f32<24>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+            return run_apply_project_f32<32>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+        }
     }
     // Tiled form: 64 x 64 per wave, 256 channels x 128 tokens per workgroup; a map too small to give
     // every CU such a tile takes 64-token tiles (measured on the 2048- and 1024-token workloads: 33

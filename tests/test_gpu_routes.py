@@ -161,3 +161,11 @@ def test_fp32_states_take_one_rounding_a_tile(B, H, W, heads, scales):
     # tile and wave and up to 16 tiles, added separately, 0.6 u sqrt(8 + 8) = 1.4e-7; in one chain of 256, 4.0e-7 (of 176, 3.4e-7)
     assert err <= 2.0e-7
     assert float(d[..., 16].norm() / want[..., 16].norm()) <= 1.0e-7
+
+
+# fp32 maps that fill the tiled forms' pieces: normalise-and-apply in pieces of 64 tokens (two images, ragged) and of 128, the
+# Q/K/V projection tiled as well (all but the first)
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(3, 256, 61, 71, 16, ()), (1, 160, 127, 129, 10, (5,)), (2, 256, 127, 129, 16, ())])
+def test_fp32_tiled_kernels_on_full_maps(B, C, H, W, heads, scales):
+    print(f"routes: fp32 tiled {B}x{C}x{H}x{W} heads={heads}", flush=True)
+    base.check_module(wk.random_module(101 + C, "f32", B, C, H, W, heads, 16, scales), "f32", heads, 16, scales, stages=False)
