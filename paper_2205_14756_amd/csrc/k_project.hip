@@ -742,12 +742,23 @@ hipError_t run_qkv_project_ws(const void* x, const void* w_qkv, void* q_ms, long
     }
 }
 
+// Whether an fp32 Q/K/V projection of up to 256 input channels is the tiled form's: where its pieces of 256 channels x 128 tokens, in
+// whole rounds over the compute units (and whole groups of channel pieces, see run_project_tiled), are nearly as full as the
+// other form's of 64 x 32.  Modules, us tiled / weight-stationary: 2 x 16384 tokens of 256 channels 178.5 / 182.7, of 224 (0.92 as
+// full) 161.3 / 165.8; of 192 (0.75) 141.8 / 121.1.
+bool tiled_fp32_pays(long n_tokens, int c_out) {
+    const long cus = compute_units(), rb = (c_out + 255) / 256;
+    long rounds = ((n_tokens + 127) / 128 * rb + cus - 1) / cus;
+    if (rounds > rb) rounds = (rounds + rb - 1) / rb * rb;
+    return 10 * ((n_tokens + 31) / 32 * 32) * ((c_out + 63) / 64 * 64) >= 9 * rounds * cus * (128 * 256);
+}
+
 template <class T>
 hipError_t run_qkv_project(const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw,
                            long kv_tok_stride, long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads,
                            hipStream_t stream) {
     const int c_out = 3 * heads * 16;
-    if (c_in <= 256) {
+    if (c_in <= 256 && !(sizeof(T) == 4 && tiled_fp32_pays(n_tokens, c_out))) {
         const bool through = n_tokens * c_out * (long)sizeof(T) <= kThroughBytes;
         return through ? run_qkv_project_ws<T, true>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span,
                                                      n_tokens, c_in, heads, stream)
