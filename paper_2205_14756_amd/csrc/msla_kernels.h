@@ -87,9 +87,10 @@ hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, co
                                 const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
                                 int n_hb, int c_out, float eps, hipStream_t stream);
 
-// The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots and
-// few enough tokens that the weights are what a workgroup mostly fetches (k_small.hip).  They return
-// hipErrorNotSupported, without launching, for anything else.
+// The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots (k_small.hip): the callers take the
+// projections where few enough tokens make the weights what a workgroup mostly fetches (small_product), the apply + projection there
+// and, whatever the number of tokens, up to 384 output channels (launch_apply_project).  They return hipErrorNotSupported, without
+// launching, for other types and contractions.
 hipError_t launch_small_linear(int dt, const void* x, const void* w, void* y, long n_tokens, int c_in, int c_out,
                                hipStream_t stream);
 hipError_t launch_small_qkv_project(int dt, const void* x, const void* w_qkv, void* q_ms, long q_ms_stride,

@@ -169,3 +169,12 @@ def test_fp32_states_take_one_rounding_a_tile(B, H, W, heads, scales):
 def test_fp32_tiled_kernels_on_full_maps(B, C, H, W, heads, scales):
     print(f"routes: fp32 tiled {B}x{C}x{H}x{W} heads={heads}", flush=True)
     base.check_module(wk.random_module(101 + C, "f32", B, C, H, W, heads, 16, scales), "f32", heads, 16, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# long contractions beyond the few-token limit (more than 8 tile x channel-block pairs a compute unit), up to 384 channels: workgroups
+# walk eight and more tiles over four images with ragged ends; 33, 48 and 64 head-branches (24, 24 and 32 chunks of weights)
+@pytest.mark.parametrize("C,heads,scales", [(272, 11, (3, 5)), (384, 24, (5,)), (272, 32, (5,))])
+def test_long_contraction_of_many_tokens(dtype, C, heads, scales):
+    print(f"routes: long contraction, many tokens {dtype} 4x{C}x61x91 heads={heads}", flush=True)
+    base.check_module(wk.random_module(51 + heads, dtype, 4, C, 61, 91, heads, 16, scales), dtype, heads, 16, scales, stages=False)
