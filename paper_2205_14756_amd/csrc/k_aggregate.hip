@@ -403,6 +403,12 @@ __global__ __launch_bounds__(256 * NH) void raw_state_kernel(AggregateArgs a) {
     }
 }
 
+// The same state without the matrix cores: wavefront-level outer products on the vector ALUs and a
+// shuffle reduction.  Four lanes share a token: lane (token slot l / 4, part p = l % 4) holds the
+// token's 16 rectified K channels and its V channels 4p..4p+3, and accumulates KV[e][4p + j] for all
+// e (64 fp32 sums) plus, in part 0's lanes, Ksum[e]; a wave takes 16 tokens per step.  At the end the
+// 16 token slots are summed with xor-shuffles and the four waves through LDS.  It exists so that the
+// choice of MFMA for this contraction can be measured (msla_forward_opts, MSLA_OPT_STATE_VALU).
 template <class T>
 __global__ __launch_bounds__(kAggThreads) void raw_state_valu_kernel(AggregateArgs a) {
     typedef Traits<T> Tr;
