@@ -42,19 +42,9 @@ struct PlainDest {
     T* y;
     long n_tokens;
     int c_out;
-    // optional residual [n_tokens, c_out] that the tiled kernel adds to the fp32 sums before their one
-    // rounding (y = res + x w^T); nullptr: none
-    const T* res = nullptr;
     // optional activation applied to the fp32 sums before their one rounding: -1 none, 0 ReLU,
     // 1 hard-swish a * clip(a + 3, 0, 6) / 6, evaluated as a * clip(a / 6 + 1/2, 0, 1) (the FFN's expand projection)
     int act = -1;
-    __host__ __device__ __forceinline__ bool has_residual() const { return res != nullptr; }
-    // 16 bytes of the residual at (token, channel), zero past the ends
-    __device__ __forceinline__ u32x4 residual16(long tok, int oc) const {
-        u32x4 r = {0u, 0u, 0u, 0u};
-        if (tok < n_tokens && oc < c_out) r = *(const u32x4*)(res + tok * c_out + oc);
-        return r;
-    }
     __device__ __forceinline__ f32x4 activate(f32x4 v) const {
         if (act == 0) {
 #pragma unroll
@@ -107,8 +97,6 @@ struct PlainDest {
 // a head-major map must stay below 2^31 bytes (32-bit offsets inside a tile's resource).
 template <class T, bool kThrough = false>
 struct QkvSplitDest {
-    __host__ __device__ __forceinline__ bool has_residual() const { return false; }
-    __device__ __forceinline__ u32x4 residual16(long, int) const { return u32x4{0u, 0u, 0u, 0u}; }
     __device__ __forceinline__ f32x4 activate(f32x4 v) const { return v; }
     T* q_ms;
     long q_ms_stride;
@@ -173,8 +161,6 @@ struct QkvSplitDest {
 // goes to is known when the kernel is compiled: no branches, one offset a lane.
 template <class T, bool kThrough = false>
 struct QkvHeadDest {
-    __host__ __device__ __forceinline__ bool has_residual() const { return false; }
-    __device__ __forceinline__ u32x4 residual16(long, int) const { return u32x4{0u, 0u, 0u, 0u}; }
     __device__ __forceinline__ f32x4 activate(f32x4 v) const { return v; }
     T* q_ms;
     long q_ms_stride;
@@ -345,13 +331,7 @@ __global__ __launch_bounds__(ProjTile<T>::kThreads) void project_kernel(const T*
 #pragma unroll
                     for (int jt = 0; jt < 4; ++jt) acc[io][jt] = ep.activate(acc[io][jt]);
             }
-            if (ep.has_residual()) {
-                const long tok0 = (long)cb * G::BC;
-                G::epilogue_lds_residual(acc, here, rb * G::BR, wr, wc, ep.tile(tok0),
-                                         [&](int row, int oc) { return ep.residual16(tok0 + row, oc); });
-            } else {
-                G::epilogue_lds(acc, here, rb * G::BR, wr, wc, ep.tile(cb * G::BC));
-            }
+            G::epilogue_lds(acc, here, rb * G::BR, wr, wc, ep.tile(cb * G::BC));
             G::zero(acc);
             slab = 0;
             --left;
@@ -663,7 +643,7 @@ hipError_t run_project_tiled(const void* x, const void* w, long n_tokens, int c_
     return hipGetLastError();
 }
 
-// the weight-stationary form of a plain projection (at most 256 input channels, no residual)
+// the weight-stationary form of a plain projection (at most 256 input channels)
 template <class T, class Epilogue>
 hipError_t run_project_ws_plain(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
                                 hipStream_t stream) {
@@ -685,9 +665,9 @@ template <class T, class Epilogue>
 hipError_t run_project(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
                        hipStream_t stream) {
     static_assert(std::is_same<Epilogue, PlainDest<T>>::value, "the Q/K/V projection chooses for itself");
-    if (n_tokens * c_out * (long)sizeof(T) <= kThroughBytes && !ep.has_residual() && c_in <= 256)
-        return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, PlainDest<T, true>{ep.y, n_tokens, c_out, nullptr, ep.act}, stream);
-    if (!ep.has_residual() && c_in <= 256) return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, ep, stream);
+    if (n_tokens * c_out * (long)sizeof(T) <= kThroughBytes && c_in <= 256)
+        return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, PlainDest<T, true>{ep.y, n_tokens, c_out, ep.act}, stream);
+    if (c_in <= 256) return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, ep, stream);
     return run_project_tiled<T>(x, w, n_tokens, c_in, c_out, ep, stream);
 }
 
@@ -708,20 +688,9 @@ hipError_t launch_linear(int dt, const void* x, const void* w, void* y, long n_t
 hipError_t launch_linear_act(int dt, const void* x, const void* w, void* y, long n_tokens, int c_in, int c_out, int act,
                              hipStream_t stream) {
     switch (dt) {
-        case 0: return run_project<float>(x, w, n_tokens, c_in, c_out, PlainDest<float>{(float*)y, n_tokens, c_out, nullptr, act}, stream);
-        case 1: return run_project<_Float16>(x, w, n_tokens, c_in, c_out, PlainDest<_Float16>{(_Float16*)y, n_tokens, c_out, nullptr, act}, stream);
-        case 2: return run_project<__bf16>(x, w, n_tokens, c_in, c_out, PlainDest<__bf16>{(__bf16*)y, n_tokens, c_out, nullptr, act}, stream);
-    }
-    return hipErrorInvalidValue;
-}
-
-// y = res + x w^T (the FFN's hidden -> C projection with the block's residual: Section 3.1, Fig. 2 left)
-hipError_t launch_linear_residual(int dt, const void* x, const void* w, const void* res, void* y, long n_tokens,
-                                  int c_in, int c_out, hipStream_t stream) {
-    switch (dt) {
-        case 0: return run_project<float>(x, w, n_tokens, c_in, c_out, PlainDest<float>{(float*)y, n_tokens, c_out, (const float*)res}, stream);
-        case 1: return run_project<_Float16>(x, w, n_tokens, c_in, c_out, PlainDest<_Float16>{(_Float16*)y, n_tokens, c_out, (const _Float16*)res}, stream);
-        case 2: return run_project<__bf16>(x, w, n_tokens, c_in, c_out, PlainDest<__bf16>{(__bf16*)y, n_tokens, c_out, (const __bf16*)res}, stream);
+        case 0: return run_project<float>(x, w, n_tokens, c_in, c_out, PlainDest<float>{(float*)y, n_tokens, c_out, act}, stream);
+        case 1: return run_project<_Float16>(x, w, n_tokens, c_in, c_out, PlainDest<_Float16>{(_Float16*)y, n_tokens, c_out, act}, stream);
+        case 2: return run_project<__bf16>(x, w, n_tokens, c_in, c_out, PlainDest<__bf16>{(__bf16*)y, n_tokens, c_out, act}, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -746,7 +715,7 @@ hipError_t run_qkv_project_ws(const void* x, const void* w_qkv, void* q_ms, long
 // whole rounds over the compute units (and whole groups of channel pieces, see run_project_tiled), are nearly as full as the
 // other form's of 64 x 32.  Modules, us tiled / weight-stationary: 2 x 16384 tokens of 256 channels 178.5 / 182.7, of 224 (0.92 as
 // full) 161.3 / 165.8; of 192 (0.75) 141.8 / 121.1.
-bool tiled_fp32_pays(long n_tokens, int c_out) {
+static bool tiled_fp32_pays(long n_tokens, int c_out) {
     const long cus = compute_units(), rb = (c_out + 255) / 256;
     long rounds = ((n_tokens + 127) / 128 * rb + cus - 1) / cus;
     if (rounds > rb) rounds = (rounds + rb - 1) / rb * rb;

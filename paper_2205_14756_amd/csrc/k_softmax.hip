@@ -8,9 +8,9 @@
 // ever stored), so that the ratio to the linear form is a fair one.  Two kernels: the 16-bit types take
 // softmax_attention32_kernel (below), fp32 the following one.  A workgroup of 4 waves takes
 // 64 queries of one (image, head), a wave 16 of them, and walks over the keys 64 at a time:
-//     S^T[key][query] = K . Q^T      one 16x16x16 MFMA per 16 keys; lane (query x16, q) gets keys 4q..4q+3
+//     S^T[key][query] = K . Q^T      four 16x16x4 MFMAs per 16 keys; lane (query x16, q) gets keys 4q..4q+3
 //     running max per query (in-lane over 16 values, two shuffles over the four q groups), P = 2^(S - max)
-//     O^T[f][query]  += V^T . P^T    one MFMA per 16 keys; P's fragment is S's, rounded to the storage type
+//     O^T[f][query]  += V^T . P^T    the same; P's fragment is S's
 // K (row-major) and V (transposed, so a lane's four keys are contiguous) go through LDS once per
 // workgroup and key block, the next block's loads in flight during the arithmetic.
 #include "msla_device.h"
@@ -22,14 +22,11 @@ namespace {
 constexpr int kSmQ = 64;        // queries per workgroup
 constexpr int kSmK = 64;        // keys per iteration
 
-template <class T>
-__global__ __launch_bounds__(256) void softmax_attention_kernel(const T* __restrict__ qkv, T* __restrict__ att, int N,
+__global__ __launch_bounds__(256) void softmax_attention_kernel(const float* __restrict__ qkv, float* __restrict__ att, int N,
                                                                 int heads, int q_blocks) {
-    typedef Traits<T> Tr;
-    typedef typename Tr::Frag Frag;
-    constexpr int kFragBytes = 4 * (int)sizeof(T);
-    constexpr int kKRow = 16 * (int)sizeof(T) + kFragBytes;          // K tile [key][16 d], padded
-    constexpr int kVRow = kSmK * (int)sizeof(T) + kFragBytes;        // V^T tile [f][64 keys], padded
+    typedef Traits<float> Tr;
+    constexpr int kKRow = 16 * 4 + 16;                               // K tile [key][16 d], padded
+    constexpr int kVRow = kSmK * 4 + 16;                             // V^T tile [f][64 keys], padded
     __shared__ __attribute__((aligned(16))) char ldsK[2][kSmK * kKRow];
     __shared__ __attribute__((aligned(16))) char ldsV[2][16 * kVRow];
 
@@ -38,46 +35,40 @@ __global__ __launch_bounds__(256) void softmax_attention_kernel(const T* __restr
     const int b = blockIdx.x / (q_blocks * heads);
     const int wave = threadIdx.x >> 6, lane = lane_id(), x16 = lane & 15, q = lane >> 4;
     const long ts = 3L * heads * 16;                                  // elements from token to token
-    const T* base = qkv + (long)b * N * ts + (long)h * 48;
+    const float* base = qkv + (long)b * N * ts + (long)h * 48;
 
     // this lane's query (column x16 of the wave's 16): its channels 4q..4q+3, scaled by log2(e)/sqrt(d)
     const int my_query = qb * kSmQ + wave * 16 + x16;
-    Frag qf = frag_zero<T>();
-    if (my_query < N) qf = load_frag<T>(base + (long)my_query * ts + q * 4);
+    f32x4 qf = {0.f, 0.f, 0.f, 0.f};
+    if (my_query < N) qf = load_frag<float>(base + (long)my_query * ts + q * 4);
     constexpr float kScale = 0.25f * 1.4426950408889634f;             // 1/sqrt(16) * log2(e)
 
-    // cooperative loads of a key block: thread t < 128 brings 8 d-channels (or 4, fp32) of K, t >= 128 of V
-    constexpr int kVec = 16 / (int)sizeof(T);                         // elements per 16-byte vector
-    constexpr int kVecPerRow = 16 / kVec;                             // 2 (16-bit) or 4 (fp32)
-    constexpr int kRowsPerPass = 128 / kVecPerRow;                    // keys covered by 128 threads
-    constexpr int kPasses = kSmK / kRowsPerPass;                      // 1 (16-bit) or 2 (fp32)
+    // cooperative loads of a key block: thread t < 128 brings 4 d-channels of K, t >= 128 of V, of two keys
+    constexpr int kRowsPerPass = 32;                                  // keys covered by 128 threads, four a key
+    constexpr int kPasses = kSmK / kRowsPerPass;
     const int half = threadIdx.x >> 7, t7 = threadIdx.x & 127;
     u32x4 stage[kPasses];
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
-            const int key = k0 + p * kRowsPerPass + t7 / kVecPerRow;
+            const int key = k0 + p * kRowsPerPass + t7 / 4;
             u32x4 v = {0u, 0u, 0u, 0u};
-            if (key < N) v = *(const u32x4*)(base + (long)key * ts + 16 + half * 16 + (t7 % kVecPerRow) * kVec);
+            if (key < N) v = *(const u32x4*)(base + (long)key * ts + 16 + half * 16 + (t7 % 4) * 4);
             stage[p] = v;
         }
     };
     auto park = [&](int buf) {
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
-            const int key = p * kRowsPerPass + t7 / kVecPerRow;
-            const int c0 = (t7 % kVecPerRow) * kVec;
+            const int key = p * kRowsPerPass + t7 / 4;
+            const int c0 = (t7 % 4) * 4;
             if (half == 0) {
-                // K: row-major, two (four) 8-byte pieces so that the padded rows stay 8-byte aligned
-                const u32x4 v = stage[p];
-                *(u32x2*)(ldsK[buf] + key * kKRow + c0 * (int)sizeof(T)) = u32x2{v[0], v[1]};
-                *(u32x2*)(ldsK[buf] + key * kKRow + c0 * (int)sizeof(T) + 8) = u32x2{v[2], v[3]};
+                // K: row-major (fragments go to and from these rows as two 8-byte words: 16-byte ones take 0.6 % longer)
+                store_frag<float>(ldsK[buf] + key * kKRow + c0 * 4, __builtin_bit_cast(f32x4, stage[p]));
             } else {
-                // V: transposed, element by element
-                T e[kVec];
-                __builtin_memcpy(e, &stage[p], 16);
+                const f32x4 e = __builtin_bit_cast(f32x4, stage[p]);          // V: transposed, element by element
 #pragma unroll
-                for (int j = 0; j < kVec; ++j) *(T*)(ldsV[buf] + (c0 + j) * kVRow + key * (int)sizeof(T)) = e[j];
+                for (int j = 0; j < 4; ++j) *(float*)(ldsV[buf] + (c0 + j) * kVRow + key * 4) = e[j];
             }
         }
     };
@@ -98,7 +89,7 @@ __global__ __launch_bounds__(256) void softmax_attention_kernel(const T* __restr
         f32x4 s[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const Frag kf = load_frag<T>(ldsK[buf] + (g * 16 + x16) * kKRow + q * kFragBytes);
+            const f32x4 kf = load_frag<float>(ldsK[buf] + (g * 16 + x16) * kKRow + q * 16);
             s[g] = Tr::mma16(z, kf, qf);
         }
         float mx = -INFINITY;
@@ -123,12 +114,9 @@ __global__ __launch_bounds__(256) void softmax_attention_kernel(const T* __restr
             f32x4 p;
 #pragma unroll
             for (int r = 0; r < 4; ++r) p[r] = exp2f(s[g][r] - m_new);
-            // the sum runs over what the matrix instruction sees, i.e. over the rounded weights
-            const Frag pf = frag_from_f32<T>(p);
-            const f32x4 pr = frag_to_f32<T>(pf);
-            l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
-            const Frag vf = load_frag<T>(ldsV[buf] + x16 * kVRow + (g * 16 + q * 4) * (int)sizeof(T));
-            o = Tr::mma16(o, vf, pf);
+            l_run += (p[0] + p[1]) + (p[2] + p[3]);
+            const f32x4 vf = load_frag<float>(ldsV[buf] + x16 * kVRow + (g * 16 + q * 4) * 4);
+            o = Tr::mma16(o, vf, p);
         }
         if (blk + 1 < n_blocks) park(buf ^ 1);
         __syncthreads();
@@ -137,10 +125,10 @@ __global__ __launch_bounds__(256) void softmax_attention_kernel(const T* __restr
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
     const float inv = 1.0f / l_run;
-    // lane (query x16, q) holds channels f = 4q..4q+3 of its query: 8 (16) contiguous bytes
+    // lane (query x16, q) holds channels f = 4q..4q+3 of its query: 16 contiguous bytes
     if (my_query < N)
-        store_frag<T>(att + ((long)b * N + my_query) * (heads * 16) + h * 16 + q * 4,
-                      frag_from_f32<T>(f32x4{o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv}));
+        *(f32x4*)(att + ((long)b * N + my_query) * (heads * 16) + h * 16 + q * 4) =
+            f32x4{o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
 }
 
 // ---------------------------------------------------------------- 16-bit storage types
@@ -365,7 +353,7 @@ hipError_t run_softmax(const void* qkv, void* att, int B, int N, int heads, hipS
         const int q_blocks = (N + kSmQ - 1) / kSmQ;
         const long nblocks = (long)B * heads * q_blocks;
         if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((softmax_attention_kernel<T>), dim3((unsigned)nblocks), dim3(256), 0, stream, (const T*)qkv, (T*)att,
+        hipLaunchKernelGGL(softmax_attention_kernel, dim3((unsigned)nblocks), dim3(256), 0, stream, (const float*)qkv, (float*)att,
                            N, heads, q_blocks);
         return hipGetLastError();
     }

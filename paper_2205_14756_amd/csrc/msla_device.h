@@ -229,20 +229,16 @@ __device__ __forceinline__ void buf_store16(BufRsrc r, unsigned voffset, u32x4 v
 // a vector instruction that overwrites the store's data registers, where this chip needs one: with
 // the data registers reused right behind the store, the first word of some lanes came out wrong in
 // about one launch in twenty.
-__device__ __forceinline__ void buf_store16_at(BufRsrc r, unsigned voffset, unsigned soffset, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(voffset + soffset), 0, 0);
+template <bool kThrough>
+__device__ __forceinline__ void buf_store16_at_as(BufRsrc r, unsigned voffset, unsigned soffset, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(voffset + soffset), 0, kThrough ? 16 : 0);
 }
-// The same store written through to memory (the sc1 cache-policy bit): for output that no later
-// kernel of the module reads.  Such lines are not left dirty in L2, where they would displace the
+// kThrough, and the following: written through to memory (the sc1 cache-policy bit).  buf_store16_stream: for output that no
+// later kernel of the module reads.  Such lines are not left dirty in L2, where they would displace the
 // maps the next call's kernels re-read and wait for the write-back at the end of the kernel; it
 // measures slightly better than the non-temporal hint and clearly better than a plain store.
 __device__ __forceinline__ void buf_store16_stream(BufRsrc r, unsigned voffset, u32x4 v) {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)voffset, 0, 16);
-}
-// ... with a wave-uniform byte offset (buf_store16_at), through or not
-template <bool kThrough>
-__device__ __forceinline__ void buf_store16_at_as(BufRsrc r, unsigned voffset, unsigned soffset, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(voffset + soffset), 0, kThrough ? 16 : 0);
 }
 __device__ __forceinline__ u32x2 buf_load8(BufRsrc r, unsigned voffset) {
     return __builtin_amdgcn_raw_buffer_load_b64(r, (int)voffset, 0, 0);

@@ -111,9 +111,6 @@ hipError_t launch_ffn_dw_project(int dt, const void* h, const void* w_dw, const 
 //   y[n, o] = act(sum_c x[n, c] * w[o, c])   (k_project.hip; the activation is applied to the fp32 sums)
 hipError_t launch_linear_act(int dt, const void* x, const void* w, void* y, long n_tokens, int c_in, int c_out, int act,
                              hipStream_t stream);
-//   y[n, o] = res[n, o] + sum_c x[n, c] * w[o, c]   (k_project.hip, tiled form; the residual joins the fp32 sums)
-hipError_t launch_linear_residual(int dt, const void* x, const void* w, const void* res, void* y, long n_tokens,
-                                  int c_in, int c_out, hipStream_t stream);
 
 // Softmax attention per image and head on qkv [B, N, 3*heads*16] -> att [B, N, heads*16] (k_softmax.hip)
 hipError_t launch_softmax_attention(int dt, const void* qkv, void* att, int B, int N, int heads, hipStream_t stream);
