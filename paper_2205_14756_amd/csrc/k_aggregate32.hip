@@ -14,10 +14,12 @@
 // Operand precision as in the head-size-16 kernel: depthwise sums and aggregated K/V as hi + lo pairs for
 // bf16; for fp16 the Q sums as hi + lo, the K and V operands rounded once.
 // What bounds it is the vector ALU (two thirds of a SIMD's cycles with two waves on it).  Two waves a SIMD is what the
-// register plan is for: the grouped 1x1 operands and the raw tokens are read from LDS where they are used, a filter row's
-// pixels and taps are not read ahead, matrix results go to ordinary registers (compiler flag).  8 x 8 heads, 64 x 128
-// tokens, fp16: this kernel 136 -> 85 us, the module 239 -> 193; with one wave a SIMD and 388 registers, half of them on
-// their way between register files, the reads ahead did not hide what a second wave does.
+// register plan is for, with 3x3 and 5x5 filters: the grouped 1x1 operands and the raw tokens are read from LDS where they are
+// used, a filter row's pixels and taps are not read ahead, matrix results go to ordinary registers (compiler flag).  8 x 8
+// heads, 64 x 128 tokens, fp16, 5x5: this kernel 136 -> 85 us, the module 239 -> 193; with one wave a SIMD and 388 registers, half of
+// them on their way between register files, the reads ahead did not hide what a second wave does.  The LDS holds one
+// workgroup with a 7x7 filter (92 KB in fp16, 101 in bf16), so one wave a SIMD it is there (kAhead): 24 heads, 4 x 64 x 64 tokens, the
+// module 380 -> 352 us in fp16, 414 -> 397 in bf16 (361 and 417 without the reads ahead).
 // Per-workgroup partial states [32][33] go to the buffer that the plain finalize kernel sums in a fixed order.
 #include "msla_device.h"
 #include "msla_kernels.h"
@@ -60,6 +62,10 @@ __global__ __launch_bounds__(kThreads32, (Agg32Lds<T, KS>::kWaves)) void aggrega
     typedef Traits<T> Tr;
     typedef typename Tr::Frag Frag;
     typedef Agg32Lds<T, KS> L;
+    // One wave a SIMD: every read of a filter row is sent out before the first result is used -- with the raw branch, whose
+    // compiled code otherwise waits for each tap (8 x 64 x 128 tokens, 8 heads, 7x7, the module: fp16 279 -> 270 us, bf16 328 -> 309);
+    // without it (a module's second scale) the compiler's own order is the better one (3x3 and 7x7, fp16 358 and 365).
+    constexpr bool kAhead = L::kWaves == 1 && kRaw;
     constexpr int P = L::P;
     constexpr int SZ = (int)sizeof(T);
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -215,12 +221,20 @@ __global__ __launch_bounds__(kThreads32, (Agg32Lds<T, KS>::kWaves)) void aggrega
                     Frag px[4 + KS - 1];
 #pragma unroll
                     for (int c = 0; c < 4 + KS - 1; ++c) px[c] = pixel(map, ib, u, c);
+                    typedef typename std::conditional<sizeof(Tap) == 2, Frag, f32x4>::type Taps;
+                    auto taps = [&](int v) { return *(const Taps*)(wt + (u * KS + v) * D32); };
+                    Taps ahead[kAhead ? KS : 1];
+                    if constexpr (kAhead) {
+#pragma unroll
+                        for (int v = 0; v < KS; ++v) ahead[v] = taps(v);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
 #pragma unroll
                     for (int v = 0; v < KS; ++v) {
-                        const Tap* w = wt + (u * KS + v) * D32;
+                        const Taps w = kAhead ? ahead[kAhead ? v : 0] : taps(v);
                         f32x4 w4;
-                        if constexpr (sizeof(Tap) == 2) w4 = frag_to_f32<T>(load_frag<T>(w));
-                        else w4 = *(const f32x4*)w;
+                        if constexpr (sizeof(Tap) == 2) w4 = frag_to_f32<T>(w);
+                        else w4 = w;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const f32x4 d4 = frag_to_f32<T>(px[r + v]);
