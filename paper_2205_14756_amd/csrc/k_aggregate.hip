@@ -335,9 +335,8 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
 // Branch-0 state when the module has no aggregated scale: the raw K, V tokens
 // of (image, head, chunk of 64-token groups), same operand path as above.  A workgroup is NH neighbouring heads, four waves
 // each: one, or -- where Q, K and V of all heads are interleaved in a token's row, so that four heads are three whole
-// cache lines -- four, and the lines come to a compute unit once (core of 65536 tokens, 16 heads, fp16: 69.9 -> 60.9 us; with
-// fewer heads than that half of the waves idle, 22.8 -> 23.7 us for the gradient of 1400 tokens, 2 heads; a map of K and V
-// only, whose heads are half lines, gains nothing).
+// cache lines -- four, and the lines come to a compute unit once (core of 65536 tokens, 16 heads, fp16: 69.9 -> 60.9 us; see
+// run_raw_state for where that pays; a map of K and V only, whose heads are half lines, gains nothing).
 template <class T, int NH>
 __global__ __launch_bounds__(256 * NH) void raw_state_kernel(AggregateArgs a) {
     typedef Traits<T> Tr;
@@ -615,9 +614,13 @@ hipError_t run_raw_state(const AggregateArgs& a, hipStream_t stream) {
     if (a.state_valu)
         hipLaunchKernelGGL((raw_state_valu_kernel<T>), dim3((unsigned)nblocks), dim3(kAggThreads), 0, stream, a);
     else {
-        if (a.heads >= 4 && a.k_ts == 48L * a.heads)
-            hipLaunchKernelGGL((raw_state_kernel<T, 4>), dim3((unsigned)((long)a.B * ((a.heads + 3) / 4) * a.nchunks)), dim3(1024),
-                               0, stream, a);
+        // Four heads a workgroup: sixteen waves, so the chip is only evenly loaded where such workgroups come in whole rounds
+        // over the compute units, nine tenths of their head places taken.  This kernel, us with one / with four heads (places
+        // taken): the gradient of 8 x 8192 tokens, 16 heads, 18 / 17 (all), of 8 x 8192, 13 heads, 21.3 / 29.9 (320 workgroups in
+        // two rounds, 0.51), of 4 x 8470, 27 heads, 25.5 / 34.9 (0.53); 1600 tokens, 8 heads, the whole gradient 22.5 / 23.0 (0.2).
+        const long four = (long)a.B * ((a.heads + 3) / 4) * a.nchunks, cus = compute_units();
+        if (a.k_ts == 48L * a.heads && 10 * nblocks >= 9 * 4 * ((four + cus - 1) / cus * cus))
+            hipLaunchKernelGGL((raw_state_kernel<T, 4>), dim3((unsigned)four), dim3(1024), 0, stream, a);
         else
             hipLaunchKernelGGL((raw_state_kernel<T, 1>), dim3((unsigned)nblocks), dim3(256), 0, stream, a);
     }

@@ -178,3 +178,11 @@ def test_fp32_tiled_kernels_on_full_maps(B, C, H, W, heads, scales):
 def test_long_contraction_of_many_tokens(dtype, C, heads, scales):
     print(f"routes: long contraction, many tokens {dtype} 4x{C}x61x91 heads={heads}", flush=True)
     base.check_module(wk.random_module(51 + heads, dtype, 4, C, 61, 91, heads, 16, scales), dtype, heads, 16, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+# four heads a workgroup, which takes about a whole round of workgroups over the chip: 16 heads, 16 chunks; 11 heads (the
+# last workgroup of an image's three one short), 12 chunks; ragged ends of both
+@pytest.mark.parametrize("B,H,W,heads", [(4, 10, 101, 16), (7, 20, 37, 11)])
+def test_raw_state_of_four_heads_a_workgroup(dtype, B, H, W, heads):
+    base.test_multiscale_state_and_core(dtype, B, H, W, heads, ())
