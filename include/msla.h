@@ -172,8 +172,10 @@ msla_status msla_multiscale_state(const void* qkv, const void* w_dw, const void*
  *   - q_ms must be given (not NULL): the Q tokens of every branch are an output here;
  *   - a shape whose per-state buffers exceed that array returns MSLA_ERR_WORKSPACE with nothing
  *     enqueued.  They take B*S*heads*(1088*(chunks+1) + 2052) bytes plus alignment, chunks being
- *     the number of workgroups one state's reduction is split over (enough to fill the GPU:
- *     2 at B*heads = 128, 32 at B*heads = 8); 8 MiB covers e.g. 1500 states at 2 chunks.
+ *     the number of workgroups one state's reduction is split over (enough to fill the GPU; at most
+ *     256 / (B*heads) for the 16-bit types with one aggregated scale, 128 / (B*heads) where a 3x3 and
+ *     a 5x5 scale share a launch, 1024 / (B*heads) in fp32 and without aggregated scales, each
+ *     rounded up, and never more than an image has tiles); 8 MiB covers e.g. 1500 states at 2 chunks.
  * It calls no allocating routine.  Every call on a GPU uses that GPU's one array, so calls that
  * overlap on one GPU (different streams, or threads) race: serialise them.  Nothing in the array has
  * to start at zero and nothing in it survives as a result: each call overwrites what it reads. */
