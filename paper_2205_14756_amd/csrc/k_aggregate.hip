@@ -55,12 +55,16 @@ struct HeadMaps {
     long q_ts, k_ts, v_ts;   // elements per token
 };
 
-template <class T, int KS>
+// kRaw, 16-bit types: the raw branch's state is summed as well (a template argument, for the reason given at
+// aggregate32_kernel).  fp32 keeps the run-time branch, with which the compiler's order is 1 to 3 % faster (the core of 4 x 64 x
+// 128 tokens, 8 heads, 7x7 75.5 us, 77.8 with the argument); tests/test_wait_states.py checks what is built.
+template <class T, int KS, bool kRaw>
 __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a) {
     typedef Traits<T> Tr;
     typedef typename Tr::Frag Frag;
     typedef AggLds<T, KS> L;
     constexpr int P = L::P;
+    const bool do_raw = sizeof(T) == 2 ? kRaw : a.do_raw != 0;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* tile = lds;
     float* wts = (float*)(lds + (L::kBytes - L::kWtsBytes));
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
                     ks_agg_t += (kf[0] + kf[1]) + (kf[2] + kf[3]);
                     if constexpr (Tr::kHiLo) frag_split<T>(kf, aggK[r], aggK_lo[r]);
                     else aggK[r] = frag_from_f32<T>(kf);
-                    if (a.do_raw) {
+                    if (do_raw) {
                         const Frag rk = frag_relu<T>(frag_from_f32<T>(Tr::mma16(z, rawf, ident)));
                         rawK[r] = rk;
                         const f32x4 rf = frag_to_f32<T>(rk);
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
                     } else {
                         kv_agg_t = Tr::mma16(kv_agg_t, aggK[r], frag_from_f32<T>(vf));
                     }
-                    if (a.do_raw) {
+                    if (do_raw) {
                         const Frag rv = frag_from_f32<T>(Tr::mma16(z, rawf, ident));
                         kv_raw_t = Tr::mma16(kv_raw_t, rawK[r], rv);
                     }
@@ -322,7 +326,7 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
     __syncthreads();
     for (int j = threadIdx.x; j < 2 * kStateSize; j += kAggThreads) {
         const int which = j / kStateSize, idx = j - which * kStateSize;   // 0: aggregated, 1: raw
-        if (which == 1 && !a.do_raw) continue;
+        if (which == 1 && !do_raw) continue;
         const int e = idx / 17, f = idx - e * 17;
         // KV[e][f] sits in lane (f, e / 4), element e % 4
         const int src = f < 16 ? which * 256 + ((e >> 2) * 16 + f) * 4 + (e & 3) : 512 + which * 16 + e;
@@ -586,15 +590,21 @@ __global__ __launch_bounds__(320) void state_finalize_kernel(const float* __rest
     }
 }
 
-template <class T, int KS>
-hipError_t run_aggregate_ks(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
+template <class T, int KS, bool kRaw>
+hipError_t run_aggregate_as(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
     constexpr int kLds = AggLds<T, KS>::kBytes;
     if (kLds > 48 * 1024) {   // above the default dynamic-LDS limit (the CU has 160 KB)
-        const hipError_t e = allow_dynamic_lds<aggregate_kernel<T, KS>>(kLds);
+        const hipError_t e = allow_dynamic_lds<aggregate_kernel<T, KS, kRaw>>(kLds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((aggregate_kernel<T, KS>), dim3(nblocks), dim3(kAggThreads), kLds, stream, a);
+    hipLaunchKernelGGL((aggregate_kernel<T, KS, kRaw>), dim3(nblocks), dim3(kAggThreads), kLds, stream, a);
     return hipGetLastError();
+}
+template <class T, int KS>
+hipError_t run_aggregate_ks(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
+    if constexpr (sizeof(T) == 2)
+        if (!a.do_raw) return run_aggregate_as<T, KS, false>(a, nblocks, stream);
+    return run_aggregate_as<T, KS, true>(a, nblocks, stream);
 }
 
 template <class T>

@@ -186,3 +186,13 @@ def test_long_contraction_of_many_tokens(dtype, C, heads, scales):
 @pytest.mark.parametrize("B,H,W,heads", [(4, 10, 101, 16), (7, 20, 37, 11)])
 def test_raw_state_of_four_heads_a_workgroup(dtype, B, H, W, heads):
     base.test_multiscale_state_and_core(dtype, B, H, W, heads, ())
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# scales after the first, which have no raw branch, in launches of their own: matrix-core kernel (equal scales and a third one
+# share no launch) and general kernel (7x7), on whole tiles and ragged ones
+@pytest.mark.parametrize("B,H,W,heads,scales", [(1, 32, 64, 4, (5, 5)), (2, 21, 45, 3, (3, 3, 5)), (1, 32, 64, 4, (7, 7)),
+                                                (2, 21, 45, 3, (5, 7, 7))])
+def test_later_scales_in_launches_of_their_own(dtype, B, H, W, heads, scales):
+    print(f"routes: later scales {dtype} {B}x{H}x{W} {scales}", flush=True)
+    base.check_module(wk.random_module(23 + W, dtype, B, 16 * heads, H, W, heads, 16, scales), dtype, heads, 16, scales)
