@@ -92,9 +92,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // The kernel's body for workgroup `bid` of `nblocks` (a launch may hold the workgroups of two scales, see
 // aggregate_mfma_pair_kernel).  nblocks is the number of (image, head, chunk) triples rounded up to whole rounds over the
 // XCDs, so that neighbouring heads share an L2 whatever their number; workgroups past the last triple end at once.
-// kRaw: the raw branch's state is summed as well (a template argument and not a run-time branch: such a branch between a matrix
-// instruction and the reader of its result is where the compiler (ROCm 7.2) has left out wait states); kCopyRawQ: and its Q copied.
-template <class T, int KS, bool kRaw, bool kCopyRawQ>
+template <class T, int KS, bool kCopyRawQ>
 __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsigned bid, unsigned nblocks) {
     typedef Traits<T> Tr;
     typedef typename Tr::Frag Frag;
@@ -265,7 +263,9 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
                     if (row_interior && lx0 + x16 >= P && gy < a.H && tx0 - P + lx0 + x16 < a.W)
                         store_frag<T>(q_ms + (tok_first + lx0 + x16) * q_ms_ts + h * 16 + q * 4, bt.qf[rr][cg]);
                 }
-                if (kRaw && row_interior) {
+                // (a run-time branch: as a template argument the bf16 3x3 kernel takes 109 us instead of 105 for 9 x 101 x 99 tokens, 16
+                // heads; that no result is read too early behind the jump, tests/test_wait_states.py checks in what is built)
+                if (a.do_raw && row_interior) {
                     // raw branch: tokens of this tile's interior only (each token belongs to one tile)
                     Frag rk = frag_relu_bits<T>(dk);
                     if (cg == 0) {      // the first columns are halo
@@ -306,7 +306,7 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
                 if (js <= 4 && lys >= P && lys < P + MTH && lxs < P + MTW && gys < a.H && gxs < a.W)
                     store_frag<T>(q_ms + (img_tok0 + (long)gys * a.W + gxs) * q_ms_ts + h * 16 + q * 4, bt.qtail);
             }
-            if constexpr (kRaw) {
+            if (a.do_raw) {
                 Frag rk = frag_relu_bits<T>(dk);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
@@ -607,7 +607,7 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
     __syncthreads();
     for (int j = threadIdx.x; j < 2 * kStateSize; j += kThreads) {
         const int which = j / kStateSize, idx = j - which * kStateSize;   // 0: aggregated, 1: raw
-        if (which == 1 && !kRaw) continue;
+        if (which == 1 && !a.do_raw) continue;
         const int e = idx / 17, f = idx - e * 17;
         float s;
         if (f == 16) {
@@ -626,9 +626,9 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
     }
 }
 
-template <class T, int KS, bool kRaw, bool kCopyRawQ>
+template <class T, int KS, bool kCopyRawQ>
 __global__ __launch_bounds__(kThreads) void aggregate_mfma_kernel(AggregateArgs a) {
-    aggregate_mfma_body<T, KS, kRaw, kCopyRawQ>(a, blockIdx.x, gridDim.x);
+    aggregate_mfma_body<T, KS, kCopyRawQ>(a, blockIdx.x, gridDim.x);
 }
 
 // Two aggregated scales in one launch: the first half of the grid works on scale A, the second on scale
@@ -640,23 +640,24 @@ __global__ __launch_bounds__(kThreads) void aggregate_mfma_kernel(AggregateArgs 
 template <class T, int KSA, int KSB, bool kCopyRawQ>
 __global__ __launch_bounds__(kThreads) void aggregate_mfma_pair_kernel(AggregateArgs a0, AggregateArgs a1) {
     const unsigned half = gridDim.x >> 1;
-    if (blockIdx.x < half) aggregate_mfma_body<T, KSA, true, kCopyRawQ>(a0, blockIdx.x, half);
-    else aggregate_mfma_body<T, KSB, false, false>(a1, blockIdx.x - half, half);
+    if (blockIdx.x < half) aggregate_mfma_body<T, KSA, kCopyRawQ>(a0, blockIdx.x, half);
+    else aggregate_mfma_body<T, KSB, false>(a1, blockIdx.x - half, half);
 }
 
-template <class T, int KS, bool kRaw, bool kCopyRawQ>
-hipError_t run_ks_as(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
-    constexpr int kLds = MLds<KS>::kBytes;
-    const hipError_t e = allow_dynamic_lds<aggregate_mfma_kernel<T, KS, kRaw, kCopyRawQ>>(kLds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((aggregate_mfma_kernel<T, KS, kRaw, kCopyRawQ>), dim3(nblocks), dim3(kThreads), kLds, stream, a);
-    return hipGetLastError();
-}
 template <class T, int KS>
 hipError_t run_ks(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
-    // the raw branch and the copy of its Q tokens into the multi-scale map are compiled in only where they are wanted
-    if (!a.do_raw) return a.copy_raw_q ? hipErrorInvalidValue : run_ks_as<T, KS, false, false>(a, nblocks, stream);
-    return a.copy_raw_q ? run_ks_as<T, KS, true, true>(a, nblocks, stream) : run_ks_as<T, KS, true, false>(a, nblocks, stream);
+    constexpr int kLds = MLds<KS>::kBytes;
+    // the copy of the raw Q tokens into the multi-scale map is compiled in only where it is wanted
+    if (a.copy_raw_q) {
+        const hipError_t e = allow_dynamic_lds<aggregate_mfma_kernel<T, KS, true>>(kLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((aggregate_mfma_kernel<T, KS, true>), dim3(nblocks), dim3(kThreads), kLds, stream, a);
+    } else {
+        const hipError_t e = allow_dynamic_lds<aggregate_mfma_kernel<T, KS, false>>(kLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((aggregate_mfma_kernel<T, KS, false>), dim3(nblocks), dim3(kThreads), kLds, stream, a);
+    }
+    return hipGetLastError();
 }
 
 long whole_rounds(long nblocks) { return (nblocks + 7) / 8 * 8; }
@@ -691,7 +692,7 @@ template <class T>
 hipError_t run_pair(const AggregateArgs& a0, const AggregateArgs& a1, hipStream_t stream) {
     const long nblocks = whole_rounds((long)a0.B * a0.heads * a0.nchunks);
     if (nblocks <= 0 || 2 * nblocks > 0x7fffffffL) return hipErrorInvalidValue;
-    if (!a0.do_raw || a1.do_raw || a1.copy_raw_q) return hipErrorNotSupported;       // (the first scale of a module does the raw branch)
+    if (a1.copy_raw_q) return hipErrorNotSupported;       // (the first scale of a module copies it)
     for (const AggregateArgs* a : {&a0, &a1}) {
         if ((const char*)a->v != (const char*)a->k + 16 * sizeof(T) || a->v_ts != a->k_ts || a->v_hs != a->k_hs)
             return hipErrorNotSupported;
