@@ -661,10 +661,32 @@ hipError_t run_project_ws_plain(const void* x, const void* w, long n_tokens, int
     }
 }
 
+// How full the tiled form's pieces of 256 channels x 128 tokens are, in whole rounds over the compute units (and whole groups of
+// channel pieces, see run_project_tiled), against the weight-stationary form's of 64 x 32: per mille.  An fp32 product of 129 to 256
+// input channels is the tiled form's
+// - for Q/K/V from 900 on: modules, us tiled / weight-stationary, 2 x 16384 tokens of 256 channels (1000) 178.5 / 182.7, of 224 (917)
+//   161.3 / 165.8; of 192 (750) 141.8 / 121.1;
+// - for a plain destination from 1000 on, the contraction's padding counted as well (the weight-stationary form has kernels for
+//   192 and 256 slots, the tiled one takes steps of 32): 16384 tokens, 160 -> 480 channels (1200) 27.6 / 31.9, 32768, 224 -> 672 (1048)
+//   91.8 / 101.6, 65536, 256 -> 768 (1000) 201 / 214, 256 -> 256 71.9 / 73.7; 32768, 256 -> 672 (917) 102.4 / 103.2.
+// Shorter contractions are bound by memory, and the tiled form's epilogue costs it (65536, 80 -> 256, 36.1 / 31.2).
+static long tiled_fp32_fill(long n_tokens, int c_out) {
+    const long cus = compute_units(), rb = (c_out + 255) / 256;
+    long rounds = ((n_tokens + 127) / 128 * rb + cus - 1) / cus;
+    if (rounds > rb) rounds = (rounds + rb - 1) / rb * rb;
+    return 1000 * ((n_tokens + 31) / 32 * 32) * ((c_out + 63) / 64 * 64) / (rounds * cus * (128 * 256));
+}
+static bool tiled_fp32_pays(long n_tokens, int c_in, int c_out) {
+    const long slots = c_in <= 192 ? 192 : 256;
+    return tiled_fp32_fill(n_tokens, c_out) * slots / ((c_in + 31) / 32 * 32) >= 1000;
+}
+
 template <class T, class Epilogue>
 hipError_t run_project(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
                        hipStream_t stream) {
     static_assert(std::is_same<Epilogue, PlainDest<T>>::value, "the Q/K/V projection chooses for itself");
+    if (sizeof(T) == 4 && c_in > 128 && c_in <= 256 && tiled_fp32_pays(n_tokens, c_in, c_out))
+        return run_project_tiled<T>(x, w, n_tokens, c_in, c_out, ep, stream);
     if (n_tokens * c_out * (long)sizeof(T) <= kThroughBytes && c_in <= 256)
         return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, PlainDest<T, true>{ep.y, n_tokens, c_out, ep.act}, stream);
     if (c_in <= 256) return run_project_ws_plain<T>(x, w, n_tokens, c_in, c_out, ep, stream);
@@ -711,23 +733,12 @@ hipError_t run_qkv_project_ws(const void* x, const void* w_qkv, void* q_ms, long
     }
 }
 
-// Whether an fp32 Q/K/V projection of up to 256 input channels is the tiled form's: where its pieces of 256 channels x 128 tokens, in
-// whole rounds over the compute units (and whole groups of channel pieces, see run_project_tiled), are nearly as full as the
-// other form's of 64 x 32.  Modules, us tiled / weight-stationary: 2 x 16384 tokens of 256 channels 178.5 / 182.7, of 224 (0.92 as
-// full) 161.3 / 165.8; of 192 (0.75) 141.8 / 121.1.
-static bool tiled_fp32_pays(long n_tokens, int c_out) {
-    const long cus = compute_units(), rb = (c_out + 255) / 256;
-    long rounds = ((n_tokens + 127) / 128 * rb + cus - 1) / cus;
-    if (rounds > rb) rounds = (rounds + rb - 1) / rb * rb;
-    return 10 * ((n_tokens + 31) / 32 * 32) * ((c_out + 63) / 64 * 64) >= 9 * rounds * cus * (128 * 256);
-}
-
 template <class T>
 hipError_t run_qkv_project(const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw,
                            long kv_tok_stride, long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads,
                            hipStream_t stream) {
     const int c_out = 3 * heads * 16;
-    if (c_in <= 256 && !(sizeof(T) == 4 && tiled_fp32_pays(n_tokens, c_out))) {
+    if (c_in <= 256 && !(sizeof(T) == 4 && c_in > 128 && tiled_fp32_fill(n_tokens, c_out) >= 900)) {
         const bool through = n_tokens * c_out * (long)sizeof(T) <= kThroughBytes;
         return through ? run_qkv_project_ws<T, true>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span,
                                                      n_tokens, c_in, heads, stream)

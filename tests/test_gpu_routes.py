@@ -196,3 +196,9 @@ def test_raw_state_of_four_heads_a_workgroup(dtype, B, H, W, heads):
 def test_later_scales_in_launches_of_their_own(dtype, B, H, W, heads, scales):
     print(f"routes: later scales {dtype} {B}x{H}x{W} {scales}", flush=True)
     base.check_module(wk.random_module(23 + W, dtype, B, 16 * heads, H, W, heads, 16, scales), dtype, heads, 16, scales)
+
+
+# fp32 products that fill the tiled form's pieces, whose contraction the weight-stationary form would pad; a ragged end
+@pytest.mark.parametrize("n,c_in,c_out", [(16384, 160, 480), (16301, 144, 496)])
+def test_fp32_linear_on_full_maps(n, c_in, c_out):
+    base.test_linear("f32", n, c_in, c_out)
