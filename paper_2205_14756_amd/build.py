@@ -11,8 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmsla.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["k_project.hip", "k_aggregate.hip", "k_aggregate_mfma.hip", "k_aggregate32.hip", "k_apply.hip", "k_small.hip", "k_ffn.hip", "k_softmax.hip", "k_backward.hip", "k_generic.hip", "k_layout.hip", "msla_static.hip", "msla_api.cpp"]
-HEADERS = ["msla_device.h", "gemm_tile.h", "msla_kernels.h", os.path.join("..", "..", "include", "msla.h")]
+SOURCES = ["k_project.hip", "k_aggregate.hip", "k_aggregate_mfma.hip", "k_aggregate_small.hip", "k_aggregate32.hip", "k_apply.hip", "k_small.hip", "k_ffn.hip", "k_softmax.hip", "k_backward.hip", "k_generic.hip", "k_layout.hip", "msla_static.hip", "msla_api.cpp"]
+HEADERS = ["msla_device.h", "aggregate_sweep.h", "gemm_tile.h", "msla_kernels.h", os.path.join("..", "..", "include", "msla.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 code generation is switched off for every device compile
@@ -21,6 +21,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
 # kernels whose MFMA results are consumed by vector instructions right away: let the matrix
 # instructions write VGPRs instead of AGPRs (saves one copy per result register)
 PER_SOURCE = {"k_aggregate_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "k_aggregate_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "k_aggregate.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "k_aggregate32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 

@@ -518,9 +518,9 @@ __global__ __launch_bounds__(320) void state_finalize_kernel(const float* __rest
     if (j < kStateSize) {
         const float* p = partials + (long)s_id * nchunks * kStateSize + j;
         // the additions stay in chunk order; a batch of loads is in flight at once (past the last chunk they read the last
-        // one again), so up to 16 chunks cost one memory latency -- in a loop unrolled by eight every chunk of a remainder
-        // cost one (modules: 2 x 5184 tokens, 4 heads, bf16 27.6 -> 26.2 us; 2048 tokens, 32 heads 34.8 -> 34.1; the gradient of 1400
-        // tokens 22.5 -> 21.5)
+        // one again), so up to 32 chunks cost one memory latency -- in a loop unrolled by eight every chunk of a remainder
+        // cost one (modules, 16 in flight: 2 x 5184 tokens, 4 heads, bf16 27.6 -> 26.2 us; 2048 tokens, 32 heads 34.8 -> 34.1; the
+        // gradient of 1400 tokens 22.5 -> 21.5)
         auto sum = [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
             for (int c0 = 0; c0 < nchunks; c0 += kBatch) {
@@ -533,7 +533,8 @@ __global__ __launch_bounds__(320) void state_finalize_kernel(const float* __rest
         };
         if (nchunks <= 4) sum(std::integral_constant<int, 4>{});
         else if (nchunks <= 8) sum(std::integral_constant<int, 8>{});
-        else sum(std::integral_constant<int, 16>{});
+        else if (nchunks <= 16) sum(std::integral_constant<int, 16>{});
+        else sum(std::integral_constant<int, 32>{});
         kv32[(long)s_id * kStateSize + j] = v;
         const int e = j / 17, f = j - e * 17;
         if (split > 0 && f < 16 && e / split != f / split) v = 0.f;

@@ -38,7 +38,7 @@
 // the row operand of KV, Q's (transposed product) going to HBM.
 #include <algorithm>
 
-#include "msla_device.h"
+#include "aggregate_sweep.h"
 #include "msla_kernels.h"
 
 namespace msla {
@@ -54,40 +54,12 @@ template <int KS>
 struct MLds {
     static constexpr int P = (KS - 1) / 2;
     static constexpr int LH = MTH + 2 * P, LW = MTW + 2 * P;
-    static constexpr int kRowBytes = 72;                       // 36 columns, 8-byte aligned
-    static constexpr int kChanRaw = LH * kRowBytes;
-    // The channel stride is an odd number of 8-byte slots (16 slots = all 32 banks).  A staging
-    // write puts 16 channels of one x-block side by side: 16 different slots mod 16.  A sweeping
-    // read covers, per 16 lanes, 4 x-blocks of the channels {g, g+4, g+8, g+12}: their strides are
-    // 0, 4, 8, 12 slots mod 16 (times an odd number), the x-blocks fill the gaps.
-    static constexpr int kChanBytes = kChanRaw + ((kChanRaw / 8) % 2 == 0 ? 8 : 0);
+    static constexpr int kRowBytes = kPlanarRowBytes;
+    static constexpr int kChanBytes = planar_chan_bytes(LH);
     static constexpr int kPlanarBytes = 48 * kChanBytes;
-    static constexpr int kTokStride = 80;                      // transposition buffer: 16 tokens x 16 fp32 (+pad)
-    static constexpr int kTransBytes = 16 * kTokStride;
     static constexpr int kBytes = 2 * kPlanarBytes + kSweepWaves * 2 * kTransBytes;   // two tiles in flight; two transposition buffers per sweeping wave
     static_assert(LW <= 36 && (kChanBytes / 8) % 2 == 1, "LDS layout");
 };
-
-template <class T> struct M4;
-template <> struct M4<_Float16> {
-    static __device__ __forceinline__ f32x4 mma(f16x4 a, f16x4 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_4x4x4f16(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct M4<__bf16> {
-    static __device__ __forceinline__ f32x4 mma(bf16x4 a, bf16x4 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c,
-                                                      0, 0, 0);
-    }
-};
-
-// Compiler-level ordering of LDS traffic inside one wave (the hardware already
-// executes a wave's LDS instructions in order).
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The kernel's body for workgroup `bid` of `nblocks` (a launch may hold the workgroups of two scales, see
 // aggregate_mfma_pair_kernel).  nblocks is the number of (image, head, chunk) triples rounded up to whole rounds over the
@@ -118,10 +90,9 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
     const int w4 = wave & 3;              // staging wave index
     const int sw = (wave - 4) & (kSweepWaves - 1);   // sweeping wave index
     const int x16 = lane & 15, q = lane >> 4;      // 16x16 MFMA view of the lane
-    const int blk = lane >> 2, sub = lane & 3;     // 4x4x4 view: block, row/column inside it
-    // block -> channel of the group: 16 consecutive lanes take channels 4 apart (LDS banks, see MLds)
-    const int chn = 4 * (blk & 3) + (blk >> 2);
-    char* trans = lds + 2 * L::kPlanarBytes + sw * 2 * L::kTransBytes;
+    const int sub = lane & 3;                      // 4x4x4 view: output inside a block
+    const int chn = sweep_channel(lane);           // ... and its channel
+    char* trans = lds + 2 * L::kPlanarBytes + sw * 2 * kTransBytes;
 
     const T* wdw = (const T*)a.w_dw + (long)h * 48 * KS * KS;
     const T* wgp = (const T*)a.w_gpw + (long)h * 48 * 16;
@@ -333,7 +304,11 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
     // batches still in flight (the scheduler must not mix the three batches here either: entering
     // the loop with batch 0 requested last would make every wait in the loop cover the youngest
     // loads as well).
+    // row threadIdx.x % 16 of V's grouped 1x1, for the very end: requested here, off the end's chain of dependent steps
+    Vec w_v[2];
     if (role == 0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) w_v[i] = ((const Vec*)(wgp + (2 * 16 + x16) * 16))[i];
         Batch ring0, ring1, ring2;
         TileAt here = tile_at(tile_begin);
         issue(here, 0, ring0, n_my_tiles > 0);
@@ -359,37 +334,23 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
     } else {
     // Toeplitz operands of the three 16-channel groups: lane (channel chn, output i = sub).  Each
     // sweeping wave copies the head's 48 x KS x KS filter taps, coalesced, into its own transposition
-    // buffers (idle until its first sweep) and picks its band entries from there with branch-free
-    // LDS reads (index clamped, value masked).  Nothing here involves another wave, so the staging
+    // buffers (idle until its first sweep), takes its channels' taps from there as words and shifts them into place.
+    // Nothing here involves another wave, so the staging
     // waves fill the first tile buffer meanwhile without a workgroup barrier.
     Frag toep[3][KS][NS];
     {
-        constexpr int kTaps = 48 * KS * KS;
-        static_assert((kTaps + 1) * sizeof(T) <= 2 * L::kTransBytes, "tap table");
-        constexpr int kVecs = kTaps * (int)sizeof(T) / 16;      // 16-byte pieces: a head's taps are a multiple
-        static_assert(kVecs * 16 == kTaps * (int)sizeof(T), "tap table in 16-byte pieces");
-        T* wl = (T*)trans;
+        constexpr int kVecs = 48 * KS * KS * (int)sizeof(T) / 16;      // 16-byte pieces: a head's taps are a multiple
+        static_assert(kVecs * 16 == 48 * KS * KS * (int)sizeof(T) && kVecs * 16 <= 2 * kTransBytes, "tap table in 16-byte pieces");
         u32x4 piece[(kVecs + 63) / 64];
 #pragma unroll
         for (int j = 0; j < (kVecs + 63) / 64; ++j)
             if (j * 64 + lane < kVecs) piece[j] = ((const u32x4*)wdw)[j * 64 + lane];
 #pragma unroll
         for (int j = 0; j < (kVecs + 63) / 64; ++j)
-            if (j * 64 + lane < kVecs) ((u32x4*)wl)[j * 64 + lane] = piece[j];
-        if (lane == 0) wl[kTaps] = Tr::from_f32(0.f);     // the entry read by masked-out slots
+            if (j * 64 + lane < kVecs) ((u32x4*)trans)[j * 64 + lane] = piece[j];
         wave_lds_fence();
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
-#pragma unroll
-            for (int u = 0; u < KS; ++u)
-#pragma unroll
-                for (int s = 0; s < NS; ++s)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int v = 4 * s + k - sub;
-                        const int idx = (v >= 0 && v < KS) ? ((t * 16 + chn) * KS + u) * KS + v : kTaps;
-                        toep[t][u][s][k] = wl[idx];
-                    }
+        for (int t = 0; t < 3; ++t) make_toeplitz<T, KS>(load_taps<T, KS>((const T*)trans, t * 16 + chn), sub, toep[t]);
         wave_lds_fence();
     }
     // grouped 1x1 weights of Q and K as 16x16 operands: lane (o, q) holds w[o][4q..4q+3]
@@ -401,175 +362,10 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
         const char* planar = lds + (step & 1) * L::kPlanarBytes;
         const int ty0 = here.ty0, tx0 = here.tx0;
         here = tile_after(here);
-        // ---------------- depthwise sweep: this wave's strip (16 columns) x part (kSweepRows rows)
-        constexpr int R = kSweepRows;
-        const int col0 = 16 * strip + 4 * sub;            // interior column of this lane's x-block
-        const int gy0 = ty0 + R * part;
-        const int gx0 = tx0 + col0;
         const bool ragged = ty0 + MTH > a.H || tx0 + MTW > a.W;      // wave-uniform
-        Frag aggK[R], aggK_lo[R];
-        // The three passes (K, V, Q) form one flat, fully unrolled sequence of input rows.  A finished
-        // output row goes through three stages in three consecutive iterations, so that no stage
-        // waits for the one before it: (1) hand the row to LDS for transposition (K, Q) or to the
-        // lane permutation (V); (2) pick it up in operand layout and issue the grouped-1x1 / state
-        // MFMA; (3) rectify, pack, store.  Two transposition buffers alternate.
-        constexpr int NR = R + 2 * P;
-        f32x4 acc[KS];
-        Frag s1v[2][2];                   // V (hi, lo) after the lane permutation
-        f32x4 s2v[2];                     // MFMA results awaiting stage 3
-        u32x2 q_held = {0u, 0u};          // an even Q row awaiting its partner
-        auto pass_t = [](int pass) { return pass == 0 ? 1 : pass == 1 ? 2 : 0; };     // K, V, Q
-        // A finished row sits as lane (channel chn, x-block sub) = 4 tokens of one channel.  It is
-        // rounded to the operand type first (hi and lo halves for bf16), so everything that moves is
-        // 8 bytes per lane.
-        auto stage1 = [&](int it, f32x4 o) {
-            const int t = pass_t(it / NR), y = it % NR - (KS - 1);
-            const int gy = gy0 + y;
-            // the wait states between a 4x4x4 matrix instruction and a reader of its result, written out: the compiler (ROCm
-            // 7.2) leaves them out on the path that jumps over the masking below (bf16, paired launch)
-            if (t == 1) asm volatile("s_nop 4" : "+v"(o));
-            if (t == 1 && ragged) {
-                // tokens outside the image contribute nothing: their aggregated K is made 0, which
-                // also removes their V from the state; Q rows of such tokens are simply not stored.
-                // (Only a tile that sticks out of the image has such tokens.)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (gy >= a.H || gx0 + i >= a.W) o[i] = 0.f;
-            }
-            Frag hi, lo;
-            if constexpr (Tr::kHiLo) frag_split<T>(o, hi, lo);
-            else hi = frag_from_f32<T>(o);
-            if (t == 2) {
-                // V: lane (channel c, q) <- the lane that swept channel c, x-block q: tokens (x-block q, i),
-                // the K operand's order
-                const int from = 4 * (4 * (x16 & 3) + (x16 >> 2)) + q;
-                const u32x2 h2 = __builtin_bit_cast(u32x2, hi);
-                s1v[it & 1][0] = __builtin_bit_cast(Frag, u32x2{(unsigned)__shfl((int)h2[0], from),
-                                                                (unsigned)__shfl((int)h2[1], from)});
-                if constexpr (Tr::kHiLo) {
-                    const u32x2 l2 = __builtin_bit_cast(u32x2, lo);
-                    s1v[it & 1][1] = __builtin_bit_cast(Frag, u32x2{(unsigned)__shfl((int)l2[0], from),
-                                                                    (unsigned)__shfl((int)l2[1], from)});
-                }
-            } else {
-                // K, Q: the lane's 4 tokens of one channel go into a [token][channel] fp32 matrix; stage 2
-                // picks up a token's 4 channels with one 16-byte read
-                char* tb = trans + (it & 1) * L::kTransBytes;
-                wave_lds_fence();
-#pragma unroll
-                for (int i = 0; i < 4; ++i) *(float*)(tb + (4 * sub + i) * L::kTokStride + chn * 4) = o[i];
-                wave_lds_fence();
-            }
-        };
-        // Stage 2 is split: the transposed row is requested from LDS at the top of an iteration and
-        // used after the iteration's depthwise MFMAs, which cover the LDS latency.
-        auto stage2_read = [&](int it) {
-            const char* tb = trans + (it & 1) * L::kTransBytes;
-            return *(const f32x4*)(tb + x16 * L::kTokStride + q * 16);
-        };
-        auto stage2 = [&](int it, f32x4 tq) {
-            const int t = pass_t(it / NR), y = it % NR - (KS - 1);
-            if (t == 2) {
-                if constexpr (Tr::kHiLo) {
-                    kv_agg = Tr::mma16(kv_agg, aggK[y], s1v[it & 1][0]);
-                    kv_agg = Tr::mma16(kv_agg, aggK[y], s1v[it & 1][1]);
-                    kv_agg = Tr::mma16(kv_agg, aggK_lo[y], s1v[it & 1][0]);
-                } else {
-                    kv_agg = Tr::mma16(kv_agg, aggK[y], s1v[it & 1][0]);
-                }
-                return;
-            }
-            // The depthwise sums of Q always go to the grouped 1x1 as hi + lo pairs, whatever the
-            // storage type: which components of the aggregated Q pass the rectifier of Eq. (2) is a
-            // discrete decision, so that Q must carry the accuracy of its fp32 sums up to the one
-            // rounding of its store (a sum rounded to 11 bits first moves a component that is small
-            // against its 16 terms across zero).  K only feeds the sums of Eq. (3), which are
-            // continuous in it: fp16 takes its depthwise sums rounded once.
-            Frag dwf, dwf_lo;
-            if (Tr::kHiLo || t == 0) frag_split<T>(tq, dwf, dwf_lo);
-            else dwf = frag_from_f32<T>(tq);
-            if (t == 1) {
-                f32x4 kf = Tr::mma16(z, dwf, gpw_k);
-                if constexpr (Tr::kHiLo) kf = Tr::mma16(kf, dwf_lo, gpw_k);
-                s2v[it & 1] = kf;
-            } else {
-                f32x4 qq = Tr::mma16(z, gpw_q, dwf);
-                qq = Tr::mma16(qq, gpw_q, dwf_lo);
-                s2v[it & 1] = qq;
-            }
-        };
-        auto stage3 = [&](int it) {
-            const int t = pass_t(it / NR), y = it % NR - (KS - 1);
-            if (t == 1) {
-                const f32x4 kf = relu_bits_f32(s2v[it & 1]);       // Eq. (2): relu(K), one integer max per value
-                ks_agg += (kf[0] + kf[1]) + (kf[2] + kf[3]);
-                if constexpr (Tr::kHiLo) frag_split<T>(kf, aggK[y], aggK_lo[y]);
-                else aggK[y] = frag_from_f32<T>(kf);
-            } else if (t == 0) {
-                // lane (token x16 = 4*xblock + i, q): channels 4q..4q+3 of image row gy0 + y, 8 bytes.
-                // Two rows share one store (a store instruction costs the same whatever its width): an
-                // even row waits for the next one, then the odd 16-lane groups of the one are swapped
-                // with the even groups of the other, which leaves lane (x16, q) with channels
-                // 8*(q/2) .. +7 of its token in row y - 1 + q % 2.
-                static_assert(R % 2 == 0, "Q rows are stored in pairs");
-                const u32x2 v = __builtin_bit_cast(u32x2, frag_from_f32<T>(s2v[it & 1]));
-                if (y % 2 == 0) {
-                    q_held = v;
-                } else {
-                    const u32x2 s0 = __builtin_amdgcn_permlane16_swap(q_held[0], v[0], false, false);
-                    const u32x2 s1 = __builtin_amdgcn_permlane16_swap(q_held[1], v[1], false, false);
-                    const int gy = gy0 + y - 1 + (q & 1);
-                    const int gx = tx0 + 16 * strip + x16;
-                    const unsigned off = (unsigned)(gy * a.W + gx) * q_ms_tb + (q >> 1) * 8 * (unsigned)sizeof(T);
-                    buf_store16(rout, gy < a.H && gx < a.W ? off : kOobOffset, u32x4{s0[0], s1[0], s0[1], s1[1]});
-                }
-            }
-        };
-        // input row i of the flat sequence: 8 columns (two k-steps) of this lane's channel and x-block
-        Frag din[2][2];
-        auto fetch_row = [&](int i, Frag (&d)[2]) {
-            const int t = pass_t(i / NR), r = i % NR;
-            const char* src = planar + (t * 16 + chn) * L::kChanBytes + (R * part + r) * L::kRowBytes + col0 * 2;
-            d[0] = load_frag<T>(src);
-            d[1] = load_frag<T>(src + 8);
-        };
-        fetch_row(0, din[0]);
-        static_for<0, 3 * NR + 2>([&](auto it_c) {
-            constexpr int it = decltype(it_c)::value;
-            // iteration i finishes an output row iff it is the KS-th or a later input row of its pass
-            constexpr auto has_row = [](int i) { return i >= 0 && i < 3 * NR && i % NR >= KS - 1; };
-            constexpr bool kPickUp = has_row(it - 1) && ((it - 1) / NR != 1);     // K or Q row in the transposition buffer
-            // LDS requests first: the next input row and the row handed over one iteration ago
-            if constexpr (it + 1 < 3 * NR) fetch_row(it + 1, din[(it + 1) & 1]);
-            f32x4 tq = z;
-            if constexpr (kPickUp) tq = stage2_read(it - 1);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (it < 3 * NR) {
-                const int pass = it / NR, r = it % NR;
-                const int t = pass_t(pass);
-                if (r == 0) {
-#pragma unroll
-                    for (int i = 0; i < KS; ++i) acc[i] = z;
-                }
-#pragma unroll
-                for (int u = 0; u < KS; ++u) {
-                    const int y = r - u;
-                    if (y < 0 || y >= R) continue;
-                    acc[y % KS] = M4<T>::mma(toep[t][u][0], din[it & 1][0], acc[y % KS]);
-                    acc[y % KS] = M4<T>::mma(toep[t][u][1], din[it & 1][1], acc[y % KS]);
-                }
-            }
-            if constexpr (has_row(it - 1)) stage2(it - 1, tq);
-            if constexpr (has_row(it - 2)) stage3(it - 2);
-            if constexpr (has_row(it)) {
-                // output row y of 16 channels x 16 tokens is complete: lane (channel chn, x-block sub)
-                // holds the 4 tokens gx0..gx0+3 of image row gy0 + y
-                const int y = it % NR - (KS - 1);
-                const f32x4 o = acc[y % KS];
-                acc[y % KS] = z;
-                stage1(it, o);
-            }
-        });
+        sweep_rows<T, KS, kSweepRows, L::kChanBytes>(planar + kSweepRows * part * kPlanarRowBytes + 16 * strip * (int)sizeof(T), trans, toep,
+                                                     gpw_q, gpw_k, a.H, a.W, ty0 + kSweepRows * part, tx0 + 16 * strip, ragged, rout,
+                                                     q_ms_tb, kv_agg, ks_agg);
         }
         __syncthreads();
     }
@@ -605,25 +401,24 @@ __device__ __forceinline__ void aggregate_mfma_body(const AggregateArgs& a, unsi
         msum[j] = wave_sum(((e >> 2) * 16 + c) * 4 + (e & 3));
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < 2 * kStateSize; j += kThreads) {
-        const int which = j / kStateSize, idx = j - which * kStateSize;   // 0: aggregated, 1: raw
-        if (which == 1 && !a.do_raw) continue;
-        const int e = idx / 17, f = idx - e * 17;
-        float s;
-        if (f == 16) {
-            s = wave_sum(512 + which * 16 + e);
-        } else if (which == 1) {
-            s = wave_sum(256 + ((e >> 2) * 16 + f) * 4 + (e & 3));
-        } else {
-            // the grouped 1x1 of V, applied to the summed state: KV[e][f] = sum_c M[e][c] w_gpw[f][c]
-            const T* wv = wgp + (2 * 16 + f) * 16;
-            s = 0.f;
-#pragma unroll
-            for (int c = 0; c < 16; ++c) s = fmaf(msum[e * 16 + c], Tr::to_f32(wv[c]), s);
-        }
+    auto put = [&](int which, int e, int f, float s) {      // 0: aggregated, 1: raw
         const int branch = which == 0 ? a.branch : 0;
-        a.partials[((((long)b * a.S + branch) * a.heads + h) * a.nchunks + chunk) * kStateSize + idx] = s;
+        a.partials[((((long)b * a.S + branch) * a.heads + h) * a.nchunks + chunk) * kStateSize + e * 17 + f] = s;
+    };
+    const int e = (threadIdx.x >> 4) & 15;
+    if (role == 0) {
+        // the grouped 1x1 of V, applied to the summed state: KV[e][f] = sum_c M[e][c] w_gpw[f][c]
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) s = fmaf(msum[e * 16 + c], Tr::to_f32(w_v[c >> 3][c & 7]), s);
+        put(0, e, x16, s);
+    } else if (threadIdx.x < 512) {
+        if (a.do_raw) put(1, e, x16, wave_sum(256 + ((e >> 2) * 16 + x16) * 4 + (e & 3)));
+    } else if (threadIdx.x < 512 + 32) {
+        const int which = e & 1;
+        if (which == 0 || a.do_raw) put(which, x16, 16, wave_sum(512 + which * 16 + x16));
     }
+    static_assert(kThreads >= 544, "a thread for every sum");
 }
 
 template <class T, int KS, bool kCopyRawQ>
@@ -713,6 +508,7 @@ hipError_t launch_aggregate_mfma_pair(int dt, const AggregateArgs& a0, const Agg
 #ifdef MSLA_AGG_NO_MFMA
     return hipErrorNotSupported;
 #endif
+    if (a0.small) return a1.copy_raw_q ? hipErrorNotSupported : launch_aggregate_small(dt, a0, &a1, stream);
     switch (dt) {
         case 1: return run_pair<_Float16>(a0, a1, stream);
         case 2: return run_pair<__bf16>(a0, a1, stream);
@@ -724,6 +520,7 @@ hipError_t launch_aggregate_mfma(int dt, const AggregateArgs& a, hipStream_t str
 #ifdef MSLA_AGG_NO_MFMA
     return hipErrorNotSupported;      // build knob: every case takes the general kernel (as oversized images do)
 #endif
+    if (a.small) return launch_aggregate_small(dt, a, nullptr, stream);
     switch (dt) {
         case 1: return run<_Float16>(a, stream);
         case 2: return run<__bf16>(a, stream);

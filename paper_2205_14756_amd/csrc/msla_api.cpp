@@ -33,6 +33,7 @@ struct Shape {
     int scales[kMaxScales];
     // state reduction split
     int nchunks, tiles_per_chunk;
+    bool small;         // one workgroup a tile of 8 x 32 tokens (k_aggregate_small.hip)
 };
 
 // How many workgroups share a state's tiles in the fp32 aggregation kernels, at most `most`.  Two of them are resident on a
@@ -80,6 +81,7 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     s->B = B; s->H = H; s->W = W; s->heads = heads; s->S = 1 + n_scales;
     s->N = N; s->T = T; s->Ct = heads * 16; s->n_scales = n_scales;
     for (int i = 0; i < n_scales; ++i) s->scales[i] = scales[i];
+    s->small = false;
     // Split each (image, head) over enough workgroups to fill the chip; every
     // workgroup then emits one partial state.  A "tile" is 8x32 (fp32) or 16x32 (16-bit types)
     // tokens for the aggregating kernels, 64 consecutive tokens when there is no aggregated scale.
@@ -138,18 +140,62 @@ Workspace carve(const Shape& s, msla_dtype dt, bool with_maps = true) {
     return w;
 }
 
+// Maps of few tiles: the aggregation as one workgroup per tile of 8 x 32 tokens (k_aggregate_small.hip) instead of pipelined
+// workgroups that walk tiles of 16 x 32 (k_aggregate_mfma.hip).  It needs a 3x3 or a 5x5 scale or one of each, and pays while its
+// workgroups are all on the chip at once, two a compute unit with one scale, one with two.
+//
+// In the module that kernel also computes Q, K and V, up to kAggSmallMaxC input channels (what it holds in registers and LDS).
+// Us a module, fp16, separate projection and tiles of 16 x 32 / this: 8192 tokens, 128 channels (256 workgroups) 23.3 / 19.1;
+// 2 x 8192 of 128 (512) 27.6 / 25.8; 4 x 8192 of 64 (512) 27.8 / 23.5; 2048 of 192, 3x3 25.6 / 21.4; bf16, 3x3 + 5x5, 4096 tokens of 96 (192)
+// 24.9 / 22.1.  Past the limits: 3 x 8192 of 128 (768) 31.4 / 32.9; 3x3 + 5x5, 3 x 4096 of 128 (384) 32.9 / 34.1.
+// With 256 channels a workgroup a head reads too much: 2048 tokens 25.4 with a separate projection, 25.8 without.
+//
+// With Q, K and V from memory (the core, and modules of more channels) it pays up to one workgroup a compute unit:
+// 2048 tokens, 32 heads of 512 channels (256) 34.1 / 32.1, the core of 8192 tokens, 8 heads (256) 19.7 / 17.3, of 2 x 8192 (512) 23.6 / 24.4.
+bool small_map(const Shape& s, msla_dtype dt, bool fused) {
+    if (dt == MSLA_F32 || s.n_scales < 1 || s.n_scales > 2) return false;
+    for (int i = 0; i < s.n_scales; ++i)
+        if (s.scales[i] != 3 && s.scales[i] != 5) return false;
+    if (s.n_scales == 2 && s.scales[0] == s.scales[1]) return false;
+    const long tiles = (long)((s.H + msla::kAggSmallTileH - 1) / msla::kAggSmallTileH) *
+                       ((s.W + msla::kAggSmallTileW - 1) / msla::kAggSmallTileW);
+    return tiles * s.B * s.heads <= (fused && s.n_scales == 1 ? 2L : 1L) * msla::compute_units();
+}
+void make_small(Shape* s) {
+    s->small = true;
+    s->nchunks = (s->H + msla::kAggSmallTileH - 1) / msla::kAggSmallTileH * ((s->W + msla::kAggSmallTileW - 1) / msla::kAggSmallTileW);
+    s->tiles_per_chunk = 1;
+}
+// The module's workspace; with more channels than the small maps' kernel projects, its partial states are part of it.
+Workspace carve_module(Shape* s, int C, msla_dtype dt) {
+    if (C > msla::kAggSmallMaxC && small_map(*s, dt, false)) make_small(s);
+    return carve(*s, dt);
+}
+// make_small where the K|V map of the workspace is not used (the kernel computes K and V, or the caller's map is read): the partial
+// states of the smaller tiles, more of them, take its place, and the workspace keeps its size.  False if they do not fit.
+bool make_small_in_kv(Shape* s, msla_dtype dt, Workspace* w) {
+    Shape t = *s;
+    make_small(&t);
+    const size_t need = (size_t)t.B * t.S * t.heads * t.nchunks * 272 * sizeof(float);
+    if (need > (size_t)kv_padded_tokens(t) * 2 * t.Ct * elem_size(dt)) return false;
+    *s = t;
+    w->partials = w->kv_raw;
+    return true;
+}
+
 size_t dw_weight_elems(const Shape& s, int upto) {
     size_t n = 0;
     for (int i = 0; i < upto; ++i) n += (size_t)3 * s.Ct * s.scales[i] * s.scales[i];
     return n;
 }
 
-// Aggregation + state for all branches.  The raw maps are given as three strided views.
+// Aggregation + state for all branches.  The raw maps are given as three strided views; with w_qkv (small maps of the module), they are
+// still to be computed from x [T, C], which all three views are.
 msla_status run_state(const Shape& s, msla_dtype dt, const void* q, long q_ts, int q_hs, const void* k,
                       long k_ts, int k_hs, const void* v, long v_ts, int v_hs, const void* w_dw,
                       const void* w_gpw, char* ws, const Workspace& wo, void* q_ms, int copy_raw_q,
                       hipStream_t stream, unsigned options = 0, void* event_before_finalize = nullptr,
-                      int state_split = 0) {
+                      int state_split = 0, const void* w_qkv = nullptr, int C = 0) {
     const size_t e = elem_size(dt);
     msla::AggregateArgs a;
     a.q = q; a.k = k; a.v = v;
@@ -159,6 +205,8 @@ msla_status run_state(const Shape& s, msla_dtype dt, const void* q, long q_ts, i
     a.partials = reinterpret_cast<float*>(ws + wo.partials);
     a.B = s.B; a.H = s.H; a.W = s.W; a.heads = s.heads; a.S = s.S;
     a.nchunks = s.nchunks; a.tiles_per_chunk = s.tiles_per_chunk;
+    a.small = s.small;
+    a.w_qkv = w_qkv; a.C = C;
     const bool aggregate = stage_wanted(options, MSLA_OPT_STAGE_AGGREGATE);
     if (s.n_scales == 0 && aggregate) {
         a.w_dw = nullptr; a.w_gpw = nullptr; a.ks = 0; a.branch = 0; a.do_raw = 1; a.copy_raw_q = copy_raw_q;
@@ -295,7 +343,7 @@ msla_status paired8_plan(int B, int C, int H, int W, int heads, const int* scale
     p->w_dw = off;  off += align_up(dw_weight_elems(s, n_scales) * e + 16);
     p->w_gpw = off; off += align_up((size_t)n_scales * 3 * s.Ct * 16 * e + 16);
     p->inner = off;
-    p->inner_bytes = carve(s, dt).total;
+    p->inner_bytes = carve_module(&s, C, dt).total;
     p->total = off + p->inner_bytes;
     return MSLA_OK;
 }
@@ -377,7 +425,7 @@ msla_status msla_workspace_bytes(int B, int C, int H, int W, int heads, int head
     const msla_status st = check_shape(B, H, W, heads, head_dim, scales, n_scales, (int)dt, &s);
     if (st != MSLA_OK) return st;
     if (C % 16 != 0) return MSLA_ERR_UNSUPPORTED;
-    *bytes = carve(s, dt).total;
+    *bytes = carve_module(&s, C, dt).total;
     return MSLA_OK;
 }
 
@@ -429,8 +477,10 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     if (C % 16 != 0) return MSLA_ERR_UNSUPPORTED;
     // channel-planar x / out: the result is parked where K|V lived, which must be large enough
     if (layout == MSLA_NCHW && C > 2 * s.Ct) return MSLA_ERR_UNSUPPORTED;
-    const Workspace wo = carve(s, dt);
+    Workspace wo = carve_module(&s, C, dt);
     if (workspace_bytes < wo.total) return MSLA_ERR_WORKSPACE;
+    // (a call that selects or times stages has the projection as a stage of its own)
+    const bool fused = C <= msla::kAggSmallMaxC && options == 0 && events == nullptr && small_map(s, dt, true) && make_small_in_kv(&s, dt, &wo);
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
@@ -458,14 +508,18 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     const long kv_ts = hm ? 32 : 2L * s.Ct;                       // elements from token to token
     const long kv_hs = hm ? kv_padded_tokens(s) * 32 : 32;        // ... from head to head
     const long kv_span = hm ? kv_padded_tokens(s) * 2 * s.Ct : s.T * 2 * s.Ct;
-    if (stage_wanted(options, MSLA_OPT_STAGE_PROJECT) &&
+    if (stage_wanted(options, MSLA_OPT_STAGE_PROJECT) && !fused &&
         msla::launch_qkv_project((int)dt, x_tok, w_qkv, q_ms, q_ms_ts, kv_raw, kv_ts, kv_hs, kv_span, s.T, C, s.heads,
                                  hs) != hipSuccess)
         return MSLA_ERR_LAUNCH;
     if (!mark(1)) return MSLA_ERR_LAUNCH;
     // aggregation + Eq. (3) state
-    st = run_state(s, dt, q_ms, q_ms_ts, 16, kv_raw, kv_ts, (int)kv_hs, kv_raw + 16 * e, kv_ts, (int)kv_hs, w_dw, w_gpw,
-                   ws, wo, q_ms, /*copy_raw_q=*/0, hs, options, events ? events[2] : nullptr, state_split);
+    if (fused)
+        st = run_state(s, dt, x_tok, C, 0, x_tok, C, 0, x_tok, C, 0, w_dw, w_gpw, ws, wo, q_ms, /*copy_raw_q=*/0, hs, options, nullptr,
+                       state_split, w_qkv, C);
+    else
+        st = run_state(s, dt, q_ms, q_ms_ts, 16, kv_raw, kv_ts, (int)kv_hs, kv_raw + 16 * e, kv_ts, (int)kv_hs, w_dw, w_gpw,
+                       ws, wo, q_ms, /*copy_raw_q=*/0, hs, options, events ? events[2] : nullptr, state_split);
     if (st != MSLA_OK) return st;
     if (!mark(3)) return MSLA_ERR_LAUNCH;
     // normalise-and-apply fused with the output projection
@@ -557,8 +611,9 @@ msla_status msla_core_forward(const void* qkv, const void* w_dw, const void* w_g
     Shape s;
     msla_status st = check_shape(B, H, W, heads, head_dim, scales, n_scales, (int)dt, &s);
     if (st != MSLA_OK) return st;
-    const Workspace wo = carve(s, dt);
+    Workspace wo = carve(s, dt);
     if (workspace_bytes < wo.total) return MSLA_ERR_WORKSPACE;
+    if (small_map(s, dt, false)) make_small_in_kv(&s, dt, &wo);
     hipStream_t hs = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     const size_t e = elem_size(dt);

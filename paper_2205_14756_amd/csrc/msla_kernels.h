@@ -41,6 +41,10 @@ struct AggregateArgs {
     int do_raw;              // also accumulate the branch-0 state from the raw K, V
     int copy_raw_q;          // also copy the raw Q into the branch-0 columns of q_ms
     int state_valu = 0;      // raw-state kernel only: vector ALUs + shuffles instead of the matrix cores
+    int small = 0;           // aggregate_mfma: one workgroup a tile of 8 x 32 tokens (nchunks tiles, tiles_per_chunk 1)
+    // ... and with those, optionally: compute Q, K and V from x [T, C] = q = k = v and w_qkv [3*Ct, C] (and write the raw Q)
+    const void* w_qkv = nullptr;
+    int C = 0;
 };
 hipError_t launch_aggregate(int dt, const AggregateArgs& a, hipStream_t stream);
 
@@ -48,6 +52,11 @@ hipError_t launch_aggregate(int dt, const AggregateArgs& a, hipStream_t stream);
 // (16 x 32-token tiles; needs v == k + 16 elements with equal strides).  Returns
 // hipErrorNotSupported without launching when one image's maps span 2^31 bytes or more.
 hipError_t launch_aggregate_mfma(int dt, const AggregateArgs& a, hipStream_t stream);
+
+// Same contract for maps of few tiles (k_aggregate_small.hip): one workgroup a tile of 8 x 32 tokens, so nchunks is the number
+// of such tiles and tiles_per_chunk is 1; a 3x3 or 5x5 scale, or one of each (`second`, else null).  launch_aggregate_mfma and
+// launch_aggregate_mfma_pair hand over to it.
+hipError_t launch_aggregate_small(int dt, const AggregateArgs& a, const AggregateArgs* second, hipStream_t stream);
 
 // Two aggregated scales (3x3 and 5x5, either order) of the same module in one launch; hipErrorNotSupported,
 // without launching, for anything else (then the caller launches them one by one).
@@ -168,6 +177,9 @@ inline hipError_t allow_dynamic_lds(int bytes) {
 
 constexpr int kAggTileH = 8;        // vector-ALU kernel (fp32 storage)
 constexpr int kAggTileW = 32;
+constexpr int kAggSmallTileH = 8;   // the same, one tile a workgroup (k_aggregate_small.hip)
+constexpr int kAggSmallTileW = 32;
+constexpr int kAggSmallMaxC = 192;  // input channels with which that kernel computes Q, K and V itself
 constexpr int kAggMfmaTileH = 16;   // matrix-core kernel (fp16 / bf16 storage)
 constexpr int kAggMfmaTileW = 32;
 

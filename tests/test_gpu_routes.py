@@ -202,3 +202,39 @@ def test_later_scales_in_launches_of_their_own(dtype, B, H, W, heads, scales):
 @pytest.mark.parametrize("n,c_in,c_out", [(16384, 160, 480), (16301, 144, 496)])
 def test_fp32_linear_on_full_maps(n, c_in, c_out):
     base.test_linear("f32", n, c_in, c_out)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# one workgroup a tile of 8 x 32 tokens, Q, K and V computed there: 16, 48, 64, 80, 128, 144 and 192 input channels (the last step of
+# 32 half empty in four of them), one and two scales in either order, several images, one pixel, ragged tiles, 252 workgroups; then 208
+# channels (Q, K and V read) and the first shape past a round of workgroups
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 16, 1, 1, 1, (5,)), (3, 48, 9, 33, 3, (3,)), (2, 64, 8, 32, 4, (3, 5)),
+                                                  (1, 80, 17, 31, 5, (5, 3)), (7, 128, 23, 40, 6, (5,)), (2, 144, 7, 65, 9, (3,)),
+                                                  (1, 192, 40, 60, 12, (3, 5)), (2, 208, 21, 45, 13, (3, 5)), (1, 128, 64, 128, 8, (5,)),
+                                                  (1, 48, 8, 32 * 43, 6, (5,))])
+def test_small_maps(dtype, B, C, H, W, heads, scales):
+    print(f"routes: small map {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
+    base.check_module(wk.random_module(37 + C + H, dtype, B, C, H, W, heads, 16, scales), dtype, heads, 16, scales)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(2, 80, 19, 45, 5, (5,)), (1, 128, 33, 70, 8, (3, 5)), (3, 192, 9, 32, 4, (3,))])
+def test_small_map_with_its_own_projection_equals_the_stages(dtype, B, C, H, W, heads, scales):
+    # a call that selects stages (here: all of them) has the projection as a kernel of its own and larger tiles: the stored Q, K and V
+    # are the same, the states are summed in another order
+    print(f"routes: small map, stages {dtype} {B}x{C}x{H}x{W}", flush=True)
+    t = wk.random_module(3 + H, dtype, B, C, H, W, heads, 16, scales)
+    wdw, wg = base.weights(t, dtype, scales)
+    args = (base.dev(t["x"], dtype), base.dev(t["w_qkv"], dtype), wdw, wg, base.dev(t["w_proj"], dtype), heads, 16, scales)
+    stages = msla.MSLA_OPT_STAGE_PROJECT | msla.MSLA_OPT_STAGE_AGGREGATE | msla.MSLA_OPT_STAGE_FINALIZE | msla.MSLA_OPT_STAGE_APPLY
+    # (bytes around the result and behind the workspace must stay as they are)
+    n = msla.msla_workspace_bytes(B, C, H, W, heads, 16, scales, base.TDT[dtype])
+    ws = torch.full((n + 256,), 77, dtype=torch.uint8, device="cuda")
+    room = torch.full((B * H * W + 2, C), 7.0, dtype=base.TDT[dtype], device="cuda")
+    out = room[1:-1].view(B, H, W, C)
+    msla.msla_forward(*args, out=out, workspace=ws[:n])
+    want = msla.msla_forward(*args, options=stages)
+    torch.cuda.synchronize()
+    assert bool((room[0] == 7.0).all()) and bool((room[-1] == 7.0).all()) and bool((ws[n:] == 77).all())
+    u = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]       # what differs is a last rounding here and there
+    assert float((out.float() - want.float()).norm() / want.float().norm()) <= u
