@@ -33,7 +33,8 @@ constexpr int TH = kAggTileH;   // tile rows
 constexpr int TW = kAggTileW;   // tile columns; a strip is 4 tokens, 8 strips per row
 constexpr int kAggThreads = 256;
 
-template <class T, int KS>
+// kOne: one tile a workgroup (see aggregate_kernel)
+template <class T, int KS, int kOne = 0>
 struct AggLds {
     static constexpr int P = (KS - 1) / 2;
     static constexpr int LH = TH + 2 * P, LW = TW + 2 * P;
@@ -42,10 +43,11 @@ struct AggLds {
     // active cycles were bank conflicts in fp32).
     typedef HaloPlanes<LH, LW, (int)sizeof(T), 4> Planes;
     static constexpr int kMapBytes = 4 * Planes::kPlane;
-    static constexpr int kTileBytes = 2 * kMapBytes;
+    static constexpr int kTileBytes = (kOne ? 3 : 2) * kMapBytes;
     static constexpr int kWtsBytes = 3 * KS * KS * 16 * 4;     // fp32 [t][tap][16 ch]
     static constexpr int kRedBytes = 4 * (2 * 256 + 2 * 16) * 4;   // per wave: 2 x 64 lanes x 4 + 2 x 16 Ksum
-    static constexpr int kBytes = (kTileBytes > kRedBytes ? kTileBytes : kRedBytes) + kWtsBytes;
+    static constexpr int kHandBytes = kOne ? 4 * 4 * 64 * 16 : 0;   // kOne: aggregated K on its way to the waves that have V
+    static constexpr int kBytes = (kTileBytes > kRedBytes ? kTileBytes : kRedBytes) + kWtsBytes + kHandBytes;
 };
 
 // The three raw maps of one head (pointers already offset to the head).
@@ -58,19 +60,31 @@ struct HeadMaps {
 // kRaw, 16-bit types: the raw branch's state is summed as well (a template argument, for the reason given at
 // aggregate32_kernel).  fp32 keeps the run-time branch, with which the compiler's order is 1 to 3 % faster (the core of 4 x 64 x
 // 128 tokens, 8 heads, 7x7 75.5 us, 77.8 with the argument); tests/test_wait_states.py checks what is built.
-template <class T, int KS, bool kRaw>
-__global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a) {
+// kOne (fp32): a workgroup has one tile, and there is one workgroup a compute unit or fewer.  Then nothing hides a map's way from
+// memory or a sweep's latencies: all maps come at once, and there are four waves for each; those with V take the aggregated K
+// over from those with K.  1: twelve waves, those with Q have the raw branch as well.  2: a tile is two workgroups of eight waves,
+// one with K and V, one with Q and the raw branch (with all twelve on it, a unit's vector ALUs are what a tile waits for).
+// Us a module, 0 / 1 / 2: 1024 tokens, 64 channels (16 tiles) 23.1 / 20.8 / 19.6; 4096 of 128 (128 tiles) 32.8 / 29.6 / 28.0; 8192 of 128
+// (256 tiles) 41.1 / 38.0 / -; 4096 of 64 with 7x7 (64 tiles) 29.5 / 26.4 / 22.6.
+template <int kOne>
+constexpr int kAggThreadsOf = kOne == 0 ? kAggThreads : kOne == 1 ? 3 * kAggThreads : 2 * kAggThreads;
+template <class T, int KS, bool kRaw, int kOne>
+__global__ __launch_bounds__(kAggThreadsOf<kOne>) void aggregate_kernel(AggregateArgs a) {
     typedef Traits<T> Tr;
     typedef typename Tr::Frag Frag;
-    typedef AggLds<T, KS> L;
+    typedef AggLds<T, KS, kOne> L;
+    constexpr int kThreads = kAggThreadsOf<kOne>;
     constexpr int P = L::P;
     const bool do_raw = sizeof(T) == 2 ? kRaw : a.do_raw != 0;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* tile = lds;
-    float* wts = (float*)(lds + (L::kBytes - L::kWtsBytes));
+    float* wts = (float*)(lds + (L::kBytes - L::kWtsBytes - L::kHandBytes));
+    f32x4* hand = (f32x4*)(lds + (L::kBytes - L::kHandBytes));
     float* red = (float*)lds;   // reused after the last tile
 
-    const unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
+    unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
+    const int half = kOne == 2 ? Lid & 1 : 0;           // which of a tile's two workgroups
+    if constexpr (kOne == 2) Lid >>= 1;
     const int h = Lid % a.heads;
     const int chunk = (Lid / a.heads) % a.nchunks;
     const int b = Lid / (a.heads * a.nchunks);
@@ -78,17 +92,21 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
     const long N = (long)a.H * a.W;
     const long img_tok0 = (long)b * N;
 
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int lane = lane_id(), wave = (threadIdx.x >> 6) & 3;
+    // kOne: the pass that this wave takes: K, V, Q; 3: the raw branch, which is 2's as well if there is no 3
+    const int role = 2 * half + __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const bool raw_role = role == (kOne == 2 ? 3 : 2);
     const int x16 = lane & 15, q = lane >> 4;
 
     // depthwise filters of this head -> LDS as fp32 [t][tap][16]
-    {
+    auto stash_filters = [&] {
         const T* wdw = (const T*)a.w_dw + (long)h * 48 * KS * KS;
-        for (int it = threadIdx.x; it < 48 * KS * KS; it += kAggThreads) {
+        for (int it = threadIdx.x; it < 48 * KS * KS; it += kThreads) {
             const int ch = it / (KS * KS), tap = it - ch * (KS * KS);
             wts[((ch >> 4) * KS * KS + tap) * 16 + (ch & 15)] = Tr::to_f32(wdw[it]);
         }
-    }
+    };
+    if constexpr (!kOne) stash_filters();
     // grouped 1x1 weights of (h, t) as an MFMA operand: lane (o, q) holds w[o][4q..4q+3]
     Frag gpw[3];
 #pragma unroll
@@ -124,15 +142,16 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
     constexpr int SZ = (int)sizeof(T);
     constexpr int VPT = 16 * SZ / 16;                              // 16-byte vectors per pixel of one map
     constexpr int kItems = L::LH * L::LW * VPT;
-    constexpr int kPer = (kItems + kAggThreads - 1) / kAggThreads;
-    u32x4 pre[kPer];
+    constexpr int kPer = (kItems + kThreads - 1) / kThreads;
+    constexpr int kMaps = kOne ? 3 : 1;                            // maps in flight at once
+    u32x4 pre_maps[kMaps][kPer];
     // this thread's pixels of a halo tile: row and column in it (a row no image has for those past the last)
     int item_y[kPer], item_x[kPer];
     const int item_v = threadIdx.x % VPT;
-    static_assert(kAggThreads % VPT == 0, "a thread keeps its channels");
+    static_assert(kThreads % VPT == 0, "a thread keeps its channels");
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-        const int it = threadIdx.x + j * kAggThreads, pix = it / VPT;
+        const int it = threadIdx.x + j * kThreads, pix = it / VPT;
         item_y[j] = it < kItems ? pix / L::LW : 1 << 30;
         item_x[j] = pix % L::LW;
     }
@@ -140,6 +159,7 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
         const int ty0 = (tile_id / tiles_x) * TH, tx0 = (tile_id % tiles_x) * TW;
         const T* base = pass == 0 ? maps.k : pass == 1 ? maps.v : maps.q;
         const long ts = pass == 0 ? maps.k_ts : pass == 1 ? maps.v_ts : maps.q_ts;
+        u32x4(&pre)[kPer] = pre_maps[kOne ? pass : 0];
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int gy = ty0 - P + item_y[j], gx = tx0 - P + item_x[j];
@@ -149,7 +169,8 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
             pre[j] = val;
         }
     };
-    auto stash = [&](char* buf) {
+    auto stash = [&](char* buf, int pass) {
+        const u32x4(&pre)[kPer] = pre_maps[kOne ? pass : 0];
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             if (item_y[j] < L::LH) {
@@ -174,11 +195,19 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
         else return __builtin_bit_cast(Frag, *(const u32x2*)p);
     };
     int cur = 0;
-    if (tile_begin < tile_end) {
+    if constexpr (kOne) {
+#pragma unroll
+        for (int pass = 0; pass < 3; ++pass)
+            if (pass < 2 || kOne == 1 || half == 1) fetch(tile_begin, pass);
+        stash_filters();
+#pragma unroll
+        for (int pass = 0; pass < 3; ++pass)
+            if (pass < 2 || kOne == 1 || half == 1) stash(tile + pass * L::kMapBytes, pass);
+    } else if (tile_begin < tile_end) {
         fetch(tile_begin, 0);
-        stash(tile);
+        stash(tile, 0);
     }
-    __syncthreads();   // first map staged, wts written
+    __syncthreads();   // first map (kOne: all three) staged, wts written
 
     for (int tile_id = tile_begin; tile_id < tile_end; ++tile_id) {
         const int ty0 = (tile_id / tiles_x) * TH, tx0 = (tile_id % tiles_x) * TW;
@@ -189,18 +218,20 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
         const long tok0 = img_tok0 + (long)gy * a.W + gx0;
 
         Frag aggK[4], aggK_lo[4], rawK[4];
+        f32x4 aggV[4];          // kOne
         // order K, V, Q: K's operands are kept for the V pass; Q only stores
 #pragma unroll
         for (int pass = 0; pass < 3; ++pass) {
             const int t = (pass == 0) ? 1 : (pass == 1) ? 2 : 0;
+            if (kOne && pass != role) continue;
             float acc[4][4];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
-            const bool more = pass < 2 || tile_id + 1 < tile_end;
+            const bool more = !kOne && (pass < 2 || tile_id + 1 < tile_end);
             if (more) fetch(pass < 2 ? tile_id : tile_id + 1, pass < 2 ? pass + 1 : 0);
-            const char* src = tile + cur * L::kMapBytes;
+            const char* src = tile + (kOne ? pass : cur) * L::kMapBytes;
             const float* wt = wts + t * KS * KS * 16 + q * 4;
             if (t == 1) {
                 ks_agg += ks_agg_t;
@@ -261,7 +292,8 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
                     ks_agg_t += (kf[0] + kf[1]) + (kf[2] + kf[3]);
                     if constexpr (Tr::kHiLo) frag_split<T>(kf, aggK[r], aggK_lo[r]);
                     else aggK[r] = frag_from_f32<T>(kf);
-                    if (do_raw) {
+                    if constexpr (kOne) hand[(wave * 4 + r) * 64 + lane] = aggK[r];
+                    if (!kOne && do_raw) {
                         const Frag rk = frag_relu<T>(frag_from_f32<T>(Tr::mma16(z, rawf, ident)));
                         rawK[r] = rk;
                         const f32x4 rf = frag_to_f32<T>(rk);
@@ -277,10 +309,12 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
                         kv_agg_t = Tr::mma16(kv_agg_t, aggK[r], vh);
                         kv_agg_t = Tr::mma16(kv_agg_t, aggK[r], vl);
                         kv_agg_t = Tr::mma16(kv_agg_t, aggK_lo[r], vh);
+                    } else if constexpr (kOne) {
+                        aggV[r] = vf;
                     } else {
                         kv_agg_t = Tr::mma16(kv_agg_t, aggK[r], frag_from_f32<T>(vf));
                     }
-                    if (do_raw) {
+                    if (!kOne && do_raw) {
                         const Frag rv = frag_from_f32<T>(Tr::mma16(z, rawf, ident));
                         kv_raw_t = Tr::mma16(kv_raw_t, rawK[r], rv);
                     }
@@ -296,9 +330,32 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
                 }
             }
             // the next stage's map: registers -> the other buffer (free since the barrier of the stage before)
-            if (more) stash(tile + (cur ^ 1) * L::kMapBytes);
-            __syncthreads();
+            if (more) stash(tile + (cur ^ 1) * L::kMapBytes, 0);
+            if constexpr (!kOne) __syncthreads();
             cur ^= 1;
+        }
+        if constexpr (kOne) {
+            static_assert(sizeof(T) == 4, "fp32 operands");
+            __syncthreads();
+            if (role == 1) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) kv_agg_t = Tr::mma16(kv_agg_t, hand[(wave * 4 + r) * 64 + lane], aggV[r]);
+            } else if (raw_role && do_raw) {
+                // the raw branch of tile rows 2 * wave and the next, sixteen tokens a step: lane (channel x16, q) reads tokens q, 4 + q ..
+                const char* ch = tile + (x16 >> 2) * L::Planes::kPlane + (x16 & 3) * 4;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4 rk, rv;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        const char* p = ch + L::Planes::at(wave * 2 + (g >> 1) + P, (g & 1) * 16 + 4 * s + q + P);
+                        rk[s] = fmaxf(*(const float*)p, 0.f);
+                        rv[s] = *(const float*)(p + L::kMapBytes);
+                    }
+                    ks_raw_t += (rk[0] + rk[1]) + (rk[2] + rk[3]);
+                    kv_raw_t = Tr::mma16(kv_raw_t, rk, rv);
+                }
+            }
         }
     }
 
@@ -316,17 +373,18 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(AggregateArgs a)
     constexpr int kWaveFloats = 2 * 256 + 2 * 16;
     {
         float* mine = red + wave * kWaveFloats;
-        *(f32x4*)(mine + lane * 4) = kv_agg;
-        *(f32x4*)(mine + 256 + lane * 4) = kv_raw;
+        if (!kOne || role == 1) *(f32x4*)(mine + lane * 4) = kv_agg;
+        if (!kOne || raw_role) *(f32x4*)(mine + 256 + lane * 4) = kv_raw;
         if (q == 0) {
-            mine[512 + x16] = ks_agg;
-            mine[512 + 16 + x16] = ks_raw;
+            if (!kOne || role == 0) mine[512 + x16] = ks_agg;
+            if (!kOne || raw_role) mine[512 + 16 + x16] = ks_raw;
         }
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < 2 * kStateSize; j += kAggThreads) {
+    for (int j = threadIdx.x; j < 2 * kStateSize; j += kThreads) {
         const int which = j / kStateSize, idx = j - which * kStateSize;   // 0: aggregated, 1: raw
         if (which == 1 && !do_raw) continue;
+        if (kOne == 2 && which != half) continue;
         const int e = idx / 17, f = idx - e * 17;
         // KV[e][f] sits in lane (f, e / 4), element e % 4
         const int src = f < 16 ? which * 256 + ((e >> 2) * 16 + f) * 4 + (e & 3) : 512 + which * 16 + e;
@@ -591,21 +649,30 @@ __global__ __launch_bounds__(320) void state_finalize_kernel(const float* __rest
     }
 }
 
-template <class T, int KS, bool kRaw>
+template <class T, int KS, bool kRaw, int kOne>
 hipError_t run_aggregate_as(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
-    constexpr int kLds = AggLds<T, KS>::kBytes;
+    constexpr int kLds = AggLds<T, KS, kOne>::kBytes;
+    static_assert(kLds <= 160 * 1024, "LDS layout");
     if (kLds > 48 * 1024) {   // above the default dynamic-LDS limit (the CU has 160 KB)
-        const hipError_t e = allow_dynamic_lds<aggregate_kernel<T, KS, kRaw>>(kLds);
+        const hipError_t e = allow_dynamic_lds<aggregate_kernel<T, KS, kRaw, kOne>>(kLds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((aggregate_kernel<T, KS, kRaw>), dim3(nblocks), dim3(kAggThreads), kLds, stream, a);
+    hipLaunchKernelGGL((aggregate_kernel<T, KS, kRaw, kOne>), dim3(kOne == 2 ? 2 * nblocks : nblocks), dim3(kAggThreadsOf<kOne>), kLds,
+                       stream, a);
     return hipGetLastError();
 }
 template <class T, int KS>
 hipError_t run_aggregate_ks(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
-    if constexpr (sizeof(T) == 2)
-        if (!a.do_raw) return run_aggregate_as<T, KS, false>(a, nblocks, stream);
-    return run_aggregate_as<T, KS, true>(a, nblocks, stream);
+    if constexpr (sizeof(T) == 2) {
+        if (!a.do_raw) return run_aggregate_as<T, KS, false, 0>(a, nblocks, stream);
+    } else if (a.tiles_per_chunk == 1) {
+        // one tile a workgroup, and a compute unit for each (twelve waves with a 7x7 filter would spill)
+        const unsigned cus = (unsigned)compute_units();
+        if (2 * nblocks <= cus) return run_aggregate_as<T, KS, true, 2>(a, nblocks, stream);
+        if constexpr (KS < 7)
+            if (nblocks <= cus) return run_aggregate_as<T, KS, true, 1>(a, nblocks, stream);
+    }
+    return run_aggregate_as<T, KS, true, 0>(a, nblocks, stream);
 }
 
 template <class T>

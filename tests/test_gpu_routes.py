@@ -238,3 +238,13 @@ def test_small_map_with_its_own_projection_equals_the_stages(dtype, B, C, H, W, 
     assert bool((room[0] == 7.0).all()) and bool((room[-1] == 7.0).all()) and bool((ws[n:] == 77).all())
     u = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]       # what differs is a last rounding here and there
     assert float((out.float() - want.float()).norm() / want.float().norm()) <= u
+
+
+# fp32 maps of one tile a workgroup: a tile as two workgroups (128 tile-heads and fewer, three of them ragged), as one of twelve waves
+# (144 and 256, not with 7x7), and the first shape past that; several scales (later ones have no raw branch)
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 16, 1, 1, 1, (7,)), (2, 48, 19, 45, 3, (3, 5)), (3, 32, 9, 33, 2, (5, 7)),
+                                                  (1, 32, 64, 64, 8, (5,)), (1, 32, 61, 63, 9, (3, 5)), (1, 32, 64, 64, 9, (7,)),
+                                                  (2, 16, 64, 61, 8, (5, 3)), (1, 32, 64, 64, 17, (5,))])
+def test_fp32_small_maps(B, C, H, W, heads, scales):
+    print(f"routes: fp32 small {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
+    base.check_module(wk.random_module(43 + W + heads, "f32", B, C, H, W, heads, 16, scales), "f32", heads, 16, scales)
