@@ -200,7 +200,7 @@ __global__ __launch_bounds__(512) void ffn_dw_project_kernel(const T* __restrict
 // 8-15 (two per SIMD) only stage halo tiles and do the depthwise pass.  Everything in LDS is
 // double-buffered and one barrier ends each step.  In step i
 //   consumers   park W2 slab i+1, request slab i+2, multiply slab i  (token tile i%2 x weight tile i%2)
-//   producers   park halo i+2, request halo i+3, depthwise pass of slab i+1 -> token tile (i+1)%2
+//   producers   park halo i+2, request halo i+3; depthwise pass of slab i+1 -> token tile (i+1)%2
 // so every buffer written in a step was last read in the step before.  Rows are 128 bytes, unpadded, with
 // the 16-byte chunk index XOR-ed with (row / 2) % 8 (full rate for operand reads and row-order writes).
 // Requires one image's expanded map to stay below 2^31 bytes (32-bit offsets in a buffer resource).
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
             c_lds[y] = tok * 128 + ((dvec ^ ((tok >> 1) & 7)) * 16);
         }
         u32x4 rh[kHaloVec];
-        for (int i = -3; i < n_slab; ++i) {
+        auto stage_halo = [&](int i) {
             if (i + 2 >= 0 && i + 2 < n_slab) {           // park halo i+2
                 char* hd = ldsH + (i & 1) * (8 * kPlane);
 #pragma unroll
@@ -385,6 +385,13 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
                     rh[j] = buf_load16(hres, (h_glb[j] != kOobOffset && k_bytes + (pt & 7) * 16 < e_bytes) ? h_glb[j] + k_bytes
                                                                                                      : kOobOffset, 0);
             }
+        };
+        // Half of the waves park and request before their depthwise pass, half behind it: the LDS and the address path get a step's
+        // halo in two portions instead of one, and of a SIMD's two producers one is always at the vector ALU (us a call: 8 x 8192 tokens,
+        // 256 -> 1024 channels 130.9 -> 129.6; 8192, 128 -> 512 17.8 -> 17.2; 4 x 4096, 192 -> 768, bf16 34.4 -> 33.4; 2048, 512 -> 2048 51.5 -> 50.0)
+        const bool park_first = wave >= 12;
+        for (int i = -3; i < n_slab; ++i) {
+            if (park_first) stage_halo(i);
             if (i + 1 >= 0 && i + 1 < n_slab) {           // depthwise 3x3 + activation of slab i+1
                 const char* hs = ldsH + ((i + 1) & 1) * (8 * kPlane) + d_lds;
                 char* cd = ldsC + ((i + 1) & 1) * kTok;
@@ -427,6 +434,7 @@ __global__ __launch_bounds__(1024) void ffn_dw_project_split_kernel(const T* __r
                     *(u32x4*)(cd + c_lds[y]) = __builtin_bit_cast(u32x4, o);
                 }
             }
+            if (!park_first) stage_halo(i);
             __syncthreads();
         }
     }
