@@ -2,7 +2,10 @@
 // (Section 3.1, last paragraph, with d = 32: depthwise k x k, grouped 1x1 with 3*heads groups of 32
 // channels, then KV = sum_n relu(K_n)^T [V_n, 1] per image / branch / head).
 //
-// The form of the general head-size-16 kernel (k_aggregate.hip) with every 16 x 16 block doubled: one
+// Two kernels.  3x3 and 5x5 filters take the second (aggregate32_mfma_kernel, depthwise on the matrix cores); 7x7 filters, whose Toeplitz
+// operands would span more than eight input columns, and maps of 2 GiB and more the first (aggregate32_kernel):
+//
+// the form of the general head-size-16 kernel (k_aggregate.hip) with every 16 x 16 block doubled: one
 // workgroup owns one (image, head) and a run of 8 x 32-token tiles; per tile it stages the halo tile of the
 // head's raw K, V and Q channels in LDS, one map at a time (the next one on its way while the current one is
 // swept), and each of its 4 waves takes 2 tile rows.  A lane (strip, q) owns 4
@@ -21,7 +24,9 @@
 // workgroup with a 7x7 filter (92 KB in fp16, 101 in bf16), so one wave a SIMD it is there (kAhead): 24 heads, 4 x 64 x 64 tokens, the
 // module 380 -> 352 us in fp16, 414 -> 397 in bf16 (361 and 417 without the reads ahead).
 // Per-workgroup partial states [32][33] go to the buffer that the plain finalize kernel sums in a fixed order.
-#include "msla_device.h"
+#include <algorithm>
+
+#include "aggregate_sweep.h"
 #include "msla_kernels.h"
 
 namespace msla {
@@ -365,6 +370,498 @@ __global__ __launch_bounds__(kThreads32, (Agg32Lds<T, KS>::kWaves)) void aggrega
     }
 }
 
+// ---------------------------------------------------------------- 3x3 and 5x5 filters: depthwise on the matrix cores
+// The head-size-16 kernel's form (k_aggregate_mfma.hip) for heads of 32: four waves stage, eight sweep tiles of 16 x 32 tokens, the
+// depthwise convolution is a Toeplitz product on 4x4x4 matrix instructions.  A head's three maps of 32 channels do not fit the
+// LDS twice, so the pipeline steps from map to map (K, V, Q) with two buffers of one map; a step's map is two blocks of 16
+// channels, swept one after the other.  What that changes: the Toeplitz operands of all six blocks wait in LDS (a wave needs
+// another 20 registers of them every half step); the first block's depthwise sums wait in registers for the second's, and the
+// grouped 1x1 contracts over all 32 in one instruction; a staging wave reads its rows' raw K back in the V step for the raw state.
+// Aggregated K stays in registers from its step to V's; V's grouped 1x1 is applied to the summed state at the end.
+// Us a module, the first kernel / this: 8 x 8192 tokens, 8 heads, 5x5 fp16 182.9 / 152.8, bf16 199.8 / 154.6; 2048 tokens, 8 heads
+// 41.4 / 32.7; 2 x 4096, 4 heads, 3x3 35.8 / 27.8; 16384 tokens, 2 heads, 3x3 + 5x5 64.0 / 42.4.  The first of these, this kernel 91.8 -> 58.6 (vector ALU 44 % of a SIMD's cycles, matrix pipe 36 %, LDS 52 %); errors as before or smaller (V is
+// rounded once less).
+template <int KS>
+struct Mfma32Lds {
+    static constexpr int P = (KS - 1) / 2;
+    static constexpr int LH = kAggMfmaTileH + 2 * P, LW = kAggMfmaTileW + 2 * P;
+    static constexpr int kChanBytes = planar_chan_bytes(LH);
+    static constexpr int kMapBytes = D32 * kChanBytes;
+    static constexpr int kToepBytes = 6 * KS * 2 * 64 * 8;              // [map][block][filter row][k-step][lane]
+    static constexpr int kWvBytes = D32 * D32 * 2;                      // V's grouped 1x1
+    static constexpr int kWork = 2 * kMapBytes + 8 * 2 * kTransBytes;   // two maps in flight, the sweeping waves' transposition buffers
+    static constexpr int kBytes = kWork + kToepBytes + kWvBytes;
+    static constexpr int kWaveFloats = NB * NB * 256 + D32;             // per wave: accumulator quads of its state, Ksum
+    static_assert(kMapBytes % 16 == 0 && LW <= 36 && kBytes <= 160 * 1024 && (12 * kWaveFloats + D32 * D32) * 4 <= kWork, "LDS layout");
+};
+
+// One map's sweep of one wave: 16 columns x 4 rows.  kMap: 0 Q, 1 K, 2 V.
+template <class T, int KS, int kMap, int kChanBytes>
+__device__ __forceinline__ void sweep32(const char* rows, char* trans, const char* toep_lds, const typename Traits<T>::Vec (&gpw)[NB], int H,
+                                        int W, int gy0, int gx_first, bool ragged, BufRsrc rout, unsigned q_ms_tb,
+                                        typename Traits<T>::Frag (&aggK)[NB][4], typename Traits<T>::Frag (&aggK_lo)[NB][4],
+                                        f32x4 (&kv_agg)[NB][NB], float (&ks_agg)[NB]) {
+    typedef Traits<T> Tr;
+    typedef typename Tr::Frag Frag;
+    typedef typename Tr::Vec Vec;
+    constexpr int R = 4, NR = R + KS - 1;
+    constexpr bool kWide = Tr::kHiLo || kMap == 0;      // depthwise sums as hi + lo pairs
+    const int lane = lane_id(), x16 = lane & 15, q = lane >> 4, sub = lane & 3;
+    const int chn = sweep_channel(lane);
+    const int gx0 = gx_first + 4 * sub;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[KS];
+    Frag s1v[2][2], dw0[R], dw0_lo[R];      // the first block's depthwise sums of each row
+    f32x4 s2v[2][NB];
+    u32x2 q_held[NB];
+    auto stage1 = [&](int it, f32x4 o) {
+        const int y = it % NR - (KS - 1);
+        // (the wait states between a 4x4x4 matrix instruction and a reader of its result: see sweep_rows)
+        if (kMap == 1) asm volatile("s_nop 4" : "+v"(o));
+        if (kMap == 1 && ragged) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (gy0 + y >= H || gx0 + i >= W) o[i] = 0.f;
+        }
+        if constexpr (kMap == 2) {
+            Frag hi, lo;
+            if constexpr (Tr::kHiLo) frag_split<T>(o, hi, lo);
+            else hi = frag_from_f32<T>(o);
+            const int from = 4 * (4 * (x16 & 3) + (x16 >> 2)) + q;
+            const u32x2 h2 = __builtin_bit_cast(u32x2, hi);
+            s1v[it & 1][0] = __builtin_bit_cast(Frag, u32x2{(unsigned)__shfl((int)h2[0], from), (unsigned)__shfl((int)h2[1], from)});
+            if constexpr (Tr::kHiLo) {
+                const u32x2 l2 = __builtin_bit_cast(u32x2, lo);
+                s1v[it & 1][1] = __builtin_bit_cast(Frag, u32x2{(unsigned)__shfl((int)l2[0], from), (unsigned)__shfl((int)l2[1], from)});
+            }
+        } else {
+            char* tb = trans + (it & 1) * kTransBytes;
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(float*)(tb + (4 * sub + i) * kTransTokStride + chn * 4) = o[i];
+            wave_lds_fence();
+        }
+    };
+    auto both = [](Frag a, Frag b) {
+        Vec v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v[r] = a[r];
+            v[4 + r] = b[r];
+        }
+        return v;
+    };
+    auto stage2 = [&](int it, f32x4 tq) {
+        const int ib = it / NR, y = it % NR - (KS - 1);
+        if constexpr (kMap == 2) {
+#pragma unroll
+            for (int ok = 0; ok < NB; ++ok) {
+                kv_agg[ok][ib] = Tr::mma16(kv_agg[ok][ib], aggK[ok][y], s1v[it & 1][0]);
+                if constexpr (Tr::kHiLo) {
+                    kv_agg[ok][ib] = Tr::mma16(kv_agg[ok][ib], aggK[ok][y], s1v[it & 1][1]);
+                    kv_agg[ok][ib] = Tr::mma16(kv_agg[ok][ib], aggK_lo[ok][y], s1v[it & 1][0]);
+                }
+            }
+        } else {
+            Frag hi, lo;
+            if constexpr (kWide) frag_split<T>(tq, hi, lo);
+            else hi = frag_from_f32<T>(tq);
+            if (ib == 0) {
+                dw0[y] = hi;
+                if constexpr (kWide) dw0_lo[y] = lo;
+                return;
+            }
+            const Vec vh = both(dw0[y], hi);
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                s2v[it & 1][ob] = kMap == 1 ? Tr::mma_vec(z, vh, gpw[ob]) : Tr::mma_vec(z, gpw[ob], vh);
+                if constexpr (kWide) {
+                    const Vec vl = both(dw0_lo[y], lo);
+                    s2v[it & 1][ob] = kMap == 1 ? Tr::mma_vec(s2v[it & 1][ob], vl, gpw[ob]) : Tr::mma_vec(s2v[it & 1][ob], gpw[ob], vl);
+                }
+            }
+        }
+    };
+    auto stage3 = [&](int it) {
+        const int y = it % NR - (KS - 1);
+        if (it / NR == 0) return;
+        if constexpr (kMap == 1) {
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                const f32x4 kf = relu_bits_f32(s2v[it & 1][ob]);
+                ks_agg[ob] += (kf[0] + kf[1]) + (kf[2] + kf[3]);
+                if constexpr (Tr::kHiLo) frag_split<T>(kf, aggK[ob][y], aggK_lo[ob][y]);
+                else aggK[ob][y] = frag_from_f32<T>(kf);
+            }
+        } else if constexpr (kMap == 0) {
+            const int gy = gy0 + y - 1 + (q & 1), gx = gx_first + x16;
+            const unsigned off = gy < H && gx < W ? (unsigned)(gy * W + gx) * q_ms_tb + (q >> 1) * 16 : kOobOffset;
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                const u32x2 v = __builtin_bit_cast(u32x2, frag_from_f32<T>(s2v[it & 1][ob]));
+                if (y % 2 == 0) {
+                    q_held[ob] = v;
+                } else {
+                    const u32x2 s0 = __builtin_amdgcn_permlane16_swap(q_held[ob][0], v[0], false, false);
+                    const u32x2 s1 = __builtin_amdgcn_permlane16_swap(q_held[ob][1], v[1], false, false);
+                    buf_store16(rout, off + ob * 32, u32x4{s0[0], s1[0], s0[1], s1[1]});
+                }
+            }
+        }
+    };
+    Frag toep[KS][2], din[2][2];
+    auto fetch_row = [&](int i, Frag (&d)[2]) {
+        const char* src = rows + (i / NR * 16 + chn) * kChanBytes + i % NR * kPlanarRowBytes + sub * 8;
+        d[0] = load_frag<T>(src);
+        d[1] = load_frag<T>(src + 8);
+    };
+    auto fetch_toep = [&](int ib) {
+#pragma unroll
+        for (int u = 0; u < KS; ++u)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) toep[u][s] = load_frag<T>(toep_lds + (((kMap * NB + ib) * KS + u) * 2 + s) * 512 + lane * 8);
+    };
+    fetch_toep(0);
+    fetch_row(0, din[0]);
+    static_for<0, 2 * NR + 2>([&](auto it_c) {
+        constexpr int it = decltype(it_c)::value;
+        constexpr auto has_row = [](int i) { return i >= 0 && i < 2 * NR && i % NR >= KS - 1; };
+        if constexpr (it + 1 < 2 * NR) fetch_row(it + 1, din[(it + 1) & 1]);
+        f32x4 tq = z;
+        if constexpr (has_row(it - 1) && kMap != 2) tq = *(const f32x4*)(trans + ((it - 1) & 1) * kTransBytes + x16 * kTransTokStride + q * 16);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (it < 2 * NR) {
+            constexpr int r = it % NR;
+            if constexpr (it == NR) fetch_toep(1);
+            if constexpr (r == 0) {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) acc[i] = z;
+            }
+#pragma unroll
+            for (int u = 0; u < KS; ++u) {
+                const int y = r - u;
+                if (y < 0 || y >= R) continue;
+                acc[y % KS] = M4<T>::mma(toep[u][0], din[it & 1][0], acc[y % KS]);
+                acc[y % KS] = M4<T>::mma(toep[u][1], din[it & 1][1], acc[y % KS]);
+            }
+        }
+        if constexpr (has_row(it - 1)) stage2(it - 1, tq);
+        if constexpr (has_row(it - 2)) stage3(it - 2);
+        if constexpr (has_row(it)) {
+            constexpr int y = it % NR - (KS - 1);
+            const f32x4 o = acc[y % KS];
+            acc[y % KS] = z;
+            stage1(it, o);
+        }
+    });
+}
+
+constexpr int kMfma32Threads = 12 * 64;
+template <class T, int KS, bool kRaw>
+__global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(AggregateArgs a) {
+    typedef Traits<T> Tr;
+    typedef typename Tr::Frag Frag;
+    typedef typename Tr::Vec Vec;
+    typedef Mfma32Lds<KS> L;
+    constexpr int P = L::P, SZ = (int)sizeof(T), MTH = kAggMfmaTileH, MTW = kAggMfmaTileW;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    char* const toep_lds = lds + L::kWork;
+    char* const wv_lds = toep_lds + L::kToepBytes;
+    float* const red = (float*)lds;             // reused after the last tile
+
+    const unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
+    if (Lid >= (unsigned)a.B * a.heads * a.nchunks) return;
+    const int h = Lid % a.heads;
+    const int chunk = (Lid / a.heads) % a.nchunks;
+    const int b = Lid / (a.heads * a.nchunks);
+    const int Ct = a.heads * D32;
+    const long N = (long)a.H * a.W, img_tok0 = (long)b * N;
+    const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    const T* wgp = (const T*)a.w_gpw + (long)h * 3 * D32 * D32;
+    T* q_ms = (T*)a.q_ms;
+    const unsigned q_ms_tb = (unsigned)(a.S * Ct * SZ);
+
+    const int tiles_x = (a.W + MTW - 1) / MTW, n_tiles = tiles_x * ((a.H + MTH - 1) / MTH);
+    const int tile_begin = chunk * a.tiles_per_chunk;
+    const int tile_end = min(n_tiles, tile_begin + a.tiles_per_chunk);
+    const int n_my = tile_end > tile_begin ? tile_end - tile_begin : 0;
+    struct TileAt {
+        int ty0, tx0;
+    };
+    auto tile_after = [&](TileAt t) {
+        t.tx0 += MTW;
+        if (t.tx0 >= tiles_x * MTW) { t.tx0 = 0; t.ty0 += MTH; }
+        return t;
+    };
+    TileAt here = {tile_begin / tiles_x * MTH, tile_begin % tiles_x * MTW};
+    // this wave's state: a staging wave's raw, a sweeping wave's aggregated
+    f32x4 kv[NB][NB], ks4[NB];
+    float ks[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        ks4[i] = z;
+        ks[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) kv[i][j] = z;
+    }
+
+    if (wave < 4) {
+        // ---------------- staging: as in the head-size-16 kernel, a lane's 16-byte load being 8 of the 32 channels of one map
+        const char* base[3] = {(const char*)((const T*)a.k + (long)h * a.k_hs + img_tok0 * a.k_ts),
+                               (const char*)((const T*)a.v + (long)h * a.v_hs + img_tok0 * a.v_ts),
+                               (const char*)((const T*)a.q + (long)h * a.q_hs + img_tok0 * a.q_ts)};
+        const long ts[3] = {a.k_ts, a.v_ts, a.q_ts};
+        Vec sel[NB];
+        Frag ones;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) sel[i][r] = Tr::from_f32(q * 8 + r == 16 * i + x16 ? 1.0f : 0.0f);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ones[r] = Tr::from_f32(1.0f);
+        struct Batch {
+            u32x4 v[2][2], tail;
+        };
+        auto tail_jbase = [](int it) { return it == 2 ? 0 : 4; };
+        auto issue = [&](TileAt at, int m, int it, Batch& bt, bool live) {
+            const BufRsrc r = make_rsrc(base[m], ((N - 1) * ts[m] + D32) * (long)SZ);
+            const unsigned tb = (unsigned)(ts[m] * SZ);
+#pragma unroll
+            for (int rr = 0; rr < 2; ++rr) {
+                const int ly = wave + 4 * (it + rr), gy = at.ty0 - P + ly;
+                const bool row_ok = live && ly < L::LH && gy >= 0 && gy < a.H;
+#pragma unroll
+                for (int cg = 0; cg < 2; ++cg) {
+                    const int gx = at.tx0 - P + cg * 16 + x16;
+                    bt.v[rr][cg] = buf_load16(r, row_ok && gx >= 0 && gx < a.W ? (unsigned)(gy * a.W + gx) * tb + q * 16 : kOobOffset, 0);
+                }
+            }
+            if (it != 0) {
+                const int j = tail_jbase(it) + (x16 >> 2), ly = wave + 4 * j, lx = 32 + (x16 & 3);
+                const int gy = at.ty0 - P + ly, gx = at.tx0 - P + lx;
+                const bool ok = live && j <= 4 && ly < L::LH && lx < L::LW && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+                bt.tail = buf_load16(r, ok ? (unsigned)(gy * a.W + gx) * tb + q * 16 : kOobOffset, 0);
+            }
+        };
+        const BufRsrc rraw = make_rsrc(q_ms + img_tok0 * a.S * Ct + h * D32, ((N - 1) * a.S * Ct + D32) * (long)SZ);
+        auto consume = [&](TileAt at, auto mc, auto itc, const Batch& bt, char* planar, const char* planar_k) {
+            constexpr int m = decltype(mc)::value, it = decltype(itc)::value;
+            // What a group of 16 tokens (this lane: tokens 4q .. 4q + 3 of channels x16 and 16 + x16) adds to the raw state, in the V step;
+            // its K is where the lane put it a step ago.  own: which of the four tokens are the tile's.
+            auto raw = [&](const Frag (&v)[NB], const char* k, bool own0, bool own1, bool own2, bool own3) {
+                if constexpr (kRaw && m == 1) {
+                    Frag rk[NB];
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        rk[i] = frag_relu_bits<T>(load_frag<T>(k + i * 16 * L::kChanBytes));
+                        if (!own0) rk[i][0] = Tr::from_f32(0.f);
+                        if (!own1) rk[i][1] = Tr::from_f32(0.f);
+                        if (!own2) rk[i][2] = Tr::from_f32(0.f);
+                        if (!own3) rk[i][3] = Tr::from_f32(0.f);
+                    }
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        ks4[i] = Tr::mma16(ks4[i], rk[i], ones);
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) kv[i][j] = Tr::mma16(kv[i][j], rk[i], v[j]);
+                    }
+                }
+            };
+#pragma unroll
+            for (int rr = 0; rr < 2; ++rr) {
+                const int ly = wave + 4 * (it + rr), gy = at.ty0 - P + ly;
+                if (ly >= L::LH) break;
+                const bool own_row = ly >= P && ly < P + MTH;
+                f32x4 d[2][NB];
+#pragma unroll
+                for (int cg = 0; cg < 2; ++cg)
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) d[cg][i] = Tr::mma_vec(z, __builtin_bit_cast(Vec, bt.v[rr][cg]), sel[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                const int at_lds = x16 * L::kChanBytes + ly * kPlanarRowBytes + q * 8;
+#pragma unroll
+                for (int cg = 0; cg < 2; ++cg) {
+                    Frag f[NB];
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        f[i] = frag_from_f32<T>(d[cg][i]);
+                        store_frag<T>(planar + at_lds + i * 16 * L::kChanBytes + cg * 32, f[i]);
+                    }
+                    const int c0 = cg * 16 + 4 * q;     // (the first P columns are halo; the last are the tail's)
+                    if (own_row) raw(f, planar_k + at_lds + cg * 32, c0 >= P, c0 + 1 >= P, c0 + 2 >= P, c0 + 3 >= P);
+                    if constexpr (kRaw && m == 2) {
+                        const int gx = at.tx0 - P + cg * 16 + x16;
+                        buf_store16(rraw, own_row && cg * 16 + x16 >= P && gy < a.H && gx < a.W ? (unsigned)(gy * a.W + gx) * q_ms_tb + q * 16 : kOobOffset,
+                                    bt.v[rr][cg]);
+                    }
+                }
+            }
+            if constexpr (it != 0) {
+                const int j = tail_jbase(it) + q, ly = wave + 4 * j;
+                const bool row_ok = j <= 4 && ly < L::LH, own_row = row_ok && ly >= P && ly < P + MTH;
+                f32x4 d[NB];
+                Frag f[NB];
+#pragma unroll
+                for (int i = 0; i < NB; ++i) d[i] = Tr::mma_vec(z, __builtin_bit_cast(Vec, bt.tail), sel[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                const int at_lds = x16 * L::kChanBytes + (row_ok ? ly : 0) * kPlanarRowBytes + 64;
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    f[i] = frag_from_f32<T>(d[i]);
+                    if (row_ok) store_frag<T>(planar + at_lds + i * 16 * L::kChanBytes, f[i]);
+                }
+                raw(f, planar_k + at_lds, own_row && 32 < P + MTW, own_row && 33 < P + MTW, own_row && 34 < P + MTW, own_row && 35 < P + MTW);
+                if constexpr (kRaw && m == 2) {
+                    const int js = tail_jbase(it) + (x16 >> 2), lys = wave + 4 * js, lxs = 32 + (x16 & 3);
+                    const int gys = at.ty0 - P + lys, gxs = at.tx0 - P + lxs;
+                    buf_store16(rraw, js <= 4 && lys >= P && lys < P + MTH && lxs < P + MTW && gys < a.H && gxs < a.W
+                                          ? (unsigned)(gys * a.W + gxs) * q_ms_tb + q * 16 : kOobOffset, bt.tail);
+                }
+            }
+        };
+        Batch ring[3];
+        static_for<0, 3>([&](auto i) {
+            issue(here, 0, 2 * decltype(i)::value, ring[decltype(i)::value], n_my > 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        int buf = 0;
+        for (int i = 0; i < n_my; ++i) {
+            const TileAt next = tile_after(here);
+            const bool more = i + 1 < n_my;
+            static_for<0, 3>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                char* planar = lds + buf * L::kMapBytes;
+                static_for<0, 3>([&](auto i3) {
+                    constexpr int n = decltype(i3)::value;
+                    consume(here, mc, std::integral_constant<int, 2 * n>{}, ring[n], planar, lds + (buf ^ 1) * L::kMapBytes);
+                    issue(m < 2 ? here : next, (m + 1) % 3, 2 * n, ring[n], m < 2 || more);
+                });
+                buf ^= 1;
+                __syncthreads();
+            });
+            here = next;
+        }
+        __syncthreads();
+    } else {
+        // ---------------- sweeping; before the first map is staged, waves 0 .. 5 make the Toeplitz operands of a block each (map, block of
+        // 16 channels) and wave 6 brings V's grouped 1x1
+        const int sw = wave - 4;
+        if (sw < 6) {
+            Frag toep[KS][2];
+            make_toeplitz<T, KS>(load_taps<T, KS>((const T*)a.w_dw + (long)h * 3 * D32 * KS * KS, sw * 16 + sweep_channel(lane)), lane & 3, toep);
+#pragma unroll
+            for (int u = 0; u < KS; ++u)
+#pragma unroll
+                for (int s = 0; s < 2; ++s) store_frag<T>(toep_lds + ((sw * KS + u) * 2 + s) * 512 + lane * 8, toep[u][s]);
+        } else if (sw == 6) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) ((u32x4*)wv_lds)[i * 64 + lane] = ((const u32x4*)(wgp + 2 * D32 * D32))[i * 64 + lane];
+        }
+        // grouped 1x1 of Q and K, contraction slots {4q .. 4q + 3} and {16 + 4q ..}: lane (o, q) of output block ob
+        Vec gpw[2][NB];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                const T* row = wgp + (t * D32 + ob * 16 + x16) * D32 + q * 4;
+                const u32x2 lo = *(const u32x2*)row, hi = *(const u32x2*)(row + 16);
+                gpw[t][ob] = __builtin_bit_cast(Vec, u32x4{lo[0], lo[1], hi[0], hi[1]});
+            }
+        const int strip = sw & 1, part = sw >> 1;
+        const BufRsrc rout = make_rsrc(q_ms + img_tok0 * a.S * Ct + (long)a.branch * Ct + h * D32, ((N - 1) * a.S * Ct + D32) * (long)SZ);
+        char* const trans = lds + 2 * L::kMapBytes + sw * 2 * kTransBytes;
+        Frag aggK[NB][4], aggK_lo[NB][4];
+        int buf = 0;
+        __syncthreads();
+        for (int i = 0; i < n_my; ++i) {
+            const int gy0 = here.ty0 + 4 * part, gx = here.tx0 + 16 * strip;
+            const bool ragged = here.ty0 + MTH > a.H || here.tx0 + MTW > a.W;
+            auto sweep = [&](auto mapc, const Vec(&g)[NB]) {
+                sweep32<T, KS, decltype(mapc)::value, L::kChanBytes>(lds + buf * L::kMapBytes + 4 * part * kPlanarRowBytes + 16 * strip * SZ, trans,
+                                                                     toep_lds, g, a.H, a.W, gy0, gx, ragged, rout, q_ms_tb, aggK, aggK_lo, kv, ks);
+                buf ^= 1;
+                __syncthreads();
+            };
+            sweep(std::integral_constant<int, 1>{}, gpw[1]);
+            sweep(std::integral_constant<int, 2>{}, gpw[1]);
+            sweep(std::integral_constant<int, 0>{}, gpw[0]);
+            here = tile_after(here);
+        }
+    }
+
+    // ---------------- workgroup partial state: per wave [K block][V block][lane] accumulator quads, then [32] Ksum
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        ks[i] += __shfl_xor(ks[i], 16);
+        ks[i] += __shfl_xor(ks[i], 32);
+    }
+    __syncthreads();   // tile memory is dead from here on
+    float* const msum = red + 12 * L::kWaveFloats;              // [32][32] summed pre-1x1 state of the aggregated branch
+    {
+        float* mine = red + wave * L::kWaveFloats;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) *(f32x4*)(mine + (i * NB + j) * 256 + lane * 4) = kv[i][j];
+            if (wave < 4) {
+                if (x16 == 0) *(f32x4*)(mine + NB * NB * 256 + i * 16 + q * 4) = ks4[i];
+            } else if (q == 0) {
+                mine[NB * NB * 256 + i * 16 + x16] = ks[i];
+            }
+        }
+    }
+    __syncthreads();
+    auto sum = [&](int src, bool of_raw) {      // fixed order
+        float s = 0.f;
+        if (of_raw) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s += red[w * L::kWaveFloats + src];
+        } else {
+#pragma unroll
+            for (int w = 4; w < 12; ++w) s += red[w * L::kWaveFloats + src];
+        }
+        return s;
+    };
+    auto put = [&](int branch, int e, int f, float s) {
+        a.partials[((((long)b * a.S + branch) * a.heads + h) * a.nchunks + chunk) * kState32 + e * (D32 + 1) + f] = s;
+    };
+    for (int j = threadIdx.x; j < D32 * D32; j += kMfma32Threads) {
+        const int e = j >> 5, c = j & 31, src = ((e >> 4) * NB + (c >> 4)) * 256 + (((e & 15) >> 2) * 16 + (c & 15)) * 4 + (e & 3);
+        msum[j] = sum(src, false);
+        if constexpr (kRaw) put(0, e, c, sum(src, true));
+    }
+    if (threadIdx.x < D32) {
+        put(a.branch, threadIdx.x, D32, sum(NB * NB * 256 + threadIdx.x, false));
+        if constexpr (kRaw) put(0, threadIdx.x, D32, sum(NB * NB * 256 + threadIdx.x, true));
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < D32 * D32; j += kMfma32Threads) {
+        // the grouped 1x1 of V, applied to the summed state: KV[e][f] = sum_c M[e][c] w_gpw[f][c]
+        const int e = j >> 5, f = j & 31;
+        float s = 0.f;
+#pragma unroll
+        for (int c8 = 0; c8 < D32 / 8; ++c8) {
+            const Vec w = *(const Vec*)(wv_lds + (f * D32 + c8 * 8) * SZ);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) s = fmaf(msum[e * D32 + c8 * 8 + c], Tr::to_f32(w[c]), s);
+        }
+        put(a.branch, e, f, s);
+    }
+}
+
+template <class T, int KS, bool kRaw>
+hipError_t run_mfma32(const AggregateArgs& a, hipStream_t stream) {
+    constexpr int kLds = Mfma32Lds<KS>::kBytes;
+    const hipError_t e = allow_dynamic_lds<aggregate32_mfma_kernel<T, KS, kRaw>>(kLds);
+    if (e != hipSuccess) return e;
+    const long nblocks = ((long)a.B * a.heads * a.nchunks + 7) / 8 * 8;         // whole rounds over the XCDs
+    if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((aggregate32_mfma_kernel<T, KS, kRaw>), dim3((unsigned)nblocks), dim3(kMfma32Threads), kLds, stream, a);
+    return hipGetLastError();
+}
+
 template <class T, int KS, bool kRaw>
 hipError_t run_ks32_raw(const AggregateArgs& a, unsigned nblocks, hipStream_t stream) {
     constexpr int kLds = Agg32Lds<T, KS>::kBytes;
@@ -384,6 +881,14 @@ template <class T>
 hipError_t run32(const AggregateArgs& a, hipStream_t stream) {
     const long nblocks = (long)a.B * a.heads * a.nchunks;
     if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
+    if (aggregate32_on_matrix_cores(a.ks, (long)a.H * a.W, std::max(std::max(a.q_ts, a.k_ts), std::max(a.v_ts, (long)a.S * a.heads * D32)))) {
+        if ((a.do_raw != 0) != (a.copy_raw_q != 0)) return hipErrorInvalidValue;
+        AggregateArgs g = a;        // tiles of 16 rows
+        const long tiles = (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW);
+        g.tiles_per_chunk = (int)((tiles + a.nchunks - 1) / a.nchunks);
+        if (a.ks == 3) return a.do_raw ? run_mfma32<T, 3, true>(g, stream) : run_mfma32<T, 3, false>(g, stream);
+        return a.do_raw ? run_mfma32<T, 5, true>(g, stream) : run_mfma32<T, 5, false>(g, stream);
+    }
     if (a.ks == 3) return run_ks32<T, 3>(a, (unsigned)nblocks, stream);
     if (a.ks == 5) return run_ks32<T, 5>(a, (unsigned)nblocks, stream);
     if (a.ks == 7) return run_ks32<T, 7>(a, (unsigned)nblocks, stream);

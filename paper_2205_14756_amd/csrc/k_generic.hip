@@ -17,6 +17,7 @@
 // Head size 8 needs no kernels of its own: two heads side by side are one head of 16 whose grouped 1x1 is
 // block-diagonal and whose state is used block by block (pair_head8_weights_kernel arranges the weights
 // that way; the finalize step of the head-size-16 path masks the state operands).
+#include <algorithm>
 #include <type_traits>
 
 #include "msla_device.h"
@@ -521,9 +522,21 @@ hipError_t run_generic(const GenericArgs& a, hipStream_t stream) {
             g.q_ms = a.q_ms;
             g.partials = a.partials;
             g.B = a.B; g.H = a.H; g.W = a.W; g.heads = a.heads; g.S = S;
-            g.nchunks = a.nchunks;
+            // one workgroup a compute unit where every scale has the matrix-core kernel (never more partial states than the plan has room for)
+            GenericArgs c = a;
+            const long widest = (long)std::max(3, S) * a.heads * D;
+            bool all = true;
+            for (int i = 0; i < a.n_scales; ++i) all = all && aggregate32_on_matrix_cores(a.scales[i], (long)a.H * a.W, widest);
+            if (all) {
+                const long tiles16 = (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW);
+                const long states = (long)a.B * a.heads;
+                const long want = std::min(std::min((long)a.nchunks, tiles16), std::max(1L, (compute_units() + states - 1) / states));
+                const long tpc = (tiles16 + want - 1) / want;
+                c.nchunks = (int)((tiles16 + tpc - 1) / tpc);
+            }
+            g.nchunks = c.nchunks;
             const long tiles = (long)((a.H + kAggTileH - 1) / kAggTileH) * ((a.W + kAggTileW - 1) / kAggTileW);
-            g.tiles_per_chunk = (int)((tiles + a.nchunks - 1) / a.nchunks);
+            g.tiles_per_chunk = (int)((tiles + c.nchunks - 1) / c.nchunks);
             for (int i = 0; i < a.n_scales; ++i) {
                 const int ks = a.scales[i];
                 g.w_dw = (const T*)a.w_dw + dw_off;
@@ -536,7 +549,7 @@ hipError_t run_generic(const GenericArgs& a, hipStream_t stream) {
                 const hipError_t e = launch_aggregate32(sizeof(T) == 2 && std::is_same<T, _Float16>::value ? 1 : 2, g, stream);
                 if (e != hipSuccess) return e;
             }
-            return finish_generic<T, D>(a, N, stream);
+            return finish_generic<T, D>(c, N, stream);
         }
     }
     for (int s = 0; s < S; ++s) {

@@ -65,6 +65,11 @@ hipError_t launch_aggregate_mfma_pair(int dt, const AggregateArgs& a0, const Agg
 // The same contract for heads of 32 channels, fp16 / bf16 (k_aggregate32.hip): maps with 32 channels per head and
 // kind, w_gpw rows of 32, partial states [.., nchunks, 32*33], 8 x 32-token tiles.  hipErrorNotSupported for fp32.
 hipError_t launch_aggregate32(int dt, const AggregateArgs& a, hipStream_t stream);
+// Whether it takes the matrix-core kernel: tiles of 16 x 32 tokens, one workgroup of twelve waves a compute unit (`widest`: elements from
+// token to token of the widest map; 32-bit byte offsets)
+inline bool aggregate32_on_matrix_cores(int ks, long tokens, long widest) {
+    return (ks == 3 || ks == 5) && tokens * widest * 2 <= 0x7fffffffL;
+}
 
 // Raw-branch-only variant for n_scales == 0 (no convolution): state of branch 0, optional Q copy.
 hipError_t launch_raw_state(int dt, const AggregateArgs& a, hipStream_t stream);

@@ -248,3 +248,15 @@ def test_small_map_with_its_own_projection_equals_the_stages(dtype, B, C, H, W, 
 def test_fp32_small_maps(B, C, H, W, heads, scales):
     print(f"routes: fp32 small {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
     base.check_module(wk.random_module(43 + W + heads, "f32", B, C, H, W, heads, 16, scales), "f32", heads, 16, scales)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# heads of 32, depthwise on the matrix cores: one token, tiles one short of and one past 16 x 32, workgroups that walk two tiles with a ragged
+# end and an image count that leaves the last one empty, two scales in either order (the second without the raw branch); with a 7x7
+# scale beside it (chunks counted for the other kernel, some of them without a tile)
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 32, 1, 1, 1, (5,)), (2, 64, 15, 31, 2, (3,)), (1, 96, 17, 33, 3, (5,)),
+                                                  (16, 64, 47, 95, 2, (5, 3)), (3, 160, 33, 64, 5, (3, 5)), (1, 32, 70, 100, 1, (3, 7)),
+                                                  (2, 64, 16, 32, 2, (7, 5))])
+def test_head_size_32_on_the_matrix_cores(dtype, B, C, H, W, heads, scales):
+    print(f"routes: head size 32 {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
+    base.check_module(wk.random_module(59 + C + H, dtype, B, C, H, W, heads, 32, scales), dtype, heads, 32, scales, stages=False)
