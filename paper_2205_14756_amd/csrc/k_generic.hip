@@ -530,7 +530,7 @@ hipError_t run_generic(const GenericArgs& a, hipStream_t stream) {
             if (all) {
                 const long tiles16 = (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW);
                 const long states = (long)a.B * a.heads;
-                const long want = std::min(std::min((long)a.nchunks, tiles16), std::max(1L, (compute_units() + states - 1) / states));
+                const long want = chunks_in_rounds(states, tiles16, std::min((long)a.nchunks, tiles16), compute_units());
                 const long tpc = (tiles16 + want - 1) / want;
                 c.nchunks = (int)((tiles16 + tpc - 1) / tpc);
             }

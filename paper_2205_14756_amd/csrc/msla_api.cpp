@@ -103,6 +103,7 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     if (want < 1) want = 1;
     if (want > tiles) want = tiles;
     if (n_scales > 0 && dt == MSLA_F32) want = fp32_chunks(s, tiles, want);
+    else if (n_scales > 0) want = msla::chunks_in_rounds((long)B * heads, tiles, want, target_blocks);
     const long tpc = (tiles + want - 1) / want;
     s->tiles_per_chunk = (int)tpc;
     s->nchunks = (int)((tiles + tpc - 1) / tpc);

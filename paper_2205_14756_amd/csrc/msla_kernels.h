@@ -65,6 +65,25 @@ hipError_t launch_aggregate_mfma_pair(int dt, const AggregateArgs& a0, const Agg
 // The same contract for heads of 32 channels, fp16 / bf16 (k_aggregate32.hip): maps with 32 channels per head and
 // kind, w_gpw rows of 32, partial states [.., nchunks, 32*33], 8 x 32-token tiles.  hipErrorNotSupported for fp32.
 hipError_t launch_aggregate32(int dt, const AggregateArgs& a, hipStream_t stream);
+// How many workgroups share a state's `tiles` in the matrix-core aggregation kernels, at most `most`, if `places` of them run at once: the
+// number whose rounds over the places cost least, a round being the workgroup's tiles and about one more for its start and end.  Of
+// equals the smallest.  (3 x 70 x 70 tokens, 6 heads of 32, 3x3 + 5x5, bf16, 270 workgroups of one tile are two rounds, 144 of two are one:
+// 94.6 and 84.2 us a module; 5 x 90 x 90, 11 heads of 16, 5x5, fp16, 275 and 220 workgroups: 76.4 and 63.4.)
+inline long chunks_in_rounds(long states, long tiles, long most, long places) {
+    long best = most, best_cost = 0;
+    for (int r = 1; r <= 5; ++r) {
+        const long want = r < 5 ? places * r / states : most;
+        if (want < 1 || want > most) continue;
+        const long tpc = (tiles + want - 1) / want, n = (tiles + tpc - 1) / tpc;
+        const long cost = (n * states + places - 1) / places * (tpc + 1);
+        if (best_cost == 0 || cost < best_cost) {
+            best = want;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 // Whether it takes the matrix-core kernel: tiles of 16 x 32 tokens, one workgroup of twelve waves a compute unit (`widest`: elements from
 // token to token of the widest map; 32-bit byte offsets)
 inline bool aggregate32_on_matrix_cores(int ks, long tokens, long widest) {

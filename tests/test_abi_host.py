@@ -192,3 +192,24 @@ def _fp32_chunks(lib, B, H, W, heads, scales):
 ])
 def test_fp32_workgroups_fill_whole_rounds(lib, B, H, W, heads, scales, chunks):
     assert chunks in _fp32_chunks(lib, B, H, W, heads, scales)
+
+
+def _f16_chunks(lib, B, H, W, heads, scales):
+    """The same for the 16-bit matrix-core aggregation."""
+    up = lambda v: (v + 255) // 256 * 256
+    T, Ct, states = B * H * W, 16 * heads, B * heads * (1 + len(scales))
+    fixed = up(T * (1 + len(scales)) * Ct * 2) + up((T + 31) // 32 * 32 * 2 * Ct * 2) + up(states * 1088) + up(states * 2048) + up(states * 4)
+    st, n = _ws(lib, B, Ct, H, W, heads, 16, scales, F16)
+    assert st == OK
+    return [c for c in range(1, 1025) if fixed + up(states * c * 1088) == n]
+
+
+@pytest.mark.parametrize("B,H,W,heads,scales,chunks", [
+    (8, 64, 128, 16, (5,), 2),              # 256 workgroups, 8 tiles each
+    (5, 90, 90, 11, (5,), 4),               # 220 in one round with 5 tiles, not 275 in two with 4
+    (3, 64, 100, 17, (3, 5), 2),            # two scales share the chip: 102 of each in one round, not 153 in two
+    (9, 100, 100, 6, (3,), 4),              # 216 in one round
+    (2, 64, 128, 400, (5,), 1),             # more states than places
+])
+def test_matrix_core_workgroups_fill_whole_rounds(lib, B, H, W, heads, scales, chunks):
+    assert chunks in _f16_chunks(lib, B, H, W, heads, scales)
