@@ -275,25 +275,28 @@ __global__ __launch_bounds__(kGenThreads) void generic_apply_kernel(const T* __r
 // projection's token operand, and never to memory.  A workgroup of eight waves owns 256 output channels, 32 a wave, whose
 // weights stay in registers (KCH chunks of 32 slots, one chunk a head-branch); it walks over tiles of 32 tokens of one
 // image, and wave w makes the rows of head-branches w and w + 8.  Two tiles, one barrier a tile, Q requested a tile ahead.
-// What bounds it is the matrix pipe: 4 x 512 cycles of fp32 products for the rows and 1024 for the projection a wave and
-// tile.  Against rows to memory and a projection of its own, whole modules: 8 x 8192 tokens, 16 head-branches, fp16 200.9 ->
+// With fp32 states the matrix pipe bounds it: 4 x 512 cycles of fp32 products for the rows and 1024 for the projection a wave and
+// tile.  With the states in three 16-bit parts (kParts) the rows take 4 x 144 cycles: this kernel 50 -> 40 us at 8 x 8192 tokens, 16
+// head-branches, the errors of the module the same to three digits (fp16 3.85e-4, bf16 2.92e-3).  Against rows to memory and a projection of its own, whole modules: 8 x 8192 tokens, 16 head-branches, fp16 200.9 ->
 // 183.5 us; 3200, 12, bf16 48.0 -> 46.0; 1024, 4, fp16 34.9 -> 30.5.
 // LDS: an attention row is KCH*64 bytes, the 16-byte chunk index XOR-ed with token % 16, so that the sixteen tokens of an
 // operand read or a row store meet sixteen different chunks of the banks; the weights are dealt out through the same
 // memory, 128 bytes of every row at a time.
-template <class T, int KCH>
+template <class T, int KCH, bool kParts>
 struct Apply32Project {
     static constexpr int kThreads = 512, TB = 32, kChan = 256, kHbw = KCH / 8;
     static constexpr int kRow = KCH * 64, kTile = TB * kRow, kStage = kChan * 128;
-    static constexpr int kLds = 2 * kTile > kStage ? 2 * kTile : kStage;
+    static constexpr int kWork = 2 * kTile > kStage ? 2 * kTile : kStage;
+    static constexpr int kTail = 2 * (2 * 1024 + 64) + 16;  // a head-branch's second and third parts: two operands of the state each, the quarters of Ksum; eps
+    static constexpr int kLds = kWork + (kParts ? KCH * kTail : 0);
     static constexpr int kSlabs = KCH / 2;
 };
-template <class T, int KCH>
+template <class T, int KCH, bool kParts>
 __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __restrict__ q_ms, const float* __restrict__ kv32,
                                                                  const T* __restrict__ w_proj, T* __restrict__ out, int N,
                                                                  int n_hb, int c_out, int n_cg, int tiles_per_image,
                                                                  long n_tt, long tiles_per_block, float eps) {
-    typedef Apply32Project<T, KCH> S;
+    typedef Apply32Project<T, KCH, kParts> S;
     typedef Traits<T> Tr;
     typedef typename Tr::Vec Vec;
     typedef Traits<float> F32;
@@ -367,54 +370,158 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
         *(u32x4*)(lds + row * S::kRow + ((c ^ (row & 15)) * 16)) = u32x4{0u, 0u, 0u, 0u};
     }
 
-    f32x4 st[S::kHbw][2][2];
-    float ksum[S::kHbw][8];
+    // kParts: a head-branch's state and Ksum are operands of the storage type, each value in three parts (its first, second and third 8
+    // or 11 significant bits: together all 24 that it has), times a power of two that puts the largest at 512 to 1024 (numerator and
+    // denominator scale together).  The first part stays in registers, the others wait in LDS, where only this wave looks for them.
+    // Else they are fp32 operands.
+    typedef typename std::conditional<kParts, Vec, f32x4[2]>::type State;
+    State st[S::kHbw][2];           // kParts: [output half]; else [contraction half][output half]
+    typename std::conditional<kParts, Vec, float[8]>::type ksum[S::kHbw];
     const int fo = 8 * (x16 >> 2) + (x16 & 3);
     int img = -1;
+    auto tail = [&](int i) { return lds + S::kWork + (wave + 8 * i) * S::kTail; };
     auto load_states = [&](int b) {
         img = b;
+        if constexpr (kParts) {
 #pragma unroll
-        for (int i = 0; i < S::kHbw; ++i) {
-            const int m = wave + 8 * i;
-            const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+            for (int i = 0; i < S::kHbw; ++i) {
+                const int m = wave + 8 * i;
+                const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+                float v[3][8], mx = 0.f;
 #pragma unroll
-            for (int jc = 0; jc < 2; ++jc)
+                for (int e = 0; e < 8; ++e) {
+                    v[0][e] = s[(8 * q + e) * 33 + fo];
+                    v[1][e] = s[(8 * q + e) * 33 + fo + 4];
+                    v[2][e] = s[(8 * q + e) * 33 + 32];
+                }
 #pragma unroll
-                for (int jo = 0; jo < 2; ++jo)
+                for (int j = 0; j < 3; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) st[i][jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
+                    for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[j][e]) < INFINITY ? fabsf(v[j][e]) : 0.f);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) ksum[i][e] = s[(8 * q + e) * 33 + 32];
+                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+                float scale = 1.0f;
+                if (mx > 0.f) {
+                    int ex;
+                    frexpf(mx, &ex);
+                    scale = ldexpf(1.0f, ex < -100 ? 110 : 10 - ex);
+                }
+                // (an eps so small that the scale takes it below the normal range must not become 0: 0 / eps is what a token without
+                // anything above zero gives)
+                const float scaled_eps = eps > 0.f ? fmaxf(eps * scale, 1.1754944e-38f) : 0.f;
+                if (lane == 0) *(float*)(tail(i) + S::kTail - 16) = scaled_eps;
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    Vec part[3];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        float x = v[j][e] * scale;
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            part[p][e] = Tr::from_f32(x);
+                            x = fabsf(x) < INFINITY ? x - Tr::to_f32(part[p][e]) : 0.f;
+                        }
+                    }
+                    if (j < 2) st[i][j] = part[0];
+                    else ksum[i] = part[0];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        if (j < 2) *(Vec*)(tail(i) + p * 2048 + j * 1024 + lane * 16) = part[1 + p];
+                        else if (x16 == 0) *(Vec*)(tail(i) + 4096 + p * 64 + q * 16) = part[1 + p];
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::kHbw; ++i) {
+                const int m = wave + 8 * i;
+                const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+#pragma unroll
+                for (int jc = 0; jc < 2; ++jc)
+#pragma unroll
+                    for (int jo = 0; jo < 2; ++jo)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) st[i][jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ksum[i][e] = s[(8 * q + e) * 33 + 32];
+            }
         }
     };
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     auto make_rows = [&](int to) {
+        if constexpr (kParts) {
 #pragma unroll
-        for (int i = 0; i < S::kHbw; ++i) {
-            const int m = wave + 8 * i;
-            if (m < n_hb) {
+            for (int i = 0; i < S::kHbw; ++i) {
+                const int m = wave + 8 * i;
+                if (m < n_hb) {
+                    Vec f[2];
+                    f32x4 num[2][2], den[2];
 #pragma unroll
-                for (int jt = 0; jt < 2; ++jt) {
-                    const Vec f = __builtin_bit_cast(Vec, qv[i][jt]);
-                    float rq[8], den = 0.f;
+                    for (int jt = 0; jt < 2; ++jt) {
+                        f[jt] = __builtin_bit_cast(Vec, qv[i][jt]);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        rq[e] = fmaxf(Tr::to_f32(f[e]), 0.f);
-                        den = fmaf(rq[e], ksum[i][e], den);
+                        for (int e = 0; e < 8; ++e) f[jt][e] = Tr::from_f32(fmaxf(Tr::to_f32(f[jt][e]), 0.f));
+                        num[jt][0] = num[jt][1] = den[jt] = z;
                     }
-                    den += __shfl_xor(den, 16);
-                    den += __shfl_xor(den, 32);
-                    const f32x4 lo = {rq[0], rq[1], rq[2], rq[3]}, hi = {rq[4], rq[5], rq[6], rq[7]};
-                    const f32x4 n0 = F32::mma16(F32::mma16(z, st[i][0][0], lo), st[i][1][0], hi);
-                    const f32x4 n1 = F32::mma16(F32::mma16(z, st[i][0][1], lo), st[i][1][1], hi);
-                    const float inv = 1.0f / (den + eps);
-                    Vec o;
+                    const float scaled_eps = *(const float*)(tail(i) + S::kTail - 16);
+                    // small parts first; every row of the denominator's product is the same
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        o[r] = Tr::from_f32(n0[r] * inv);
-                        o[4 + r] = Tr::from_f32(n1[r] * inv);
+                    for (int p = 2; p >= 0; --p) {
+                        const char* at = tail(i) + (p - 1) * 2048 + lane * 16;
+                        const Vec s0 = p > 0 ? *(const Vec*)at : st[i][0], s1 = p > 0 ? *(const Vec*)(at + 1024) : st[i][1];
+                        const Vec sk = p > 0 ? *(const Vec*)(tail(i) + 4096 + (p - 1) * 64 + q * 16) : ksum[i];
+#pragma unroll
+                        for (int jt = 0; jt < 2; ++jt) {
+                            num[jt][0] = Tr::mma_vec(num[jt][0], s0, f[jt]);
+                            num[jt][1] = Tr::mma_vec(num[jt][1], s1, f[jt]);
+                            den[jt] = Tr::mma_vec(den[jt], sk, f[jt]);
+                        }
                     }
-                    *(u32x4*)(lds + to + (jt * 16 + x16) * S::kRow + (((m * 4 + q) ^ x16) * 16)) = __builtin_bit_cast(u32x4, o);
+#pragma unroll
+                    for (int jt = 0; jt < 2; ++jt) {
+                        const f32x4 n0 = num[jt][0], n1 = num[jt][1];
+                        const float inv = 1.0f / (den[jt][0] + scaled_eps);
+                        Vec o;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            o[r] = Tr::from_f32(n0[r] * inv);
+                            o[4 + r] = Tr::from_f32(n1[r] * inv);
+                        }
+                        *(u32x4*)(lds + to + (jt * 16 + x16) * S::kRow + (((m * 4 + q) ^ x16) * 16)) = __builtin_bit_cast(u32x4, o);
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::kHbw; ++i) {
+                const int m = wave + 8 * i;
+                if (m < n_hb) {
+#pragma unroll
+                    for (int jt = 0; jt < 2; ++jt) {
+                        const Vec f = __builtin_bit_cast(Vec, qv[i][jt]);
+                        float rq[8], den = 0.f;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            rq[e] = fmaxf(Tr::to_f32(f[e]), 0.f);
+                            den = fmaf(rq[e], ksum[i][e], den);
+                        }
+                        den += __shfl_xor(den, 16);
+                        den += __shfl_xor(den, 32);
+                        const f32x4 lo = {rq[0], rq[1], rq[2], rq[3]}, hi = {rq[4], rq[5], rq[6], rq[7]};
+                        const f32x4 n0 = F32::mma16(F32::mma16(z, st[i][0][0], lo), st[i][1][0], hi);
+                        const f32x4 n1 = F32::mma16(F32::mma16(z, st[i][0][1], lo), st[i][1][1], hi);
+                        const float inv = 1.0f / (den + eps);
+                        Vec o;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            o[r] = Tr::from_f32(n0[r] * inv);
+                            o[4 + r] = Tr::from_f32(n1[r] * inv);
+                        }
+                        *(u32x4*)(lds + to + (jt * 16 + x16) * S::kRow + (((m * 4 + q) ^ x16) * 16)) = __builtin_bit_cast(u32x4, o);
+                    }
                 }
             }
         }
@@ -456,21 +563,32 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
     }
 }
 
+template <class T, int KCH, bool kParts>
+hipError_t run_apply32_project_as(const GenericArgs& a, int N, int n_cg, int tpi, long n_tt, long per, hipStream_t stream) {
+    typedef Apply32Project<T, KCH, kParts> S;
+    static_assert(S::kLds <= 160 * 1024, "LDS layout");
+    const long nblocks = (n_tt + per - 1) / per * n_cg;
+    const hipError_t e = allow_dynamic_lds<apply32_project_kernel<T, KCH, kParts>>(S::kLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((apply32_project_kernel<T, KCH, kParts>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds, stream,
+                       (const T*)a.q_ms, a.kv32, (const T*)a.w_proj, (T*)a.out, N, (1 + a.n_scales) * a.heads, a.c_out, n_cg, tpi, n_tt,
+                       per, a.eps);
+    return hipGetLastError();
+}
 template <class T, int KCH>
 hipError_t run_apply32_project(const GenericArgs& a, int N, hipStream_t stream) {
-    typedef Apply32Project<T, KCH> S;
-    const int n_hb = (1 + a.n_scales) * a.heads, n_cg = (a.c_out + S::kChan - 1) / S::kChan;
+    typedef Apply32Project<T, KCH, false> S;
+    const int n_cg = (a.c_out + S::kChan - 1) / S::kChan;
     const int tpi = (N + S::TB - 1) / S::TB;
     const long n_tt = (long)a.B * tpi;
     if (n_tt * n_cg > 0x7fffffffL) return hipErrorInvalidValue;
     const long groups = compute_units() / n_cg > 0 ? compute_units() / n_cg : 1;       // one workgroup a CU (registers)
     const long per = (n_tt + groups - 1) / groups;
-    const long nblocks = (n_tt + per - 1) / per * n_cg;
-    const hipError_t e = allow_dynamic_lds<apply32_project_kernel<T, KCH>>(S::kLds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((apply32_project_kernel<T, KCH>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds, stream,
-                       (const T*)a.q_ms, a.kv32, (const T*)a.w_proj, (T*)a.out, N, n_hb, a.c_out, n_cg, tpi, n_tt, per, a.eps);
-    return hipGetLastError();
+    // States in parts of the storage type cost their making, 1.5 us an image, and save two thirds of a tile's matrix cycles.  Us a module, fp32
+    // operands / parts: 8 x 8192 tokens, 16 head-branches (8 tiles a workgroup) 152.9 / 143.3, 4 x 8192, 8 (4 tiles) 43.5 / 41.8; 3 x 8192, 16 (3)
+    // 68.4 / 71.6, 2 x 8192, 16 (2) 49.5 / 49.7, 2048, 16 (1) 32.7 / 34.3.
+    return per >= 4 ? run_apply32_project_as<T, KCH, true>(a, N, n_cg, tpi, n_tt, per, stream)
+                    : run_apply32_project_as<T, KCH, false>(a, N, n_cg, tpi, n_tt, per, stream);
 }
 
 // fixed-order sum of the partial states, then the normalise-and-apply pass

@@ -260,3 +260,11 @@ def test_fp32_small_maps(B, C, H, W, heads, scales):
 def test_head_size_32_on_the_matrix_cores(dtype, B, C, H, W, heads, scales):
     print(f"routes: head size 32 {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
     base.check_module(wk.random_module(59 + C + H, dtype, B, C, H, W, heads, 32, scales), dtype, heads, 32, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# heads of 32, the state's operands in three parts (four 32-token tiles a workgroup and more, some of two images): 2 and 10 head-branches
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(3, 32, 100, 91, 1, (5,)), (3, 160, 100, 91, 5, (3,))])
+def test_head_size_32_states_in_parts(dtype, B, C, H, W, heads, scales):
+    print(f"routes: head size 32, states in parts {dtype} {B}x{C}x{H}x{W}", flush=True)
+    base.check_module(wk.random_module(67 + C, dtype, B, C, H, W, heads, 32, scales), dtype, heads, 32, scales, stages=False)
