@@ -1,4 +1,4 @@
-// 1x1 projections with a long contraction (257 .. 1024 slots) for the 16-bit storage types:
+// 1x1 projections with a long contraction (257 .. 1024 slots; the second of them up to 4096 in parts) for the 16-bit storage types:
 // the Q/K/V projection of a wide module (Section 3.1: Q = x W_Q ...) of few tokens, and the fused
 // normalise-and-apply + output projection (Eq. (3) + Section 3.1, last sentence) of a module with
 // more than 32 head-branches that has few tokens or at most 384 output channels.
@@ -69,13 +69,15 @@ struct SmallAttArgs {
 };
 
 // KC: contraction length in 32-slot chunks (weights: 4*KC registers).  kAtt: the row operand is
-// the attention map of Eq. (3), made on the fly from src = the multi-scale Q map.
-template <class T, int KC, bool kAtt, class Dest>
+// the attention map of Eq. (3), made on the fly from src = the multi-scale Q map.  kMulti: a longer contraction in n_parts parts of
+// KC chunks, each with its weights, its head-branches' rows and its products (for workgroups of a tile or two: every tile
+// fetches the weights again).
+template <class T, int KC, bool kAtt, bool kMulti, class Dest>
 __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* __restrict__ src,
                                                                      const T* __restrict__ w, Dest dest,
                                                                      SmallAttArgs aa, long n_tokens, int K,
                                                                      int c_out, int n_cb, long n_tiles,
-                                                                     int tiles_per_image) {
+                                                                     int tiles_per_image, int n_parts) {
     typedef Traits<T> Tr;
     typedef typename Tr::Vec Vec;
     typedef typename Tr::Frag Frag;
@@ -114,13 +116,14 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
     constexpr int kVecs = KC * 4 * kSmallTB / kSmallThreads;      // 16-byte vectors per thread
     static_assert(kVecs * kSmallThreads == KC * 4 * kSmallTB, "tile copy");
     u32x4 v[kVecs];
+    unsigned part_col = 0;                            // kMulti: the part's first byte of a row
     auto fetch_tile = [&](Origin o) {
         const BufRsrc sres = make_rsrc(src + o.tok0 * K, (long)o.rows * row_bytes);
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
             const int id = i * kSmallThreads + threadIdx.x;
             const int row = id / (KC * 4), c = id - row * (KC * 4);
-            v[i] = buf_load16(sres, c * 16u < row_bytes ? row * row_bytes + c * 16u : kOobOffset, 0);
+            v[i] = buf_load16(sres, part_col + c * 16u < row_bytes ? row * row_bytes + part_col + c * 16u : kOobOffset, 0);
         }
     };
     // ---- state operands of the wave's head-branches m = wave, wave + 8, ...: a ring of kRing, so that an
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
     // requested ahead of the weights: everything a workgroup's first tile waits for is in flight at once
     // (bf16 with 32 chunks has no registers for that beside its weights: with it, 46 registers spilled and a module of
     // 2 x 4096 tokens, 512 channels went from 88 to 126 us.  It asks for each thing where it uses it.)
-    constexpr bool kEarly = !(kHiLo && KC == 32);
+    constexpr bool kEarly = !kMulti && !(kHiLo && KC == 32);
     Origin org = origin(first_tile);
     auto fetch_first = [&]() {
         fetch_tile(org);
@@ -154,7 +157,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
     // apart, which the memory path serves several times slower -- and dealt out through LDS, a round
     // of 256 contraction slots at a time, the next round's requests in flight meanwhile.
     Vec wf[KC];
-    {
+    auto load_weights = [&]() {
         constexpr int kRounds = KC / 8;
         const BufRsrc wres = make_rsrc(w, (long)c_out * row_bytes);
         u32x4 stage[2][8];
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
                 const int id = i * kSmallThreads + threadIdx.x;
                 const int row = id >> 5, c = id & 31;
                 const int ch = cb * kSmallChanBlock + row;
-                const unsigned col = r * 512u + c * 16u;
+                const unsigned col = part_col + r * 512u + c * 16u;
                 v[i] = buf_load16(wres, (ch < c_out && col < row_bytes) ? (unsigned)ch * row_bytes + col : kOobOffset, 0);
             }
         };
@@ -187,19 +190,27 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
                                          ((((j & 1) * 4 + q) ^ g16) * 16)));
         });
         __syncthreads();
-    }
+    };
+    if constexpr (!kMulti) load_weights();
 
     for (long tile = first_tile; tile < n_tiles; tile += tile_step) {
-        if constexpr (!kEarly) fetch_first();
+        if constexpr (kMulti) org = origin(tile);
         const long tok0 = org.tok0;
         const int rows = org.rows;
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 1
+        for (int part = 0; part < (kMulti ? n_parts : 1); ++part) {
+        if constexpr (kMulti) part_col = part * (KC * 64u);
+        if constexpr (!kEarly) fetch_first();
+        if constexpr (kMulti) load_weights();
+        const int m0 = kMulti ? part * (2 * KC) : 0;  // the part's first head-branch
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
             const int id = i * kSmallThreads + threadIdx.x;
             const int row = id / (KC * 4), c = id - row * (KC * 4);
             *(u32x4*)(tile_hi + (c >> 3) * kSlabBytes + row * 128 + swz(row, c & 7) * 16) = v[i];
         }
-        const bool more = tile + tile_step < n_tiles;
+        const bool more = !kMulti && tile + tile_step < n_tiles;
         if (more) {
             org = origin(tile + tile_step);
             if constexpr (kEarly) fetch_tile(org);
@@ -212,7 +223,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
             const long img = tok0 / aa.N, img_next = org.tok0 / aa.N;
             const f32x4 z = {0.f, 0.f, 0.f, 0.f};
             auto unit = [&](int m, Vec s_kv, Vec s_ks, float s_eps) {
-                const bool live = m < aa.n_hb;
+                const bool live = m0 + m < aa.n_hb;
 #pragma unroll
                 for (int jt = 0; jt < 2; ++jt) {
                     const int row = jt * 16 + x16;
@@ -248,7 +259,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
             } else {
 #pragma unroll 1
                 for (int i = 0; i < kUnitsM; ++i) {
-                    fetch_state_of(img, 0, wave + 8 * i);
+                    fetch_state_of(img, 0, m0 + wave + 8 * i);
                     unit(wave + 8 * i, a_kv[0], a_ks[0], eps_s[0]);
                 }
             }
@@ -256,7 +267,6 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
         __syncthreads();
 
         // ---- 16 channels x 32 tokens per wave: D[channel 4q+r][token x16]
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         const int frag_off = x16 * 128 + (q ^ g16) * 16;
 #pragma unroll
         for (int kk = 0; kk < KC; ++kk) {
@@ -267,6 +277,8 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
                 if constexpr (kHiLo)
                     acc[jt] = Tr::mma_vec(acc[jt], wf[kk], __builtin_bit_cast(Vec, *(const u32x4*)(tile_lo + off)));
             }
+        }
+        if constexpr (kMulti) __syncthreads();        // the tile's memory takes the next part's weights
         }
         // ---- lane (token x16, q): channels 4q..4q+3 of the wave's group, 8 bytes
         if (ch0 < c_out) {
@@ -282,7 +294,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
     }
 }
 
-template <class T, int KC, bool kAtt, class Dest>
+template <class T, int KC, bool kAtt, bool kMulti, class Dest>
 hipError_t run_small(const void* src, const void* w, Dest dest, SmallAttArgs aa, long n_tokens, int K, int c_out,
                      long n_tiles, int tiles_per_image, hipStream_t stream) {
     const int n_cb = (c_out + kSmallChanBlock - 1) / kSmallChanBlock;
@@ -297,20 +309,24 @@ hipError_t run_small(const void* src, const void* w, Dest dest, SmallAttArgs aa,
     if (groups < 1) groups = 1;
     const long per = (n_tiles + groups - 1) / groups;
     groups = (n_tiles + per - 1) / per;
-    const hipError_t e = allow_dynamic_lds<small_project_kernel<T, KC, kAtt, Dest>>(kLds);
+    const hipError_t e = allow_dynamic_lds<small_project_kernel<T, KC, kAtt, kMulti, Dest>>(kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((small_project_kernel<T, KC, kAtt, Dest>), dim3((unsigned)(groups * n_cb)),
+    hipLaunchKernelGGL((small_project_kernel<T, KC, kAtt, kMulti, Dest>), dim3((unsigned)(groups * n_cb)),
                        dim3(kSmallThreads), kLds, stream, (const T*)src, (const T*)w, dest, aa, n_tokens, K, c_out,
-                       n_cb, n_tiles, tiles_per_image);
+                       n_cb, n_tiles, tiles_per_image, (K + KC * 32 - 1) / (KC * 32));
     return hipGetLastError();
 }
 
 template <class T, bool kAtt, class Dest>
 hipError_t run_small_k(const void* src, const void* w, Dest dest, SmallAttArgs aa, long n_tokens, int K, int c_out,
                        long n_tiles, int tiles_per_image, hipStream_t stream) {
-    if (K <= 512) return run_small<T, 16, kAtt, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
-    if (K <= 768) return run_small<T, 24, kAtt, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
-    if (K <= 1024) return run_small<T, 32, kAtt, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
+    if (K <= 512) return run_small<T, 16, kAtt, false, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
+    if (K <= 768) return run_small<T, 24, kAtt, false, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
+    if (K <= 1024) return run_small<T, 32, kAtt, false, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
+    if constexpr (kAtt) {
+        // (parts of 768 slots; of 1024, bf16 would spill)
+        return run_small<T, 24, kAtt, true, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
+    }
     return hipErrorNotSupported;
 }
 

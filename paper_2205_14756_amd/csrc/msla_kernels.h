@@ -120,7 +120,7 @@ hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, co
                                 const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
                                 int n_hb, int c_out, float eps, hipStream_t stream);
 
-// The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots (k_small.hip): the callers take the
+// The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots (k_small.hip; apply + projection up to 4096): the callers take the
 // projections where few enough tokens make the weights what a workgroup mostly fetches (small_product), the apply + projection there
 // and, whatever the number of tokens, up to 384 output channels (launch_apply_project).  They return hipErrorNotSupported, without
 // launching, for other types and contractions.

@@ -268,3 +268,13 @@ def test_head_size_32_on_the_matrix_cores(dtype, B, C, H, W, heads, scales):
 def test_head_size_32_states_in_parts(dtype, B, C, H, W, heads, scales):
     print(f"routes: head size 32, states in parts {dtype} {B}x{C}x{H}x{W}", flush=True)
     base.check_module(wk.random_module(67 + C, dtype, B, C, H, W, heads, 32, scales), dtype, heads, 32, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# contractions of more than 1024 slots in parts of 768: 1040 and 1536 slots, 1600 (a third part of 64), 4096 (the last that takes it; a sixth
+# part of 256) and 4112; ragged tiles of several images, channels past the output, with the block's residual
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(2, 272, 5, 13, 65, ()), (3, 512, 7, 19, 32, (3, 5)), (1, 400, 6, 11, 25, (3, 5, 7)),
+                                                  (1, 144, 3, 7, 128, (5,)), (1, 144, 3, 7, 257, ())])
+def test_long_contraction_in_parts(dtype, B, C, H, W, heads, scales):
+    print(f"routes: long contraction in parts {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
+    base.check_module(wk.random_module(73 + heads, dtype, B, C, H, W, heads, 16, scales), dtype, heads, 16, scales, stages=False)
