@@ -476,6 +476,12 @@ hipError_t run_dw_project_split(const void* h, const void* w_dw, const void* w2,
         return r8x16 <= r4x32 ? run_dw_project_split_as<T, ACT, 2, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)
                               : run_dw_project_split_as<T, ACT, 2, 128, 32>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
     }
+    // More than 128 channels in blocks of 128, each of which does the depthwise pass again, while those are one round: a slab's step is shorter
+    // with half the weights to stage and to multiply.  Us with 256 / 128: 512 tokens, 512 -> 2048 channels 47.9 / 44.0, 2048, 256 -> 1024 26.9 /
+    // 24.6, 8192 (256 blocks) 31.5 / 29.3; past a round 16384 (512) 38.2 / 50.8.
+    const long b64 = (long)B * ((H + 3) / 4) * ((W + 15) / 16);
+    if (b64 * ((c_out + 127) / 128) <= cus)
+        return run_dw_project_split_as<T, ACT, 1, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
     if (r64 <= r8x16 && r64 <= r4x32)
         return run_dw_project_split_as<T, ACT, 1, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
     return r4x32 <= r8x16 ? run_dw_project_split_as<T, ACT, 2, 256, 32>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream)

@@ -278,3 +278,10 @@ def test_head_size_32_states_in_parts(dtype, B, C, H, W, heads, scales):
 def test_long_contraction_in_parts(dtype, B, C, H, W, heads, scales):
     print(f"routes: long contraction in parts {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
     base.check_module(wk.random_module(73 + heads, dtype, B, C, H, W, heads, 16, scales), dtype, heads, 16, scales, stages=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# more than 128 channels on few tokens: channel blocks of 128 (two, the second short; three; 256 blocks in all), and one block past a round
+@pytest.mark.parametrize("B,C,H,W,hidden", [(1, 144, 5, 17, 80), (2, 272, 9, 18, 96), (2, 160, 32, 128, 64), (1, 144, 43, 192, 64)])
+def test_ffn_channel_blocks_of_small_maps(dtype, B, C, H, W, hidden):
+    block.test_ffn(dtype, 1, B, C, H, W, hidden)
