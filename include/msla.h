@@ -112,7 +112,8 @@ msla_status msla_forward(const void* x, const void* w_qkv, const void* w_dw,
  *       aggregation + partial Eq. (3) states; the fixed-order sum of the partial states; the
  *       fused normalise-and-apply + output projection.  A stage reads what the stages before it
  *       left in `workspace`, so a complete call with the same arguments must have run on that
- *       workspace before; MSLA_NHWC only (else MSLA_ERR_UNSUPPORTED).
+ *       workspace before; MSLA_NHWC only (else MSLA_ERR_UNSUPPORTED).  On small 16-bit maps of up to 192
+ *       channels the aggregation kernel computes Q, K and V itself: _PROJECT enqueues nothing there.
  * Any other bit returns MSLA_ERR_INVALID_ARG. */
 #define MSLA_OPT_GENERAL_AGGREGATION 1u
 #define MSLA_OPT_STAGE_PROJECT 2u
@@ -130,7 +131,8 @@ msla_status msla_forward_opts(const void* x, const void* w_qkv, const void* w_dw
 
 /* msla_forward with stage timing (for benchmarks; same computation, Section 3.1).
  * events: HOST array of 5 hipEvent_t created by the caller with timing enabled.  They are
- * recorded on `stream`: [0] before the first kernel, [1] after the Q/K/V projection,
+ * recorded on `stream`: [0] before the first kernel, [1] after the Q/K/V projection (small maps of
+ * up to 192 channels, 16-bit: part of the aggregation kernel, so right after [0]),
  * [2] after the aggregation kernels (partial states written), [3] after the state
  * finalize kernel, [4] after the fused apply + output projection. */
 msla_status msla_forward_profiled(const void* x, const void* w_qkv, const void* w_dw,

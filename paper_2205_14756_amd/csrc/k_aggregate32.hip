@@ -379,8 +379,8 @@ __global__ __launch_bounds__(kThreads32, (Agg32Lds<T, KS>::kWaves)) void aggrega
 // grouped 1x1 contracts over all 32 in one instruction; a staging wave reads its rows' raw K back in the V step for the raw state.
 // Aggregated K stays in registers from its step to V's; V's grouped 1x1 is applied to the summed state at the end.
 // Us a module, the first kernel / this: 8 x 8192 tokens, 8 heads, 5x5 fp16 182.9 / 152.8, bf16 199.8 / 154.6; 2048 tokens, 8 heads
-// 41.4 / 32.7; 2 x 4096, 4 heads, 3x3 35.8 / 27.8; 16384 tokens, 2 heads, 3x3 + 5x5 64.0 / 42.4.  The first of these, this kernel 91.8 -> 58.6 (vector ALU 44 % of a SIMD's cycles, matrix pipe 36 %, LDS 52 %); errors as before or smaller (V is
-// rounded once less).
+// 41.4 / 32.7; 2 x 4096, 4 heads, 3x3 35.8 / 27.8; 16384 tokens, 2 heads, 3x3 + 5x5 64.0 / 42.4.  The first of these, this kernel 91.8 ->
+// 58.6 (vector ALU 44 % of a SIMD's cycles, matrix pipe 36 %, LDS 52 %); errors as before or smaller (V is rounded once less).
 template <int KS>
 struct Mfma32Lds {
     static constexpr int P = (KS - 1) / 2;

@@ -247,7 +247,8 @@ msla_status run_state(const Shape& s, msla_dtype dt, const void* q, long q_ts, i
                                                : msla::launch_aggregate_mfma((int)dt, a, stream);
         // an image whose maps exceed the matrix-core kernel's 32-bit offsets takes the general kernel,
         // whose tiles are half as high: the same number of chunks, twice the tiles in each
-        if (e_launch == hipErrorNotSupported) {
+        // (not with Q, K and V still to be computed; such maps are small)
+        if (e_launch == hipErrorNotSupported && a.w_qkv == nullptr) {
             msla::AggregateArgs g = a;
             const long tiles = (long)((s.H + msla::kAggTileH - 1) / msla::kAggTileH) *
                                ((s.W + msla::kAggTileW - 1) / msla::kAggTileW);
@@ -480,8 +481,9 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     if (layout == MSLA_NCHW && C > 2 * s.Ct) return MSLA_ERR_UNSUPPORTED;
     Workspace wo = carve_module(&s, C, dt);
     if (workspace_bytes < wo.total) return MSLA_ERR_WORKSPACE;
-    // (a call that selects or times stages has the projection as a stage of its own)
-    const bool fused = C <= msla::kAggSmallMaxC && options == 0 && events == nullptr && small_map(s, dt, true) && make_small_in_kv(&s, dt, &wo);
+    // (whatever the stages wanted: they read what a complete call left in the workspace)
+    const bool fused = C <= msla::kAggSmallMaxC && !(options & MSLA_OPT_GENERAL_AGGREGATION) && small_map(s, dt, true) &&
+                       make_small_in_kv(&s, dt, &wo);
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
@@ -516,8 +518,8 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     if (!mark(1)) return MSLA_ERR_LAUNCH;
     // aggregation + Eq. (3) state
     if (fused)
-        st = run_state(s, dt, x_tok, C, 0, x_tok, C, 0, x_tok, C, 0, w_dw, w_gpw, ws, wo, q_ms, /*copy_raw_q=*/0, hs, options, nullptr,
-                       state_split, w_qkv, C);
+        st = run_state(s, dt, x_tok, C, 0, x_tok, C, 0, x_tok, C, 0, w_dw, w_gpw, ws, wo, q_ms, /*copy_raw_q=*/0, hs, options,
+                       events ? events[2] : nullptr, state_split, w_qkv, C);
     else
         st = run_state(s, dt, q_ms, q_ms_ts, 16, kv_raw, kv_ts, (int)kv_hs, kv_raw + 16 * e, kv_ts, (int)kv_hs, w_dw, w_gpw,
                        ws, wo, q_ms, /*copy_raw_q=*/0, hs, options, events ? events[2] : nullptr, state_split);
