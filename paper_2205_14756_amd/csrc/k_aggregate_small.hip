@@ -13,7 +13,8 @@
 // Projection: 16 tokens x 48 channels a step, D[token][channel] = x W^T with x fragments straight from memory and the head's 48
 // rows of weights in LDS; a lane ends up with four tokens of one channel, which is the channel-planar form that the sweep wants.
 // Values are rounded to the storage type there, exactly as when Q, K and V are stored between two kernels.  Q of the tile's own
-// tokens goes to the multi-scale map through an identity matrix.
+// tokens, for the multi-scale map, is multiplied again with the operands swapped: through an identity matrix, an infinite value (an
+// fp16 overflow) would turn the same channel of its 15 neighbours into NaN.
 #include <algorithm>
 #include <type_traits>
 
@@ -204,14 +205,14 @@ __global__ __launch_bounds__(kSmallThreads, KSB == 0 ? 4 : 2) void aggregate_sma
 #pragma unroll
     for (int first = 0; first < L::kPer; first += kHalf) {
     // Q, K, V of a group: lane (channel x16, q), tokens 4q .. 4q + 3 of it
-    f32x4 d_all[kHalf][3];
+    f32x4 d_all[kHalf][3], dq_all[kHalf];       // (dq_all: Q the other way round, lane (token x16, q) with channels 4q .. 4q + 3)
     if constexpr (kProject) {
         if (first > 0) fetch_x(first);
         // (a weight operand is read once for all of a wave's groups)
 #pragma unroll
         for (int j = 0; j < kHalf; ++j)
 #pragma unroll
-            for (int t = 0; t < 3; ++t) d_all[j][t] = z;
+            for (int t = 0; t < 3; ++t) d_all[j][t] = dq_all[j] = z;
 #pragma unroll
         for (int s = 0; s < KC; ++s)
 #pragma unroll
@@ -219,8 +220,10 @@ __global__ __launch_bounds__(kSmallThreads, KSB == 0 ? 4 : 2) void aggregate_sma
                 const Vec wf = *(const Vec*)(w_lds + (t * 16 + x16) * L::kWPitch + s * 64 + q * 16);
 #pragma unroll
                 for (int j = 0; j < kHalf; ++j)
-                    if (first + j + 1 < L::kPer || wave + kSmallWaves * (first + j) < L::kGroups)
+                    if (first + j + 1 < L::kPer || wave + kSmallWaves * (first + j) < L::kGroups) {
                         d_all[j][t] = Tr::mma_vec(d_all[j][t], __builtin_bit_cast(Vec, xf[j][s]), wf);
+                        if (t == 0) dq_all[j] = Tr::mma_vec(dq_all[j], wf, __builtin_bit_cast(Vec, xf[j][s]));
+                    }
             }
         // the wait states between the last of these and whatever touches its registers next, written out: the compiler (ROCm 7.2) counts
         // one too many on the path on which a wave has no last group
@@ -261,7 +264,7 @@ __global__ __launch_bounds__(kSmallThreads, KSB == 0 ? 4 : 2) void aggregate_sma
             // raw Q, token-major: lane (token slot x16, q) with channels 4q .. 4q + 3
             const int t = own_token(g, x16);
             Frag out;
-            if constexpr (kProject) out = frag_from_f32<T>(Tr::mma16(z, dq, ident));
+            if constexpr (kProject) out = frag_from_f32<T>(dq_all[j]);
             else out = __builtin_bit_cast(Frag, qf[j]);
             if (t >= 0) store_frag<T>(q_ms + (img_tok0 + t) * (long)a.S * Ct + h * 16 + q * 4, out);
         }

@@ -288,3 +288,25 @@ def test_long_contraction_in_parts(dtype, B, C, H, W, heads, scales):
 @pytest.mark.parametrize("B,C,H,W,hidden", [(1, 144, 5, 17, 80), (2, 272, 9, 18, 96), (2, 160, 32, 128, 64), (1, 144, 43, 192, 64)])
 def test_ffn_channel_blocks_of_small_maps(dtype, B, C, H, W, hidden):
     block.test_ffn(dtype, 1, B, C, H, W, hidden)
+
+
+def test_small_map_keeps_an_overflow_to_its_own_token():
+    # one token's Q overflows fp16 in every head; its K and V stay small, so no other token's row may notice
+    B, C, H, W, heads = 1, 64, 9, 33, 4
+    t = wk.random_module(19, "f16", B, C, H, W, heads, 16, ())
+    x, w = t["x"].copy(), t["w_qkv"].reshape(heads, 3, 16, C).copy()
+    x[..., 0] = 0.0
+    w[:, 0, :, 0], w[:, 1:, :, 0] = 8.0, 0.0
+    rng = np.random.default_rng(5)
+    dw = np.zeros((48 * heads, 5, 5))
+    dw[:, 2, 2] = 1.0                                   # (the aggregated branch is the raw one: nothing spreads over the filter's taps)
+    gp = rng.standard_normal((48 * heads, 16)) / 4.0
+    w_proj = np.concatenate([rng.standard_normal((C, 16 * heads)) / 8.0, np.zeros((C, 16 * heads))], 1)      # ... and is left out
+    dev = lambda a: base.dev(np.ascontiguousarray(a), "f16")
+    def rows(big):
+        x[0, 4, 7, 0] = big
+        out = msla.msla_forward(dev(x), dev(w.reshape(48 * heads, C)), dev(dw.reshape(-1)), dev(gp[None]), dev(w_proj), heads, 16, (5,))
+        return np.delete(base.host(out).reshape(H * W, C), 4 * W + 7, 0)
+
+    want, got = rows(0.0), rows(6.0e4)
+    assert np.isfinite(want).all() and np.array_equal(got, want)
