@@ -378,6 +378,11 @@ __global__ __launch_bounds__(kThreads32, (Agg32Lds<T, KS>::kWaves)) void aggrega
 // another 20 registers of them every half step); the first block's depthwise sums wait in registers for the second's, and the
 // grouped 1x1 contracts over all 32 in one instruction; a staging wave reads its rows' raw K back in the V step for the raw state.
 // Aggregated K stays in registers from its step to V's; V's grouped 1x1 is applied to the summed state at the end.
+// A Q that is not finite (an fp16 overflow of one token) must not pass the zeros that surround a filter's taps in its operand, or
+// the selecting products of the staging: times them it would be NaN in tokens outside the filter's reach.  A tile that has one is staged
+// again with zeros in its place, and the sweeping waves mark what it reaches.  (In K or V it makes the image's states
+// of that head useless, wherever it goes.)  With the grouped 1x1 operands of Q and K in LDS (registers for the rest) this costs nothing: a module
+// of 8 x 8192 tokens, 8 heads, fp16 143.1 -> 142.0 us, bf16 145.4 -> 144.0; 128 x 128, 2 heads, 3x3 + 5x5, bf16 45.4 -> 44.1.
 // Us a module, the first kernel / this: 8 x 8192 tokens, 8 heads, 5x5 fp16 182.9 / 152.8, bf16 199.8 / 154.6; 2048 tokens, 8 heads
 // 41.4 / 32.7; 2 x 4096, 4 heads, 3x3 35.8 / 27.8; 16384 tokens, 2 heads, 3x3 + 5x5 64.0 / 42.4.  The first of these, this kernel 91.8 ->
 // 58.6 (vector ALU 44 % of a SIMD's cycles, matrix pipe 36 %, LDS 52 %); errors as before or smaller (V is rounded once less).
@@ -390,7 +395,9 @@ struct Mfma32Lds {
     static constexpr int kToepBytes = 6 * KS * 2 * 64 * 8;              // [map][block][filter row][k-step][lane]
     static constexpr int kWvBytes = D32 * D32 * 2;                      // V's grouped 1x1
     static constexpr int kWork = 2 * kMapBytes + 8 * 2 * kTransBytes;   // two maps in flight, the sweeping waves' transposition buffers
-    static constexpr int kBytes = kWork + kToepBytes + kWvBytes;
+    static constexpr int kGpwBytes = 2 * NB * 64 * 16;                  // grouped 1x1 of Q and K as operands: [map][output block][lane]
+    static constexpr int kLostBytes = LH * 8;                           // [tile row] columns whose raw Q is not finite
+    static constexpr int kBytes = kWork + kToepBytes + kWvBytes + kGpwBytes + kLostBytes;
     static constexpr int kWaveFloats = NB * NB * 256 + D32;             // per wave: accumulator quads of its state, Ksum
     static_assert(kMapBytes % 16 == 0 && LW <= 36 && kBytes <= 160 * 1024 && (12 * kWaveFloats + D32 * D32) * 4 <= kWork, "LDS layout");
 };
@@ -556,6 +563,13 @@ __device__ __forceinline__ void sweep32(const char* rows, char* trans, const cha
     });
 }
 
+// lane_id() out of nothing, so that neither it nor what is made of it stays in a register from before
+__device__ __forceinline__ int lane_id_again() {
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)zero));
+}
+
 constexpr int kMfma32Threads = 12 * 64;
 template <class T, int KS, bool kRaw>
 __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(AggregateArgs a) {
@@ -567,6 +581,8 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* const toep_lds = lds + L::kWork;
     char* const wv_lds = toep_lds + L::kToepBytes;
+    char* const gpw_lds = wv_lds + L::kWvBytes;
+    unsigned long long* const lost = (unsigned long long*)(gpw_lds + L::kGpwBytes);
     float* const red = (float*)lds;             // reused after the last tile
 
     const unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
@@ -646,6 +662,42 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
             }
         };
         const BufRsrc rraw = make_rsrc(q_ms + img_tok0 * a.S * Ct + h * D32, ((N - 1) * a.S * Ct + D32) * (long)SZ);
+        // 0 while all of this wave's Q is finite (the selected values are sums over a token's channels: one that is not finite is in all)
+        float finite = 0.f;
+        auto check = [&](f32x4 d) { finite = fmaf((d[0] + d[1]) + (d[2] + d[3]), 0.f, finite); };
+        // This wave's rows of a Q map that is not: stored again, value by value, without the products and with zeros for what is not
+        // finite, and the columns of those tokens noted.
+        auto restage = [&](TileAt at, char* planar) {
+            const BufRsrc r = make_rsrc(base[2], ((N - 1) * ts[2] + D32) * (long)SZ);
+            const unsigned tb = (unsigned)(ts[2] * SZ), top = std::is_same<T, _Float16>::value ? 0x7c00u : 0x7f80u;
+            const int l = lane_id_again();      // (nothing of this is worth a register while maps are staged)
+            const int x = l & 15, c8 = (l >> 4) * 8;
+            wave_lds_fence();
+#pragma unroll 1
+            for (int ly = wave; ly < L::LH; ly += 4) {
+                const int gy = at.ty0 - P + ly;
+                unsigned long long cols = 0;
+#pragma unroll 1
+                for (int cg = 0; cg < 3; ++cg) {
+                    const int lx = cg * 16 + x, gx = at.tx0 - P + lx;
+                    const bool in = lx < L::LW && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+                    const u32x4 v = buf_load16(r, in ? (unsigned)(gy * a.W + gx) * tb + c8 * 2 : kOobOffset, 0);
+                    bool bad = false;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const unsigned bits = (v[i >> 1] >> (16 * (i & 1))) & 0xffffu;
+                        const bool this_bad = (bits & top) == top;
+                        bad = bad || this_bad;
+                        if (lx < L::LW)
+                            *(unsigned short*)(planar + (c8 + i) * L::kChanBytes + ly * kPlanarRowBytes + lx * SZ) = (unsigned short)(this_bad ? 0u : bits);
+                    }
+                    unsigned long long m = __ballot(bad);
+                    m |= m >> 32;
+                    cols |= ((m | m >> 16) & 0xffffu) << (cg * 16);
+                }
+                if (l == 0) lost[ly] = cols;
+            }
+        };
         auto consume = [&](TileAt at, auto mc, auto itc, const Batch& bt, char* planar, const char* planar_k) {
             constexpr int m = decltype(mc)::value, it = decltype(itc)::value;
             // What a group of 16 tokens (this lane: tokens 4q .. 4q + 3 of channels x16 and 16 + x16) adds to the raw state, in the V step;
@@ -683,6 +735,7 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
                 const int at_lds = x16 * L::kChanBytes + ly * kPlanarRowBytes + q * 8;
 #pragma unroll
                 for (int cg = 0; cg < 2; ++cg) {
+                    if constexpr (m == 2) check(d[cg][0]);
                     Frag f[NB];
 #pragma unroll
                     for (int i = 0; i < NB; ++i) {
@@ -706,6 +759,7 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
 #pragma unroll
                 for (int i = 0; i < NB; ++i) d[i] = Tr::mma_vec(z, __builtin_bit_cast(Vec, bt.tail), sel[i]);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (m == 2) check(d[0]);
                 const int at_lds = x16 * L::kChanBytes + (row_ok ? ly : 0) * kPlanarRowBytes + 64;
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
@@ -738,6 +792,12 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
                     consume(here, mc, std::integral_constant<int, 2 * n>{}, ring[n], planar, lds + (buf ^ 1) * L::kMapBytes);
                     issue(m < 2 ? here : next, (m + 1) % 3, 2 * n, ring[n], m < 2 || more);
                 });
+                if constexpr (m == 2) {
+                    const int l = lane_id_again();
+                    if (wave + 4 * l < L::LH) lost[wave + 4 * l] = 0;
+                    if (__any(!(finite == 0.f))) restage(here, planar);
+                    finite = 0.f;
+                }
                 buf ^= 1;
                 __syncthreads();
             });
@@ -758,17 +818,18 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
         } else if (sw == 6) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) ((u32x4*)wv_lds)[i * 64 + lane] = ((const u32x4*)(wgp + 2 * D32 * D32))[i * 64 + lane];
+        } else {
+            // grouped 1x1 of Q and K, contraction slots {4q .. 4q + 3} and {16 + 4q ..}: lane (o, q) of output block ob.  A sweep reads its own
+            // (16 registers that the others have for themselves)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int ob = 0; ob < NB; ++ob) {
+                    const T* row = wgp + (t * D32 + ob * 16 + x16) * D32 + q * 4;
+                    const u32x2 lo = *(const u32x2*)row, hi = *(const u32x2*)(row + 16);
+                    *(u32x4*)(gpw_lds + (t * NB + ob) * 1024 + lane * 16) = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                }
         }
-        // grouped 1x1 of Q and K, contraction slots {4q .. 4q + 3} and {16 + 4q ..}: lane (o, q) of output block ob
-        Vec gpw[2][NB];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int ob = 0; ob < NB; ++ob) {
-                const T* row = wgp + (t * D32 + ob * 16 + x16) * D32 + q * 4;
-                const u32x2 lo = *(const u32x2*)row, hi = *(const u32x2*)(row + 16);
-                gpw[t][ob] = __builtin_bit_cast(Vec, u32x4{lo[0], lo[1], hi[0], hi[1]});
-            }
         const int strip = sw & 1, part = sw >> 1;
         const BufRsrc rout = make_rsrc(q_ms + img_tok0 * a.S * Ct + (long)a.branch * Ct + h * D32, ((N - 1) * a.S * Ct + D32) * (long)SZ);
         char* const trans = lds + 2 * L::kMapBytes + sw * 2 * kTransBytes;
@@ -778,15 +839,36 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
         for (int i = 0; i < n_my; ++i) {
             const int gy0 = here.ty0 + 4 * part, gx = here.tx0 + 16 * strip;
             const bool ragged = here.ty0 + MTH > a.H || here.tx0 + MTW > a.W;
-            auto sweep = [&](auto mapc, const Vec(&g)[NB]) {
+            auto sweep = [&](auto mapc) {
+                Vec g[NB] = {};
+                if constexpr (decltype(mapc)::value < 2) {
+#pragma unroll
+                    for (int ob = 0; ob < NB; ++ob) g[ob] = *(const Vec*)(gpw_lds + (decltype(mapc)::value * NB + ob) * 1024 + lane_id_again() * 16);
+                }
                 sweep32<T, KS, decltype(mapc)::value, L::kChanBytes>(lds + buf * L::kMapBytes + 4 * part * kPlanarRowBytes + 16 * strip * SZ, trans,
                                                                      toep_lds, g, a.H, a.W, gy0, gx, ragged, rout, q_ms_tb, aggK, aggK_lo, kv, ks);
+                if constexpr (decltype(mapc)::value == 0) {
+                    // tokens with a Q that is not finite in the filter's reach: not a number, in all channels (lane: one token)
+                    const int l = lane_id_again();          // (nothing of this is worth a register during the sweeps)
+                    if (__any(lost[4 * part + (l < 4 + KS - 1 ? l : 0)] != 0)) {
+                        const int y = l >> 4, x = l & 15;
+                        unsigned long long hit = 0;
+#pragma unroll 1
+                        for (int u = 0; u < KS; ++u) hit |= lost[4 * part + y + u];
+                        const bool mine = (hit >> (16 * strip + x) & ((1u << KS) - 1)) != 0 && gy0 + y < a.H && gx + x < a.W;
+                        const unsigned nan = std::is_same<T, _Float16>::value ? 0x7e007e00u : 0x7fc07fc0u;
+                        __builtin_amdgcn_s_waitcnt(0);      // (the stores of these tokens above come first)
+#pragma unroll 1
+                        for (int i = 0; i < 4; ++i)
+                            buf_store16(rout, mine ? (unsigned)((gy0 + y) * a.W + gx + x) * q_ms_tb + i * 16 : kOobOffset, u32x4{nan, nan, nan, nan});
+                    }
+                }
                 buf ^= 1;
                 __syncthreads();
             };
-            sweep(std::integral_constant<int, 1>{}, gpw[1]);
-            sweep(std::integral_constant<int, 2>{}, gpw[1]);
-            sweep(std::integral_constant<int, 0>{}, gpw[0]);
+            sweep(std::integral_constant<int, 1>{});
+            sweep(std::integral_constant<int, 2>{});
+            sweep(std::integral_constant<int, 0>{});
             here = tile_after(here);
         }
     }

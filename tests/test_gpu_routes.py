@@ -310,3 +310,34 @@ def test_small_map_keeps_an_overflow_to_its_own_token():
 
     want, got = rows(0.0), rows(6.0e4)
     assert np.isfinite(want).all() and np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# one token's Q overflows in every channel, in the middle of a tile of 16 x 32 and at the corner of four: tokens in a filter's reach get nothing from
+# that branch (their aggregated Q is not a number, which the rectifier takes for 0), all others are bit for bit what they were
+@pytest.mark.parametrize("scales,at", [((5,), (6, 9)), ((3,), (16, 31)), ((3, 5), (15, 32)), ((5, 3), (0, 0)), ((5,), (35, 44))])
+def test_head_size_32_keeps_an_overflow_in_the_filters_reach(dtype, scales, at):
+    B, C, H, W, heads, Ct = 2, 64, 36, 45, 2, 64
+    print(f"routes: head size 32, overflow {dtype} {scales} {at}", flush=True)
+    t = wk.random_module(31, dtype, B, C, H, W, heads, 32, scales)
+    x, w = t["x"].copy(), t["w_qkv"].reshape(heads, 3, 32, C).copy()
+    x[..., 0] = 0.0
+    w[:, 0, :, 0], w[:, 1:, :, 0] = 8.0, 0.0
+    wdw, wg = base.weights(t, dtype, scales)
+
+    def rows(big, branches):
+        x[1, at[0], at[1], 0] = big
+        wp = t["w_proj"].reshape(C, 1 + len(scales), Ct).copy()
+        wp[:, [b for b in range(1 + len(scales)) if b not in branches]] = 0.0
+        args = [base.dev(np.ascontiguousarray(a), dtype) for a in (x, w.reshape(3 * Ct, C), wp.reshape(C, -1))]
+        return base.host(msla.msla_forward(args[0], args[1], wdw, wg, args[2], heads, 32, scales)).reshape(B, H, W, C)
+
+    got, every = rows(6.0e4 if dtype == "f16" else 3.0e38, range(1 + len(scales))), range(1 + len(scales))
+    dy, dx = np.abs(np.arange(H) - at[0])[:, None], np.abs(np.arange(W) - at[1])[None]
+    reached = np.stack([np.full((H, W), False)] + [np.maximum(dy, dx) <= k // 2 for k in scales])
+    for some in set(map(tuple, reached.reshape(len(reached), -1).T)):
+        here = (reached == np.array(some)[:, None, None]).all(0)
+        here[at] = False                                # (its own raw Q is infinite)
+        want = rows(0.0, [b for b in every if not some[b]])
+        assert np.isfinite(got[1][here]).all() and np.array_equal(got[1][here], want[1][here]), f"branches reached: {some}"
+    assert np.array_equal(got[0], rows(0.0, every)[0])
