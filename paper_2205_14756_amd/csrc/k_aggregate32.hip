@@ -563,13 +563,6 @@ __device__ __forceinline__ void sweep32(const char* rows, char* trans, const cha
     });
 }
 
-// lane_id() out of nothing, so that neither it nor what is made of it stays in a register from before
-__device__ __forceinline__ int lane_id_again() {
-    int zero = 0;
-    asm volatile("" : "+v"(zero));
-    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)zero));
-}
-
 constexpr int kMfma32Threads = 12 * 64;
 template <class T, int KS, bool kRaw>
 __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(AggregateArgs a) {

@@ -277,8 +277,9 @@ __global__ __launch_bounds__(kGenThreads) void generic_apply_kernel(const T* __r
 // image, and wave w makes the rows of head-branches w and w + 8.  Two tiles, one barrier a tile, Q requested a tile ahead.
 // With fp32 states the matrix pipe bounds it: 4 x 512 cycles of fp32 products for the rows and 1024 for the projection a wave and
 // tile.  With the states in three 16-bit parts (kParts) the rows take 4 x 144 cycles: this kernel 50 -> 40 us at 8 x 8192 tokens, 16
-// head-branches, the errors of the module the same to three digits (fp16 3.85e-4, bf16 2.92e-3).  Against rows to memory and a projection of its own, whole modules: 8 x 8192 tokens, 16 head-branches, fp16 200.9 ->
-// 183.5 us; 3200, 12, bf16 48.0 -> 46.0; 1024, 4, fp16 34.9 -> 30.5.
+// head-branches, the errors of the module as with fp32 states (fp16 3.8e-4, bf16 2.9e-3).  Against rows to memory and a
+// projection of its own, whole modules: 8 x 8192 tokens, 16 head-branches, fp16 200.9 -> 183.5 us; 3200, 12, bf16 48.0 -> 46.0; 1024, 4, fp16
+// 34.9 -> 30.5.
 // LDS: an attention row is KCH*64 bytes, the 16-byte chunk index XOR-ed with token % 16, so that the sixteen tokens of an
 // operand read or a row store meet sixteen different chunks of the banks; the weights are dealt out through the same
 // memory, 128 bytes of every row at a time.
@@ -287,7 +288,8 @@ struct Apply32Project {
     static constexpr int kThreads = 512, TB = 32, kChan = 256, kHbw = KCH / 8;
     static constexpr int kRow = KCH * 64, kTile = TB * kRow, kStage = kChan * 128;
     static constexpr int kWork = 2 * kTile > kStage ? 2 * kTile : kStage;
-    static constexpr int kTail = 2 * (2 * 1024 + 64) + 16;  // a head-branch's second and third parts: two operands of the state each, the quarters of Ksum; eps
+    // a head-branch's second and third parts, two operands of the state each; all three of Ksum, in quarters; eps
+    static constexpr int kTail = 2 * 2 * 1024 + 3 * 64 + 16;
     static constexpr int kLds = kWork + (kParts ? KCH * kTail : 0);
     static constexpr int kSlabs = KCH / 2;
 };
@@ -371,18 +373,34 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
     }
 
     // kParts: a head-branch's state and Ksum are operands of the storage type, each value in three parts (its first, second and third 8
-    // or 11 significant bits: together all 24 that it has), times a power of two that puts the largest at 512 to 1024 (numerator and
-    // denominator scale together).  The first part stays in registers, the others wait in LDS, where only this wave looks for them.
-    // Else they are fp32 operands.
+    // or 11 significant bits), times a power of two that puts the largest at 2^14 to 2^15 (numerator and denominator scale together).
+    // fp16 ends at 2^-24, so its second and third parts are kept 2^12 times larger and their products' sums scaled back before the first
+    // part's are added: all 24 bits of every value down to kLeast, 2^-28 of the largest (bf16: 2^-115).  A wave whose head-branches have a
+    // smaller one that is not 0 takes fp32 products, as without kParts, with the states from memory (in_parts).  The state's first part stays in
+    // registers, the others and Ksum wait in LDS, where only this wave looks for them.  Else they are fp32 operands.
+    constexpr bool kF16 = std::is_same<T, _Float16>::value;
+    constexpr float kUp = kF16 ? 4096.0f : 1.0f, kLeast = kF16 ? 0x1p-13f : 0x1p-100f;
     typedef typename std::conditional<kParts, Vec, f32x4[2]>::type State;
     State st[S::kHbw][2];           // kParts: [output half]; else [contraction half][output half]
-    typename std::conditional<kParts, Vec, float[8]>::type ksum[S::kHbw];
+    float ksum[kParts ? 1 : S::kHbw][8];
     const int fo = 8 * (x16 >> 2) + (x16 & 3);
-    int img = -1;
     auto tail = [&](int i) { return lds + S::kWork + (wave + 8 * i) * S::kTail; };
+    auto load_fp32 = [&](int b, int m, f32x4 (&sv)[2][2], float (&sk)[8]) {
+        const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+        const int l = kParts ? lane_id_again() : lane, q = l >> 4, fo = 8 * ((l & 15) >> 2) + (l & 3);
+#pragma unroll
+        for (int jc = 0; jc < 2; ++jc)
+#pragma unroll
+            for (int jo = 0; jo < 2; ++jo)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sv[jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sk[e] = s[(8 * q + e) * 33 + 32];
+    };
     auto load_states = [&](int b) {
-        img = b;
+        bool in_parts = kParts;
         if constexpr (kParts) {
+            const int l = lane_id_again(), x16 = l & 15, q = l >> 4, fo = 8 * (x16 >> 2) + (x16 & 3);     // (no register for this during the tiles)
 #pragma unroll
             for (int i = 0; i < S::kHbw; ++i) {
                 const int m = wave + 8 * i;
@@ -404,55 +422,83 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
                 if (mx > 0.f) {
                     int ex;
                     frexpf(mx, &ex);
-                    scale = ldexpf(1.0f, ex < -100 ? 110 : 10 - ex);
+                    scale = ldexpf(1.0f, ex < -100 ? 115 : 15 - ex);
                 }
                 // (an eps so small that the scale takes it below the normal range must not become 0: 0 / eps is what a token without
                 // anything above zero gives)
                 const float scaled_eps = eps > 0.f ? fmaxf(eps * scale, 1.1754944e-38f) : 0.f;
-                if (lane == 0) *(float*)(tail(i) + S::kTail - 16) = scaled_eps;
+                if (l == 0) *(float*)(tail(i) + S::kTail - 16) = scaled_eps;
+                bool small = false;
 #pragma unroll
                 for (int j = 0; j < 3; ++j) {
                     Vec part[3];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         float x = v[j][e] * scale;
+                        small = small || (v[j][e] != 0.f && fabsf(x) < kLeast);     // (as & and |, without branches, it costs 31 registers in scratch)
 #pragma unroll
                         for (int p = 0; p < 3; ++p) {
                             part[p][e] = Tr::from_f32(x);
-                            x = fabsf(x) < INFINITY ? x - Tr::to_f32(part[p][e]) : 0.f;
+                            x = fabsf(x) < INFINITY ? (x - Tr::to_f32(part[p][e])) * (p == 0 ? kUp : 1.0f) : 0.f;
                         }
                     }
                     if (j < 2) st[i][j] = part[0];
-                    else ksum[i] = part[0];
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        if (j < 2) *(Vec*)(tail(i) + p * 2048 + j * 1024 + lane * 16) = part[1 + p];
-                        else if (x16 == 0) *(Vec*)(tail(i) + 4096 + p * 64 + q * 16) = part[1 + p];
+                    for (int p = 0; p < 3; ++p) {
+                        if (j < 2 && p > 0) *(Vec*)(tail(i) + (p - 1) * 2048 + j * 1024 + l * 16) = part[p];
+                        else if (j == 2 && x16 == 0) *(Vec*)(tail(i) + 4096 + p * 64 + q * 16) = part[p];
                     }
                 }
+                in_parts = in_parts && !__any(small);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         } else {
 #pragma unroll
-            for (int i = 0; i < S::kHbw; ++i) {
-                const int m = wave + 8 * i;
-                const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
-#pragma unroll
-                for (int jc = 0; jc < 2; ++jc)
-#pragma unroll
-                    for (int jo = 0; jo < 2; ++jo)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) st[i][jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ksum[i][e] = s[(8 * q + e) * 33 + 32];
-            }
+            for (int i = 0; i < S::kHbw; ++i) load_fp32(b, wave + 8 * i, st[i], ksum[i]);
         }
+        return in_parts;
     };
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-    auto make_rows = [&](int to) {
-        if constexpr (kParts) {
+    // where chunk c + q of token x16's row is (16 chunks further on: 256 bytes)
+    auto row_at = [&](int c) { return x16 * S::kRow + ((c + q) ^ x16) * 16; };
+    auto rows_fp32 = [&](int to, int i, const f32x4 (&sv)[2][2], const float (&sk)[8]) {
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt) {
+            const Vec f = __builtin_bit_cast(Vec, qv[i][jt]);
+            float rq[8], den = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                rq[e] = fmaxf(Tr::to_f32(f[e]), 0.f);
+                den = fmaf(rq[e], sk[e], den);
+            }
+            den += __shfl_xor(den, 16);
+            den += __shfl_xor(den, 32);
+            const f32x4 lo = {rq[0], rq[1], rq[2], rq[3]}, hi = {rq[4], rq[5], rq[6], rq[7]};
+            const f32x4 n0 = F32::mma16(F32::mma16(z, sv[0][0], lo), sv[1][0], hi);
+            const f32x4 n1 = F32::mma16(F32::mma16(z, sv[0][1], lo), sv[1][1], hi);
+            const float inv = 1.0f / (den + eps);
+            Vec o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                o[r] = Tr::from_f32(n0[r] * inv);
+                o[4 + r] = Tr::from_f32(n1[r] * inv);
+            }
+            *(u32x4*)(lds + to + jt * 16 * S::kRow + row_at(wave * 4) + i * 512) = __builtin_bit_cast(u32x4, o);
+        }
+    };
+    auto make_rows = [&](int to, int b, auto in_parts) {
+        if constexpr (kParts && !in_parts) {
+#pragma unroll
+            for (int i = 0; i < S::kHbw; ++i)
+                if (wave + 8 * i < n_hb) {
+                    f32x4 sv[2][2];
+                    float sk[8];
+                    load_fp32(b, wave + 8 * i, sv, sk);
+                    rows_fp32(to, i, sv, sk);
+                }
+        } else if constexpr (kParts) {
 #pragma unroll
             for (int i = 0; i < S::kHbw; ++i) {
                 const int m = wave + 8 * i;
@@ -472,12 +518,24 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
                     for (int p = 2; p >= 0; --p) {
                         const char* at = tail(i) + (p - 1) * 2048 + lane * 16;
                         const Vec s0 = p > 0 ? *(const Vec*)at : st[i][0], s1 = p > 0 ? *(const Vec*)(at + 1024) : st[i][1];
-                        const Vec sk = p > 0 ? *(const Vec*)(tail(i) + 4096 + (p - 1) * 64 + q * 16) : ksum[i];
+                        const Vec sk = *(const Vec*)(tail(i) + 4096 + p * 64 + q * 16);
 #pragma unroll
                         for (int jt = 0; jt < 2; ++jt) {
                             num[jt][0] = Tr::mma_vec(num[jt][0], s0, f[jt]);
                             num[jt][1] = Tr::mma_vec(num[jt][1], s1, f[jt]);
                             den[jt] = Tr::mma_vec(den[jt], sk, f[jt]);
+                        }
+                        if constexpr (kF16) {
+                            if (p == 1) {
+#pragma unroll
+                                for (int jt = 0; jt < 2; ++jt) {
+#pragma unroll
+                                    for (int jo = 0; jo < 2; ++jo)
+#pragma unroll
+                                        for (int r = 0; r < 4; ++r) num[jt][jo][r] *= 1.0f / kUp;
+                                    den[jt][0] *= 1.0f / kUp;       // (its other rows are not used)
+                                }
+                            }
                         }
                     }
 #pragma unroll
@@ -490,75 +548,56 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
                             o[r] = Tr::from_f32(n0[r] * inv);
                             o[4 + r] = Tr::from_f32(n1[r] * inv);
                         }
-                        *(u32x4*)(lds + to + (jt * 16 + x16) * S::kRow + (((m * 4 + q) ^ x16) * 16)) = __builtin_bit_cast(u32x4, o);
+                        *(u32x4*)(lds + to + jt * 16 * S::kRow + row_at(wave * 4) + i * 512) = __builtin_bit_cast(u32x4, o);
                     }
                 }
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < S::kHbw; ++i) {
-                const int m = wave + 8 * i;
-                if (m < n_hb) {
+            for (int i = 0; i < S::kHbw; ++i)
+                if (wave + 8 * i < n_hb) rows_fp32(to, i, st[i], ksum[i]);
+        }
+    };
+    // The tiles of image b up to t_end: a tile's rows, the next one's Q on its way, its projection.  A loop for each kind of state: with the
+    // choice inside a tile, 8 x 8192 tokens, 8 heads, take 146.3 us in fp16 and 146.8 in bf16 instead of 143.7 and 145.5.  (With 16 head-branches
+    // the kernel has every register there is; five of the prologue's wait in scratch, outside of these loops.)
+    long t = t_begin;
+    auto tiles = [&](int b, auto in_parts) {
+        const long last = (long)(b + 1) * tiles_per_image < t_end ? (long)(b + 1) * tiles_per_image : t_end;
+        for (; t < last; ++t) {
+            const int here = (int)((t - t_begin) & 1) * S::kTile, n0 = (int)(t % tiles_per_image) * S::TB;
+            make_rows(here, b, in_parts);
+            if (t + 1 < t_end) fetch_q(t + 1);
+            __syncthreads();                // rows of tile t complete; nobody reads the other tile any more
+            f32x4 acc[2][2] = {{z, z}, {z, z}};
+            if (live) {
+#pragma unroll
+                for (int kk = 0; kk < KCH; ++kk)
 #pragma unroll
                     for (int jt = 0; jt < 2; ++jt) {
-                        const Vec f = __builtin_bit_cast(Vec, qv[i][jt]);
-                        float rq[8], den = 0.f;
+                        const Vec bf = __builtin_bit_cast(Vec, *(const u32x4*)(lds + here + jt * 16 * S::kRow + row_at(kk % 4 * 4) + kk / 4 * 256));
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            rq[e] = fmaxf(Tr::to_f32(f[e]), 0.f);
-                            den = fmaf(rq[e], ksum[i][e], den);
-                        }
-                        den += __shfl_xor(den, 16);
-                        den += __shfl_xor(den, 32);
-                        const f32x4 lo = {rq[0], rq[1], rq[2], rq[3]}, hi = {rq[4], rq[5], rq[6], rq[7]};
-                        const f32x4 n0 = F32::mma16(F32::mma16(z, st[i][0][0], lo), st[i][1][0], hi);
-                        const f32x4 n1 = F32::mma16(F32::mma16(z, st[i][0][1], lo), st[i][1][1], hi);
-                        const float inv = 1.0f / (den + eps);
-                        Vec o;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            o[r] = Tr::from_f32(n0[r] * inv);
-                            o[4 + r] = Tr::from_f32(n1[r] * inv);
-                        }
-                        *(u32x4*)(lds + to + (jt * 16 + x16) * S::kRow + (((m * 4 + q) ^ x16) * 16)) = __builtin_bit_cast(u32x4, o);
+                        for (int io = 0; io < 2; ++io) acc[io][jt] = Tr::mma_vec(acc[io][jt], wf[io][kk], bf);
                     }
+                // two 8-byte fragments leave in one 16-byte store (lane groups swapped: channels 16 (q % 2) + 8 (q / 2) .. +7)
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt) {
+                    const u32x2 even = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[0][jt]));
+                    const u32x2 odd = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[1][jt]));
+                    const u32x2 s0 = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
+                    const u32x2 s1 = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+                    const int n = n0 + jt * 16 + x16, oc = ch0 + (q & 1) * 16 + (q >> 1) * 8;
+                    if (n < N && oc < c_out) *(u32x4*)(out + ((long)b * N + n) * c_out + oc) = u32x4{s0[0], s1[0], s0[1], s1[1]};
                 }
             }
         }
     };
-    load_states((int)(t_begin / tiles_per_image));
-    make_rows(0);
-    for (long t = t_begin; t < t_end; ++t) {
-        const int here = (int)((t - t_begin) & 1) * S::kTile, next = S::kTile - here;
-        const bool more = t + 1 < t_end;
-        if (more) fetch_q(t + 1);
-        __syncthreads();                    // rows of tile t complete; nobody reads the other tile any more
-        const int b = (int)(t / tiles_per_image), n0 = (int)(t % tiles_per_image) * S::TB;
-        f32x4 acc[2][2] = {{z, z}, {z, z}};
-        if (live) {
-#pragma unroll
-            for (int kk = 0; kk < KCH; ++kk)
-#pragma unroll
-                for (int jt = 0; jt < 2; ++jt) {
-                    const Vec bf = __builtin_bit_cast(Vec, *(const u32x4*)(lds + here + (jt * 16 + x16) * S::kRow + (((kk * 4 + q) ^ x16) * 16)));
-#pragma unroll
-                    for (int io = 0; io < 2; ++io) acc[io][jt] = Tr::mma_vec(acc[io][jt], wf[io][kk], bf);
-                }
-            // two 8-byte fragments leave in one 16-byte store (lane groups swapped: channels 16 (q % 2) + 8 (q / 2) .. +7)
-#pragma unroll
-            for (int jt = 0; jt < 2; ++jt) {
-                const u32x2 even = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[0][jt]));
-                const u32x2 odd = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[1][jt]));
-                const u32x2 s0 = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
-                const u32x2 s1 = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
-                const int n = n0 + jt * 16 + x16, oc = ch0 + (q & 1) * 16 + (q >> 1) * 8;
-                if (n < N && oc < c_out) *(u32x4*)(out + ((long)b * N + n) * c_out + oc) = u32x4{s0[0], s1[0], s0[1], s1[1]};
-            }
-        }
-        if (more) {
-            const int b_next = (int)((t + 1) / tiles_per_image);
-            if (b_next != img) load_states(b_next);
-            make_rows(next);
+    while (t < t_end) {
+        const int b = (int)(t / tiles_per_image);
+        if (load_states(b)) {
+            if constexpr (kParts) tiles(b, std::true_type{});
+        } else {
+            tiles(b, std::false_type{});
         }
     }
 }

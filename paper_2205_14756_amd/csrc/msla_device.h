@@ -40,6 +40,12 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+// lane_id() out of nothing, so that neither it nor what is made of it stays in a register from before
+__device__ __forceinline__ int lane_id_again() {
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)zero));
+}
 
 template <class T> struct Traits;
 

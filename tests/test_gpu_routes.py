@@ -341,3 +341,44 @@ def test_head_size_32_keeps_an_overflow_in_the_filters_reach(dtype, scales, at):
         want = rows(0.0, [b for b in every if not some[b]])
         assert np.isfinite(got[1][here]).all() and np.array_equal(got[1][here], want[1][here]), f"branches reached: {some}"
     assert np.array_equal(got[0], rows(0.0, every)[0])
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# heads of 32, states in parts (2 and 10 head-branches): rows of the state 2^-13, 2^-24, 2^-27 and 2^-36 of the largest, each from one token, and queries
+# that see one or two of them.  Such a query's attention is that token's V (or their mean by weight), so what is left is one rounding of
+# it: half a unit of the storage type, 2^-11 or 2^-8 of the value, and 1 % of that for the fp32 sums
+@pytest.mark.parametrize("heads", [1, 5])
+def test_head_size_32_states_in_parts_of_wide_range(dtype, heads):
+    print(f"routes: head size 32, states of wide range {dtype} heads={heads}", flush=True)
+    B, H, W, C, Ct = 3, 100, 91, 96 * heads, 32 * heads
+    N, rng = H * W, np.random.default_rng(heads)
+    q, k = -np.abs(rng.standard_normal((B, N, heads, 32))), np.zeros((B, N, heads, 32))
+    v = np.sign(rng.standard_normal((B, N, heads, 32))) * (1.0 + np.abs(rng.standard_normal((B, N, heads, 32))))
+    k[..., :16] = 1024.0                                # Ksum 2^23.2
+    lone = {16 + i: 2.0 ** s for i, s in enumerate((10, -1, -4, -13))}
+    for i, (e, size) in enumerate(lone.items()):
+        k[:, 700 * i + 33, :, e] = size
+    seen = [(16,), (17,), (18,), (19,), (17, 18), (18, 19), (0, 3)]
+    for i, es in enumerate(seen):
+        q[:, i::len(seen) + 1][..., list(es)] = 1.0
+    q[:, len(seen)::len(seen) + 1][..., ::3] *= -1.0
+    q, k, v = (wk.round_to_dtype(a, dtype) for a in (q, k, v))
+    x = np.stack([q, k, v], 3).reshape(B, H, W, C)
+    dw = np.zeros((3 * Ct, 3, 3))
+    dw[:, 1, 1] = 1.0                                   # (the aggregated branch is the raw one)
+    w_proj = np.zeros((C, 2 * Ct))
+    w_proj[:2 * Ct] = np.eye(2 * Ct)
+    dev = lambda a: base.dev(np.ascontiguousarray(a), dtype)
+    got = base.host(msla.msla_forward(dev(x), dev(np.eye(C)), dev(dw.reshape(-1)), dev(np.tile(np.eye(32), (3 * heads, 1))[None]), dev(w_proj),
+                                      heads, 32, (3,), 1e-15)).reshape(B, N, C)[..., :2 * Ct].reshape(B, N, 2, heads, 32)
+    r, ks = np.maximum(q, 0.0), k.sum(1)
+    num = np.einsum("bnhe,bhef->bnhf", r, np.einsum("bnhe,bnhf->bhef", k, v))
+    want = num / (np.einsum("bnhe,bhe->bnh", r, ks) + 1e-15)[..., None]
+    tol = 1.01 * {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]
+    for branch in range(2):
+        for i, es in enumerate(seen[:-1]):
+            rows = slice(i, None, len(seen) + 1)
+            err = np.abs(got[:, rows, branch] - want[:, rows]) / np.abs(want[:, rows])
+            assert err.max() <= tol, f"branch {branch}, channels {es}: {err.max():.3e}"
+        err = np.linalg.norm(got[:, :, branch] - want) / np.linalg.norm(want)
+        assert err <= tol, f"branch {branch}: {err:.3e}"
