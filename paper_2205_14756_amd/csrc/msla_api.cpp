@@ -102,8 +102,12 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     long want = (target_blocks + (long)B * heads - 1) / ((long)B * heads);
     if (want < 1) want = 1;
     if (want > tiles) want = tiles;
+    // (a 7x7 scale takes the general kernel, two of whose workgroups share a compute unit: rounds of one would leave it half idle.  Us a
+    // module, bf16, 7x7, with those rounds / without: 9 x 23 x 113 tokens, 19 heads 218 / 174, 10 x 72 x 24, 22 heads 175 / 148)
+    bool sevens = false;
+    for (int i = 0; i < n_scales; ++i) sevens = sevens || scales[i] == 7;
     if (n_scales > 0 && dt == MSLA_F32) want = fp32_chunks(s, tiles, want);
-    else if (n_scales > 0) want = msla::chunks_in_rounds((long)B * heads, tiles, want, target_blocks);
+    else if (n_scales > 0 && !sevens) want = msla::chunks_in_rounds((long)B * heads, tiles, want, target_blocks);
     const long tpc = (tiles + want - 1) / want;
     s->tiles_per_chunk = (int)tpc;
     s->nchunks = (int)((tiles + tpc - 1) / tpc);

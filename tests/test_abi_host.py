@@ -210,6 +210,8 @@ def _f16_chunks(lib, B, H, W, heads, scales):
     (3, 64, 100, 17, (3, 5), 2),            # two scales share the chip: 102 of each in one round, not 153 in two
     (9, 100, 100, 6, (3,), 4),              # 216 in one round
     (2, 64, 128, 400, (5,), 1),             # more states than places
+    (9, 23, 113, 19, (7,), 2),              # a 7x7 scale: the general kernel, two workgroups a compute unit, 342 of them
+    (10, 72, 24, 22, (3, 7), 2),
 ])
 def test_matrix_core_workgroups_fill_whole_rounds(lib, B, H, W, heads, scales, chunks):
     assert chunks in _f16_chunks(lib, B, H, W, heads, scales)
