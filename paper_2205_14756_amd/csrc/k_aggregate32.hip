@@ -579,23 +579,30 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
     float* const red = (float*)lds;             // reused after the last tile
 
     const unsigned Lid = xcd_remap(blockIdx.x, gridDim.x);
-    if (Lid >= (unsigned)a.B * a.heads * a.nchunks) return;
+    const int tiles_x = (a.W + MTW - 1) / MTW, n_tiles = tiles_x * ((a.H + MTH - 1) / MTH);
+    const int filled = (n_tiles + a.tiles_per_chunk - 1) / a.tiles_per_chunk;      // (of nchunks)
+    if (Lid >= (unsigned)a.B * a.heads * filled) return;
     const int h = Lid % a.heads;
-    const int chunk = (Lid / a.heads) % a.nchunks;
-    const int b = Lid / (a.heads * a.nchunks);
+    const int chunk = (Lid / a.heads) % filled;
+    const int b = Lid / (a.heads * filled);
     const int Ct = a.heads * D32;
     const long N = (long)a.H * a.W, img_tok0 = (long)b * N;
     const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
+    for (int c = chunk + filled; c < a.nchunks; c += filled)       // chunks without tiles: empty sums
+        for (int j = threadIdx.x; j < kState32; j += kMfma32Threads) {
+            float* to = a.partials + (((long)b * a.S * a.heads + h) * a.nchunks + c) * kState32 + j;
+            to[(long)a.branch * a.heads * a.nchunks * kState32] = 0.f;
+            if constexpr (kRaw) to[0] = 0.f;
+        }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     const T* wgp = (const T*)a.w_gpw + (long)h * 3 * D32 * D32;
     T* q_ms = (T*)a.q_ms;
     const unsigned q_ms_tb = (unsigned)(a.S * Ct * SZ);
 
-    const int tiles_x = (a.W + MTW - 1) / MTW, n_tiles = tiles_x * ((a.H + MTH - 1) / MTH);
     const int tile_begin = chunk * a.tiles_per_chunk;
     const int tile_end = min(n_tiles, tile_begin + a.tiles_per_chunk);
-    const int n_my = tile_end > tile_begin ? tile_end - tile_begin : 0;
+    const int n_my = tile_end - tile_begin;
     struct TileAt {
         int ty0, tx0;
     };
@@ -770,7 +777,7 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
         };
         Batch ring[3];
         static_for<0, 3>([&](auto i) {
-            issue(here, 0, 2 * decltype(i)::value, ring[decltype(i)::value], n_my > 0);
+            issue(here, 0, 2 * decltype(i)::value, ring[decltype(i)::value], true);
             __builtin_amdgcn_sched_barrier(0);
         });
         int buf = 0;
@@ -931,7 +938,10 @@ hipError_t run_mfma32(const AggregateArgs& a, hipStream_t stream) {
     constexpr int kLds = Mfma32Lds<KS>::kBytes;
     const hipError_t e = allow_dynamic_lds<aggregate32_mfma_kernel<T, KS, kRaw>>(kLds);
     if (e != hipSuccess) return e;
-    const long nblocks = ((long)a.B * a.heads * a.nchunks + 7) / 8 * 8;         // whole rounds over the XCDs
+    const long tiles = (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW);
+    const long filled = (tiles + a.tiles_per_chunk - 1) / a.tiles_per_chunk;
+    if (filled > a.nchunks) return hipErrorInvalidValue;
+    const long nblocks = ((long)a.B * a.heads * filled + 7) / 8 * 8;         // whole rounds over the XCDs
     if (nblocks <= 0 || nblocks > 0x7fffffffL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((aggregate32_mfma_kernel<T, KS, kRaw>), dim3((unsigned)nblocks), dim3(kMfma32Threads), kLds, stream, a);
     return hipGetLastError();
@@ -960,7 +970,11 @@ hipError_t run32(const AggregateArgs& a, hipStream_t stream) {
         if ((a.do_raw != 0) != (a.copy_raw_q != 0)) return hipErrorInvalidValue;
         AggregateArgs g = a;        // tiles of 16 rows
         const long tiles = (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW);
-        g.tiles_per_chunk = (int)((tiles + a.nchunks - 1) / a.nchunks);
+        // The chunks may have been counted for a 7x7 scale beside it, more than this kernel has tiles or compute units for: its workgroups
+        // are counted by themselves and clear the states of the chunks that are left over.  (With a workgroup for every chunk, the empty ones
+        // were whole XCDs: 131 x 167 tokens, 6 heads, 3x3 + 7x7, fp16 176.3 us a module, now 159.7; 3 x 151 x 11, 9 heads, 5x5 + 7x7, bf16 156.4, 139.0.)
+        const long want = chunks_in_rounds((long)a.B * a.heads, tiles, std::min((long)a.nchunks, tiles), compute_units());
+        g.tiles_per_chunk = (int)((tiles + want - 1) / want);
         if (a.ks == 3) return a.do_raw ? run_mfma32<T, 3, true>(g, stream) : run_mfma32<T, 3, false>(g, stream);
         return a.do_raw ? run_mfma32<T, 5, true>(g, stream) : run_mfma32<T, 5, false>(g, stream);
     }
