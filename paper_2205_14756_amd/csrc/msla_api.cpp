@@ -157,6 +157,9 @@ Workspace carve(const Shape& s, msla_dtype dt, bool with_maps = true) {
 //
 // With Q, K and V from memory (the core, and modules of more channels) it pays up to one workgroup a compute unit:
 // 2048 tokens, 32 heads of 512 channels (256) 34.1 / 32.1, the core of 8192 tokens, 8 heads (256) 19.7 / 17.3, of 2 x 8192 (512) 23.6 / 24.4.
+// With two scales it sweeps them one after the other where the other kernel has compute units for both, and twice as many partial states
+// tell where they are many a state: not above 64 tiles an image, and from four heads on (two in bf16).  The core, 3x3 + 5x5, fp16: 65536 tokens, 1 head 21.9 /
+// 24.3, 4 x 16384, 1 head 18.8 / 19.6, 25600, 2 heads 21.6 / 22.5, 8192, 8 heads 21.4 / 21.2; bf16: 65536, 1 head 23.0 / 25.0, 8192, 4 heads 20.5 / 20.1.
 bool small_map(const Shape& s, msla_dtype dt, bool fused) {
     if (dt == MSLA_F32 || s.n_scales < 1 || s.n_scales > 2) return false;
     for (int i = 0; i < s.n_scales; ++i)
@@ -164,6 +167,7 @@ bool small_map(const Shape& s, msla_dtype dt, bool fused) {
     if (s.n_scales == 2 && s.scales[0] == s.scales[1]) return false;
     const long tiles = (long)((s.H + msla::kAggSmallTileH - 1) / msla::kAggSmallTileH) *
                        ((s.W + msla::kAggSmallTileW - 1) / msla::kAggSmallTileW);
+    if (!fused && s.n_scales == 2 && (tiles > 64 || s.heads < (dt == MSLA_BF16 ? 2 : 4))) return false;
     return tiles * s.B * s.heads <= (fused && s.n_scales == 1 ? 2L : 1L) * msla::compute_units();
 }
 void make_small(Shape* s) {
