@@ -161,6 +161,9 @@ Workspace carve(const Shape& s, msla_dtype dt, bool with_maps = true) {
 // tell where they are many a state: not above 64 tiles an image, and from four heads on (two in bf16).  The core, 3x3 + 5x5, fp16: 65536 tokens, 1 head 21.9 /
 // 24.3, 4 x 16384, 1 head 18.8 / 19.6, 25600, 2 heads 21.6 / 22.5, 8192, 8 heads 21.4 / 21.2; bf16: 65536, 1 head 23.0 / 25.0, 8192, 4 heads 20.5 / 20.1.
 bool small_map(const Shape& s, msla_dtype dt, bool fused) {
+#ifdef MSLA_AGG_NO_MFMA
+    return false;       // (the build without the matrix-core aggregation has nothing that computes Q, K and V)
+#endif
     if (dt == MSLA_F32 || s.n_scales < 1 || s.n_scales > 2) return false;
     for (int i = 0; i < s.n_scales; ++i)
         if (s.scales[i] != 3 && s.scales[i] != 5) return false;

@@ -138,6 +138,9 @@ hipError_t launch_aggregate(int dt, const AggregateArgs& a, hipStream_t) {
     return hipSuccess;
 }
 hipError_t launch_aggregate_mfma(int dt, const AggregateArgs& a, hipStream_t) {
+#ifdef MSLA_AGG_NO_MFMA
+    return hipErrorNotSupported;
+#endif
     check_aggregate(dt, a, 16, "aggregate (matrix cores)");
     if ((long)a.nchunks * a.tiles_per_chunk <
         (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW))
@@ -146,6 +149,9 @@ hipError_t launch_aggregate_mfma(int dt, const AggregateArgs& a, hipStream_t) {
     return hipSuccess;
 }
 hipError_t launch_aggregate_mfma_pair(int dt, const AggregateArgs& a0, const AggregateArgs& a1, hipStream_t s) {
+#ifdef MSLA_AGG_NO_MFMA
+    return hipErrorNotSupported;
+#endif
     if (!((a0.ks == 3 && a1.ks == 5) || (a0.ks == 5 && a1.ks == 3))) return hipErrorNotSupported;
     (void)launch_aggregate_mfma(dt, a0, s);
     (void)launch_aggregate_mfma(dt, a1, s);

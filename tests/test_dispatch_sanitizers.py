@@ -15,10 +15,11 @@ HIP_INCLUDE = "/opt/rocm/include"
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(os.path.join(HIP_INCLUDE, "hip")),
                     reason="needs g++ and the HIP headers")
-def test_dispatcher_hands_every_kernel_pointers_inside_the_callers_buffers(tmp_path):
+@pytest.mark.parametrize("knobs", [[], ["-DMSLA_AGG_NO_MFMA"]], ids=["as_built", "without_matrix_core_aggregation"])
+def test_dispatcher_hands_every_kernel_pointers_inside_the_callers_buffers(tmp_path, knobs):
     exe = str(tmp_path / "sanitize_dispatch")
     cmd = ["g++", "-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
-           "-D__HIP_PLATFORM_AMD__", "-I" + HIP_INCLUDE, "-Wno-unused-result",
+           "-D__HIP_PLATFORM_AMD__", *knobs, "-I" + HIP_INCLUDE, "-Wno-unused-result",
            os.path.join(ROOT, "tests", "sanitize_dispatch_driver.cpp"),
            os.path.join(ROOT, "paper_2205_14756_amd", "csrc", "msla_api.cpp"), "-o", exe]
     build = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
