@@ -13,6 +13,9 @@
 namespace {
 
 constexpr int kMaxScales = 7;
+// Compute units that a call's plan counts on: an MI355X's, whatever device is current, because the plan decides the workspace's size, which a
+// host may ask for before it touches a device.  (How a launch shares out its plan asks the device: compute_units().)
+constexpr long kPlanUnits = 256;
 constexpr unsigned kStageBits = MSLA_OPT_STAGE_PROJECT | MSLA_OPT_STAGE_AGGREGATE | MSLA_OPT_STAGE_FINALIZE |
                                 MSLA_OPT_STAGE_APPLY;
 // with no stage bit set every stage runs
@@ -39,20 +42,20 @@ struct Shape {
 // How many workgroups share a state's tiles in the fp32 aggregation kernels, at most `most`.  Two of them are resident on a
 // compute unit (one with a 7x7 filter, by its LDS), so what a grid costs is its rounds over those places, each the
 // workgroup's tiles and 1.4 more for its start and end, 0.2 with the long tiles of a 7x7 filter (4 x 8192 tokens, 8 heads,
-// 5x5: one round of 8 tiles 99.9 us a module, two rounds of 4 104.5).  The numbers that fill 1 .. 4 times 256 places are
+// 5x5: one round of 8 tiles 99.9 us a module, two rounds of 4 104.5).  The numbers that fill 1 .. 4 times kPlanUnits places are
 // tried, and `most`; of equals the smallest is taken.  6 x 50 x 144 tokens, 14 heads, the core, 504 workgroups with 6 tiles each
 // against 588 with 5, which are two rounds: 5x5 125 and 152 us; 7x7, 252 with 12 against those 588, three rounds: 197 and 242.
 long fp32_chunks(const Shape* s, long tiles, long most) {
     const long states = (long)s->B * s->heads;
     long best = most, best_cost = 0;
     for (int r = 0; r <= 4; ++r) {
-        const long want = r < 4 ? 256L * (r + 1) / states : most;
+        const long want = r < 4 ? kPlanUnits * (r + 1) / states : most;
         if (want < 1 || want > most) continue;
         const long tpc = (tiles + want - 1) / want, blocks = states * ((tiles + tpc - 1) / tpc);
         long cost = 0;
         for (int i = 0; i < s->n_scales; ++i) {
             const bool wide = s->scales[i] == 7;
-            const long places = wide ? 256 : 512;
+            const long places = (wide ? 1 : 2) * kPlanUnits;
             cost += (blocks + places - 1) / places * (5 * tpc + (wide ? 1 : 7));
         }
         if (best_cost == 0 || cost < best_cost) {
@@ -92,10 +95,10 @@ msla_status check_shape(int B, int H, int W, int heads, int head_dim, const int*
     } else if (n_scales > 0) {
         tiles = (long)((H + msla::kAggMfmaTileH - 1) / msla::kAggMfmaTileH) *
                 ((W + msla::kAggMfmaTileW - 1) / msla::kAggMfmaTileW);
-        target_blocks = 256;   // one pipelined 8-wave workgroup per CU; each builds its operands once
+        target_blocks = kPlanUnits;   // one pipelined 8-wave workgroup per CU; each builds its operands once
         // (a 3x3 and a 5x5 scale share one launch: one workgroup per CU over both halves of that grid)
         if (n_scales == 2 && scales[0] + scales[1] == 8 && scales[0] != scales[1] && scales[0] != 1 && scales[1] != 1)
-            target_blocks = 128;
+            target_blocks = kPlanUnits / 2;
     } else {
         tiles = (N + 63) / 64;
     }
@@ -171,7 +174,7 @@ bool small_map(const Shape& s, msla_dtype dt, bool fused) {
     const long tiles = (long)((s.H + msla::kAggSmallTileH - 1) / msla::kAggSmallTileH) *
                        ((s.W + msla::kAggSmallTileW - 1) / msla::kAggSmallTileW);
     if (!fused && s.n_scales == 2 && (tiles > 64 || s.heads < (dt == MSLA_BF16 ? 2 : 4))) return false;
-    return tiles * s.B * s.heads <= (fused && s.n_scales == 1 ? 2L : 1L) * msla::compute_units();
+    return tiles * s.B * s.heads <= (fused && s.n_scales == 1 ? 2L : 1L) * kPlanUnits;
 }
 void make_small(Shape* s) {
     s->small = true;

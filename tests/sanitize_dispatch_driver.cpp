@@ -77,8 +77,9 @@ void release_all() {
 
 // ---------------------------------------------------------------- the HIP runtime calls of the dispatcher
 extern "C" {
-hipError_t hipGetDevice(int* d) { *d = 0; return hipErrorNoDevice; }
-hipError_t hipDeviceGetAttribute(int*, hipDeviceAttribute_t, int) { return hipErrorNoDevice; }
+static int g_device_calls = 0;
+hipError_t hipGetDevice(int* d) { ++g_device_calls; *d = 0; return hipErrorNoDevice; }
+hipError_t hipDeviceGetAttribute(int*, hipDeviceAttribute_t, int) { ++g_device_calls; return hipErrorNoDevice; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t) {
     inside(dst, bytes, "copy destination");
@@ -400,6 +401,9 @@ int main() {
         expect(msla_linear(x, w, y, 1031, 256, 1024, (msla_dtype)dt, nullptr), MSLA_OK, "linear");
         release_all();
     }
+    // (a workspace's size is a function of shape alone: nothing above asks for a device, and no stand-in does)
+    g_case = "device queries";
+    if (g_device_calls != 0) fail("the dispatcher asked for the current device");
     if (g_failures) {
         std::fprintf(stderr, "%d failures\n", g_failures);
         return 1;
