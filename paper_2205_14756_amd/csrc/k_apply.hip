@@ -1023,11 +1023,12 @@ hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, co
     // head-branches, fp16: 190 us a module tiled, 172; 6 x 7055, 288, 54, bf16: 264, 246; with four, 8 x 4096, 512, 64: fp16 224,
     // 229, bf16 239, 270)
     const int K = n_hb * 16;
-    // Beyond 1024 slots, in parts, while a workgroup has at most two pieces of 32 tokens x 128 channels (each fetches its weights).  Us a
+    // Beyond 1024 slots, in parts, while there are at most two pieces of 32 tokens x 128 channels a compute unit and a workgroup walks at most
+    // two of them (each fetches its weights; 896 channels leave four units idle, and 73 tiles would be three for some).  Us a
     // module, tiled / in parts, 512 channels, 3x3 + 5x5: 512 tokens fp16 65.0 / 34.7, bf16 74.3 / 37.9; 2048 bf16 (256 pieces) 78.8 / 44.1,
     // 2 x 2048 fp16 (512) 76.4 / 63.6, 4 x 2048 (1024) 89.2 / 105.7; 3 x 45 x 45 of 352, bf16 (576) 87.4 / 93.0.
-    const long pieces = (n_tokens / tokens_per_image) * ((tokens_per_image + 31) / 32) * ((c_out + 127) / 128);
-    if (dt != 0 && K > 1024 && K <= 4096 && pieces <= 2L * compute_units())
+    const long tiles = (n_tokens / tokens_per_image) * ((tokens_per_image + 31) / 32), pieces = tiles * ((c_out + 127) / 128);
+    if (dt != 0 && K > 1024 && K <= 4096 && pieces <= 2L * compute_units() && small_tiles_a_workgroup(tiles, c_out) <= 2)
         return launch_small_apply_project(dt, q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, stream);
     if (n_hb > 32 && (small_product(dt, n_tokens, K, c_out) || (dt != 0 && K <= 1024 && c_out <= 384)))
         return launch_small_apply_project(dt, q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out,

@@ -305,10 +305,7 @@ hipError_t run_small(const void* src, const void* w, Dest dest, SmallAttArgs aa,
     // time, and a second round of workgroups fetches them again (2048 tokens, 512 channels, 32 + 32 heads, fp16: 34.8 us
     // a module with one a CU, 35.6 with two where they fit, 37.1 with a grid for two and a remainder;
     // 3 x 1961 tokens, 192 channels, 36 head-branches, bf16: 70.1 against 74.2).
-    long groups = compute_units() / n_cb;
-    if (groups < 1) groups = 1;
-    const long per = (n_tiles + groups - 1) / groups;
-    groups = (n_tiles + per - 1) / per;
+    const long per = small_tiles_a_workgroup(n_tiles, c_out), groups = (n_tiles + per - 1) / per;
     const hipError_t e = allow_dynamic_lds<small_project_kernel<T, KC, kAtt, kMulti, Dest>>(kLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((small_project_kernel<T, KC, kAtt, kMulti, Dest>), dim3((unsigned)(groups * n_cb)),
@@ -325,7 +322,7 @@ hipError_t run_small_k(const void* src, const void* w, Dest dest, SmallAttArgs a
     if (K <= 1024) return run_small<T, 32, kAtt, false, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
     if constexpr (kAtt) {
         // (parts of 768 slots; of 1024, bf16 would spill)
-        return run_small<T, 24, kAtt, true, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
+        if (K <= 4096) return run_small<T, 24, kAtt, true, Dest>(src, w, dest, aa, n_tokens, K, c_out, n_tiles, tiles_per_image, stream);
     }
     return hipErrorNotSupported;
 }

@@ -120,7 +120,7 @@ hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, co
                                 const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
                                 int n_hb, int c_out, float eps, hipStream_t stream);
 
-// The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots (k_small.hip; apply + projection up to 4096): the callers take the
+// The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots (k_small.hip; apply + projection up to 4096, in parts): the callers take the
 // projections where few enough tokens make the weights what a workgroup mostly fetches (small_product), the apply + projection there
 // and, whatever the number of tokens, up to 384 output channels (launch_apply_project).  They return hipErrorNotSupported, without
 // launching, for other types and contractions.
@@ -132,6 +132,11 @@ hipError_t launch_small_qkv_project(int dt, const void* x, const void* w_qkv, vo
 hipError_t launch_small_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
                                       const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
                                       int n_hb, int c_out, float eps, hipStream_t stream);
+// Tiles of 32 tokens that a workgroup of those kernels walks: one workgroup a compute unit, of 128 output channels
+inline long small_tiles_a_workgroup(long n_tiles, int c_out) {
+    const long n_cb = (c_out + 127) / 128, groups = compute_units() / n_cb > 0 ? compute_units() / n_cb : 1;
+    return (n_tiles + groups - 1) / groups;
+}
 // whether a [n_tokens x K] by [K x c_out] product is "small" in that sense
 inline bool small_product(int dt, long n_tokens, int K, int c_out) {
     return dt != 0 && K > 256 && K <= 1024 && ((n_tokens + 31) / 32) * ((c_out + 127) / 128) <= 8L * compute_units();
