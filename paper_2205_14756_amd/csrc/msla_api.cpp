@@ -187,7 +187,9 @@ Workspace carve_module(Shape* s, int C, msla_dtype dt) {
     return carve(*s, dt);
 }
 // make_small where the K|V map of the workspace is not used (the kernel computes K and V, or the caller's map is read): the partial
-// states of the smaller tiles, more of them, take its place, and the workspace keeps its size.  False if they do not fit.
+// states of the smaller tiles, more of them, take its place, and the workspace keeps its size.  False if they do not fit: 1088 bytes a
+// tile, head and branch against 64 a token and head, so an image needs some 17 tokens a tile and branch.  One pixel, or a map three columns wide,
+// keeps the larger tiles (and there is nothing to gain: 4 x 24 x 3 tokens, 4 heads, 3x3 + 5x5, fp16 21.3 us a module).
 bool make_small_in_kv(Shape* s, msla_dtype dt, Workspace* w) {
     Shape t = *s;
     make_small(&t);

@@ -138,10 +138,36 @@ hipError_t launch_aggregate(int dt, const AggregateArgs& a, hipStream_t) {
         fail("aggregate: the chunks do not cover the image's tiles");
     return hipSuccess;
 }
+// one workgroup a tile of 8 x 32 tokens; with w_qkv, Q, K and V are still to be computed from x [T, C]
+static int g_small_maps = 0, g_small_modules = 0;
+static hipError_t check_small(int dt, const AggregateArgs& a) {
+    ++g_small_maps;
+    if (a.nchunks != ((a.H + kAggSmallTileH - 1) / kAggSmallTileH) * ((a.W + kAggSmallTileW - 1) / kAggSmallTileW) || a.tiles_per_chunk != 1)
+        fail("aggregate (small maps): not one chunk a tile");
+    if (a.ks != 3 && a.ks != 5) fail("aggregate (small maps): filter size");
+    if (a.w_qkv == nullptr) {
+        check_aggregate(dt, a, 16, "aggregate (small maps)");
+        return hipSuccess;
+    }
+    ++g_small_modules;
+    const size_t e = esz(dt), T = (size_t)a.B * a.H * a.W, Ct = (size_t)a.heads * 16;
+    const size_t x = T * a.C * e, partials = (size_t)a.B * a.S * a.heads * a.nchunks * 272 * 4;
+    if (a.q != a.k || a.q != a.v || a.C > kAggSmallMaxC) fail("aggregate (small maps): x");
+    inside(a.q, x, "aggregate (small maps) x");
+    inside(a.w_qkv, 3 * Ct * a.C * e, "aggregate (small maps) w_qkv");
+    inside(a.w_dw, 3 * Ct * a.ks * a.ks * e, "aggregate (small maps) w_dw of the scale");
+    inside(a.w_gpw, 3 * Ct * 16 * e, "aggregate (small maps) w_gpw of the scale");
+    inside(a.q_ms, T * a.S * Ct * e, "aggregate (small maps) q_ms");
+    inside(a.partials, partials, "aggregate (small maps) partial states");
+    if (a.branch < 1 || a.branch >= a.S) fail("aggregate (small maps): branch index out of range");
+    disjoint({{a.q, x, "x"}, {a.q_ms, T * a.S * Ct * e, "q_ms"}, {a.partials, partials, "partial states"}});
+    return hipSuccess;
+}
 hipError_t launch_aggregate_mfma(int dt, const AggregateArgs& a, hipStream_t) {
 #ifdef MSLA_AGG_NO_MFMA
     return hipErrorNotSupported;
 #endif
+    if (a.small) return check_small(dt, a);
     check_aggregate(dt, a, 16, "aggregate (matrix cores)");
     if ((long)a.nchunks * a.tiles_per_chunk <
         (long)((a.H + kAggMfmaTileH - 1) / kAggMfmaTileH) * ((a.W + kAggMfmaTileW - 1) / kAggMfmaTileW))
@@ -388,6 +414,9 @@ int main() {
         {1, 128, 30, 40, 16, 8, {5}},         // heads of 8: pairs on the head-size-16 path
         {2, 64, 7, 9, 8, 8, {}},
         {5, 32, 3, 500, 2, 16, {5}},          // wide and flat
+        {2, 96, 40, 50, 6, 16, {5, 3}},       // a small map with two scales
+        {1, 16, 1, 33, 1, 16, {5}},           // ... and the smallest whose partial states fit where K|V would be
+        {1, 192, 17, 40, 24, 8, {3}},         // ... in pairs of heads of 8
     };
     for (const Mod& m : mods)
         for (int dt = 0; dt < 3; ++dt) run_module(m, dt);
@@ -401,6 +430,10 @@ int main() {
         expect(msla_linear(x, w, y, 1031, 256, 1024, (msla_dtype)dt, nullptr), MSLA_OK, "linear");
         release_all();
     }
+#ifndef MSLA_AGG_NO_MFMA
+    g_case = "small maps";
+    if (msla::g_small_maps == 0 || msla::g_small_modules == 0 || msla::g_small_maps == msla::g_small_modules) fail("a kind of small map was not reached");
+#endif
     // (a workspace's size is a function of shape alone: nothing above asks for a device, and no stand-in does)
     g_case = "device queries";
     if (g_device_calls != 0) fail("the dispatcher asked for the current device");

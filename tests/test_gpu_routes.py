@@ -206,12 +206,15 @@ def test_fp32_linear_on_full_maps(n, c_in, c_out):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 # one workgroup a tile of 8 x 32 tokens, Q, K and V computed there: 16, 48, 64, 80, 128, 144 and 192 input channels (the last step of
-# 32 half empty in four of them), one and two scales in either order, several images, one pixel, ragged tiles, 252 workgroups; then 208
-# channels (Q, K and V read) and the first shape past a round of workgroups
-@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 16, 1, 1, 1, (5,)), (3, 48, 9, 33, 3, (3,)), (2, 64, 8, 32, 4, (3, 5)),
+# 32 half empty in four of them), one and two scales in either order, several images, ragged tiles; one row of 33 tokens (fewer, as the one pixel,
+# have no room for their partial states and keep the separate projection); with one scale 258 and 512 workgroups, the most there are, and 513; with
+# two 256 and 258; then 208 channels (Q, K and V read)
+@pytest.mark.parametrize("B,C,H,W,heads,scales", [(1, 16, 1, 1, 1, (5,)), (1, 16, 1, 33, 1, (5,)), (1, 16, 1, 33, 1, (3, 5)),
+                                                  (3, 48, 9, 33, 3, (3,)), (2, 64, 8, 32, 4, (3, 5)),
                                                   (1, 80, 17, 31, 5, (5, 3)), (7, 128, 23, 40, 6, (5,)), (2, 144, 7, 65, 9, (3,)),
                                                   (1, 192, 40, 60, 12, (3, 5)), (2, 208, 21, 45, 13, (3, 5)), (1, 128, 64, 128, 8, (5,)),
-                                                  (1, 48, 8, 32 * 43, 6, (5,))])
+                                                  (4, 64, 64, 128, 4, (5,)), (1, 48, 149, 285, 3, (5,)),
+                                                  (2, 64, 62, 127, 4, (3, 5)), (1, 48, 8, 32 * 43, 6, (3, 5)), (1, 48, 8, 32 * 43, 6, (5,))])
 def test_small_maps(dtype, B, C, H, W, heads, scales):
     print(f"routes: small map {dtype} {B}x{C}x{H}x{W} heads={heads} scales={scales}", flush=True)
     base.check_module(wk.random_module(37 + C + H, dtype, B, C, H, W, heads, 16, scales), dtype, heads, 16, scales)
