@@ -396,3 +396,40 @@ def test_head_size_32_states_in_parts_of_wide_range(dtype, heads):
             assert err.max() <= tol, f"branch {branch}, channels {es}: {err.max():.3e}"
         err = np.linalg.norm(got[:, :, branch] - want) / np.linalg.norm(want)
         assert err <= tol, f"branch {branch}: {err:.3e}"
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# the core with two scales: four heads and 64 tiles an image, the last that the small tiles take, and 65; one, two and three heads (two and three: in bf16)
+@pytest.mark.parametrize("B,H,W,heads,scales", [(1, 64, 250, 4, (3, 5)), (1, 100, 160, 4, (5, 3)), (2, 19, 45, 1, (3, 5)), (3, 9, 70, 2, (5, 3)),
+                                                (1, 40, 33, 3, (3, 5))])
+def test_core_of_small_maps_with_two_scales(dtype, B, H, W, heads, scales):
+    base.test_multiscale_state_and_core(dtype, B, H, W, heads, scales)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# heads of 32, an image whose map of two heads spans more than 2 GiB: 3x3 and 5x5 on the vector ALUs, each with the raw branch and without.  What the
+# projection takes of the first head is compared with a module of that head alone, whose map has half the size: a value may differ by four roundings (of
+# the aggregated maps, the attention and the result), and by more at one token in a thousand (Eq. (3) is ill-posed at some)
+@pytest.mark.parametrize("scales", [(3, 5), (5, 3)])
+def test_head_size_32_maps_beyond_2_gib(dtype, scales):
+    H = W = 2600
+    print(f"routes: head size 32, beyond 2 GiB {dtype} {scales}", flush=True)
+    assert H * W * 96 * 2 * 2 > 2 ** 31 > H * W * 96 * 2
+    t = wk.random_module(83, dtype, 1, 16, 8, 8, 2, 32, scales)
+    x = torch.randn(1, H, W, 16, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").to(base.TDT[dtype])
+    wdw, wg = base.weights(t, dtype, scales)
+    w_qkv, w_proj = base.dev(t["w_qkv"], dtype), base.dev(t["w_proj"], dtype).view(16, 3, 2, 32).clone()
+    w_proj[:, :, 1] = 0.0
+    both = msla.msla_forward(x, w_qkv, wdw, wg, w_proj.view(16, 192), 2, 32, scales)
+    at, first = 0, []
+    for k in scales:
+        first.append(wdw.reshape(-1)[at:at + 96 * k * k])
+        at += 192 * k * k
+    one = msla.msla_forward(x, w_qkv[:96].contiguous(), torch.cat(first), wg[:, :96].contiguous(), w_proj[:, :, 0].reshape(16, 96).contiguous(), 1, 32,
+                            scales)
+    torch.cuda.synchronize()
+    rms = float(one.float().square().mean().sqrt())
+    off = (both.float() - one.float()).abs() > 4 * {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype] * one.float().abs().clamp(min=rms)
+    share = float(off.any(-1).float().mean())
+    print(f"  tokens further off: {share:.2e}", flush=True)
+    assert bool(torch.isfinite(both).all()) and share <= 1e-3
