@@ -588,12 +588,6 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
     const int Ct = a.heads * D32;
     const long N = (long)a.H * a.W, img_tok0 = (long)b * N;
     const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
-    for (int c = chunk + filled; c < a.nchunks; c += filled)       // chunks without tiles: empty sums
-        for (int j = threadIdx.x; j < kState32; j += kMfma32Threads) {
-            float* to = a.partials + (((long)b * a.S * a.heads + h) * a.nchunks + c) * kState32 + j;
-            to[(long)a.branch * a.heads * a.nchunks * kState32] = 0.f;
-            if constexpr (kRaw) to[0] = 0.f;
-        }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     const T* wgp = (const T*)a.w_gpw + (long)h * 3 * D32 * D32;
@@ -835,6 +829,12 @@ __global__ __launch_bounds__(kMfma32Threads) void aggregate32_mfma_kernel(Aggreg
         char* const trans = lds + 2 * L::kMapBytes + sw * 2 * kTransBytes;
         Frag aggK[NB][4], aggK_lo[NB][4];
         int buf = 0;
+        for (int c = chunk + filled; c < a.nchunks; c += filled)       // chunks without tiles: empty sums
+            for (int j = threadIdx.x - 256; j < kState32; j += kMfma32Threads - 256) {
+                float* to = a.partials + (((long)b * a.S * a.heads + h) * a.nchunks + c) * kState32 + j;
+                to[(long)a.branch * a.heads * a.nchunks * kState32] = 0.f;
+                if constexpr (kRaw) to[0] = 0.f;
+            }
         __syncthreads();
         for (int i = 0; i < n_my; ++i) {
             const int gy0 = here.ty0 + 4 * part, gx = here.tx0 + 16 * strip;
