@@ -307,8 +307,10 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
     const unsigned L = xcd_remap(blockIdx.x, gridDim.x);
     const int cg = (int)(L % (unsigned)n_cg);
     const long t_begin = (long)(L / (unsigned)n_cg) * tiles_per_block;
-    const long t_end = t_begin + tiles_per_block < n_tt ? t_begin + tiles_per_block : n_tt;
-    if (t_begin >= t_end) return;
+    if (t_begin >= n_tt) return;
+    const int n_my = (int)(t_begin + tiles_per_block < n_tt ? tiles_per_block : n_tt - t_begin);
+    // the tile at hand: image and number in it (n_tt fits 31 bits)
+    int img = (int)((unsigned)t_begin / (unsigned)tiles_per_image), at = (int)t_begin - img * tiles_per_image;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id(), x16 = lane & 15, q = lane >> 4;
     const int K = n_hb * 32;
@@ -318,8 +320,7 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
     // Q of this wave's head-branches, both 16-token groups of a tile (a token past the image's end reads its last one, a
     // head-branch past the last reads the first: their rows are not written)
     u32x4 qv[S::kHbw][2];
-    auto fetch_q = [&](long t) {
-        const int b = (int)(t / tiles_per_image), n0 = (int)(t % tiles_per_image) * S::TB;
+    auto fetch_q = [&](int b, int n0) {
 #pragma unroll
         for (int i = 0; i < S::kHbw; ++i)
 #pragma unroll
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
                 qv[i][jt] = *(const u32x4*)(q_ms + ((long)b * N + (n < N ? n : N - 1)) * K + (m < n_hb ? m : 0) * 32 + q * 8);
             }
     };
-    fetch_q(t_begin);
+    fetch_q(img, at * S::TB);
 
     // weights: fragment (io, kk) = rows ch0 + 16 io + x16, slots 32 kk + 8q .. +7; slots past K and rows past c_out are zero
     Vec wf[2][KCH];
@@ -558,17 +559,21 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
                 if (wave + 8 * i < n_hb) rows_fp32(to, i, st[i], ksum[i]);
         }
     };
-    // The tiles of image b up to t_end: a tile's rows, the next one's Q on its way, its projection.  A loop for each kind of state: with the
+    // The tiles of an image: a tile's rows, the next one's Q on its way, its projection.  A loop for each kind of state: with the
     // choice inside a tile, 8 x 8192 tokens, 8 heads, take 146.3 us in fp16 and 146.8 in bf16 instead of 143.7 and 145.5.  (With 16 head-branches
     // the kernel has every register there is; five of the prologue's wait in scratch, outside of these loops.)
-    long t = t_begin;
-    auto tiles = [&](int b, auto in_parts) {
-        const long last = (long)(b + 1) * tiles_per_image < t_end ? (long)(b + 1) * tiles_per_image : t_end;
-        for (; t < last; ++t) {
-            const int here = (int)((t - t_begin) & 1) * S::kTile, n0 = (int)(t % tiles_per_image) * S::TB;
+    int i_tile = 0;
+    auto tiles = [&](auto in_parts) {
+        const int b = img;
+        for (; i_tile < n_my && img == b; ++i_tile) {
+            const int here = (i_tile & 1) * S::kTile, n0 = at * S::TB;
             make_rows(here, b, in_parts);
-            if (t + 1 < t_end) fetch_q(t + 1);
-            __syncthreads();                // rows of tile t complete; nobody reads the other tile any more
+            if (++at == tiles_per_image) {
+                ++img;
+                at = 0;
+            }
+            if (i_tile + 1 < n_my) fetch_q(img, at * S::TB);
+            __syncthreads();                // rows of the tile complete; nobody reads the other tile any more
             f32x4 acc[2][2] = {{z, z}, {z, z}};
             if (live) {
 #pragma unroll
@@ -592,12 +597,11 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
             }
         }
     };
-    while (t < t_end) {
-        const int b = (int)(t / tiles_per_image);
-        if (load_states(b)) {
-            if constexpr (kParts) tiles(b, std::true_type{});
+    while (i_tile < n_my) {
+        if (load_states(img)) {
+            if constexpr (kParts) tiles(std::true_type{});
         } else {
-            tiles(b, std::false_type{});
+            tiles(std::false_type{});
         }
     }
 }
