@@ -103,7 +103,9 @@ __device__ __forceinline__ void make_toeplitz(const TapWords<KS>& tw, int sub, t
     });
 }
 
-// The sweep of one wave: 16 columns x R rows of a tile whose halo lies in LDS, channel by channel, Q, K, V.  `rows` points at
+// The sweep of one wave: 16 columns x R rows of a tile whose halo lies in LDS, channel by channel, Q, K, V.  (The zeros around
+// a filter's taps are multiplied too: a Q that is not finite makes the aggregated Q of tokens up to five columns away NaN, in whose branch the
+// rectifier then finds nothing, where the filter alone would reach KS / 2.)  `rows` points at
 // the strip's first input row and column; gy0, gx_first are the image row and column of its first output; rout covers
 // this head's channels of the branch in the image's Q map.  `ragged` (wave-uniform): some of the tile lies outside the image.
 // Adds to the state: kv_agg (V before its grouped 1x1), ks_agg.

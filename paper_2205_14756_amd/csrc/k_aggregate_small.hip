@@ -6,9 +6,9 @@
 // instruction of the next, and 2 us more to its first data.  So there is one kernel less (the projection's
 // products for a tile, halo included, take 1.5 us), all eight waves stage the tile with every load in flight
 // at once, and then all eight sweep it (aggregate_sweep.h), instead of four waves staging for eight others as in the kernel that
-// walks many tiles (k_aggregate_mfma.hip).  8192 tokens of 128 channels, 8 heads, fp16: 8.5 us from first to last instruction (first
-// data at 2.5, staged at 5.7, swept at 7.5) where projection, launch and aggregation took 5.5 + 1.7 + 8.8; the module
-// 23.4 -> 19.0 us, the block 44.0 -> 38.6.
+// walks many tiles (k_aggregate_mfma.hip).  8192 tokens of 128 channels, 8 heads, fp16: some 9 us from first to last instruction (first
+// data at 2.5, staged at 6, swept in 1.8) where projection, launch and aggregation took 5.5 + 1.7 + 8.8; the module
+// 23.5 -> 19.8 us, the block 44.4 -> 38.5.
 //
 // Projection: 16 tokens x 48 channels a step, D[token][channel] = x W^T with x fragments straight from memory and the head's 48
 // rows of weights in LDS; a lane ends up with four tokens of one channel, which is the channel-planar form that the sweep wants.
@@ -53,8 +53,8 @@ struct SLds {
 
 // KSB: a second scale of the same module (0: none), with its filters w_dw_b, w_gpw_b and branch_b; it sweeps the same staged tile.
 // One scale leaves room for two workgroups a compute unit, 128 registers a wave, if x goes through them in two halves, one after
-// the other, and the filter's operands are made when the tile is staged.  That costs a lone workgroup nothing measurable (8192
-// tokens, 8 heads 19.1 us a module either way).  Two scales would spill.
+// the other, and the filter's operands are made when the tile is staged.  That costs a lone workgroup nothing measurable.  Two scales
+// would spill.
 template <class T, int KSA, int KSB, int KC>
 __global__ __launch_bounds__(kSmallThreads, KSB == 0 ? 4 : 2) void aggregate_small_kernel(AggregateArgs a, const T* w_dw_b, const T* w_gpw_b,
                                                                            int branch_b) {

@@ -153,13 +153,13 @@ Workspace carve(const Shape& s, msla_dtype dt, bool with_maps = true) {
 // workgroups are all on the chip at once, two a compute unit with one scale, one with two.
 //
 // In the module that kernel also computes Q, K and V, up to kAggSmallMaxC input channels (what it holds in registers and LDS).
-// Us a module, fp16, separate projection and tiles of 16 x 32 / this: 8192 tokens, 128 channels (256 workgroups) 23.3 / 19.1;
-// 2 x 8192 of 128 (512) 27.6 / 25.8; 4 x 8192 of 64 (512) 27.8 / 23.5; 2048 of 192, 3x3 25.6 / 21.4; bf16, 3x3 + 5x5, 4096 tokens of 96 (192)
-// 24.9 / 22.1.  Past the limits: 3 x 8192 of 128 (768) 31.4 / 32.9; 3x3 + 5x5, 3 x 4096 of 128 (384) 32.9 / 34.1.
-// With 256 channels a workgroup a head reads too much: 2048 tokens 25.4 with a separate projection, 25.8 without.
+// Us a module, fp16, separate projection and tiles of 16 x 32 / this: 8192 tokens, 128 channels (256 workgroups) 23.5 / 19.8;
+// 2 x 8192 of 128 (512) 27.6 / 25.7; 4 x 8192 of 64 (512) 27.8 / 23.7; 2048 of 192, 3x3 25.5 / 22.1; bf16, 3x3 + 5x5, 4096 tokens of 96 (192)
+// 24.9 / 22.3.  Past the limits: 3 x 8192 of 128 (768) 31.0 / 33.4; 3x3 + 5x5, 3 x 4096 of 128 (384) 30.3 / 35.2.
+// With 256 channels a workgroup a head reads too much: 2048 tokens 25.4 with a separate projection, not below 25.8 without.
 //
 // With Q, K and V from memory (the core, and modules of more channels) it pays up to one workgroup a compute unit:
-// 2048 tokens, 32 heads of 512 channels (256) 34.1 / 32.1, the core of 8192 tokens, 8 heads (256) 19.7 / 17.3, of 2 x 8192 (512) 23.6 / 24.4.
+// 2048 tokens, 32 heads of 512 channels (256) 34.2 / 32.1, the core of 8192 tokens, 8 heads (256) 19.7 / 17.0, of 2 x 8192 (512) 23.6 / 24.1.
 // With two scales it sweeps them one after the other where the other kernel has compute units for both, and twice as many partial states
 // tell where they are many a state: not above 64 tiles an image, and from four heads on (two in bf16).  The core, 3x3 + 5x5, fp16: 65536 tokens, 1 head 21.9 /
 // 24.3, 4 x 16384, 1 head 18.8 / 19.6, 25600, 2 heads 21.6 / 22.5, 8192, 8 heads 21.4 / 21.2; bf16: 65536, 1 head 23.0 / 25.0, 8192, 4 heads 20.5 / 20.1.
