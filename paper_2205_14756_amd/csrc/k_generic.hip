@@ -331,6 +331,119 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
     };
     fetch_q(img, at * S::TB);
 
+    // kParts: a head-branch's state and Ksum are operands of the storage type, each value in three parts (its first, second and third 8
+    // or 11 significant bits), times a power of two that puts the largest at 2^14 to 2^15 (numerator and denominator scale together).
+    // fp16 ends at 2^-24, so its second and third parts are kept 2^12 times larger and their products' sums scaled back before the first
+    // part's are added: all 24 bits of every value down to kLeast, 2^-28 of the largest (bf16: 2^-115).  A wave whose head-branches have a
+    // smaller one that is not 0 takes fp32 products, as without kParts, with the states from memory (in_parts).  The state's first part stays in
+    // registers, the others and Ksum wait in LDS, where only this wave looks for them.  Else they are fp32 operands.
+    constexpr bool kF16 = std::is_same<T, _Float16>::value;
+    constexpr float kUp = kF16 ? 4096.0f : 1.0f, kLeast = kF16 ? 0x1p-13f : 0x1p-100f;
+    typedef typename std::conditional<kParts, Vec, f32x4[2]>::type State;
+    State st[S::kHbw][2];           // kParts: [output half]; else [contraction half][output half]
+    float ksum[kParts ? 1 : S::kHbw][8];
+    const int fo = 8 * (x16 >> 2) + (x16 & 3);
+    auto tail = [&](int i) { return lds + S::kWork + (wave + 8 * i) * S::kTail; };
+    auto load_fp32 = [&](int b, int m, f32x4 (&sv)[2][2], float (&sk)[8]) {
+        const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+        const int l = kParts ? lane_id_again() : lane, q = l >> 4, fo = 8 * ((l & 15) >> 2) + (l & 3);
+#pragma unroll
+        for (int jc = 0; jc < 2; ++jc)
+#pragma unroll
+            for (int jo = 0; jo < 2; ++jo)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sv[jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sk[e] = s[(8 * q + e) * 33 + 32];
+    };
+    auto read_state = [&](int b, int i, float (&v)[3][8]) {
+        const int l = lane_id_again(), q = l >> 4, fo = 8 * ((l & 15) >> 2) + (l & 3);       // (no register for this during the tiles)
+        const int m = wave + 8 * i;
+        const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[0][e] = s[(8 * q + e) * 33 + fo];
+            v[1][e] = s[(8 * q + e) * 33 + fo + 4];
+            v[2][e] = s[(8 * q + e) * 33 + 32];
+        }
+    };
+    // (whether it is whole in parts)
+    auto make_parts = [&](int i, const float (&v)[3][8], auto straight) {
+        const int l = lane_id_again(), x16 = l & 15, q = l >> 4;
+        float mx = 0.f;
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[j][e]) < INFINITY ? fabsf(v[j][e]) : 0.f);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        float scale = 1.0f;
+        if (mx > 0.f) {
+            int ex;
+            frexpf(mx, &ex);
+            scale = ldexpf(1.0f, ex < -100 ? 115 : 15 - ex);
+        }
+        // (an eps so small that the scale takes it below the normal range must not become 0: 0 / eps is what a token without
+        // anything above zero gives)
+        const float scaled_eps = eps > 0.f ? fmaxf(eps * scale, 1.1754944e-38f) : 0.f;
+        if (l == 0) *(float*)(tail(i) + S::kTail - 16) = scaled_eps;
+        bool small = false;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            Vec part[3];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float x = v[j][e] * scale;
+                // (straight: without branches, which beside the weights costs 30 registers in scratch)
+                if constexpr (straight) small = small | ((v[j][e] != 0.f) & (fabsf(x) < kLeast));
+                else small = small || (v[j][e] != 0.f && fabsf(x) < kLeast);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    part[p][e] = Tr::from_f32(x);
+                    x = fabsf(x) < INFINITY ? (x - Tr::to_f32(part[p][e])) * (p == 0 ? kUp : 1.0f) : 0.f;
+                }
+            }
+            if constexpr (kParts)
+                if (j < 2) st[i][j] = part[0];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                if (j < 2 && p > 0) *(Vec*)(tail(i) + (p - 1) * 2048 + j * 1024 + l * 16) = part[p];
+                else if (j == 2 && x16 == 0) *(Vec*)(tail(i) + 4096 + p * 64 + q * 16) = part[p];
+            }
+        }
+        return !__any(small);
+    };
+    auto wave_sees_lds = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto load_states = [&](int b) {
+        bool in_parts = kParts;
+        if constexpr (kParts) {
+#pragma unroll
+            for (int i = 0; i < S::kHbw; ++i) {
+                float v[3][8];
+                read_state(b, i, v);
+                in_parts = make_parts(i, v, std::false_type{}) && in_parts;
+            }
+            wave_sees_lds();
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::kHbw; ++i) load_fp32(b, wave + 8 * i, st[i], ksum[i]);
+        }
+        return in_parts;
+    };
+    // With 16 head-branches, the first image's states are on their way before the weights and made into parts before those take the
+    // registers (8 x 8192 tokens, 8 heads, fp16 143.5 -> 140.8 us a module, bf16 144.5 -> 142.8; with 8, 4 x 8192, 4 heads 41.9 -> 42.2).
+    constexpr bool kFirst = kParts && KCH > 8;
+    float first[kFirst ? S::kHbw : 1][3][8];
+    bool whole = false;
+    if constexpr (kFirst) {
+#pragma unroll
+        for (int i = 0; i < S::kHbw; ++i) read_state(img, i, first[i]);
+    }
+
     // weights: fragment (io, kk) = rows ch0 + 16 io + x16, slots 32 kk + 8q .. +7; slots past K and rows past c_out are zero
     Vec wf[2][KCH];
     {
@@ -347,6 +460,12 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
             }
         };
         request(0);
+        if constexpr (kFirst) {
+            whole = true;
+#pragma unroll
+            for (int i = 0; i < S::kHbw; ++i) whole = make_parts(i, first[i], std::true_type{}) && whole;
+            wave_sees_lds();
+        }
         static_for<0, S::kSlabs>([&](auto sl_c) {
             constexpr int sl = decltype(sl_c)::value;
             if constexpr (sl + 1 < S::kSlabs) request(sl + 1);
@@ -373,94 +492,6 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
         *(u32x4*)(lds + row * S::kRow + ((c ^ (row & 15)) * 16)) = u32x4{0u, 0u, 0u, 0u};
     }
 
-    // kParts: a head-branch's state and Ksum are operands of the storage type, each value in three parts (its first, second and third 8
-    // or 11 significant bits), times a power of two that puts the largest at 2^14 to 2^15 (numerator and denominator scale together).
-    // fp16 ends at 2^-24, so its second and third parts are kept 2^12 times larger and their products' sums scaled back before the first
-    // part's are added: all 24 bits of every value down to kLeast, 2^-28 of the largest (bf16: 2^-115).  A wave whose head-branches have a
-    // smaller one that is not 0 takes fp32 products, as without kParts, with the states from memory (in_parts).  The state's first part stays in
-    // registers, the others and Ksum wait in LDS, where only this wave looks for them.  Else they are fp32 operands.
-    constexpr bool kF16 = std::is_same<T, _Float16>::value;
-    constexpr float kUp = kF16 ? 4096.0f : 1.0f, kLeast = kF16 ? 0x1p-13f : 0x1p-100f;
-    typedef typename std::conditional<kParts, Vec, f32x4[2]>::type State;
-    State st[S::kHbw][2];           // kParts: [output half]; else [contraction half][output half]
-    float ksum[kParts ? 1 : S::kHbw][8];
-    const int fo = 8 * (x16 >> 2) + (x16 & 3);
-    auto tail = [&](int i) { return lds + S::kWork + (wave + 8 * i) * S::kTail; };
-    auto load_fp32 = [&](int b, int m, f32x4 (&sv)[2][2], float (&sk)[8]) {
-        const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
-        const int l = kParts ? lane_id_again() : lane, q = l >> 4, fo = 8 * ((l & 15) >> 2) + (l & 3);
-#pragma unroll
-        for (int jc = 0; jc < 2; ++jc)
-#pragma unroll
-            for (int jo = 0; jo < 2; ++jo)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sv[jc][jo][r] = s[(8 * q + 4 * jc + r) * 33 + fo + 4 * jo];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sk[e] = s[(8 * q + e) * 33 + 32];
-    };
-    auto load_states = [&](int b) {
-        bool in_parts = kParts;
-        if constexpr (kParts) {
-            const int l = lane_id_again(), x16 = l & 15, q = l >> 4, fo = 8 * (x16 >> 2) + (x16 & 3);     // (no register for this during the tiles)
-#pragma unroll
-            for (int i = 0; i < S::kHbw; ++i) {
-                const int m = wave + 8 * i;
-                const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
-                float v[3][8], mx = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    v[0][e] = s[(8 * q + e) * 33 + fo];
-                    v[1][e] = s[(8 * q + e) * 33 + fo + 4];
-                    v[2][e] = s[(8 * q + e) * 33 + 32];
-                }
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[j][e]) < INFINITY ? fabsf(v[j][e]) : 0.f);
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-                float scale = 1.0f;
-                if (mx > 0.f) {
-                    int ex;
-                    frexpf(mx, &ex);
-                    scale = ldexpf(1.0f, ex < -100 ? 115 : 15 - ex);
-                }
-                // (an eps so small that the scale takes it below the normal range must not become 0: 0 / eps is what a token without
-                // anything above zero gives)
-                const float scaled_eps = eps > 0.f ? fmaxf(eps * scale, 1.1754944e-38f) : 0.f;
-                if (l == 0) *(float*)(tail(i) + S::kTail - 16) = scaled_eps;
-                bool small = false;
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    Vec part[3];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        float x = v[j][e] * scale;
-                        small = small || (v[j][e] != 0.f && fabsf(x) < kLeast);     // (as & and |, without branches, it costs 31 registers in scratch)
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) {
-                            part[p][e] = Tr::from_f32(x);
-                            x = fabsf(x) < INFINITY ? (x - Tr::to_f32(part[p][e])) * (p == 0 ? kUp : 1.0f) : 0.f;
-                        }
-                    }
-                    if (j < 2) st[i][j] = part[0];
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) {
-                        if (j < 2 && p > 0) *(Vec*)(tail(i) + (p - 1) * 2048 + j * 1024 + l * 16) = part[p];
-                        else if (j == 2 && x16 == 0) *(Vec*)(tail(i) + 4096 + p * 64 + q * 16) = part[p];
-                    }
-                }
-                in_parts = in_parts && !__any(small);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else {
-#pragma unroll
-            for (int i = 0; i < S::kHbw; ++i) load_fp32(b, wave + 8 * i, st[i], ksum[i]);
-        }
-        return in_parts;
-    };
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     // where chunk c + q of token x16's row is (16 chunks further on: 256 bytes)
     auto row_at = [&](int c) { return x16 * S::kRow + ((c + q) ^ x16) * 16; };
@@ -560,8 +591,7 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
         }
     };
     // The tiles of an image: a tile's rows, the next one's Q on its way, its projection.  A loop for each kind of state: with the
-    // choice inside a tile, 8 x 8192 tokens, 8 heads, take 146.3 us in fp16 and 146.8 in bf16 instead of 143.7 and 145.5.  (With 16 head-branches
-    // the kernel has every register there is; five of the prologue's wait in scratch, outside of these loops.)
+    // choice inside a tile, 8 x 8192 tokens, 8 heads, took 146.3 us in fp16 and 146.8 in bf16 instead of 143.7 and 145.5.
     int i_tile = 0;
     auto tiles = [&](auto in_parts) {
         const int b = img;
@@ -598,7 +628,8 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
         }
     };
     while (i_tile < n_my) {
-        if (load_states(img)) {
+        if (!kFirst || i_tile > 0) whole = load_states(img);
+        if (whole) {
             if constexpr (kParts) tiles(std::true_type{});
         } else {
             tiles(std::false_type{});
