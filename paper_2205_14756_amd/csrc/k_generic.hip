@@ -342,7 +342,6 @@ __global__ __launch_bounds__(512, 2) void apply32_project_kernel(const T* __rest
     typedef typename std::conditional<kParts, Vec, f32x4[2]>::type State;
     State st[S::kHbw][2];           // kParts: [output half]; else [contraction half][output half]
     float ksum[kParts ? 1 : S::kHbw][8];
-    const int fo = 8 * (x16 >> 2) + (x16 & 3);
     auto tail = [&](int i) { return lds + S::kWork + (wave + 8 * i) * S::kTail; };
     auto load_fp32 = [&](int b, int m, f32x4 (&sv)[2][2], float (&sk)[8]) {
         const float* s = kv32 + ((long)b * n_hb + (m < n_hb ? m : 0)) * kState;
