@@ -673,6 +673,13 @@ msla_status msla_ffn_forward(const void* y, const void* w1, const void* w_dw, co
     if (C % 16 != 0 || hidden % 16 != 0 || T > (1L << 31)) return MSLA_ERR_UNSUPPORTED;
     if (workspace_bytes < ffn_ws_bytes(T, hidden, dt)) return MSLA_ERR_WORKSPACE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
+    // one launch where that pays (it reads y beside a block while other blocks write out, so not in place)
+    const size_t map = (size_t)T * C * elem_size(dt);
+    const char *yb = static_cast<const char*>(y), *ob = static_cast<const char*>(out);
+    if (ob + map <= yb || yb + map <= ob) {
+        const hipError_t fused = msla::launch_ffn_fused((int)dt, y, w1, w_dw, w2, out, B, C, H, W, hidden, (int)act, hs);
+        if (fused != hipErrorNotSupported) return fused == hipSuccess ? MSLA_OK : MSLA_ERR_LAUNCH;
+    }
     char* h_pre = static_cast<char*>(workspace);
     if (msla::launch_linear_act((int)dt, y, w1, h_pre, T, C, hidden, (int)act, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
     // depthwise 3x3 + activation + hidden -> C projection + residual in one kernel (the depthwise result stays on chip)

@@ -146,6 +146,11 @@ inline bool small_product(int dt, long n_tokens, int K, int c_out) {
 //   out[n, c] = res[n, c] + sum_e act(DW3x3(h))[n, e] * w2[c, e]   (one kernel: the depthwise result stays on chip)
 hipError_t launch_ffn_dw_project(int dt, const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B,
                                  int H, int W, int E, int c_out, int act, hipStream_t stream);
+
+// The whole FFN in one launch, the expanded map on chip (k_ffn_fused.hip).  Returns hipErrorNotSupported without launching
+// where the two launches above are the form to take.  out must not overlap y.
+hipError_t launch_ffn_fused(int dt, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C,
+                            int H, int W, int E, int act, hipStream_t stream);
 //   y[n, o] = act(sum_c x[n, c] * w[o, c])   (k_project.hip; the activation is applied to the fp32 sums)
 hipError_t launch_linear_act(int dt, const void* x, const void* w, void* y, long n_tokens, int c_in, int c_out, int act,
                              hipStream_t stream);

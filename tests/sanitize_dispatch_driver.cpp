@@ -271,6 +271,17 @@ hipError_t launch_ffn_dw_project(int dt, const void* h, const void* w_dw, const 
     inside(out, T * c_out * e, "ffn out");
     return hipSuccess;
 }
+hipError_t launch_ffn_fused(int dt, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C, int H,
+                            int W, int E, int, hipStream_t) {
+    // (the operands are checked, then the two launches take the call, so that their carving is checked as well)
+    const size_t e = esz(dt), T = (size_t)B * H * W;
+    inside(y, T * C * e, "fused ffn y");
+    inside(w1, (size_t)E * C * e, "fused ffn w1");
+    inside(w_dw, (size_t)E * 9 * e, "fused ffn w_dw");
+    inside(w2, (size_t)C * E * e, "fused ffn w2");
+    inside(out, T * C * e, "fused ffn out");
+    return hipErrorNotSupported;
+}
 hipError_t launch_softmax_attention(int dt, const void* qkv, void* att, int B, int N, int heads, hipStream_t) {
     inside(qkv, (size_t)B * N * 3 * heads * 16 * esz(dt), "softmax qkv");
     inside(att, (size_t)B * N * heads * 16 * esz(dt), "softmax att");

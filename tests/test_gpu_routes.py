@@ -433,3 +433,17 @@ def test_head_size_32_maps_beyond_2_gib(dtype, scales):
     share = float(off.any(-1).float().mean())
     print(f"  tokens further off: {share:.2e}", flush=True)
     assert bool(torch.isfinite(both).all()) and share <= 1e-3
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("act", [0, 1])
+# the FFN in one launch: up to 128 channels and beyond, blocks of 64 and of 128 tokens (the last two of each); one, two and three
+# slabs of hidden channels, half a slab at the end, blocks cut off on both sides, images of less than a block
+@pytest.mark.parametrize("B,C,H,W,hidden", [
+    (1, 128, 4, 16, 32), (2, 16, 1, 1, 48), (1, 112, 5, 17, 80), (3, 80, 9, 31, 16),
+    (9, 112, 12, 150, 112), (17, 128, 8, 256, 32),
+    (1, 256, 4, 16, 64), (1, 144, 7, 19, 16), (2, 208, 13, 5, 304), (11, 240, 19, 47, 336),
+    (12, 160, 12, 150, 48), (16, 256, 9, 128, 32),
+])
+def test_ffn_in_one_launch(dtype, act, B, C, H, W, hidden):
+    block.test_ffn(dtype, act, B, C, H, W, hidden)
