@@ -390,10 +390,12 @@ struct WsShape {
     static constexpr int kResident = sizeof(T) == 4 && 3 * kLds <= 160 * 1024 ? 3 : MSLA_WS_RESIDENT;
 };
 
-template <class T, int KCH, int IO, class Epilogue>
+// kPlanar: x is channel-planar, [images, c_in, plane] with plane tokens an image, instead of token-major.  A thread then brings
+// as many bytes of a tile in as many loads -- NS channels of 16 bytes' worth of tokens each -- and turns them on the way to LDS.
+template <class T, int KCH, int IO, bool kPlanar, class Epilogue>
 __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                          long n_tokens, int c_in, int c_out, int n_cg,
-                                                         long n_tt, long tiles_per_block, Epilogue ep) {
+                                                         long n_tt, long tiles_per_block, Epilogue ep, int plane) {
     typedef WsShape<T, KCH, IO> S;
     typedef typename Traits<T>::Vec Vec;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -412,7 +414,52 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
     const unsigned g_off = (threadIdx.x >> 3) * row_bytes + (threadIdx.x & 7) * 16;
     const unsigned l_off = (threadIdx.x >> 3) * S::kRow + (threadIdx.x & 7) * 16;
     u32x4 regs[S::NS];
+    // planar: channels p_ch .. p_ch + NS - 1, tokens p_tok .. p_tok + kRun - 1 of each tile; p_at is the first of them in x, p_n its
+    // place in its image, of the tile that is fetched next (tiles follow each other)
+    constexpr int kRun = 16 / (int)sizeof(T), kRuns = S::TB / kRun;
+    const int p_tok = (threadIdx.x % kRuns) * kRun, p_ch = (threadIdx.x / kRuns) * S::NS;
+    int p_n = 0;
+    const T* p_at = x;
+    if constexpr (kPlanar) {
+        const long t = t_begin * S::TB + p_tok, b = t / plane;
+        p_n = (int)(t - b * plane);
+        p_at = x + (b * c_in + p_ch) * plane + p_n;
+    }
     auto fetch = [&](long tile) {
+        if constexpr (kPlanar) {
+            const long left = tile < t_end ? n_tokens - (tile * S::TB + p_tok) : 0;       // tokens from the run's first on
+#pragma unroll
+            for (int i = 0; i < S::NS; ++i) {
+                regs[i] = u32x4{0u, 0u, 0u, 0u};
+                if (p_ch + i < c_in && left > 0) {
+                    const T* at = p_at + (long)i * plane;
+                    if (p_n + kRun <= plane && left >= kRun) {       // the whole run in one image (a row may start anywhere)
+                        __builtin_memcpy(&regs[i], __builtin_assume_aligned(at, sizeof(T)), 16);
+                    } else {
+                        T e[kRun];
+                        int n = p_n;
+#pragma unroll
+                        for (int k = 0; k < kRun; ++k) {
+                            e[k] = Traits<T>::from_f32(0.f);
+                            if (k < left) e[k] = *at;
+                            ++at;
+                            if (++n == plane) {
+                                n = 0;
+                                at += (long)(c_in - 1) * plane;
+                            }
+                        }
+                        __builtin_memcpy(&regs[i], e, 16);
+                    }
+                }
+            }
+            p_n += S::TB;
+            p_at += S::TB;
+            while (p_n >= plane) {
+                p_n -= plane;
+                p_at += (long)(c_in - 1) * plane;
+            }
+            return;
+        }
         const long tok0 = tile * S::TB;
         const BufRsrc xres = make_rsrc(x + tok0 * c_in, tile < t_end ? (n_tokens - tok0) * (long)row_bytes : 0);
 #pragma unroll
@@ -420,6 +467,30 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
             regs[i] = buf_load16(xres, (i * 128 + (threadIdx.x & 7) * 16 < row_bytes) ? g_off + i * 128 : kOobOffset, 0);
     };
     auto park = [&](char* buf) {
+        if constexpr (kPlanar) {
+            constexpr int kBytes = S::NS * (int)sizeof(T);
+            T e[S::NS][kRun];
+#pragma unroll
+            for (int i = 0; i < S::NS; ++i) __builtin_memcpy(e[i], &regs[i], 16);
+#pragma unroll
+            for (int k = 0; k < kRun; ++k) {
+                char* row = buf + (p_tok + k) * S::kRow;
+                if constexpr (128 % kBytes == 0) {               // the channels lie in one slab
+                    T v[S::NS];
+#pragma unroll
+                    for (int i = 0; i < S::NS; ++i) v[i] = e[i][k];
+                    const int at = p_ch * (int)sizeof(T);
+                    __builtin_memcpy(__builtin_assume_aligned(row + at / 128 * S::kSlab + at % 128, kBytes < 16 ? kBytes : 16), v, kBytes);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < S::NS; ++i) {
+                        const int at = (p_ch + i) * (int)sizeof(T);
+                        *(T*)(row + at / 128 * S::kSlab + at % 128) = e[i][k];
+                    }
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < S::NS; ++i) *(u32x4*)(buf + i * S::kSlab + l_off) = regs[i];
     };
@@ -579,9 +650,9 @@ __global__ __launch_bounds__(256, MSLA_WS_RESIDENT) void project_ws_kernel(const
     for (int job = 0; job < kJobs; ++job) flush_job(job);
 }
 
-template <class T, int KCH, int IO, class Epilogue>
+template <class T, int KCH, int IO, class Epilogue, bool kPlanar = false>
 hipError_t run_project_ws(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
-                          hipStream_t stream) {
+                          hipStream_t stream, int plane = 0) {
     typedef WsShape<T, KCH, IO> S;
     const int n_cg = (c_out + S::kChanBlock - 1) / S::kChanBlock;
     const long n_tt = (n_tokens + S::TB - 1) / S::TB;
@@ -592,10 +663,10 @@ hipError_t run_project_ws(const void* x, const void* w, long n_tokens, int c_in,
     const long groups = slots / n_cg > 0 ? slots / n_cg : 1;
     const long tiles_per_block = (n_tt + groups - 1) / groups;
     const long nblocks = (n_tt + tiles_per_block - 1) / tiles_per_block * n_cg;
-    const hipError_t e = allow_dynamic_lds<project_ws_kernel<T, KCH, IO, Epilogue>>(S::kLds);
+    const hipError_t e = allow_dynamic_lds<project_ws_kernel<T, KCH, IO, kPlanar, Epilogue>>(S::kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((project_ws_kernel<T, KCH, IO, Epilogue>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds,
-                       stream, (const T*)x, (const T*)w, n_tokens, c_in, c_out, n_cg, n_tt, tiles_per_block, ep);
+    hipLaunchKernelGGL((project_ws_kernel<T, KCH, IO, kPlanar, Epilogue>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds,
+                       stream, (const T*)x, (const T*)w, n_tokens, c_in, c_out, n_cg, n_tt, tiles_per_block, ep, plane);
     return hipGetLastError();
 }
 
@@ -609,15 +680,20 @@ hipError_t run_project_ws(const void* x, const void* w, long n_tokens, int c_in,
 // resident workgroups instead of three 129).  Against the tiled form, whose 256-channel x 128-token pieces leave most of
 // the chip idle on small maps and compute padding on narrow ones: that module 140 -> 126 us (this kernel 46 -> 33),
 // 1024 tokens of 64 channels 47 -> 38, 2 x 11550 of 176 189 -> 156, 576 of 256 106 -> 77.
-template <class T, class Epilogue>
+template <class T, class Epilogue, bool kPlanar = false>
 hipError_t run_project_ws32(const void* x, const void* w, long n_tokens, int c_in, int c_out, Epilogue ep,
-                            hipStream_t stream) {
-    if (c_in <= 32) return run_project_ws<T, 2, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-    if (c_in <= 64) return run_project_ws<T, 4, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-    if (c_in <= 96) return run_project_ws<T, 6, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-    if (c_in <= 128) return run_project_ws<T, 8, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-    if (c_in <= 192) return run_project_ws<T, 12, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
-    return run_project_ws<T, 16, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+                            hipStream_t stream, int plane = 0) {
+    if constexpr (kPlanar)
+        if (c_in > 128) return hipErrorInvalidValue;        // (see qkv_project_takes_planar)
+    if (c_in <= 32) return run_project_ws<T, 2, 1, Epilogue, kPlanar>(x, w, n_tokens, c_in, c_out, ep, stream, plane);
+    if (c_in <= 64) return run_project_ws<T, 4, 1, Epilogue, kPlanar>(x, w, n_tokens, c_in, c_out, ep, stream, plane);
+    if (c_in <= 96) return run_project_ws<T, 6, 1, Epilogue, kPlanar>(x, w, n_tokens, c_in, c_out, ep, stream, plane);
+    if (c_in <= 128) return run_project_ws<T, 8, 1, Epilogue, kPlanar>(x, w, n_tokens, c_in, c_out, ep, stream, plane);
+    if constexpr (!kPlanar) {
+        if (c_in <= 192) return run_project_ws<T, 12, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+        return run_project_ws<T, 16, 1, Epilogue>(x, w, n_tokens, c_in, c_out, ep, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <class T, class Epilogue>
@@ -717,49 +793,70 @@ hipError_t launch_linear_act(int dt, const void* x, const void* w, void* y, long
     return hipErrorInvalidValue;
 }
 
-// the weight-stationary form of the Q/K/V projection (at most 256 input channels)
-template <class T, bool kThrough>
+// the weight-stationary form of the Q/K/V projection (at most 256 input channels); plane > 0: of a channel-planar x
+template <class T, bool kThrough, bool kPlanar>
 hipError_t run_qkv_project_ws(const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw, long kv_tok_stride,
-                              long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads, hipStream_t stream) {
+                              long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads, hipStream_t stream, int plane) {
     const int c_out = 3 * heads * 16;
     if constexpr (sizeof(T) == 4) {
-        const QkvSplitDest<T, kThrough> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
-        return run_project_ws32<T>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
+        typedef QkvSplitDest<T, kThrough> D;
+        const D ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
+        return run_project_ws32<T, D, kPlanar>(x, w_qkv, n_tokens, c_in, c_out, ep, stream, plane);
     } else {
         // one head (48 channels) a wave
-        const QkvHeadDest<T, kThrough> ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
-        return c_in <= 128 ? run_project_ws<T, 4, 3, QkvHeadDest<T, kThrough>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream)
-                           : run_project_ws<T, 8, 3, QkvHeadDest<T, kThrough>>(x, w_qkv, n_tokens, c_in, c_out, ep, stream);
+        typedef QkvHeadDest<T, kThrough> D;
+        const D ep{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, heads * 16};
+        return c_in <= 128 ? run_project_ws<T, 4, 3, D, kPlanar>(x, w_qkv, n_tokens, c_in, c_out, ep, stream, plane)
+                           : run_project_ws<T, 8, 3, D, kPlanar>(x, w_qkv, n_tokens, c_in, c_out, ep, stream, plane);
     }
+}
+
+static bool qkv_weight_stationary(int dt, long n_tokens, int c_in, int heads) {
+    return c_in <= 256 && !(dt == 0 && c_in > 128 && tiled_fp32_fill(n_tokens, 3 * heads * 16) >= 900);
 }
 
 template <class T>
 hipError_t run_qkv_project(const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw,
                            long kv_tok_stride, long kv_head_stride, long kv_span, long n_tokens, int c_in, int heads,
-                           hipStream_t stream) {
+                           hipStream_t stream, int plane) {
     const int c_out = 3 * heads * 16;
-    if (c_in <= 256 && !(sizeof(T) == 4 && c_in > 128 && tiled_fp32_fill(n_tokens, c_out) >= 900)) {
+    if (qkv_weight_stationary(sizeof(T) == 4 ? 0 : 1, n_tokens, c_in, heads)) {
         const bool through = n_tokens * c_out * (long)sizeof(T) <= kThroughBytes;
-        return through ? run_qkv_project_ws<T, true>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span,
-                                                     n_tokens, c_in, heads, stream)
-                       : run_qkv_project_ws<T, false>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span,
-                                                      n_tokens, c_in, heads, stream);
+        auto run = [&](auto thr, auto pl) {
+            return run_qkv_project_ws<T, decltype(thr)::value, decltype(pl)::value>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride,
+                                                                                    kv_head_stride, kv_span, n_tokens, c_in, heads,
+                                                                                    stream, plane);
+        };
+        const std::true_type yes;
+        const std::false_type no;
+        if (plane > 0) return through ? run(yes, yes) : run(no, yes);
+        return through ? run(yes, no) : run(no, no);
     }
+    if (plane > 0) return hipErrorInvalidValue;
     return run_project_tiled<T>(x, w_qkv, n_tokens, c_in, c_out,
                                 QkvSplitDest<T>{(T*)q_ms, q_ms_stride, (T*)kv_raw, kv_tok_stride, kv_head_stride, kv_span,
                                                 n_tokens, heads * 16}, stream);
 }
 
+// A channel-planar x is taken as it is, without a transposition before, where the kernel's own turn costs less than that launch: each
+// group of output channels turns the tile again, and rows of 8 or 4 tokens' worth of bytes meet in few banks.  Modules, us with a
+// transposition / without: 16 bits 1 x 20 x 20 tokens, 208 channels 30.6 / 28.9, 16 x 64 x 64, 64 46.0 / 42.4, 8 x 101 x 99, 128
+// 101.4 / 100.5, 8 x 64 x 128, 256 146.7 / 133.7; fp32 (8 to 12 groups of 64 output channels from 192 on) 1600 tokens, 32 channels 23.6 / 21.5,
+// 16384, 64 41.1 / 38.5, 8192, 128 48.8 / 48.0, 16384, 128 73.0 / 75.4, 4096, 192 55.6 / 55.3, 4096, 256 68.8 / 76.8.
+bool qkv_project_takes_planar(int dt, long n_tokens, int c_in, int heads) {
+    return qkv_weight_stationary(dt, n_tokens, c_in, heads) && (dt != 0 || c_in <= 64 || (c_in <= 128 && n_tokens <= 8192));
+}
+
 hipError_t launch_qkv_project(int dt, const void* x, const void* w_qkv, void* q_ms, long q_ms_stride,
                               void* kv_raw, long kv_tok_stride, long kv_head_stride, long kv_span,
-                              long n_tokens, int c_in, int heads, hipStream_t stream) {
-    if (small_product(dt, n_tokens, c_in, 3 * heads * 16))
+                              long n_tokens, int c_in, int heads, hipStream_t stream, int plane) {
+    if (plane <= 0 && small_product(dt, n_tokens, c_in, 3 * heads * 16))
         return launch_small_qkv_project(dt, x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, n_tokens,
                                         c_in, heads, stream);
     switch (dt) {
-        case 0: return run_qkv_project<float>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, c_in, heads, stream);
-        case 1: return run_qkv_project<_Float16>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, c_in, heads, stream);
-        case 2: return run_qkv_project<__bf16>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, c_in, heads, stream);
+        case 0: return run_qkv_project<float>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, c_in, heads, stream, plane);
+        case 1: return run_qkv_project<_Float16>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, c_in, heads, stream, plane);
+        case 2: return run_qkv_project<__bf16>(x, w_qkv, q_ms, q_ms_stride, kv_raw, kv_tok_stride, kv_head_stride, kv_span, n_tokens, c_in, heads, stream, plane);
     }
     return hipErrorInvalidValue;
 }

@@ -517,9 +517,12 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     // (dead after the aggregation pass) and turned back into `out`.
     const void* x_tok = x;
     void* out_tok = out;
+    const bool x_planar = layout == MSLA_NCHW && !fused && msla::qkv_project_takes_planar((int)dt, s.T, C, s.heads);
     if (layout == MSLA_NCHW) {
-        if (msla::launch_transpose((int)dt, x, out, s.B, C, (int)s.N, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
-        x_tok = out;
+        if (!x_planar) {
+            if (msla::launch_transpose((int)dt, x, out, s.B, C, (int)s.N, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
+            x_tok = out;
+        }
         out_tok = kv_raw;
     }
     // Q/K/V projection; raw Q lands in the branch-0 columns of the multi-scale Q map
@@ -529,7 +532,7 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     const long kv_span = hm ? kv_padded_tokens(s) * 2 * s.Ct : s.T * 2 * s.Ct;
     if (stage_wanted(options, MSLA_OPT_STAGE_PROJECT) && !fused &&
         msla::launch_qkv_project((int)dt, x_tok, w_qkv, q_ms, q_ms_ts, kv_raw, kv_ts, kv_hs, kv_span, s.T, C, s.heads,
-                                 hs) != hipSuccess)
+                                 hs, x_planar ? (int)s.N : 0) != hipSuccess)
         return MSLA_ERR_LAUNCH;
     if (!mark(1)) return MSLA_ERR_LAUNCH;
     // aggregation + Eq. (3) state

@@ -22,7 +22,9 @@ hipError_t launch_linear(int dt, const void* x, const void* w, void* y, long n_t
 // padding); kv_span = elements of the whole map, below 2^30 when head-major.
 hipError_t launch_qkv_project(int dt, const void* x, const void* w_qkv, void* q_ms, long q_ms_stride,
                               void* kv_raw, long kv_tok_stride, long kv_head_stride, long kv_span,
-                              long n_tokens, int c_in, int heads, hipStream_t stream);
+                              long n_tokens, int c_in, int heads, hipStream_t stream, int plane = 0);
+// plane > 0: x is channel-planar, [n_tokens / plane, c_in, plane], which these calls take:
+bool qkv_project_takes_planar(int dt, long n_tokens, int c_in, int heads);
 
 struct AggregateArgs {
     // raw Q, K, V maps: element (token n, head h, channel e) of map m lives at

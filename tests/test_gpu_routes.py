@@ -447,3 +447,15 @@ def test_head_size_32_maps_beyond_2_gib(dtype, scales):
 ])
 def test_ffn_in_one_launch(dtype, act, B, C, H, W, hidden):
     block.test_ffn(dtype, act, B, C, H, W, hidden)
+
+
+# a channel-planar x read by the projection itself: planes shorter than a run of 8 (4) tokens and than a tile, of whole runs and odd ones,
+# tiles that span several images, one and several channels a thread, channels that do not fill the last one; fp32 at both sides
+# of the rules on channels and tokens
+@pytest.mark.parametrize("dtype,B,C,H,W,heads,scales", [
+    (dt, *shape) for dt in ("f16", "bf16", "f32") for shape in [
+        (7, 32, 1, 3, 1, ()), (5, 48, 1, 7, 2, (5,)), (3, 16, 5, 8, 1, ()), (2, 112, 11, 13, 6, (7,)), (1, 128, 9, 16, 7, ())]
+] + [("f16", 2, 208, 17, 19, 12, (3,)), ("bf16", 1, 256, 6, 11, 13, ()), ("f16", 9, 144, 77, 31, 5, (5,)),
+     ("f32", 2, 96, 9, 31, 5, (5,)), ("f32", 1, 128, 64, 129, 5, (5,)), ("f32", 2, 144, 9, 31, 6, ())])
+def test_channel_planar_input(dtype, B, C, H, W, heads, scales):
+    base.test_forward_channel_planar_layout(dtype, B, C, H, W, heads, 16, scales)
