@@ -283,7 +283,13 @@ struct WsApply {
 
 __device__ __forceinline__ int lds_swizzle(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
-template <class T, int KCH, int IO, bool kRes>
+// kOut: what becomes of the sums -- token-major rows, the same plus a residual, or a channel-planar map.  For the last the matrix
+// instructions take their operands the other way round (tokens are the result's rows), so that a lane holds four tokens of one
+// channel instead of four channels of one token: the module's result needs no transposition behind this kernel, and the
+// sums are the same ones.
+enum ApplyOut { kOutRows, kOutResidual, kOutPlanar };
+
+template <class T, int KCH, int IO, ApplyOut kOut>
 __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restrict__ q_ms,
                                                                const char* __restrict__ kvfrag,
                                                                const float* __restrict__ kvscale,
@@ -296,7 +302,7 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
     typedef Traits<T> Tr;
     typedef typename Tr::Vec Vec;
     typedef typename Tr::Frag Frag;
-    constexpr bool kHiLo = S::kHiLo;
+    constexpr bool kHiLo = S::kHiLo, kPlanar = kOut == kOutPlanar;
     constexpr int kUnits = S::kUnits;
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
@@ -486,18 +492,20 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
             bl[S::kPipeHiLo ? kk % kRing : 0][jt] = __builtin_bit_cast(
                 Vec, *(const u32x4*)(lds + tile + (frag_off ^ ((kk & 1) * 64)) + (kk >> 1) * S::kSlab + jt * 16 * S::kRow));
     };
+    auto mma = [&](int io, int jt, int kk, Vec tokens) {
+        acc[io][jt] = kPlanar ? Tr::mma_vec(acc[io][jt], tokens, wf[io][kk]) : Tr::mma_vec(acc[io][jt], wf[io][kk], tokens);
+    };
     auto mma_chunk = [&](int kk) {
 #pragma unroll
         for (int io = 0; io < IO; ++io)
 #pragma unroll
-            for (int jt = 0; jt < S::JT; ++jt) acc[io][jt] = Tr::mma_vec(acc[io][jt], wf[io][kk], bf[kk % kRing][jt]);
+            for (int jt = 0; jt < S::JT; ++jt) mma(io, jt, kk, bf[kk % kRing][jt]);
     };
     auto mma_chunk_lo = [&](int kk) {
 #pragma unroll
         for (int io = 0; io < IO; ++io)
 #pragma unroll
-            for (int jt = 0; jt < S::JT; ++jt)
-                acc[io][jt] = Tr::mma_vec(acc[io][jt], wf[io][kk], bl[S::kPipeHiLo ? kk % kRing : 0][jt]);
+            for (int jt = 0; jt < S::JT; ++jt) mma(io, jt, kk, bl[S::kPipeHiLo ? kk % kRing : 0][jt]);
     };
     auto zero_acc = [&]() {
 #pragma unroll
@@ -511,13 +519,37 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
     // one 16-byte store per lane: the odd 16-lane groups of one block are swapped with the even
     // groups of another, which leaves a lane with 8 consecutive channels -- of the two channel blocks
     // of 16 tokens (IO == 2: channels 16*(q%2) + 8*(q/2) .. +7 of token x16), or of one channel block
-    // of both token groups (IO == 1: channels 8*(q/2) .. +7 of token 16*(q%2) + x16).
+    // of both token groups (IO == 1: channels 8*(q/2) .. +7 of token 16*(q%2) + x16).  Planar: a lane (channel x16, q) holds
+    // tokens 4q..4q+3 of each block, and the groups of both token blocks swapped leave it with tokens 16*(q%2) + 8*(q/2) .. +7.
     static_assert(IO == 1 || IO == 2, "two 8-byte halves per store");
-    constexpr int kPieces = IO == 2 ? S::JT : S::JT / 2;
+    constexpr int kPieces = kPlanar ? IO : IO == 2 ? S::JT : S::JT / 2;
     Frag pend[IO][S::JT];
     BufRsrc ores;
     const unsigned out_row = (unsigned)c_out * 2u;
-    // (kRes: out = res + ..., the residual joining the fp32 sums before their one rounding --
+    // Planar: the map's rows start anywhere, which the stores take; a run of eight tokens that the image's end cuts leaves finish()
+    // element by element.  (A branch between the matrix instructions made the widest variant spill 21 registers, and a module of
+    // 8 x 53 x 67 tokens, 256 channels take 88.0 us instead of 84.9.)
+    const int p_tok = (q & 1) * 16 + (q >> 1) * 8;
+    const unsigned p_off = ((unsigned)x16 * (unsigned)N + p_tok) * 2u;
+    int p_rows = 0;
+    auto planar_at = [&](Origin o) { return out + ((size_t)(unsigned)o.b * (unsigned)c_out + ch0) * (unsigned)N + (unsigned)o.n0; };
+    auto pair_up = [&](Frag a, Frag b) {
+        const u32x2 even = __builtin_bit_cast(u32x2, a), odd = __builtin_bit_cast(u32x2, b);
+        const u32x2 s0 = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
+        const u32x2 s1 = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+        return u32x4{s0[0], s1[0], s0[1], s1[1]};
+    };
+    auto aim_out = [&](Origin o, bool live) {
+        const int rows = live ? (N - o.n0 < S::TB ? N - o.n0 : S::TB) : 0;
+        if constexpr (kPlanar) {
+            const int live_io = ch0 >= c_out ? 0 : c_out - ch0 < IO * 16 ? 1 : IO;
+            ores = make_rsrc_small(planar_at(o), (unsigned)live_io * 32u * (unsigned)N);      // (16 channels' rows each)
+            p_rows = rows;
+            return;
+        }
+        ores = make_rsrc_small(out + (size_t)o.tok * (unsigned)c_out, (unsigned)rows * out_row);
+    };
+    // (kOutResidual: out = res + ..., the residual joining the fp32 sums before their one rounding --
     // the block's y = x + MSLA(x); o is the origin of the tile the accumulators belong to)
     auto finish = [&](Origin o) {
 #pragma unroll
@@ -525,7 +557,7 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
 #pragma unroll
             for (int jt = 0; jt < S::JT; ++jt) {
                 f32x4 v = acc[io][jt];
-                if constexpr (kRes) {
+                if constexpr (kOut == kOutResidual) {
                     const int row = jt * 16 + x16, oc = ch0 + io * 16 + q * 4;
                     if (row < N - o.n0 && oc < c_out) {
                         const f32x4 r = frag_to_f32<T>(load_frag<T>(res + ((size_t)o.tok + row) * (unsigned)c_out + oc));
@@ -535,26 +567,32 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
                 }
                 pend[io][jt] = frag_from_f32<T>(v);
             }
-    };
-    auto aim_out = [&](Origin o, bool live) {
-        const int rows = live ? (N - o.n0 < S::TB ? N - o.n0 : S::TB) : 0;
-        ores = make_rsrc_small(out + (size_t)o.tok * (unsigned)c_out, (unsigned)rows * out_row);
+        if constexpr (kPlanar) {
+            const int rows = N - o.n0 < S::TB ? N - o.n0 : S::TB;
+            if (rows % 8 != 0) {
+                aim_out(o, true);
+#pragma unroll
+                for (int jt = 0; jt < S::JT; ++jt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int tok = jt * 16 + q * 4 + r;
+                        const unsigned at = tok < rows && tok >= (rows & ~7) ? ((unsigned)x16 * (unsigned)N + tok) * 2u : kOobOffset;
+#pragma unroll
+                        for (int io = 0; io < IO; ++io)
+                            buf_store2(ores, at + (unsigned)io * 32u * (unsigned)N, __builtin_bit_cast(u32x2, pend[io][jt])[r / 2] >> (r % 2 * 16));
+                    }
+            }
+        }
     };
     auto flush = [&](int p) {
-        u32x2 even, odd;
-        if constexpr (IO == 2) {
-            even = __builtin_bit_cast(u32x2, pend[0][p]);
-            odd = __builtin_bit_cast(u32x2, pend[IO - 1][p]);
-        } else {
-            even = __builtin_bit_cast(u32x2, pend[0][2 * p]);
-            odd = __builtin_bit_cast(u32x2, pend[0][2 * p + 1]);
+        if constexpr (kPlanar) {
+            buf_store16(ores, p_tok + 8 <= p_rows ? p_off + (unsigned)p * 32u * (unsigned)N : kOobOffset, pair_up(pend[p][0], pend[p][1]));
+            return;
         }
-        const u32x2 s0 = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
-        const u32x2 s1 = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+        const u32x4 v = IO == 2 ? pair_up(pend[0][p], pend[IO - 1][p]) : pair_up(pend[0][2 * p], pend[0][2 * p + 1]);
         const int row = IO == 2 ? p * 16 + x16 : (2 * p + (q & 1)) * 16 + x16;
         const int oc = ch0 + (IO == 2 ? (q & 1) * 16 : 0) + (q >> 1) * 8;
-        buf_store16_stream(ores, oc < c_out ? (unsigned)row * out_row + oc * 2u : kOobOffset,
-                           u32x4{s0[0], s1[0], s0[1], s1[1]});
+        buf_store16_stream(ores, oc < c_out ? (unsigned)row * out_row + oc * 2u : kOobOffset, v);
     };
     auto flush_all = [&](Origin o) {
         aim_out(o, true);
@@ -671,7 +709,7 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
 #pragma unroll
                 for (int io = 0; io < IO; ++io)
 #pragma unroll
-                    for (int jt = 0; jt < S::JT; ++jt) acc[io][jt] = Tr::mma_vec(acc[io][jt], wf[io][kk], lo[jt]);
+                    for (int jt = 0; jt < S::JT; ++jt) mma(io, jt, kk, lo[jt]);
             }
             finish(o);
             o = advance(o);
@@ -683,7 +721,7 @@ __global__ __launch_bounds__(512) void apply_project_ws_kernel(const T* __restri
 template <class T, int KCH, int IO>
 hipError_t run_apply_project_ws(const void* q_ms, const void* kvfrag, const float* kvscale, const void* w_proj,
                                 void* out, const void* res, long n_tokens, int N, int n_hb, int c_out, float eps,
-                                hipStream_t stream) {
+                                bool planar, hipStream_t stream) {
     typedef WsApply<T, KCH, IO> S;
     const int n_cg = (c_out + S::kChanBlock - 1) / S::kChanBlock;
     const int tiles_per_image = (N + S::TB - 1) / S::TB;
@@ -694,21 +732,18 @@ hipError_t run_apply_project_ws(const void* q_ms, const void* kvfrag, const floa
     const long groups = slots / n_cg > 0 ? slots / n_cg : 1;
     const long tiles_per_block = (n_tt + groups - 1) / groups;
     const long nblocks = (n_tt + tiles_per_block - 1) / tiles_per_block * n_cg;
-    // (the residual path is compiled apart: the headline variant has no register to spare for it)
-    if (res != nullptr) {
-        const hipError_t e = allow_dynamic_lds<apply_project_ws_kernel<T, KCH, IO, true>>(S::kLds);
+    // (compiled apart: the headline variant has no register to spare for a residual or another layout)
+    auto launch = [&](auto out_c) {
+        constexpr ApplyOut kOut = decltype(out_c)::value;
+        const hipError_t e = allow_dynamic_lds<apply_project_ws_kernel<T, KCH, IO, kOut>>(S::kLds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((apply_project_ws_kernel<T, KCH, IO, true>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds,
+        hipLaunchKernelGGL((apply_project_ws_kernel<T, KCH, IO, kOut>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds,
                            stream, (const T*)q_ms, (const char*)kvfrag, kvscale, (const T*)w_proj, (T*)out, N, n_hb,
                            c_out, n_cg, tiles_per_image, n_tt, tiles_per_block, eps, (const T*)res);
-    } else {
-        const hipError_t e = allow_dynamic_lds<apply_project_ws_kernel<T, KCH, IO, false>>(S::kLds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((apply_project_ws_kernel<T, KCH, IO, false>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds,
-                           stream, (const T*)q_ms, (const char*)kvfrag, kvscale, (const T*)w_proj, (T*)out, N, n_hb,
-                           c_out, n_cg, tiles_per_image, n_tt, tiles_per_block, eps, (const T*)res);
-    }
-    return hipGetLastError();
+        return hipGetLastError();
+    };
+    if (planar) return launch(std::integral_constant<ApplyOut, kOutPlanar>{});
+    return res != nullptr ? launch(std::integral_constant<ApplyOut, kOutResidual>{}) : launch(std::integral_constant<ApplyOut, kOutRows>{});
 }
 
 // ------------------------------------------- att fused into projection, fp32, weight-stationary
@@ -741,7 +776,7 @@ struct Ws32Apply {
     static_assert(kResident >= 1, "one workgroup fits a CU");
 };
 
-template <int KCH, int W, int JT>
+template <int KCH, int W, int JT, bool kPlanar>
 __global__ __launch_bounds__(W * 64, (Ws32Apply<KCH, W, JT>::kResident * W / 4)) void apply_project_ws32_kernel(const float* __restrict__ q_ms,
                                                                     const char* __restrict__ kvfrag,
                                                                     const float* __restrict__ w_proj, float* __restrict__ out,
@@ -853,8 +888,10 @@ __global__ __launch_bounds__(W * 64, (Ws32Apply<KCH, W, JT>::kResident * W / 4))
 #pragma unroll
             for (int kk = 0; kk < KCH; ++kk)
 #pragma unroll
-                for (int jt = 0; jt < JT; ++jt)
-                    acc[jt] = Tr::mma16(acc[jt], wf[kk], *(const f32x4*)(lds + here + (jt * 16 + x16) * S::kRow + ((kk * 4 + q) ^ sw) * 16));
+                for (int jt = 0; jt < JT; ++jt) {
+                    const f32x4 tokens = *(const f32x4*)(lds + here + (jt * 16 + x16) * S::kRow + ((kk * 4 + q) ^ sw) * 16);
+                    acc[jt] = kPlanar ? Tr::mma16(acc[jt], tokens, wf[kk]) : Tr::mma16(acc[jt], wf[kk], tokens);
+                }
         }
         if (more) {
             const int b_next = (int)((t + 1) / tiles_per_image);
@@ -867,6 +904,11 @@ __global__ __launch_bounds__(W * 64, (Ws32Apply<KCH, W, JT>::kResident * W / 4))
         if (live) {
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt) {
+                if constexpr (kPlanar) {            // (a lane has tokens 4q..4q+3 of channel x16)
+                    const int n = n0 + jt * 16 + q * 4, oc = ch0 + x16;
+                    if (oc < c_out) store_planar(out + ((size_t)b * c_out + oc) * N + n, n, N, __builtin_bit_cast(u32x4, acc[jt]));
+                    continue;
+                }
                 const int n = n0 + jt * 16 + x16, oc = ch0 + q * 4;
                 if (n < N) {
                     const long at = ((long)b * N + n) * c_out + oc;
@@ -881,7 +923,7 @@ __global__ __launch_bounds__(W * 64, (Ws32Apply<KCH, W, JT>::kResident * W / 4))
 
 template <int KCH, int W, int JT>
 hipError_t run_apply_project_ws32(const void* q_ms, const void* kvfrag, const void* w_proj, void* out,
-                                  const void* res, long n_tokens, int N, int n_hb, int c_out, float eps, hipStream_t stream) {
+                                  const void* res, long n_tokens, int N, int n_hb, int c_out, float eps, bool planar, hipStream_t stream) {
     typedef Ws32Apply<KCH, W, JT> S;
     const int n_cg = (c_out + W * 16 - 1) / (W * 16);
     const int tiles_per_image = (N + S::TB - 1) / S::TB;
@@ -891,24 +933,28 @@ hipError_t run_apply_project_ws32(const void* q_ms, const void* kvfrag, const vo
     const long groups = slots / n_cg > 0 ? slots / n_cg : 1;
     const long tiles_per_block = (n_tt + groups - 1) / groups;
     const long nblocks = (n_tt + tiles_per_block - 1) / tiles_per_block * n_cg;
-    const hipError_t e = allow_dynamic_lds<apply_project_ws32_kernel<KCH, W, JT>>(S::kLds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((apply_project_ws32_kernel<KCH, W, JT>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds, stream,
-                       (const float*)q_ms, (const char*)kvfrag, (const float*)w_proj, (float*)out, N, n_hb, c_out, n_cg,
-                       tiles_per_image, n_tt, tiles_per_block, eps, (const float*)res);
-    return hipGetLastError();
+    auto launch = [&](auto planar_c) {
+        constexpr bool kPlanar = decltype(planar_c)::value;
+        const hipError_t e = allow_dynamic_lds<apply_project_ws32_kernel<KCH, W, JT, kPlanar>>(S::kLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((apply_project_ws32_kernel<KCH, W, JT, kPlanar>), dim3((unsigned)nblocks), dim3(S::kThreads), S::kLds, stream,
+                           (const float*)q_ms, (const char*)kvfrag, (const float*)w_proj, (float*)out, N, n_hb, c_out, n_cg,
+                           tiles_per_image, n_tt, tiles_per_block, eps, (const float*)res);
+        return hipGetLastError();
+    };
+    return planar ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 template <int KCH>
 hipError_t run_apply_project_f32(const void* q_ms, const void* kvfrag, const void* w_proj, void* out, const void* res,
-                                 long n_tokens, int N, int n_hb, int c_out, float eps, hipStream_t stream) {
+                                 long n_tokens, int N, int n_hb, int c_out, float eps, bool planar, hipStream_t stream) {
     // 128 channels a workgroup (the attention rows are made once per channel group: 64 takes 122.8 instead of 114.0 us for
     // the module of 4 x 8192 tokens, 128 channels), except where that leaves half of the compute units without one and
     // there are channels to spread (576 tokens, 256 channels: 42.1 us with 128, 39.0 with 64)
     const long tiles = (n_tokens / N) * ((N + 15) / 16);
     if (c_out > 64 && 2 * tiles * ((c_out + 127) / 128) < compute_units())
-        return run_apply_project_ws32<KCH, 4, 1>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-    return run_apply_project_ws32<KCH, 8, 1>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+        return run_apply_project_ws32<KCH, 4, 1>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
+    return run_apply_project_ws32<KCH, 8, 1>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
 }
 
 template <class T>
@@ -967,31 +1013,32 @@ bool tiled_fp32_pays(long images, int N, int c_out) {
 template <class T>
 hipError_t run_apply_project(const void* q_ms, const void* kvfrag, const float* kvscale, const void* w_proj,
                              void* out, const void* res, long n_tokens, int N, int n_hb, int c_out, float eps,
-                             hipStream_t stream) {
+                             bool planar, hipStream_t stream) {
 #ifndef MSLA_APPLY_NO_WS
     if constexpr (sizeof(T) == 2) {
         // short contraction: weights and states stay in registers
         if (n_hb <= 32) {
             const bool narrow = c_out <= 128;
             if (n_hb <= 16)
-                return narrow ? run_apply_project_ws<T, 8, 1>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream)
-                              : run_apply_project_ws<T, 8, 2>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+                return narrow ? run_apply_project_ws<T, 8, 1>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream)
+                              : run_apply_project_ws<T, 8, 2>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
             if (n_hb <= 24)
-                return narrow ? run_apply_project_ws<T, 12, 1>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream)
-                              : run_apply_project_ws<T, 12, 2>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-            return narrow ? run_apply_project_ws<T, 16, 1>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream)
-                          : run_apply_project_ws<T, 16, 2>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+                return narrow ? run_apply_project_ws<T, 12, 1>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream)
+                              : run_apply_project_ws<T, 12, 2>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
+            return narrow ? run_apply_project_ws<T, 16, 1>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream)
+                          : run_apply_project_ws<T, 16, 2>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
         }
     }
 #endif
     if constexpr (sizeof(T) == 4) {
         if (n_hb <= 32 && !tiled_fp32_pays(n_tokens / N, N, c_out)) {
-            if (n_hb <= 8) return run_apply_project_f32<8>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-            if (n_hb <= 16) return run_apply_project_f32<16>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-            if (n_hb <= 24) return run_apply_project_f32<24>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
-            return run_apply_project_f32<32>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, stream);
+            if (n_hb <= 8) return run_apply_project_f32<8>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
+            if (n_hb <= 16) return run_apply_project_f32<16>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
+            if (n_hb <= 24) return run_apply_project_f32<24>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
+            return run_apply_project_f32<32>(q_ms, kvfrag, w_proj, out, res, n_tokens, N, n_hb, c_out, eps, planar, stream);
         }
     }
+    if (planar) return hipErrorInvalidValue;            // (see apply_project_writes_planar)
     // Tiled form: 64 x 64 per wave, 256 channels x 128 tokens per workgroup; a map too small to give
     // every CU such a tile takes 64-token tiles (measured on the 2048- and 1024-token workloads: 33
     // against 45 us and 17 against 25 us; still smaller workgroups were slower again)
@@ -1014,9 +1061,7 @@ hipError_t launch_apply(int dt, const void* q_ms, const void* kvfrag, const floa
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
-                                const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
-                                int n_hb, int c_out, float eps, hipStream_t stream) {
+static bool small_apply_project(int dt, long n_tokens, int tokens_per_image, int n_hb, int c_out) {
     // more head-branches than the register-resident form holds: the long-contraction kernel, which makes a token's attention
     // rows once per 128 output channels and keeps the weights, where the tiled form makes them once per 256 and fetches the
     // weights for every tile.  For few tokens, or up to three such channel groups (8 x 4096 tokens, 320 channels, 60
@@ -1028,15 +1073,31 @@ hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, co
     // module, tiled / in parts, 512 channels, 3x3 + 5x5: 512 tokens fp16 65.0 / 34.7, bf16 74.3 / 37.9; 2048 bf16 (256 pieces) 78.8 / 44.1,
     // 2 x 2048 fp16 (512) 76.4 / 63.6, 4 x 2048 (1024) 89.2 / 105.7; 3 x 45 x 45 of 352, bf16 (576) 87.4 / 93.0.
     const long tiles = (n_tokens / tokens_per_image) * ((tokens_per_image + 31) / 32), pieces = tiles * ((c_out + 127) / 128);
-    if (dt != 0 && K > 1024 && K <= 4096 && pieces <= 2L * compute_units() && small_tiles_a_workgroup(tiles, c_out) <= 2)
-        return launch_small_apply_project(dt, q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, stream);
-    if (n_hb > 32 && (small_product(dt, n_tokens, K, c_out) || (dt != 0 && K <= 1024 && c_out <= 384)))
+    if (dt != 0 && K > 1024 && K <= 4096 && pieces <= 2L * compute_units() && small_tiles_a_workgroup(tiles, c_out) <= 2) return true;
+    return n_hb > 32 && (small_product(dt, n_tokens, K, c_out) || (dt != 0 && K <= 1024 && c_out <= 384));
+}
+
+// out channel-planar, [images, c_out, tokens_per_image]: all forms but the tiled one, whose epilogue goes through LDS row by row.
+// Modules with planar x and out, us with a transposition / without: fp16 1 x 64 x 128 tokens, 128 channels 25.9 / 23.1, 6 x 128 x
+// 129, 128 102.9 / 85.9 (of which 4 are x's), 8 x 64 x 96, 256 105.8 / 101.2, 8 x 53 x 67, 256 84.7 / 84.9 (rows that start anywhere: the widest
+// form gains least), bf16 3 x 37 x 53, 192, two scales 46.6 / 43.6, 8 x 64 x 96, 256 115.4 / 105.9, fp32 1600 tokens, 32 21.5 / 18.1,
+// 4 x 64 x 128, 128 115.0 / 107.4.
+bool apply_project_writes_planar(int dt, long n_tokens, int tokens_per_image, int n_hb, int c_out) {
+    if (tokens_per_image > 0x1ffffff) return false;         // (31 bits of bytes over 32 channels' rows)
+    if (small_apply_project(dt, n_tokens, tokens_per_image, n_hb, c_out)) return true;
+    return n_hb <= 32 && !(dt == 0 && tiled_fp32_pays(n_tokens / tokens_per_image, tokens_per_image, c_out));
+}
+
+hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
+                                const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
+                                int n_hb, int c_out, float eps, hipStream_t stream, bool planar) {
+    if (small_apply_project(dt, n_tokens, tokens_per_image, n_hb, c_out))
         return launch_small_apply_project(dt, q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out,
-                                          eps, stream);
+                                          eps, stream, planar);
     switch (dt) {
-        case 0: return run_apply_project<float>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, stream);
-        case 1: return run_apply_project<_Float16>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, stream);
-        case 2: return run_apply_project<__bf16>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, stream);
+        case 0: return run_apply_project<float>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, planar, stream);
+        case 1: return run_apply_project<_Float16>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, planar, stream);
+        case 2: return run_apply_project<__bf16>(q_ms, kvfrag, kvscale, w_proj, out, res, n_tokens, tokens_per_image, n_hb, c_out, eps, planar, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -31,6 +31,7 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 // destination of output channel group g (16 channels) of token row `tok`
 template <class T>
 struct SmallPlain {
+    static constexpr bool kPlanar = false;
     T* y;
     int c_out;
     const T* res = nullptr;       // optional residual [n_tokens, c_out], added to the fp32 sums
@@ -44,10 +45,19 @@ struct SmallPlain {
         return v;
     }
 };
+// ... of a channel-planar map [images, c_out, N] (the matrix instructions take their operands the other way round for it: a lane
+// holds four tokens of one channel)
+template <class T>
+struct SmallPlanar {
+    static constexpr bool kPlanar = true;
+    T* y;
+    int c_out;
+};
 // ... for the Q/K/V projection: group g = h*3 + t; Q goes to the branch-0 columns of the
 // multi-scale Q map, K and V to the K|V map (token and head strides in elements)
 template <class T>
 struct SmallQkv {
+    static constexpr bool kPlanar = false;
     T* q_ms;
     long q_ms_stride;
     T* kv_raw;
@@ -266,22 +276,36 @@ __global__ __launch_bounds__(kSmallThreads) void small_project_kernel(const T* _
         }
         __syncthreads();
 
-        // ---- 16 channels x 32 tokens per wave: D[channel 4q+r][token x16]
+        // ---- 16 channels x 32 tokens per wave: D[channel 4q+r][token x16] (planar: D[token 4q+r][channel x16])
         const int frag_off = x16 * 128 + (q ^ g16) * 16;
 #pragma unroll
         for (int kk = 0; kk < KC; ++kk) {
 #pragma unroll
             for (int jt = 0; jt < 2; ++jt) {
                 const int off = (frag_off ^ ((kk & 1) * 64)) + (kk >> 1) * kSlabBytes + jt * 16 * 128;
-                acc[jt] = Tr::mma_vec(acc[jt], wf[kk], __builtin_bit_cast(Vec, *(const u32x4*)(tile_hi + off)));
-                if constexpr (kHiLo)
-                    acc[jt] = Tr::mma_vec(acc[jt], wf[kk], __builtin_bit_cast(Vec, *(const u32x4*)(tile_lo + off)));
+                const Vec hi = __builtin_bit_cast(Vec, *(const u32x4*)(tile_hi + off));
+                acc[jt] = Dest::kPlanar ? Tr::mma_vec(acc[jt], hi, wf[kk]) : Tr::mma_vec(acc[jt], wf[kk], hi);
+                if constexpr (kHiLo) {
+                    const Vec lo = __builtin_bit_cast(Vec, *(const u32x4*)(tile_lo + off));
+                    acc[jt] = Dest::kPlanar ? Tr::mma_vec(acc[jt], lo, wf[kk]) : Tr::mma_vec(acc[jt], wf[kk], lo);
+                }
             }
         }
         if constexpr (kMulti) __syncthreads();        // the tile's memory takes the next part's weights
         }
-        // ---- lane (token x16, q): channels 4q..4q+3 of the wave's group, 8 bytes
-        if (ch0 < c_out) {
+        if constexpr (Dest::kPlanar) {
+            // ---- lane (channel x16, q): tokens 4q..4q+3 of both groups; the odd 16-lane groups of one swapped with the even
+            // ones of the other leave it with tokens 16*(q%2) + 8*(q/2) .. +7, 16 bytes
+            const u32x2 even = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[0])), odd = __builtin_bit_cast(u32x2, frag_from_f32<T>(acc[1]));
+            const u32x2 s0 = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
+            const u32x2 s1 = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+            if (ch0 < c_out) {
+                const long b = tok0 / aa.N, n = tok0 - b * aa.N;
+                const int t = (q & 1) * 16 + (q >> 1) * 8;
+                store_planar(dest.y + (b * c_out + ch0 + x16) * aa.N + n + t, t, rows, u32x4{s0[0], s1[0], s0[1], s1[1]});
+            }
+        } else if (ch0 < c_out) {
+            // ---- lane (token x16, q): channels 4q..4q+3 of the wave's group, 8 bytes
 #pragma unroll
             for (int jt = 0; jt < 2; ++jt) {
                 const int row = jt * 16 + x16;
@@ -355,12 +379,17 @@ hipError_t launch_small_qkv_project(int dt, const void* x, const void* w_qkv, vo
 
 hipError_t launch_small_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
                                       const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
-                                      int n_hb, int c_out, float eps, hipStream_t stream) {
+                                      int n_hb, int c_out, float eps, hipStream_t stream, bool planar) {
     const int N = tokens_per_image;
     const int tpi = (N + kSmallTB - 1) / kSmallTB;
     const long n_tiles = (n_tokens / N) * tpi;
     const SmallAttArgs aa = {(const char*)kvfrag, kvscale, N, n_hb, eps};
     const int K = n_hb * 16;
+    if (planar) {
+        if (dt == 1) return run_small_k<_Float16, true>(q_ms, w_proj, SmallPlanar<_Float16>{(_Float16*)out, c_out}, aa, n_tokens, K, c_out, n_tiles, tpi, stream);
+        if (dt == 2) return run_small_k<__bf16, true>(q_ms, w_proj, SmallPlanar<__bf16>{(__bf16*)out, c_out}, aa, n_tokens, K, c_out, n_tiles, tpi, stream);
+        return hipErrorNotSupported;
+    }
     switch (dt) {
         case 1: return run_small_k<_Float16, true>(q_ms, w_proj, SmallPlain<_Float16>{(_Float16*)out, c_out, (const _Float16*)res}, aa, n_tokens, K, c_out, n_tiles, tpi, stream);
         case 2: return run_small_k<__bf16, true>(q_ms, w_proj, SmallPlain<__bf16>{(__bf16*)out, c_out, (const __bf16*)res}, aa, n_tokens, K, c_out, n_tiles, tpi, stream);

@@ -514,16 +514,18 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     if (!mark(0)) return MSLA_ERR_LAUNCH;
     // The kernels work token-major.  A channel-planar x is first turned into token-major form in
     // `out` (free until the last kernel); the token-major result is then parked in the K|V area
-    // (dead after the aggregation pass) and turned back into `out`.
+    // (dead after the aggregation pass) and turned back into `out`.  Where the projections read and write
+    // channel-planar maps themselves, neither is needed.
     const void* x_tok = x;
     void* out_tok = out;
     const bool x_planar = layout == MSLA_NCHW && !fused && msla::qkv_project_takes_planar((int)dt, s.T, C, s.heads);
+    const bool out_planar = layout == MSLA_NCHW && msla::apply_project_writes_planar((int)dt, s.T, (int)s.N, s.S * s.heads, C);
     if (layout == MSLA_NCHW) {
         if (!x_planar) {
             if (msla::launch_transpose((int)dt, x, out, s.B, C, (int)s.N, hs) != hipSuccess) return MSLA_ERR_LAUNCH;
             x_tok = out;
         }
-        out_tok = kv_raw;
+        if (!out_planar) out_tok = kv_raw;
     }
     // Q/K/V projection; raw Q lands in the branch-0 columns of the multi-scale Q map
     const bool hm = kv_head_major(s, dt);
@@ -547,9 +549,9 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     // normalise-and-apply fused with the output projection
     if (stage_wanted(options, MSLA_OPT_STAGE_APPLY) &&
         msla::launch_apply_project((int)dt, q_ms, ws + wo.kvfrag, reinterpret_cast<float*>(ws + wo.kvscale),
-                                   w_proj, out_tok, residual, s.T, (int)s.N, s.S * s.heads, C, eps, hs) != hipSuccess)
+                                   w_proj, out_tok, residual, s.T, (int)s.N, s.S * s.heads, C, eps, hs, out_planar) != hipSuccess)
         return MSLA_ERR_LAUNCH;
-    if (layout == MSLA_NCHW &&
+    if (layout == MSLA_NCHW && !out_planar &&
         msla::launch_transpose((int)dt, out_tok, out, s.B, (int)s.N, C, hs) != hipSuccess)
         return MSLA_ERR_LAUNCH;
     if (!mark(4)) return MSLA_ERR_LAUNCH;

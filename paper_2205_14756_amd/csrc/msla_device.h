@@ -208,6 +208,21 @@ __device__ __forceinline__ void store_frag(void* p, typename Traits<T>::Frag f) 
     }
 }
 
+// eight (fp32: four) tokens of one channel, t .. of a tile with `rows` tokens, to a planar map (whose rows start anywhere)
+template <class T>
+__device__ __forceinline__ void store_planar(T* at, int t, int rows, u32x4 v) {
+    constexpr int kRun = 16 / (int)sizeof(T);
+    if (t + kRun <= rows) {
+        __builtin_memcpy(__builtin_assume_aligned(at, sizeof(T)), &v, 16);
+    } else {
+        T e[kRun];
+        __builtin_memcpy(e, &v, 16);
+#pragma unroll
+        for (int i = 0; i < kRun; ++i)
+            if (t + i < rows) at[i] = e[i];
+    }
+}
+
 // Raw buffer resources: loads and stores through one are range-checked by the hardware against
 // the byte count (a load out of range returns zero, a store out of range is dropped), which
 // replaces per-lane branches at ragged ends.  Offsets are 32-bit, so a resource spans at most
@@ -248,6 +263,9 @@ __device__ __forceinline__ void buf_store16_stream(BufRsrc r, unsigned voffset, 
 }
 __device__ __forceinline__ u32x2 buf_load8(BufRsrc r, unsigned voffset) {
     return __builtin_amdgcn_raw_buffer_load_b64(r, (int)voffset, 0, 0);
+}
+__device__ __forceinline__ void buf_store2(BufRsrc r, unsigned voffset, unsigned low_half) {
+    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)low_half, r, (int)voffset, 0, 0);
 }
 __device__ __forceinline__ void buf_store8(BufRsrc r, unsigned voffset, u32x2 v) {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)voffset, 0, 0);

@@ -120,7 +120,9 @@ hipError_t launch_apply(int dt, const void* q_ms, const void* kvfrag, const floa
 // residual [n_tokens, c_out] joins the fp32 sums before their one rounding
 hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
                                 const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
-                                int n_hb, int c_out, float eps, hipStream_t stream);
+                                int n_hb, int c_out, float eps, hipStream_t stream, bool planar = false);
+// planar: out is channel-planar, [images, c_out, tokens_per_image], and there is no residual; these calls write it:
+bool apply_project_writes_planar(int dt, long n_tokens, int tokens_per_image, int n_hb, int c_out);
 
 // The same three operations for 16-bit storage types with a contraction of 257 .. 1024 slots (k_small.hip; apply + projection up to 4096, in parts): the callers take the
 // projections where few enough tokens make the weights what a workgroup mostly fetches (small_product), the apply + projection there
@@ -133,7 +135,7 @@ hipError_t launch_small_qkv_project(int dt, const void* x, const void* w_qkv, vo
                                     int heads, hipStream_t stream);
 hipError_t launch_small_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale,
                                       const void* w_proj, void* out, const void* res, long n_tokens, int tokens_per_image,
-                                      int n_hb, int c_out, float eps, hipStream_t stream);
+                                      int n_hb, int c_out, float eps, hipStream_t stream, bool planar = false);
 // Tiles of 32 tokens that a workgroup of those kernels walks: one workgroup a compute unit, of 128 output channels
 inline long small_tiles_a_workgroup(long n_tiles, int c_out) {
     const long n_cb = (c_out + 127) / 128, groups = compute_units() / n_cb > 0 ? compute_units() / n_cb : 1;

@@ -229,8 +229,10 @@ hipError_t launch_apply(int dt, const void* q_ms, const void* kvfrag, const floa
     inside(att, (size_t)n * n_hb * 16 * esz(dt), "apply att");
     return hipSuccess;
 }
+bool apply_project_writes_planar(int dt, long n, int, int n_hb, int) { return n_hb <= 32 && (dt != 0 || n <= 8192); }
 hipError_t launch_apply_project(int dt, const void* q_ms, const void* kvfrag, const float* kvscale, const void* w_proj, void* out,
-                                const void* res, long n, int tpi, int n_hb, int c_out, float, hipStream_t) {
+                                const void* res, long n, int tpi, int n_hb, int c_out, float, hipStream_t, bool planar) {
+    if (planar && res) fail("a channel-planar out has no residual");
     const size_t states = (size_t)(n / tpi) * n_hb;
     inside(q_ms, (size_t)n * n_hb * 16 * esz(dt), "apply+project q_ms");
     inside(kvfrag, states * 2048, "apply+project operand blocks");

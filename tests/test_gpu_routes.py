@@ -459,3 +459,16 @@ def test_ffn_in_one_launch(dtype, act, B, C, H, W, hidden):
      ("f32", 2, 96, 9, 31, 5, (5,)), ("f32", 1, 128, 64, 129, 5, (5,)), ("f32", 2, 144, 9, 31, 6, ())])
 def test_channel_planar_input(dtype, B, C, H, W, heads, scales):
     base.test_forward_channel_planar_layout(dtype, B, C, H, W, heads, 16, scales)
+
+
+# a channel-planar out written by the output projection itself: images shorter than a tile and than a run of 8 (4) tokens, of whole
+# runs and odd ones, output channels that do not fill a wave's block; each contraction length of the kernels that keep their weights,
+# more than 32 head-branches (one and several parts), and the tiled form, which leaves it to a transposition
+@pytest.mark.parametrize("dtype,B,C,H,W,heads,scales", [
+    (dt, *shape) for dt in ("f16", "bf16", "f32") for shape in [
+        (5, 16, 1, 3, 1, ()), (2, 144, 5, 7, 9, ()), (3, 48, 3, 11, 9, (5,)), (2, 176, 13, 8, 12, (3,)), (2, 80, 9, 15, 14, (5,)),
+        (1, 272, 7, 9, 16, (5,)), (2, 208, 17, 5, 13, (3, 5)), (3, 256, 32, 33, 16, (3,))]
+] + [("f16", 2, 144, 9, 31, 23, (3, 5)), ("bf16", 1, 352, 7, 13, 22, (3, 5)), ("f16", 1, 512, 6, 7, 32, (3, 5)), ("bf16", 1, 288, 5, 9, 36, (3, 5)),
+     ("f32", 1, 256, 129, 128, 16, (5,))])
+def test_channel_planar_output(dtype, B, C, H, W, heads, scales):
+    base.test_forward_channel_planar_layout(dtype, B, C, H, W, heads, 16, scales)
