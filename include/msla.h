@@ -35,8 +35,8 @@
  * present; branch a+1 is aggregated with a scales[a] x scales[a] kernel; every
  * aggregated branch reads the raw map).
  *   x      [B, H, W, C]            (MSLA_NHWC: a token is one row of C channels), or
- *          [B, C, H, W]            (MSLA_NCHW; turned into the token-major form by a
- *                                  transposition pass of its own before the module runs)
+ *          [B, C, H, W]            (MSLA_NCHW; read as it is, or turned token-major by a
+ *                                  pass of its own where the shape calls for that)
  *   w_qkv  [3*Ct, C]               row o = (h*3 + t)*head_dim + e, t = 0:Q 1:K 2:V,
  *                                  so each (head, Q/K/V) pair is one contiguous group
  *                                  of head_dim channels (the 3*heads groups of Section 3.1)
