@@ -63,7 +63,9 @@ struct FfnFused {
 };
 
 // 16 bytes a lane from a buffer straight into LDS at lds_at + 16 * lane (a lane out of range writes zeros).  lds_at is
-// wave-uniform.  The compiler does not know of these loads: whoever reads the data waits for them himself (wait_loads).
+// wave-uniform.  The compiler does not know of these loads: whoever reads the data waits for them himself (wait_loads).  Nor
+// does it see that they read scalar registers, which needs five wait states behind a vector instruction that wrote one (as where
+// a spilled resource comes back) and one behind a write of m0: the s_nop is these.
 typedef u32x4 RawRsrc;
 __device__ __forceinline__ RawRsrc raw_rsrc(const void* base, long bytes) {
     const unsigned long a = (unsigned long)base;
@@ -72,8 +74,7 @@ __device__ __forceinline__ RawRsrc raw_rsrc(const void* base, long bytes) {
                    (unsigned)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
 }
 __device__ __forceinline__ void load_to_lds(RawRsrc r, unsigned voffset, unsigned lds_at) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_at), "v"(voffset), "s"(r)
-                 : "memory", "m0");
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voffset), "s"(r), "{m0}"(lds_at) : "memory");
 }
 template <int kLeft>
 __device__ __forceinline__ void wait_loads_and_meet() {       // at most kLeft loads outstanding, LDS writes done, then the barrier
