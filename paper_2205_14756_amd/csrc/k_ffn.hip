@@ -465,11 +465,8 @@ hipError_t run_dw_project_split_as(const void* h, const void* w_dw, const void* 
 template <class T, int ACT>
 hipError_t run_dw_project_split(const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B, int H,
                                 int W, int E, int c_out, hipStream_t stream) {
-    const long cus = compute_units(), n_rb = c_out <= 128 ? 1 : (c_out + 255) / 256;
-    auto rounds = [&](int rows, int cols) {
-        return ((long)B * ((H + rows - 1) / rows) * ((W + cols - 1) / cols) * n_rb + cus - 1) / cus;
-    };
-    const long r64 = rounds(4, 16), r8x16 = rounds(8, 16), r4x32 = rounds(4, 32);
+    const FfnRounds r = ffn_rounds(B, H, W, c_out <= 128 ? 1 : (c_out + 255) / 256);
+    const long r64 = r.r4x16, r8x16 = r.r8x16, r4x32 = r.r4x32;
     if (c_out <= 128) {
         if (r64 <= r8x16 && r64 <= r4x32)
             return run_dw_project_split_as<T, ACT, 1, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
@@ -479,8 +476,7 @@ hipError_t run_dw_project_split(const void* h, const void* w_dw, const void* w2,
     // More than 128 channels in blocks of 128, each of which does the depthwise pass again, while those are one round: a slab's step is shorter
     // with half the weights to stage and to multiply.  Us with 256 / 128: 512 tokens, 512 -> 2048 channels 47.9 / 44.0, 2048, 256 -> 1024 26.9 /
     // 24.6, 8192 (256 blocks) 31.5 / 29.3; past a round 16384 (512) 38.2 / 50.8.
-    const long b64 = (long)B * ((H + 3) / 4) * ((W + 15) / 16);
-    if (b64 * ((c_out + 127) / 128) <= cus)
+    if (r.b4x16 * ((c_out + 127) / 128) <= compute_units())
         return run_dw_project_split_as<T, ACT, 1, 128, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);
     if (r64 <= r8x16 && r64 <= r4x32)
         return run_dw_project_split_as<T, ACT, 1, 256, 16>(h, w_dw, w2, res, out, B, H, W, E, c_out, stream);

@@ -480,25 +480,6 @@ hipError_t run_ffn_fused_as(const void* y, const void* w1, const void* w_dw, con
     return hipGetLastError();
 }
 
-// Blocks of 64 or of 128 tokens, whichever takes fewer rounds of workgroups, one a compute unit (64 where both take as many: a
-// block of 128 lasts 1.5 times as long), and the two-launch form (false) where that is the faster one.  Up to 128 channels this
-// kernel is (us, two launches / this): 256 tokens, 128 -> 512 channels 15.2 / 13.6, 8192 17.2 / 14.3, 32768 29.7 / 20.5, 64 -> 256
-// 18.2 / 12.7, 32 -> 64 12.1 / 7.6.  With more channels a compute unit takes some 1100 cycles to fetch a slab's 32 KB of weights out
-// of L2, whatever the block, so
-// - the map has to fill more than half of the chip, unless there are few slabs: 256 -> 1024, 96 / 128 / 160 / 250 blocks of 64
-//   28.4 / 30.0, 29.0 / 30.1, 34.0 / 30.1, 41.0 / 33.6; 16 blocks 160 -> 320 13.2 / 12.5 and 144 -> 576 16.6 / 18.2 (the two
-//   launches split the output channels of so few tokens over workgroups);
-// - blocks of 128 tokens in bf16, whose depthwise products are two instructions, have to fill their rounds: 256 -> 1024, 160 /
-//   240 / 324 / 392 blocks 53.1 / 55.6, 64.9 / 57.2, 107.6 / 108.4, 113.0 / 108.1 (fp16 50.6 / 48.6, 62.6 / 52.3, 102.0 / 96.7).
-static bool fused_blocks(int dt, long B, int C, int H, int W, int E, bool* small) {
-    const long cus = compute_units();
-    auto blocks = [&](int rows) { return B * ((H + rows - 1) / rows) * ((W + 15) / 16); };
-    const long b4 = blocks(4), b8 = blocks(8), r4 = (b4 + cus - 1) / cus, r8 = (b8 + cus - 1) / cus;
-    *small = r4 <= r8;
-    if (C <= 128) return true;
-    return *small ? E <= 320 || 2 * b4 > cus : dt == 1 || 100 * b8 >= 72 * r8 * cus;
-}
-
 template <class T, int ACT>
 hipError_t run_ffn_fused(bool small, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C, int H,
                          int W, int E, hipStream_t stream) {
@@ -511,13 +492,48 @@ hipError_t run_ffn_fused(bool small, const void* y, const void* w1, const void* 
 
 }  // namespace
 
-hipError_t launch_ffn_fused(int dt, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C,
-                            int H, int W, int E, int act, hipStream_t stream) {
+// One launch pays a round of workgroups, one a compute unit, and each slab in it, whatever share of its blocks' tokens and of their
+// halo is in the image; the two launches pay for the elements of the expanded map, and less a round.  So neither the number of rounds
+// nor the fill of a block decides by itself: the time of the three forms is estimated.  The constants are fitted to 508 shapes (32
+// tokens to 200 million elements of the expanded map, 16 to 256 channels, 16 to 4096 hidden ones, rows of 1 to 4096 tokens), to
+// calls in a row on several input sets in turn and on one: estimate / measured is 0.91 to 1.08 for nine shapes in ten, and the form
+// taken is within 3 % of the best of the three at 98 in 100.  Two launches / blocks of 64 tokens / of 128, us in turn (on one set):
+//   full maps: fp16 8192 tokens, 128 -> 512 channels 17.2 / 14.4 / 19.0, 32768 29.9 / 28.4 / 20.6; 65536, 256 -> 1024 132 / 127 / 106
+//     (110 / 126 / 106: the expanded map stays in the memory-side cache), bf16 136 / 134 / 115 (115 / 133 / 114);
+//   blocks mostly outside the image: fp16 8 x 1 x 4096, 128 -> 512 71 / 101 / 138, 8 x 4096 x 1 228 / 413 / 284, 2048 images of 3 x 3
+//     82 / 103 / 138; bf16 512 images of 7 x 7, 256 -> 1024 88 / 127 / 107;
+//   many slabs for few workgroups: fp16 64 tokens, 128 -> 2048 35.6 / 42.1 / 57.3; bf16 1024, 128 -> 768 20.5 / 21.5 / 32.6;
+//   more rounds of the smaller block: bf16 8 x 64 x 96, 256 -> 1024 (three or two) 118 / 102 / 112 (102 / 102 / 110).
+// A call alone on an idle GPU runs before the clocks have risen, which costs this kernel more than the memory-bound two launches: 65536
+// tokens, 256 -> 1024 take fp16 122 / 144 / 122 and bf16 127 / 157 / 136 there.
+int ffn_block_rows(int dt, int B, int C, int H, int W, int E) {
     // 32-bit byte offsets into an image, each weight matrix and the filters
     const long lim = 0x7fffffffL;
-    if (dt == 0 || C > 256 || (long)H * W * C * 2 >= lim || (long)C * E * 2 >= lim || (long)E * 18 >= lim) return hipErrorNotSupported;
-    bool small = false;
-    if (!fused_blocks(dt, B, C, H, W, E, &small)) return hipErrorNotSupported;
+    if (dt == 0 || C > 256 || (long)H * W * C * 2 >= lim || (long)C * E * 2 >= lim || (long)E * 18 >= lim) return 0;
+    struct Round {
+        double once, step[2];           // a round of workgroups: us, and us a slab in it (fp16, bf16)
+    };
+    static const Round one4[2] = {{3.3, {0.60, 0.70}}, {5.1, {0.75, 0.86}}}, one8[2] = {{4.7, {0.83, 1.13}}, {9.0, {1.17, 1.45}}},   // C <= 128, C > 128
+                       two64[2] = {{2.2, {0.42, 0.52}}, {5.9, {0.42, 0.52}}}, two128[2] = {{4.8, {0.48, 0.58}}, {8.0, {0.57, 0.66}}},
+                       two64_halves = {3.1, {0.45, 0.54}};      // (output channels in blocks of 128, see run_dw_project_split)
+    const int wide = C > 128, bf = dt == 2, n_slab = (E + 31) / 32;
+    auto us = [&](const Round& r, long rounds) { return rounds * (r.once + n_slab * r.step[bf]); };
+    const FfnRounds r = ffn_rounds(B, H, W, 1);
+    const double t4 = (wide ? 0.4 : 1.4) + us(one4[wide], r.r4x16), t8 = (wide ? 0.6 : 0.8) + us(one8[wide], r.r8x16);
+    double two = 5.8 + (wide ? 1.02e-6 : 0.81e-6) * B * H * W * E;
+    if (wide && 2 * r.b4x16 <= compute_units()) two += us(two64_halves, 1);
+    else if (r.r4x16 <= r.r8x16 && r.r4x16 <= r.r4x32) two += us(two64[wide], r.r4x16);
+    else two += us(two128[wide], r.r8x16 < r.r4x32 ? r.r8x16 : r.r4x32);
+    if (t4 > two && t8 > two) return 0;
+    const int rows = t4 <= t8 ? 4 : 8;
+    return (rows == 4 ? r.b4x16 : r.b8x16) * 1024 <= 0xffffffffL ? rows : 0;       // (a launch takes 32 bits of threads)
+}
+
+hipError_t launch_ffn_fused(int dt, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C,
+                            int H, int W, int E, int act, hipStream_t stream) {
+    const int rows = ffn_block_rows(dt, B, C, H, W, E);
+    if (rows == 0) return hipErrorNotSupported;
+    const bool small = rows == 4;
     if (dt == 1)
         return act == 0 ? run_ffn_fused<_Float16, 0>(small, y, w1, w_dw, w2, out, B, C, H, W, E, stream)
                         : run_ffn_fused<_Float16, 1>(small, y, w1, w_dw, w2, out, B, C, H, W, E, stream);

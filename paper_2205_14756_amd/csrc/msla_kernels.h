@@ -151,8 +151,21 @@ inline bool small_product(int dt, long n_tokens, int K, int c_out) {
 hipError_t launch_ffn_dw_project(int dt, const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B,
                                  int H, int W, int E, int c_out, int act, hipStream_t stream);
 
+// Blocks of rows x columns tokens over a map's ragged edges, and their rounds over the chip, one workgroup (n_rb a block) a compute unit
+struct FfnRounds {
+    long b4x16, b8x16, r4x16, r8x16, r4x32;
+};
+inline FfnRounds ffn_rounds(long B, int H, int W, long n_rb) {
+    const long cus = compute_units();
+    auto blocks = [&](long rows, long cols) { return B * ((H + rows - 1) / rows) * ((W + cols - 1) / cols); };
+    auto rounds = [&](long n) { return (n * n_rb + cus - 1) / cus; };
+    const long b4 = blocks(4, 16), b8 = blocks(8, 16);
+    return FfnRounds{b4, b8, rounds(b4), rounds(b8), rounds(blocks(4, 32))};
+}
+
 // The whole FFN in one launch, the expanded map on chip (k_ffn_fused.hip).  Returns hipErrorNotSupported without launching
-// where the two launches above are the form to take.  out must not overlap y.
+// where the two launches above are the form to take (ffn_block_rows: rows of a block, 4 or 8; 0 there).  out must not overlap y.
+int ffn_block_rows(int dt, int B, int C, int H, int W, int E);
 hipError_t launch_ffn_fused(int dt, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C,
                             int H, int W, int E, int act, hipStream_t stream);
 //   y[n, o] = act(sum_c x[n, c] * w[o, c])   (k_project.hip; the activation is applied to the fp32 sums)

@@ -215,3 +215,34 @@ def _f16_chunks(lib, B, H, W, heads, scales):
 ])
 def test_matrix_core_workgroups_fill_whole_rounds(lib, B, H, W, heads, scales, chunks):
     assert chunks in _f16_chunks(lib, B, H, W, heads, scales)
+
+
+# (dtype 1: fp16, 2: bf16; B, C, H, W, hidden) -> rows of a block of the one-launch FFN, 0: two launches.  Us of two launches /
+# blocks of four / of eight rows
+@pytest.mark.parametrize("shape,rows", [
+    ((1, 8, 128, 1, 4096, 512), 0),         # one row of tokens
+    ((2, 8, 128, 1, 4096, 512), 0),
+    ((1, 16, 128, 2, 512, 512), 0),
+    ((1, 8, 128, 4096, 1, 512), 0),         # one column
+    ((1, 4096, 64, 1, 1, 256), 0),          # images of one token, of 3 x 3, 4 x 4 and 7 x 7
+    ((1, 2048, 128, 3, 3, 512), 0),
+    ((1, 1024, 64, 4, 4, 256), 0),
+    ((2, 512, 256, 7, 7, 1024), 0),
+    ((1, 64, 256, 17, 17, 1024), 0),        # 17 = 16 + 1 columns, 4 x 4 + 1 rows
+    ((1, 1, 128, 4, 16, 2048), 0),          # many slabs for one workgroup
+    ((2, 1, 128, 32, 32, 768), 0),
+    ((1, 9, 176, 44, 159, 176), 4),         # four rounds of 64 tokens before three of 128
+    ((2, 8, 256, 64, 96, 1024), 4),         # three before two
+    ((1, 1, 128, 64, 128, 512), 4),
+    ((2, 1, 32, 8, 32, 64), 4),
+    ((1, 8, 256, 64, 128, 1024), 8),
+    ((2, 8, 256, 64, 128, 1024), 8),
+    ((1, 8, 128, 64, 128, 512), 8),
+    ((0, 1, 128, 64, 128, 512), 0),         # single precision, more channels than fit, more threads than a launch takes
+    ((1, 1, 272, 64, 128, 512), 0),
+    ((1, 160000, 16, 64, 64, 16), 0),
+])
+def test_ffn_takes_the_faster_form(lib, shape, rows):
+    f = lib._ZN4msla14ffn_block_rowsEiiiiii
+    f.argtypes, f.restype = [ctypes.c_int] * 6, ctypes.c_int
+    assert f(*shape) == rows

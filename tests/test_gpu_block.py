@@ -39,18 +39,22 @@ def host(t):
     (2, 256, 16, 24, 1024),    # the headline widths (expansion 4)
     (1, 272, 8, 8, 544),       # more than 256 input channels: other projection kernels
 ])
-def test_ffn(dtype, act, B, C, H, W, hidden):
-    print(f"ffn {dtype} act={act} B={B} C={C} {H}x{W} hidden={hidden}", flush=True)
+def test_ffn(dtype, act, B, C, H, W, hidden, launches=None, in_place=False):
+    """launches: 1 or 2 where the call has to take that form (one launch leaves the workspace alone); in_place: out is y."""
+    print(f"ffn {dtype} act={act} B={B} C={C} {H}x{W} hidden={hidden} launches={launches} in_place={in_place}", flush=True)
     rng = np.random.default_rng(C + H + hidden)
     y = wk.round_to_dtype(rng.standard_normal((B, H, W, C)), dtype)
     w = wk.ffn_weights(1000 + hidden, dtype, C, hidden)
     n_ws = msla.msla_ffn_workspace_bytes(B, C, H, W, hidden, TDT[dtype])
     ws = torch.full((n_ws + 1024,), 0xFF, dtype=torch.uint8, device="cuda")       # NaN-poisoned, guarded
-    out = torch.full((B, H, W, C), float("nan"), dtype=TDT[dtype], device="cuda")
-    msla.msla_ffn_forward(dev(y, dtype), dev(w["w1"], dtype), dev(w["w_ffn_dw"], dtype), dev(w["w2"], dtype), act,
+    y_dev = dev(y, dtype)
+    out = y_dev if in_place else torch.full((B, H, W, C), float("nan"), dtype=TDT[dtype], device="cuda")
+    msla.msla_ffn_forward(y_dev, dev(w["w1"], dtype), dev(w["w_ffn_dw"], dtype), dev(w["w2"], dtype), act,
                           out=out, workspace=ws[:n_ws])
     got = host(out)
     assert bool((ws[n_ws:] == 0xFF).all()), "bytes past the workspace were written"
+    if launches is not None:
+        assert bool((ws[:n_ws] == 0xFF).all()) == (launches == 1), f"the FFN did not take {launches} launch(es)"
     ref = blk.ffn_forward(y, w["w1"], w["w_ffn_dw"], w["w2"], act)
     assert np.isfinite(got).all()
     err = np.abs(got - ref).max() / np.abs(ref).max()

@@ -446,7 +446,14 @@ def test_head_size_32_maps_beyond_2_gib(dtype, scales):
     (12, 160, 12, 150, 48), (16, 256, 9, 128, 32),
 ])
 def test_ffn_in_one_launch(dtype, act, B, C, H, W, hidden):
-    block.test_ffn(dtype, act, B, C, H, W, hidden)
+    block.test_ffn(dtype, act, B, C, H, W, hidden, launches=1)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# the two-launch form where it is the faster one: rows and columns that leave most of a block empty, many slabs in few blocks (narrow and wide)
+@pytest.mark.parametrize("B,C,H,W,hidden", [(8, 48, 1, 1040, 208), (300, 64, 3, 3, 256), (3, 128, 4, 16, 1040), (1, 208, 9, 17, 832)])
+def test_ffn_in_two_launches(dtype, B, C, H, W, hidden):
+    block.test_ffn(dtype, 1, B, C, H, W, hidden, launches=2)
 
 
 # a channel-planar x read by the projection itself: planes shorter than a run of 8 (4) tokens and than a tile, of whole runs and odd ones,
