@@ -59,7 +59,7 @@ struct FfnFused {
     static __device__ __forceinline__ int w1_at(int row, int chunk) { return row * (kChunks1 * 16) + (chunk ^ (row & 15)) * 16; }
     // ... and of the 64-byte rows of W2 and of the token tile
     static __device__ __forceinline__ int row64_at(int row, int chunk) { return row * 64 + (chunk ^ ((row >> 2) & 3)) * 16; }
-    static_assert(kLds <= 160 * 1024 && KC % 4 == 0 && BR % 128 == 0 && (TR == 4 || TR == 8) && (ND == 4 || ND == 8), "");
+    static_assert(kLds <= 160 * 1024 && KC % 4 == 0 && BR % 128 == 0 && kW1Vec % 2 == 0 && kW2Vec % 2 == 0 && (TR == 4 || TR == 8) && (ND == 4 || ND == 8), "");
 };
 
 // 16 bytes a lane from a buffer straight into LDS at lds_at + 16 * lane (a lane out of range writes zeros).  lds_at is
@@ -75,6 +75,22 @@ __device__ __forceinline__ RawRsrc raw_rsrc(const void* base, long bytes) {
 }
 __device__ __forceinline__ void load_to_lds(RawRsrc r, unsigned voffset, unsigned lds_at) {
     asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voffset), "s"(r), "{m0}"(lds_at) : "memory");
+}
+// ... two of them from one resource, the second at voffset2 and kStep bytes further on in LDS.  kOneWait: for one such wait, which is
+// the better form up to 128 channels (the building block of 8192 tokens, 128 channels, fp16 34.82 us, 34.95 with a wait each); with
+// more it is not (the FFN of 65536 tokens, 256 -> 1024 channels 106.2, with a wait each 105.8).
+template <int kStep, bool kOneWait>
+__device__ __forceinline__ void load_pair_to_lds(RawRsrc r, unsigned voffset, unsigned voffset2, unsigned lds_at) {
+    if constexpr (!kOneWait) {
+        load_to_lds(r, voffset, lds_at);
+        load_to_lds(r, voffset2, lds_at + kStep);
+        return;
+    }
+    asm volatile(
+        "s_nop 4\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\ts_add_u32 m0, m0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
+        : "+{m0}"(lds_at)
+        : "v"(voffset), "v"(voffset2), "s"(r), "n"(kStep)
+        : "memory", "scc");
 }
 template <int kLeft>
 __device__ __forceinline__ void wait_loads_and_meet() {       // at most kLeft loads outstanding, LDS writes done, then the barrier
@@ -288,15 +304,17 @@ __global__ __launch_bounds__(S::kThreads) void ffn_fused_kernel(const T* __restr
         const int k2 = ((tid & 3) ^ ((tid >> 4) & 3)) * 16;
         const unsigned g2 = (unsigned)(tid >> 2) * e_bytes + k2;
         auto request1 = [&](int slab, int slot) {
+            auto at = [&](int j) { return g1[j % kSame] + (unsigned)(slab * 32 + j / kSame * 16) * c_bytes; };
 #pragma unroll
-            for (int j = 0; j < S::kW1Vec; ++j)
-                load_to_lds(w1res, g1[j % kSame] + (unsigned)(slab * 32 + j / kSame * 16) * c_bytes, lds_w + S::kW1At + slot * S::kW1 + j * 4096);
+            for (int j = 0; j < S::kW1Vec; j += 2)
+                load_pair_to_lds<4096, KC == 4>(w1res, at(j), at(j + 1), lds_w + S::kW1At + slot * S::kW1 + j * 4096);
         };
         auto request2 = [&](int slab, int slot) {
             const unsigned at = slab * 64 + k2 < (int)e_bytes ? g2 + (unsigned)slab * 64u : kOobOffset;
 #pragma unroll
-            for (int j = 0; j < S::kW2Vec; ++j)
-                load_to_lds(w2res, at + (unsigned)(j * 64) * e_bytes, lds_w + S::w2_slot(slot) + j * 4096);
+            for (int j = 0; j < S::kW2Vec; j += 2)
+                load_pair_to_lds<4096, KC == 4>(w2res, at + (unsigned)(j * 64) * e_bytes, at + (unsigned)((j + 1) * 64) * e_bytes,
+                                       lds_w + S::w2_slot(slot) + j * 4096);
         };
         request1(0, 0);
         request1(1, 1);

@@ -133,14 +133,16 @@ def early_scalar_reads(code):
 
 
 def unguarded_lds_loads(code):
-    """indexes of loads straight into LDS without five wait states of s_nop right before them, that is, whatever the compiler put there"""
+    """indexes of loads straight into LDS that don't have, whatever the compiler put there, five wait states right before them (of s_nop, moves
+    of m0 and loads before them), and one of s_nop behind a move of m0"""
     bad = []
     for i, (op, args, _) in enumerate(code):
         if not (op.startswith("buffer_load") and args.endswith(" lds")):
             continue
         j, waited = i - 1, 0
-        while j >= 0 and code[j][0] == "s_nop":
-            waited += int(code[j][1]) + 1
+        while j >= 0 and (code[j][0] == "s_nop" or (code[j][1].endswith(" lds") and waited) or
+                          (code[j][0].startswith("s_") and code[j][1].startswith("m0,") and waited)):
+            waited += int(code[j][1]) + 1 if code[j][0] == "s_nop" else 1
             j -= 1
         # (a branch to the load itself would go round them)
         if waited < SGPR_TO_MEMORY or any(t is not None and j + 1 < t <= i for _, _, t in code):
@@ -208,6 +210,9 @@ def test_the_walk_finds_an_early_read_of_a_scalar_register():
     # s5 through the branch, and the comparison's pair; s[12:15] was not written by the addition
     assert early_scalar_reads(code) == [(0, 5, 2), (6, 7, 0)]
     assert unguarded_lds_loads(code) == [5]
+    # (a second load rests on the first one's wait; none of them may follow a move of m0 at once)
+    pair = [("s_nop", "4", None), code[5], ("s_add_u32", "m0, m0, 0x1000", None), ("s_nop", "0", None), code[5]]
+    assert unguarded_lds_loads(pair) == [] and unguarded_lds_loads(pair[:3] + pair[4:]) == [3] and unguarded_lds_loads(pair[1:]) == [0, 3]
     code[1], code[4] = ("s_nop", "0", None), ("s_nop", "4", None)
     assert early_scalar_reads(code) == [(6, 7, 0)]
     assert unguarded_lds_loads(code) == []
