@@ -1085,6 +1085,9 @@ static bool small_apply_project(int dt, long n_tokens, int tokens_per_image, int
 bool apply_project_writes_planar(int dt, long n_tokens, int tokens_per_image, int n_hb, int c_out) {
     if (tokens_per_image > 0x1ffffff) return false;         // (31 bits of bytes over 32 channels' rows)
     if (small_apply_project(dt, n_tokens, tokens_per_image, n_hb, c_out)) return true;
+#ifdef MSLA_APPLY_NO_WS
+    if (dt != 0) return false;              // (the tiled form takes them all)
+#endif
     return n_hb <= 32 && !(dt == 0 && tiled_fp32_pays(n_tokens / tokens_per_image, tokens_per_image, c_out));
 }
 
