@@ -1088,6 +1088,10 @@ bool apply_project_writes_planar(int dt, long n_tokens, int tokens_per_image, in
 #ifdef MSLA_APPLY_NO_WS
     if (dt != 0) return false;              // (the tiled form takes them all)
 #endif
+    // fp16's widest form has no registers left for this (it spills), and its stores lose most where rows start at odd elements: there, beyond
+    // three million elements, the transposition's launch weighs less (10 x 47 x 49 tokens, 320 channels, 26 head-branches 81.1 / 86.2, 8 x 53 x
+    // 67, 256, 32 82.5 / 84.9, 2 x 219 x 39, 304, 26 68.1 / 69.6, but 3 x 81 x 19, 208, 30 34.8 / 33.4, 9 x 46 x 65, 240, 28 73.8 / 71.8).
+    if (dt == 1 && n_hb > 24 && c_out > 128 && tokens_per_image % 2 != 0 && n_tokens * c_out > (3L << 20)) return false;
     return n_hb <= 32 && !(dt == 0 && tiled_fp32_pays(n_tokens / tokens_per_image, tokens_per_image, c_out));
 }
 

@@ -843,8 +843,17 @@ hipError_t run_qkv_project(const void* x, const void* w_qkv, void* q_ms, long q_
 // transposition / without: 16 bits 1 x 20 x 20 tokens, 208 channels 30.6 / 28.9, 16 x 64 x 64, 64 46.0 / 42.4, 8 x 101 x 99, 128
 // 101.4 / 100.5, 8 x 64 x 128, 256 146.7 / 133.7; fp32 (8 to 12 groups of 64 output channels from 192 on) 1600 tokens, 32 channels 23.6 / 21.5,
 // 16384, 64 41.1 / 38.5, 8192, 128 48.8 / 48.0, 16384, 128 73.0 / 75.4, 4096, 192 55.6 / 55.3, 4096, 256 68.8 / 76.8.
-bool qkv_project_takes_planar(int dt, long n_tokens, int c_in, int heads) {
-    return qkv_weight_stationary(dt, n_tokens, c_in, heads) && (dt != 0 || c_in <= 64 || (c_in <= 128 && n_tokens <= 8192));
+// Two kinds of large 16-bit maps lose by it (us with a transposition / without, several input sets in turn):
+// - more than 20 heads (five groups of output channels), each group of which fetches x again, in pieces that start anywhere, where x has more
+//   than the 3 MB that an XCD's L2 holds beside the weights: 13 x 27 x 25 tokens, 256 channels, 27 heads 43.3 / 45.8, 13 x 185 x 15, 256, 28
+//   109.8 / 119.4, 6 x 3 x 1537, 64, 32 64.1 / 76.1 (one set 59.8 / 58.4), but 2 x 79 x 61, 160, 26 43 / 41, and up to 20 heads 0.99-1.10 times;
+// - small images, most of whose tiles span several and cut runs of eight tokens, with more than 128 channels, of which a thread brings four:
+//   131 x 9 x 9, 240 39.1 / 41.0, 950 x 4 x 5, 144 59.2 / 61.9, 384 x 7 x 11, 192 60.0 / 61.7, but 77 x 15 x 7, 192 31.3 / 30.4.
+bool qkv_project_takes_planar(int dt, long n_tokens, int c_in, int heads, int plane) {
+    if (!qkv_weight_stationary(dt, n_tokens, c_in, heads)) return false;
+    if (dt == 0) return c_in <= 64 || (c_in <= 128 && n_tokens <= 8192);
+    if (heads > 20 && n_tokens * c_in * 2 > (3L << 20)) return false;
+    return !(c_in > 128 && plane < 128 && plane % 8 != 0 && n_tokens > 8192);
 }
 
 hipError_t launch_qkv_project(int dt, const void* x, const void* w_qkv, void* q_ms, long q_ms_stride,

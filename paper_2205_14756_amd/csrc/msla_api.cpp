@@ -518,7 +518,7 @@ static msla_status forward_impl(const void* x, const void* w_qkv, const void* w_
     // channel-planar maps themselves, neither is needed.
     const void* x_tok = x;
     void* out_tok = out;
-    const bool x_planar = layout == MSLA_NCHW && !fused && msla::qkv_project_takes_planar((int)dt, s.T, C, s.heads);
+    const bool x_planar = layout == MSLA_NCHW && !fused && msla::qkv_project_takes_planar((int)dt, s.T, C, s.heads, (int)s.N);
     const bool out_planar = layout == MSLA_NCHW && msla::apply_project_writes_planar((int)dt, s.T, (int)s.N, s.S * s.heads, C);
     if (layout == MSLA_NCHW) {
         if (!x_planar) {

@@ -24,7 +24,7 @@ hipError_t launch_qkv_project(int dt, const void* x, const void* w_qkv, void* q_
                               void* kv_raw, long kv_tok_stride, long kv_head_stride, long kv_span,
                               long n_tokens, int c_in, int heads, hipStream_t stream, int plane = 0);
 // plane > 0: x is channel-planar, [n_tokens / plane, c_in, plane], which these calls take:
-bool qkv_project_takes_planar(int dt, long n_tokens, int c_in, int heads);
+bool qkv_project_takes_planar(int dt, long n_tokens, int c_in, int heads, int plane);
 
 struct AggregateArgs {
     // raw Q, K, V maps: element (token n, head h, channel e) of map m lives at

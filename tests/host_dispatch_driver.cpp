@@ -54,7 +54,7 @@ int main() {
                     const long T = (long)B * N;
                     if (T > (1L << 21)) continue;
                     for (int heads : {1, C / 16, 21, 32, 40}) {
-                        const bool in = msla::qkv_project_takes_planar(dt, T, C, heads);
+                        const bool in = msla::qkv_project_takes_planar(dt, T, C, heads, N);
                         if (in && msla::launch_qkv_project(dt, x, x, x, heads * 16, x, heads * 32, 32, T * heads * 32, T, C, heads, nullptr, N) != hipSuccess) {
                             std::fprintf(stderr, "type %d, %d x %d tokens, %d channels, %d heads: a planar x is refused\n", dt, B, N, C, heads);
                             ++g_failures;

@@ -100,7 +100,7 @@ hipError_t launch_linear(int dt, const void* x, const void* w, void* y, long n, 
 hipError_t launch_linear_act(int dt, const void* x, const void* w, void* y, long n, int c_in, int c_out, int, hipStream_t s) {
     return launch_linear(dt, x, w, y, n, c_in, c_out, s);
 }
-bool qkv_project_takes_planar(int dt, long n, int, int) { return dt != 0 || n <= 8192; }
+bool qkv_project_takes_planar(int dt, long n, int, int, int) { return dt != 0 || n <= 8192; }
 hipError_t launch_qkv_project(int dt, const void* x, const void* w_qkv, void* q_ms, long q_ms_stride, void* kv_raw,
                               long kv_tok_stride, long kv_head_stride, long kv_span, long n, int c_in, int heads, hipStream_t, int plane) {
     if (plane > 0 && n % plane != 0) fail("a channel-planar x of whole images");

@@ -246,3 +246,33 @@ def test_ffn_takes_the_faster_form(lib, shape, rows):
     f = lib._ZN4msla14ffn_block_rowsEiiiiii
     f.argtypes, f.restype = [ctypes.c_int] * 6, ctypes.c_int
     assert f(*shape) == rows
+
+
+# (dtype, tokens, channels, heads, tokens an image): whether the projection reads a channel-planar x itself
+@pytest.mark.parametrize("call,planar", [
+    ((1, 8 * 9999, 128, 16, 9999), True), ((2, 8 * 8192, 256, 16, 8192), True), ((2, 2 * 4819, 160, 26, 4819), True), ((1, 9830, 160, 21, 9830), True),
+    # many groups of output channels, each of which reads all of a large x
+    ((1, 9831, 160, 21, 9831), False), ((1, 9831, 160, 20, 9831), True), ((2, 13 * 675, 256, 27, 675), False), ((2, 6 * 4611, 64, 32, 4611), False),
+    # tiles of several images
+    ((1, 256 * 49, 256, 16, 49), False), ((2, 131 * 81, 240, 15, 81), False), ((1, 16384, 256, 16, 64), True), ((1, 65 * 127, 256, 16, 127), False),
+    ((1, 65 * 129, 256, 16, 129), True), ((1, 64 * 127, 256, 16, 127), True), ((2, 512 * 49, 128, 8, 49), True),
+    ((0, 1600, 32, 4, 1600), True), ((0, 8192, 128, 8, 8192), True), ((0, 8193, 128, 8, 8193), False), ((0, 4096, 192, 12, 4096), False),
+    ((1, 4096, 272, 16, 4096), False),
+])
+def test_projection_reads_a_planar_map_where_that_pays(lib, call, planar):
+    f = lib._ZN4msla24qkv_project_takes_planarEiliii
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    assert f(*call) == planar
+
+
+# (dtype, tokens, tokens an image, head-branches, channels): whether the output projection writes a channel-planar map itself
+@pytest.mark.parametrize("call,planar", [
+    ((1, 8 * 6144, 6144, 32, 256), True), ((2, 8 * 3551, 3551, 32, 256), True), ((1, 8 * 3551, 3551, 24, 256), True), ((1, 8 * 3551, 3551, 32, 128), True),
+    ((1, 8 * 3551, 3551, 32, 256), False), ((1, 10 * 2303, 2303, 26, 320), False),      # fp16's widest form, rows that start anywhere
+    ((1, 3 * 1539, 1539, 30, 208), True), ((1, 12288, 4095 + 1, 32, 256), True), ((1, 12289, 12289, 32, 256), False), ((1, 12290, 12290, 32, 256), True), ((1, 3 * 4095, 4095, 32, 256), True),
+    ((1, 1 << 25, 1 << 25, 16, 128), False), ((0, 1600, 1600, 4, 32), True), ((2, 4 * 8515, 8515, 40, 512), False),
+])
+def test_output_projection_writes_a_planar_map_where_that_pays(lib, call, planar):
+    f = lib._ZN4msla27apply_project_writes_planarEiliii
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    assert f(*call) == planar

@@ -476,6 +476,8 @@ def test_channel_planar_input(dtype, B, C, H, W, heads, scales):
         (5, 16, 1, 3, 1, ()), (2, 144, 5, 7, 9, ()), (3, 48, 3, 11, 9, (5,)), (2, 176, 13, 8, 12, (3,)), (2, 80, 9, 15, 14, (5,)),
         (1, 272, 7, 9, 16, (5,)), (2, 208, 17, 5, 13, (3, 5)), (3, 256, 32, 33, 16, (3,))]
 ] + [("f16", 2, 144, 9, 31, 23, (3, 5)), ("bf16", 1, 352, 7, 13, 22, (3, 5)), ("f16", 1, 512, 6, 7, 32, (3, 5)), ("bf16", 1, 288, 5, 9, 36, (3, 5)),
-     ("f32", 1, 256, 129, 128, 16, (5,))])
+     ("f32", 1, 256, 129, 128, 16, (5,)),
+     # only one of the two maps left to a transposition, by tiles of several small images, by 26 heads and by fp16's widest form on a large map of odd rows; and both
+     ("bf16", 131, 144, 9, 7, 9, ()), ("f16", 2, 192, 45, 101, 26, ()), ("f16", 1, 256, 113, 115, 14, (5,)), ("f16", 3, 256, 65, 67, 26, ())])
 def test_channel_planar_output(dtype, B, C, H, W, heads, scales):
     base.test_forward_channel_planar_layout(dtype, B, C, H, W, heads, 16, scales)
