@@ -17,12 +17,6 @@
 namespace msla {
 namespace {
 
-template <int ACT>
-__device__ __forceinline__ float activate(float a) {
-    if constexpr (ACT == 0) return fmaxf(a, 0.f);
-    else return a * __builtin_amdgcn_fmed3f(fmaf(a, 1.0f / 6.0f, 0.5f), 0.f, 1.f);      // a * clip(a + 3, 0, 6) / 6
-}
-
 // 16 bytes of consecutive channels <-> fp32
 template <class T>
 struct Pack {

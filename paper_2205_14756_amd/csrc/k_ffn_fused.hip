@@ -105,12 +105,6 @@ __device__ __forceinline__ void wait_lds_and_meet() {         // LDS reads and w
     asm volatile("" ::: "memory");
 }
 
-template <int ACT>
-__device__ __forceinline__ float activate(float a) {
-    if constexpr (ACT == 0) return fmaxf(a, 0.f);
-    else return a * __builtin_amdgcn_fmed3f(fmaf(a, 1.0f / 6.0f, 0.5f), 0.f, 1.f);      // a * clip(a + 3, 0, 6) / 6
-}
-
 // acc + t.half[TH] * h.half[HH] in fp32.  fp16 as the instruction that widens both halves itself: left to choose, the compiler
 // converts some operands ahead and keeps them, and spills.
 template <class T, bool kTapScalar, int TH, int HH>

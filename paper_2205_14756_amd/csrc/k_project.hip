@@ -43,15 +43,15 @@ struct PlainDest {
     long n_tokens;
     int c_out;
     // optional activation applied to the fp32 sums before their one rounding: -1 none, 0 ReLU,
-    // 1 hard-swish a * clip(a + 3, 0, 6) / 6, evaluated as a * clip(a / 6 + 1/2, 0, 1) (the FFN's expand projection)
+    // 1 hard-swish (the FFN's expand projection)
     int act = -1;
     __device__ __forceinline__ f32x4 activate(f32x4 v) const {
         if (act == 0) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+            for (int e = 0; e < 4; ++e) v[e] = msla::activate<0>(v[e]);
         } else if (act == 1) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = v[e] * __builtin_amdgcn_fmed3f(fmaf(v[e], 1.0f / 6.0f, 0.5f), 0.f, 1.f);
+            for (int e = 0; e < 4; ++e) v[e] = msla::activate<1>(v[e]);
         }
         return v;
     }

@@ -208,6 +208,13 @@ __device__ __forceinline__ void store_frag(void* p, typename Traits<T>::Frag f) 
     }
 }
 
+// the FFN's activations (0: ReLU, 1: hard-swish); its one-launch and two-launch forms agree bit for bit, this included
+template <int ACT>
+__device__ __forceinline__ float activate(float a) {
+    if constexpr (ACT == 0) return fmaxf(a, 0.f);
+    else return a * __builtin_amdgcn_fmed3f(fmaf(a, 1.0f / 6.0f, 0.5f), 0.f, 1.f);      // a * clip(a + 3, 0, 6) / 6
+}
+
 // eight (fp32: four) tokens of one channel, t .. of a tile with `rows` tokens, to a planar map (whose rows start anywhere)
 template <class T>
 __device__ __forceinline__ void store_planar(T* at, int t, int rows, u32x4 v) {

@@ -265,6 +265,9 @@ hipError_t launch_generic_core(int dt, const GenericArgs& a, hipStream_t) {
     }
     return hipSuccess;
 }
+// (whether the one-launch FFN takes a call, and how many calls either form got)
+static bool g_ffn_accept = false;
+static int g_ffn_one = 0, g_ffn_two = 0;
 hipError_t launch_ffn_dw_project(int dt, const void* h, const void* w_dw, const void* w2, const void* res, void* out, int B, int H,
                                  int W, int E, int c_out, int, hipStream_t) {
     const size_t e = esz(dt), T = (size_t)B * H * W;
@@ -273,18 +276,23 @@ hipError_t launch_ffn_dw_project(int dt, const void* h, const void* w_dw, const 
     inside(w2, (size_t)c_out * E * e, "ffn w2");
     inside(res, T * c_out * e, "ffn residual");
     inside(out, T * c_out * e, "ffn out");
+    disjoint({{h, T * E * e, "the expanded map"}, {out, T * c_out * e, "ffn out"}});
+    ++g_ffn_two;
     return hipSuccess;
 }
 hipError_t launch_ffn_fused(int dt, const void* y, const void* w1, const void* w_dw, const void* w2, void* out, int B, int C, int H,
                             int W, int E, int, hipStream_t) {
-    // (the operands are checked, then the two launches take the call, so that their carving is checked as well)
+    // (it reads y beside a block while other blocks write out)
     const size_t e = esz(dt), T = (size_t)B * H * W;
     inside(y, T * C * e, "fused ffn y");
     inside(w1, (size_t)E * C * e, "fused ffn w1");
     inside(w_dw, (size_t)E * 9 * e, "fused ffn w_dw");
     inside(w2, (size_t)C * E * e, "fused ffn w2");
     inside(out, T * C * e, "fused ffn out");
-    return hipErrorNotSupported;
+    disjoint({{y, T * C * e, "fused ffn y"}, {out, T * C * e, "fused ffn out"}});
+    if (!g_ffn_accept) return hipErrorNotSupported;
+    ++g_ffn_one;
+    return hipSuccess;
 }
 hipError_t launch_softmax_attention(int dt, const void* qkv, void* att, int B, int N, int heads, hipStream_t) {
     inside(qkv, (size_t)B * N * 3 * heads * 16 * esz(dt), "softmax qkv");
@@ -395,8 +403,15 @@ void run_module(const Mod& m, int dt) {
                "block forward with a short workspace");
         g_case = std::string("msla_ffn_forward ") + tag;
         char* fw = buffer("ffn workspace", fws);
-        expect(msla_ffn_forward(x, w1, wfd, w2, out, fw, fws, m.B, m.C, m.H, m.W, hidden, MSLA_ACT_RELU, mdt, nullptr), MSLA_OK,
-               "ffn forward");
+        // two launches, one, and two again: in place
+        for (int form = 0; form < 3; ++form) {
+            msla::g_ffn_accept = form > 0;
+            msla::g_ffn_one = msla::g_ffn_two = 0;
+            expect(msla_ffn_forward(x, w1, wfd, w2, form == 2 ? x : out, fw, fws, m.B, m.C, m.H, m.W, hidden, MSLA_ACT_RELU, mdt, nullptr), MSLA_OK,
+                   "ffn forward");
+            if (msla::g_ffn_one != (form == 1) || msla::g_ffn_two != (form != 1)) fail("the FFN took the other form");
+        }
+        msla::g_ffn_accept = false;
         // backward pass and softmax on the projected map as [B, N, 3*Ct]
         size_t gws = 0;
         g_case = std::string("msla_linear_attention_backward ") + tag;

@@ -79,13 +79,15 @@ def test_core_writes_attention_rows(dtype, B, H, W, heads):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-# blocks of 64 and of 128 tokens (as 4 x 32 and, the last, as 8 x 16), up to 128 and up to 256 output channels a workgroup; ragged columns and rows, channel
+# in place, which the two launches take: blocks of 64 and of 128 tokens (as 4 x 32 and, the last, as 8 x 16), up to 128 and up to 256 output channels a workgroup; out
+# of place, where one launch takes those of up to 256 channels, its blocks of 4 and of 8 rows; ragged columns and rows, channel
 # groups past the output (48, 144), a hidden size that is no whole number of slabs, a narrow map, more than one group (272)
 @pytest.mark.parametrize("B,C,H,W,hidden", [(1, 48, 5, 17, 80), (3, 48, 61, 130, 80), (2, 144, 7, 33, 144),
                                             (4, 144, 61, 113, 160), (2, 128, 50, 3, 128), (1, 272, 9, 18, 288),
                                             (6, 144, 61, 70, 64)])
 def test_ffn_block_shapes(dtype, B, C, H, W, hidden):
     block.test_ffn(dtype, 1, B, C, H, W, hidden)
+    block.test_ffn(dtype, 1, B, C, H, W, hidden, launches=2, in_place=True)
 
 
 # fp32 projections and normalise-and-apply: 32, 64, 96, 128, 192 and 256 input channels (and the first beyond), 16 channels
@@ -136,10 +138,11 @@ def test_raw_state_of_interleaved_heads(dtype, B, H, W, heads):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-# maps of few rows, many workgroups: blocks of 4 x 32 tokens by up to 128 output channels; and by 256, one row short of a block
+# maps of few rows, many workgroups, in place: blocks of 4 x 32 tokens by up to 128 output channels; and by 256, one row short of a block
 @pytest.mark.parametrize("B,C,H,W,hidden", [(40, 48, 3, 200, 80), (40, 144, 3, 200, 80)])
 def test_ffn_blocks_of_flat_maps(dtype, B, C, H, W, hidden):
     block.test_ffn(dtype, 1, B, C, H, W, hidden)
+    block.test_ffn(dtype, 1, B, C, H, W, hidden, launches=2, in_place=True)
 
 
 # fp32 states: workgroups that walk 16 tiles of 8 x 32 tokens, and fewer, over a ragged map
@@ -298,10 +301,11 @@ def test_long_contraction_in_parts_of_a_block(dtype, B, C, H, W, heads, scales):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-# more than 128 channels on few tokens: channel blocks of 128 (two, the second short; three; 256 blocks in all), and one block past a round
+# more than 128 channels on few tokens, in place: channel blocks of 128 (two, the second short; three; 256 blocks in all), and one block past a round
 @pytest.mark.parametrize("B,C,H,W,hidden", [(1, 144, 5, 17, 80), (2, 272, 9, 18, 96), (2, 160, 32, 128, 64), (1, 144, 43, 192, 64)])
 def test_ffn_channel_blocks_of_small_maps(dtype, B, C, H, W, hidden):
     block.test_ffn(dtype, 1, B, C, H, W, hidden)
+    block.test_ffn(dtype, 1, B, C, H, W, hidden, launches=2, in_place=True)
 
 
 def test_small_map_keeps_an_overflow_to_its_own_token():
@@ -447,6 +451,35 @@ def test_head_size_32_maps_beyond_2_gib(dtype, scales):
 ])
 def test_ffn_in_one_launch(dtype, act, B, C, H, W, hidden):
     block.test_ffn(dtype, act, B, C, H, W, hidden, launches=1)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+# more than 256 channels, which are two launches always: 64-token blocks of 256 output channels, 128-token ones as 8 x 16 and as 4 x 32, a second channel
+# group of 16, hidden sizes that are no whole number of slabs
+@pytest.mark.parametrize("B,C,H,W,hidden", [(6, 272, 13, 61, 80), (40, 272, 31, 7, 48), (40, 272, 3, 200, 112), (3, 272, 37, 70, 48)])
+def test_ffn_of_more_than_256_channels(dtype, B, C, H, W, hidden):
+    block.test_ffn(dtype, 1, B, C, H, W, hidden, launches=2)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("act", [0, 1])
+# in place is two launches; out of place, in 16 bits, one: blocks of 4 and of 8 rows, up to 128 channels and beyond, half a slab at the end
+@pytest.mark.parametrize("B,C,H,W,hidden", [(2, 48, 9, 31, 80), (9, 112, 12, 150, 112), (2, 208, 13, 5, 304), (12, 160, 12, 150, 48)])
+def test_ffn_in_place_and_in_one_launch_agree_bit_for_bit(dtype, act, B, C, H, W, hidden):
+    print(f"routes: ffn in place {dtype} act={act} {B}x{C}x{H}x{W} hidden={hidden}", flush=True)
+    rng = np.random.default_rng(C)
+    y = base.dev(rng.standard_normal((B, H, W, C)) * np.exp2(rng.integers(-24, 3, (B, H, W, 1))), dtype)      # (tokens of subnormal fp16 among them)
+    y[0, H // 2, W // 2, 3], y[-1, 0, 0, 5] = float("inf"), float("nan")
+    w = wk.ffn_weights(77, dtype, C, hidden)
+    args = (base.dev(w["w1"], dtype), base.dev(w["w_ffn_dw"], dtype), base.dev(w["w2"], dtype), act)
+    out = msla.msla_ffn_forward(y, *args)
+    same = msla.msla_ffn_forward(y, *args, out=y)
+    torch.cuda.synchronize()
+    assert same.data_ptr() == y.data_ptr()
+    bits = {"f32": torch.int32, "f16": torch.int16, "bf16": torch.int16}[dtype]
+    nan = torch.isnan(out)
+    assert torch.equal(nan, torch.isnan(y)) and bool(nan.any()) and not bool(nan.all())
+    assert torch.equal(out.view(bits)[~nan], y.view(bits)[~nan])
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
