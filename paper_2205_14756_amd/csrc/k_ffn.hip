@@ -6,11 +6,11 @@
 //   out = y + W2 g                       1x1 project, E -> C, no activation, residual
 // with act = ReLU or hard-swish, no bias, no normalisation.
 //
-// Two launches: the expand projection is the library's 1x1 projection kernel with the activation
-// applied to its fp32 sums; the kernel here does the rest -- depthwise 3x3, activation, the hidden -> C
-// projection and the residual -- with the depthwise result produced on chip as the projection's token
-// operand.  The block's y = x + MSLA(x) is formed in the epilogue of the attention module's output
-// projection.
+// Two launches, for fp32, for more than 256 channels, for out == y and where one launch (k_ffn_fused.hip) is not the faster
+// form: the expand projection is the library's 1x1 projection kernel with the activation applied to its fp32 sums; the kernel
+// here does the rest -- depthwise 3x3, activation, the hidden -> C projection and the residual -- with the depthwise result
+// produced on chip as the projection's token operand.  The block's y = x + MSLA(x) is formed in the epilogue of the attention
+// module's output projection.
 #include "gemm_tile.h"
 #include "msla_kernels.h"
 
@@ -450,7 +450,7 @@ hipError_t run_dw_project_split_as(const void* h, const void* w_dw, const void* 
 }
 // Rounds of workgroups, one a compute unit, over the map's ragged edges decide the block.  Blocks of 64 tokens take two
 // thirds of the time of blocks of 128 (and two of 128 channels fit a unit together): they are taken where they need no more rounds.
-// 16-bit FFNs, us with 64 / 128 tokens a block (rounds): 8192 tokens, 256 -> 1024 channels 32.4 / 42.0 (1 / 1), 16384 39.6 / 48.5
+// 16-bit FFNs as two launches (which of them are: ffn_block_rows), us with 64 / 128 tokens a block (rounds): 8192 tokens, 256 -> 1024 channels 32.4 / 42.0 (1 / 1), 16384 39.6 / 48.5
 // (1 / 1), 20480 of 192 49.0 / 41.4 (2 / 1), 24576 62.7 / 52.7 (2 / 1), 32768 79.1 / 68.0 (2 / 1), 40960, 256 -> 512 56.8 / 56.8 (3 / 2);
 // 16384, 128 -> 512 20.0 / 24.1 (1 / 1), 20480 30.6 / 26.3 (2 / 1), 32768 34.6 / 31.2 (2 / 1).
 // 128 tokens are 8 x 16 or 4 x 32, whichever takes fewer rounds (6 x 61 x 70, 192 -> 768 channels, 288 blocks of 4 x 32 or 240 of
