@@ -60,7 +60,7 @@ struct FfnFused {
     static __device__ __forceinline__ int w1_at(int row, int chunk) { return row * (kChunks1 * 16) + (chunk ^ (row & 15)) * 16; }
     // ... and of the 64-byte rows of W2 and of the token tile
     static __device__ __forceinline__ int row64_at(int row, int chunk) { return row * 64 + (chunk ^ ((row >> 2) & 3)) * 16; }
-    static_assert(kLds <= 160 * 1024 && KC % 4 == 0 && BR % 128 == 0 && kW1Vec % 2 == 0 && kW2Vec % 2 == 0 && (TR == 4 || TR == 8) && (ND == 4 || ND == 8), "");
+    static_assert(kLds <= 160 * 1024 && KC % 4 == 0 && BR % 128 == 0 && (TR == 4 || TR == 8) && (ND == 4 || ND == 8), "");
 };
 
 // 16 bytes a lane from a buffer straight into LDS at lds_at + 16 * lane (a lane out of range writes zeros).  lds_at is
@@ -77,20 +77,16 @@ __device__ __forceinline__ RawRsrc raw_rsrc(const void* base, long bytes) {
 __device__ __forceinline__ void load_to_lds(RawRsrc r, unsigned voffset, unsigned lds_at) {
     asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voffset), "s"(r), "{m0}"(lds_at) : "memory");
 }
-// ... two of them from one resource, the second at voffset2 and kStep bytes further on in LDS.  kOneWait: for one such wait, which is
-// the better form up to 128 channels (the building block of 8192 tokens, 128 channels, fp16 34.82 us, 34.95 with a wait each); with
-// more it is not (the FFN of 65536 tokens, 256 -> 1024 channels 106.2, with a wait each 105.8).
-template <int kStep, bool kOneWait>
-__device__ __forceinline__ void load_pair_to_lds(RawRsrc r, unsigned voffset, unsigned voffset2, unsigned lds_at) {
-    if constexpr (!kOneWait) {
-        load_to_lds(r, voffset, lds_at);
-        load_to_lds(r, voffset2, lds_at + kStep);
-        return;
-    }
+// ... four of them for one such wait: v0 and v1 to lds_at and kStep further on, v2 and v3 of another buffer to lds_at2 and kStep further on
+template <int kStep>
+__device__ __forceinline__ void load_four_to_lds(RawRsrc r, unsigned v0, unsigned v1, unsigned lds_at, RawRsrc r2, unsigned v2, unsigned v3,
+                                                 unsigned lds_at2) {
     asm volatile(
-        "s_nop 4\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\ts_add_u32 m0, m0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
+        "s_nop 4\n\tbuffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %5, 0 offen lds\n\t"
+        "s_mov_b32 m0, %7\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %6, 0 offen lds\n\ts_add_u32 m0, m0, %8\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %4, %6, 0 offen lds"
         : "+{m0}"(lds_at)
-        : "v"(voffset), "v"(voffset2), "s"(r), "n"(kStep)
+        : "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(r), "s"(r2), "s"(lds_at2), "n"(kStep)
         : "memory", "scc");
 }
 template <int kLeft>
@@ -298,18 +294,27 @@ __global__ __launch_bounds__(S::kThreads) void ffn_fused_kernel(const T* __restr
         }
         const int k2 = ((tid & 3) ^ ((tid >> 4) & 3)) * 16;
         const unsigned g2 = (unsigned)(tid >> 2) * e_bytes + k2;
+        auto at1 = [&](int slab, int j) { return g1[j % kSame] + (unsigned)(slab * 32 + j / kSame * 16) * c_bytes; };
+        auto at2 = [&](int slab, int j) { return (slab * 64 + k2 < (int)e_bytes ? g2 + (unsigned)slab * 64u : kOobOffset) + (unsigned)(j * 64) * e_bytes; };
         auto request1 = [&](int slab, int slot) {
-            auto at = [&](int j) { return g1[j % kSame] + (unsigned)(slab * 32 + j / kSame * 16) * c_bytes; };
 #pragma unroll
-            for (int j = 0; j < S::kW1Vec; j += 2)
-                load_pair_to_lds<4096, KC == 4>(w1res, at(j), at(j + 1), lds_w + S::kW1At + slot * S::kW1 + j * 4096);
+            for (int j = 0; j < S::kW1Vec; ++j) load_to_lds(w1res, at1(slab, j), lds_w + S::kW1At + slot * S::kW1 + j * 4096);
         };
         auto request2 = [&](int slab, int slot) {
-            const unsigned at = slab * 64 + k2 < (int)e_bytes ? g2 + (unsigned)slab * 64u : kOobOffset;
 #pragma unroll
-            for (int j = 0; j < S::kW2Vec; j += 2)
-                load_pair_to_lds<4096, KC == 4>(w2res, at + (unsigned)(j * 64) * e_bytes, at + (unsigned)((j + 1) * 64) * e_bytes,
-                                       lds_w + S::w2_slot(slot) + j * 4096);
+            for (int j = 0; j < S::kW2Vec; ++j) load_to_lds(w2res, at2(slab, j), lds_w + S::w2_slot(slot) + j * 4096);
+        };
+        // W1 of one slab and W2 of another, a step's loads.  Up to 128 channels these are four and a step is short: one wait for all of them (the
+        // building block of 8192 tokens, 128 channels, fp16 34.8-34.9 us, with no wait at all 34.9-35.0, with one each or one a pair 34.9-35.1;
+        // the FFN alone 14.35, with none 14.25, with one each 14.4).
+        auto request = [&](int slab1, int slot1, int slab2, int slot2) {
+            if constexpr (S::kW1Vec == 2 && S::kW2Vec == 2) {
+                load_four_to_lds<4096>(w1res, at1(slab1, 0), at1(slab1, 1), lds_w + S::kW1At + slot1 * S::kW1, w2res, at2(slab2, 0),
+                                       at2(slab2, 1), lds_w + S::w2_slot(slot2));
+            } else {
+                request1(slab1, slot1);
+                request2(slab2, slot2);
+            }
         };
         request1(0, 0);
         request1(1, 1);
@@ -328,8 +333,7 @@ __global__ __launch_bounds__(S::kThreads) void ffn_fused_kernel(const T* __restr
         request1(3, 0);
         wait_loads_and_meet<S::kW1Vec>();
         for (int i = 0; i < n_slab; ++i) {
-            request1(i + 4, s1);
-            request2(i + 2, s2);
+            request(i + 4, s1, i + 2, s2);
             const char* wt = lds + S::w2_slot(s0);
             const char* tok = ldsG + (i & 1) * S::kTok;
             Vec fa[IO];
