@@ -13,12 +13,12 @@
 //
 // What it saves is the expanded map (134 MB written and 1.4 times read on the headline map) and a launch; what it pays is the
 // expansion of the halo, 1.5 times (blocks of 128 tokens) or 2 times the products.  8 x 8192 tokens, 256 -> 1024 channels, fp16 132 ->
-// 106 us on several input sets in turn, 110 -> 106 on one, whose expanded map stays in the memory-side cache, 122 -> 122 for a call alone on
-// an idle GPU; 8192 tokens, 128 -> 512 channels 17.2 -> 14.4 (alone 19.8 -> 17.5).  Where it loses: see ffn_block_rows.  Bound by the waves' own instruction streams: a wave alone on its SIMD's
-// issue port sends a vector instruction every 8.5 cycles, and a step of the headline map (2500 cycles, of which 1280 of the matrix
-// pipe) takes the depthwise waves 1400, the expanding ones 1160 and the projecting ones 600 when each is alone.  Before the jobs
-// were given to different waves the same map took 156 us (eight waves that did all three), with the weights through registers,
-// requested one step ahead, 297.
+// 106 us on several input sets in turn, 110 -> 106 on one, whose expanded map stays in the memory-side cache, 122 -> 122 for a call
+// alone on an idle GPU; 8192 tokens, 128 -> 512 channels 17.2 -> 14.4 (alone 19.8 -> 17.5).  Where it loses: see ffn_block_rows.
+// Bound by the waves' own instruction streams: a wave alone on its SIMD's issue port sends a vector instruction every 8.5 cycles, and
+// a step of the headline map (2500 cycles, of which 1280 of the matrix pipe) takes the depthwise waves 1400, the expanding ones 1160
+// and the projecting ones 600 when each is alone.  Before the jobs were given to different waves the same map took 156 us (eight
+// waves that did all three), with the weights through registers, requested one step ahead, 297.
 #include "msla_device.h"
 #include "msla_kernels.h"
 
@@ -366,9 +366,9 @@ __global__ __launch_bounds__(S::kThreads) void ffn_fused_kernel(const T* __restr
         // ------------------------------------------------------------ depthwise
         // CH channels of RPL rows a lane, column x16.  The filter taps are the same for all lanes.  Eight waves keep them in scalar
         // registers, requested a slab ahead when the slab's LDS reads have arrived (any wait for an LDS read behind them would
-        // wait for them as well; with blocks of 128 tokens in bf16 the scalar registers don't suffice and the compiler keeps 102 of
-        // them, with hard-swish 38, in lanes of vector registers).  One wave a SIMD has no registers for two sets of eight channels, and no other wave beside it
-        // to cover a request: those take them from LDS, where they arrive with the weights.
+        // wait for them as well; bf16 blocks of 128 tokens have too few of these registers, and the compiler keeps 102, with
+        // hard-swish 38, in lanes of vector registers).  One wave a SIMD has no registers for two sets of eight channels, and no
+        // other wave beside it to cover a request: those take them from LDS, where they arrive with the weights.
         constexpr bool kTapsInLds = S::kTapSlot > 0;
         const int wd = wave - 8, wq = wd & 3, part = wd >> 2;
         const int sub = CH == 4 ? part * 4 : 0, row0 = (CH == 4 ? 0 : part * 4) + q * RPL;
