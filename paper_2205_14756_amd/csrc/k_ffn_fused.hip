@@ -511,11 +511,12 @@ hipError_t run_ffn_fused(bool small, const void* y, const void* w1, const void* 
 }  // namespace
 
 // One launch pays a round of workgroups, one a compute unit, and each slab in it, whatever share of its blocks' tokens and of their
-// halo is in the image; the two launches pay for the elements of the expanded map, and less a round.  So neither the number of rounds
-// nor the fill of a block decides by itself: the time of the three forms is estimated.  The constants are fitted to 508 shapes (32
-// tokens to 200 million elements of the expanded map, 16 to 256 channels, 16 to 4096 hidden ones, rows of 1 to 4096 tokens), to
-// calls in a row on several input sets in turn and on one: estimate / measured is 0.91 to 1.08 for nine shapes in ten, and the form
-// taken is within 3 % of the best of the three at 98 in 100.  Two launches / blocks of 64 tokens / of 128, us in turn (on one set):
+// halo is in the image; the two launches pay for the expanded map -- its elements, and a pass over y for every 192 (256) of its
+// channels -- and less a round.  So neither the number of rounds nor the fill of a block decides by itself: the time of the three
+// forms is estimated.  The constants are fitted to 1100 shapes (32 tokens to 200 million elements of the expanded map, 16 to 256
+// channels, 16 to 4096 hidden ones, rows of 1 to 4096 tokens), to calls in a row on several input sets in turn and on one: estimate /
+// measured is 0.93 to 1.05 for nine shapes in ten, and the form taken is within 3 % of the best of the three at 99 in 100.
+// Two launches / blocks of 64 tokens / of 128, us in turn (on one set):
 //   full maps: fp16 8192 tokens, 128 -> 512 channels 17.2 / 14.4 / 19.0, 32768 29.9 / 28.4 / 20.6; 65536, 256 -> 1024 132 / 127 / 106
 //     (110 / 126 / 106: the expanded map stays in the memory-side cache), bf16 136 / 134 / 115 (115 / 133 / 114);
 //   blocks mostly outside the image: fp16 8 x 1 x 4096, 128 -> 512 71 / 101 / 138, 8 x 4096 x 1 228 / 413 / 284, 2048 images of 3 x 3
@@ -528,20 +529,25 @@ int ffn_block_rows(int dt, int B, int C, int H, int W, int E) {
     // 32-bit byte offsets into an image, each weight matrix and the filters
     const long lim = 0x7fffffffL;
     if (dt == 0 || C > 256 || (long)H * W * C * 2 >= lim || (long)C * E * 2 >= lim || (long)E * 18 >= lim) return 0;
-    struct Round {
-        double once, step[2];           // a round of workgroups: us, and us a slab in it (fp16, bf16)
+    struct Form {
+        // us: a call; a million tokens, a channel of y; a round; a slab in it (fp16, bf16), of 64 channels in the two launches, else of 32
+        double call, channel, round, slab[2];
     };
-    static const Round one4[2] = {{3.3, {0.60, 0.70}}, {5.1, {0.75, 0.86}}}, one8[2] = {{4.7, {0.83, 1.13}}, {9.0, {1.17, 1.45}}},   // C <= 128, C > 128
-                       two64[2] = {{2.2, {0.42, 0.52}}, {5.9, {0.42, 0.52}}}, two128[2] = {{4.8, {0.48, 0.58}}, {8.0, {0.57, 0.66}}},
-                       two64_halves = {3.1, {0.45, 0.54}};      // (output channels in blocks of 128, see run_dw_project_split)
-    const int wide = C > 128, bf = dt == 2, n_slab = (E + 31) / 32;
-    auto us = [&](const Round& r, long rounds) { return rounds * (r.once + n_slab * r.step[bf]); };
+    static const Form one4[2] = {{1.63, 0.43, 2.9, {0.593, 0.701}}, {1.64, 0.59, 3.4, {0.752, 0.851}}},      // up to 128 channels, more
+                      one8[2] = {{1.24, 0.36, 4.2, {0.827, 1.13}}, {1.90, 0.58, 6.2, {1.20, 1.40}}},
+                      two64[2] = {{6.1, 0.476, 1.7, {0.885, 1.07}}, {6.9, 0.879, 2.5, {1.05, 1.24}}},
+                      two128[2] = {{6.1, 0.476, 3.0, {1.22, 1.45}}, {6.9, 0.879, 3.2, {1.61, 1.74}}},
+                      two64_halves = {6.9, 0.879, 1.3, {0.97, 1.17}};        // (output channels in blocks of 128, see run_dw_project_split)
+    const int wide = C > 128;
+    const double m_tokens = 1e-6 * B * H * W;
+    auto us = [&](const Form& f, long rounds, int slabs) { return f.call + f.channel * m_tokens * C + rounds * (f.round + slabs * f.slab[dt == 2]); };
     const FfnRounds r = ffn_rounds(B, H, W, 1);
-    const double t4 = (wide ? 0.4 : 1.4) + us(one4[wide], r.r4x16), t8 = (wide ? 0.6 : 0.8) + us(one8[wide], r.r8x16);
-    double two = 5.8 + (wide ? 1.02e-6 : 0.81e-6) * B * H * W * E;
-    if (wide && 2 * r.b4x16 <= compute_units()) two += us(two64_halves, 1);
-    else if (r.r4x16 <= r.r8x16 && r.r4x16 <= r.r4x32) two += us(two64[wide], r.r4x16);
-    else two += us(two128[wide], r.r8x16 < r.r4x32 ? r.r8x16 : r.r4x32);
+    const double t4 = us(one4[wide], r.r4x16, (E + 31) / 32), t8 = us(one8[wide], r.r8x16, (E + 31) / 32);
+    const int slabs64 = (E + 63) / 64, passes = E % 256 == 0 && E % 192 != 0 ? E / 256 : (E + 191) / 192;
+    double two = m_tokens * (0.4 * E + 55.0 * passes);
+    if (wide && 2 * r.b4x16 <= compute_units()) two += us(two64_halves, 1, slabs64);
+    else if (r.r4x16 <= r.r8x16 && r.r4x16 <= r.r4x32) two += us(two64[wide], r.r4x16, slabs64);
+    else two += us(two128[wide], r.r8x16 < r.r4x32 ? r.r8x16 : r.r4x32, slabs64);
     if (t4 > two && t8 > two) return 0;
     const int rows = t4 <= t8 ? 4 : 8;
     return (rows == 4 ? r.b4x16 : r.b8x16) * 1024 <= 0xffffffffL ? rows : 0;       // (a launch takes 32 bits of threads)

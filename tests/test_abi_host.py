@@ -231,6 +231,8 @@ def test_matrix_core_workgroups_fill_whole_rounds(lib, B, H, W, heads, scales, c
     ((1, 64, 256, 17, 17, 1024), 0),        # 17 = 16 + 1 columns, 4 x 4 + 1 rows
     ((1, 1, 128, 4, 16, 2048), 0),          # many slabs for one workgroup
     ((2, 1, 128, 32, 32, 768), 0),
+    ((2, 5, 112, 114, 222, 224), 8),        # a hidden size that the two launches' slabs of 64 and passes of 192 channels pad most
+    ((2, 15, 160, 181, 231, 80), 8),
     ((1, 9, 176, 44, 159, 176), 4),         # four rounds of 64 tokens before three of 128
     ((2, 8, 256, 64, 96, 1024), 4),         # three before two
     ((1, 1, 128, 64, 128, 512), 4),
